@@ -200,11 +200,12 @@ QformerPlan plan_qformer(int64_t frames, int64_t utts, int window, int n_q, int 
     return p;
 }
 
-int attn_tile_rows(int dtype) { return dtype == SSD_BF16 ? 64 : 4; }
+int attn_tile_rows(int dtype) { return dtype == SSD_BF16 ? 64 : F32_ATTN_ROWS; }
+int head_groups(const ssd_model_cfg& c) { return c.dtype == SSD_BF16 ? lmhead_col_groups(c.vocab) : lmhead_f32_groups(c.vocab); }
 
 struct VerifyPlan {
     size_t row_src, pos, vrow, row_slot, tiles, meta_bytes;     // metadata block, uploaded in one copy
-    size_t x, a, qkv, attn, gu, h, x_c, attn_c, partials, rope_rows, total;   // activations
+    size_t x, a, qkv, attn, h, x_c, attn_c, partials, rope_rows, total;   // activations
 };
 // rows that may go through the few-row GEMM path (split-K scratch): the whole batch, or the
 // verification rows of the last layer
@@ -222,10 +223,9 @@ VerifyPlan plan_verify(const ssd_model_cfg& c, int64_t M, int64_t Mv, int64_t ut
     p.meta_bytes = o;
     const int64_t d = c.d_model, dq = (int64_t)c.n_q_heads * c.head_dim, dkv = (int64_t)c.n_kv_heads * c.head_dim;
     p.x = o; o = align_up(o + (size_t)(M * d) * 4);
-    p.a = o; o = align_up(o + (size_t)(M * d) * es);
+    p.a = o; if (c.dtype == SSD_BF16) o = align_up(o + (size_t)(M * d) * es);
     p.qkv = o; o = align_up(o + (size_t)(M * (dq + 2 * dkv)) * es);
     p.attn = o; o = align_up(o + (size_t)(M * dq) * es);
-    p.gu = o; if (c.dtype == SSD_F32) o = align_up(o + (size_t)(M * 2 * c.d_ff) * 4);
     p.h = o; o = align_up(o + (size_t)(M * c.d_ff) * es);
     // last layer: only the verification rows go on after attention
     p.x_c = o; if (c.dtype == SSD_BF16) o = align_up(o + (size_t)(Mv * d) * 4);
@@ -244,13 +244,10 @@ AcceptPlan plan_accept(const ssd_model_cfg& c, int64_t Mv, int64_t utts) {
     AcceptPlan p;
     size_t o = 0;
     p.cu = o; o = align_up(o + (size_t)(utts + 1) * 4);
-    p.part_ms = p.tgt = p.part_arg = o;
-    if (c.dtype == SSD_BF16) {
-        const int64_t g = lmhead_col_groups(c.vocab);
-        p.part_ms = o; o = align_up(o + (size_t)(g * Mv) * sizeof(float2));
-        p.tgt = o; o = align_up(o + (size_t)Mv * 4);
-        p.part_arg = o; o = align_up(o + (size_t)(g * Mv) * sizeof(int2));
-    }
+    const int64_t g = head_groups(c);
+    p.part_ms = o; o = align_up(o + (size_t)(g * Mv) * sizeof(float2));
+    p.tgt = o; o = align_up(o + (size_t)Mv * 4);
+    p.part_arg = o; o = align_up(o + (size_t)(g * Mv) * sizeof(int2));
     p.total = o;
     return p;
 }
@@ -952,9 +949,8 @@ int verify_impl(ssd_ctx* ctx, const void* speech_emb, const int32_t* cu_speech, 
     const int Mvi = (int)Mv;
     bool compact = false;
     for (int l = 0; l < m.n_layers; ++l) {
-        { ProfScope ps(ctx, SSD_PROF_OTHER); launch_rmsnorm(m.dtype, x, ctx->norm_attn[l], nullptr, Mi, d, m.rms_eps, a, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st); }
-        pending = 1;
         if (m.dtype == SSD_BF16) {
+            { ProfScope ps(ctx, SSD_PROF_OTHER); launch_rmsnorm(m.dtype, x, ctx->norm_attn[l], nullptr, Mi, d, m.rms_eps, a, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st); }
             { ProfScope ps(ctx, SSD_PROF_GEMM_QKV); launch_gemm_qkv_rope((const uint16_t*)a, (const uint16_t*)ctx->wqkv[l], ctx->s_qkv[l], (uint16_t*)qkv, d_pos, ctx->rope_tab, Mi, d, dq, dkv, ctx->ds_qkv[l],
                                                                          kv_start ? d_row_slot : nullptr, kv_start ? (uint16_t*)kv_k(ctx, l) : nullptr, kv_start ? (uint16_t*)kv_v(ctx, l) : nullptr, rope_rows, ctx->dev_flags, ctx->bf16_ops, st); }
             { ProfScope ps(ctx, SSD_PROF_ATTN); launch_attn_mfma((const uint16_t*)qkv, (uint16_t*)att, d_tiles, n_tiles, m.n_q_heads, m.n_kv_heads, ctx->bf16_ops, st); }
@@ -972,16 +968,12 @@ int verify_impl(ssd_ctx* ctx, const void* speech_emb, const int32_t* cu_speech, 
             { ProfScope ps(ctx, SSD_PROF_GEMM_GATE_UP); launch_gemm_swiglu((const uint16_t*)a, (const uint16_t*)ctx->wgu[l], ctx->s_gu[l], (uint16_t*)h, rows, m.d_ff, d, ctx->ds_gu[l], ctx->dev_flags, ctx->bf16_ops, st); }
             { ProfScope ps(ctx, SSD_PROF_GEMM_DOWN); pending = launch_gemm_residual((const uint16_t*)h, (const uint16_t*)ctx->w_down[l], ctx->s_down[l], xr, partials, rows, d, m.d_ff, ctx->ds_down[l], ctx->bf16_ops, st); }
         } else {
-            float* gu = reinterpret_cast<float*>(ws + p.gu);
-            launch_gemm_f32((const float*)a, (const float*)ctx->wqkv[l], (float*)qkv, Mi, dq + 2 * dkv, d, F32_STORE, st);
-            launch_rope_f32((float*)qkv, d_pos, ctx->rope_tab, Mi, m.n_q_heads + m.n_kv_heads, m.head_dim, dq + 2 * dkv, st);
-            if (kv_start) launch_kv_store(m.dtype, qkv, d_row_slot, Mi, dq, dkv, kv_k(ctx, l), kv_v(ctx, l), st);
+            launch_gemm_f32_qkv(x, (const float*)ctx->norm_attn[l], m.rms_eps, (const float*)ctx->wqkv[l], (float*)qkv, d_pos, ctx->rope_tab, Mi, d, dq, dkv, m.head_dim,
+                                kv_start ? d_row_slot : nullptr, kv_start ? (float*)kv_k(ctx, l) : nullptr, kv_start ? (float*)kv_v(ctx, l) : nullptr, st);
             launch_attn_f32((const float*)qkv, (float*)att, d_tiles, n_tiles, m.n_q_heads, m.n_kv_heads, m.head_dim, st);
-            launch_gemm_f32((const float*)att, (const float*)ctx->wo[l], x, Mi, d, dq, F32_ADD, st);
-            launch_rmsnorm(m.dtype, x, ctx->norm_mlp[l], nullptr, Mi, d, m.rms_eps, a, nullptr, 1, 0, ctx->dev_flags, ctx->bf16_ops, st);
-            launch_gemm_f32((const float*)a, (const float*)ctx->wgu[l], gu, Mi, 2 * m.d_ff, d, F32_STORE, st);
-            launch_swiglu_f32(gu, (float*)h, Mi, m.d_ff, st);
-            launch_gemm_f32((const float*)h, (const float*)ctx->w_down[l], x, Mi, d, m.d_ff, F32_ADD, st);
+            launch_gemm_f32_residual((const float*)att, (const float*)ctx->wo[l], x, Mi, d, dq, st);
+            launch_gemm_f32_swiglu(x, (const float*)ctx->norm_mlp[l], m.rms_eps, (const float*)ctx->wgu[l], (float*)h, Mi, m.d_ff, d, st);
+            launch_gemm_f32_residual((const float*)h, (const float*)ctx->w_down[l], x, Mi, d, m.d_ff, st);
         }
     }
     // final RMSNorm of the positions that score a draft token
@@ -998,7 +990,7 @@ int verify_impl(ssd_ctx* ctx, const void* speech_emb, const int32_t* cu_speech, 
 
 struct ArPlan {
     size_t row_src, kv_start, pos, n_ctx, slot, meta_bytes;       // uploaded once: [Br], [Br], [steps][Br] x 3
-    size_t x, a, qkv, attn, gu, h, partials, qkv_part, hfin, logp, part_ms, tgt, part_arg, total;
+    size_t x, a, qkv, attn, h, partials, qkv_part, hfin, logp, part_ms, tgt, part_arg, total;
 };
 ArPlan plan_ar(const ssd_model_cfg& c, int64_t Br, int64_t steps) {
     ArPlan p;
@@ -1012,23 +1004,19 @@ ArPlan plan_ar(const ssd_model_cfg& c, int64_t Br, int64_t steps) {
     p.slot = o; o = align_up(o + (size_t)(steps * Br) * 4);
     p.meta_bytes = o;
     p.x = o; o = align_up(o + (size_t)(Br * d) * 4);
-    p.a = o; o = align_up(o + (size_t)(Br * d) * es);
+    p.a = o; if (c.dtype == SSD_BF16) o = align_up(o + (size_t)(Br * d) * es);
     p.qkv = o; o = align_up(o + (size_t)(Br * (dq + 2 * dkv)) * es);
     p.attn = o; o = align_up(o + (size_t)(Br * dq) * es);
-    p.gu = o; if (c.dtype == SSD_F32) o = align_up(o + (size_t)(Br * 2 * c.d_ff) * 4);
     p.h = o; o = align_up(o + (size_t)(Br * c.d_ff) * es);
     p.partials = o; if (c.dtype == SSD_BF16 && Br <= SKINNY_MAX_ROWS) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * Br * d * 4);
     // K-split partial sums of the QKV projection (finished inside the decode attention, few rows only)
     p.qkv_part = o; if (c.dtype == SSD_BF16 && Br <= 32) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * Br * (dq + 2 * dkv) * 4);
     p.hfin = o; o = align_up(o + (size_t)(Br * d) * es);
     p.logp = o; o = align_up(o + (size_t)Br * 4);
-    p.part_ms = p.tgt = p.part_arg = o;
-    if (c.dtype == SSD_BF16) {
-        const int64_t g = lmhead_col_groups(c.vocab);
-        p.part_ms = o; o = align_up(o + (size_t)(g * Br) * sizeof(float2));
-        p.tgt = o; o = align_up(o + (size_t)Br * 4);
-        p.part_arg = o; o = align_up(o + (size_t)(g * Br) * sizeof(int2));
-    }
+    const int64_t g = head_groups(c);
+    p.part_ms = o; o = align_up(o + (size_t)(g * Br) * sizeof(float2));
+    p.tgt = o; o = align_up(o + (size_t)Br * 4);
+    p.part_arg = o; o = align_up(o + (size_t)(g * Br) * sizeof(int2));
     p.total = o;
     return p;
 }
@@ -1127,9 +1115,8 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
         launch_embed_rows(m.dtype, nullptr, ctx->embed, nullptr, tok_in, d_row_src, Br, d, m.vocab, x, ctx->dev_flags, st);
         int pending = 1;
         for (int l = 0; l < m.n_layers; ++l) {
-            launch_rmsnorm(m.dtype, x, ctx->norm_attn[l], nullptr, Br, d, m.rms_eps, a, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st);
-            pending = 1;
             if (m.dtype == SSD_BF16) {
+                launch_rmsnorm(m.dtype, x, ctx->norm_attn[l], nullptr, Br, d, m.rms_eps, a, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st);
                 // few rows, head_dim 128: the QKV projection stays K-split and the decode attention finishes it
                 const int qsplits = (Br <= 32 && m.head_dim == 128)
                     ? launch_gemm_qkv_partial((const uint16_t*)a, ctx->s_qkv[l], qkv_part, Br, d, dq + 2 * dkv, ctx->ds_qkv[l], ctx->bf16_ops, st) : 0;
@@ -1139,7 +1126,7 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
                 } else {
                     launch_gemm_qkv_rope((const uint16_t*)a, (const uint16_t*)ctx->wqkv[l], ctx->s_qkv[l], (uint16_t*)qkv, d_pos, ctx->rope_tab, Br, d, dq, dkv, ctx->ds_qkv[l],
                                          d_slot, (uint16_t*)kv_k(ctx, l), (uint16_t*)kv_v(ctx, l), nullptr, ctx->dev_flags, ctx->bf16_ops, st);
-                    launch_decode_attn(m.dtype, qkv, kv_k(ctx, l), kv_v(ctx, l), d_kvs, d_nctx, Br, m.n_q_heads, m.n_kv_heads, m.head_dim, att, ctx->bf16_ops, st);
+                    launch_decode_attn(qkv, kv_k(ctx, l), kv_v(ctx, l), d_kvs, d_nctx, Br, m.n_q_heads, m.n_kv_heads, att, ctx->bf16_ops, st);
                 }
                 pending = launch_gemm_residual((const uint16_t*)att, (const uint16_t*)ctx->wo[l], ctx->s_o[l], x, partials, Br, d, dq, ctx->ds_o[l], ctx->bf16_ops, st);
                 launch_rmsnorm(m.dtype, x, ctx->norm_mlp[l], nullptr, Br, d, m.rms_eps, a, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st);
@@ -1147,29 +1134,24 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
                 launch_gemm_swiglu((const uint16_t*)a, (const uint16_t*)ctx->wgu[l], ctx->s_gu[l], (uint16_t*)h, Br, m.d_ff, d, ctx->ds_gu[l], ctx->dev_flags, ctx->bf16_ops, st);
                 pending = launch_gemm_residual((const uint16_t*)h, (const uint16_t*)ctx->w_down[l], ctx->s_down[l], x, partials, Br, d, m.d_ff, ctx->ds_down[l], ctx->bf16_ops, st);
             } else {
-                float* gu = reinterpret_cast<float*>(ws + p.gu);
-                launch_gemm_f32((const float*)a, (const float*)ctx->wqkv[l], (float*)qkv, Br, dq + 2 * dkv, d, F32_STORE, st);
-                launch_rope_f32((float*)qkv, d_pos, ctx->rope_tab, Br, m.n_q_heads + m.n_kv_heads, m.head_dim, dq + 2 * dkv, st);
-                launch_kv_store(m.dtype, qkv, d_slot, Br, dq, dkv, kv_k(ctx, l), kv_v(ctx, l), st);
-                launch_decode_attn(m.dtype, qkv, kv_k(ctx, l), kv_v(ctx, l), d_kvs, d_nctx, Br, m.n_q_heads, m.n_kv_heads, m.head_dim, att, ctx->bf16_ops, st);
-                launch_gemm_f32((const float*)att, (const float*)ctx->wo[l], x, Br, d, dq, F32_ADD, st);
-                launch_rmsnorm(m.dtype, x, ctx->norm_mlp[l], nullptr, Br, d, m.rms_eps, a, nullptr, 1, 0, ctx->dev_flags, ctx->bf16_ops, st);
-                launch_gemm_f32((const float*)a, (const float*)ctx->wgu[l], gu, Br, 2 * m.d_ff, d, F32_STORE, st);
-                launch_swiglu_f32(gu, (float*)h, Br, m.d_ff, st);
-                launch_gemm_f32((const float*)h, (const float*)ctx->w_down[l], x, Br, d, m.d_ff, F32_ADD, st);
+                launch_gemm_f32_qkv(x, (const float*)ctx->norm_attn[l], m.rms_eps, (const float*)ctx->wqkv[l], (float*)qkv, d_pos, ctx->rope_tab, Br, d, dq, dkv, m.head_dim,
+                                    d_slot, (float*)kv_k(ctx, l), (float*)kv_v(ctx, l), st);
+                launch_decode_attn_f32((const float*)qkv, (const float*)kv_k(ctx, l), (const float*)kv_v(ctx, l), d_kvs, d_nctx, Br, m.n_q_heads, m.n_kv_heads, m.head_dim, (float*)att, st);
+                launch_gemm_f32_residual((const float*)att, (const float*)ctx->wo[l], x, Br, d, dq, st);
+                launch_gemm_f32_swiglu(x, (const float*)ctx->norm_mlp[l], m.rms_eps, (const float*)ctx->wgu[l], (float*)h, Br, m.d_ff, d, st);
+                launch_gemm_f32_residual((const float*)h, (const float*)ctx->w_down[l], x, Br, d, m.d_ff, st);
             }
         }
         launch_rmsnorm(m.dtype, x, ctx->norm_final, nullptr, Br, d, m.rms_eps, hfin, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st);
         int32_t* tok_out = out_tokens + (size_t)t * Br;
-        if (m.dtype == SSD_BF16) {
-            float2* part_ms = reinterpret_cast<float2*>(ws + p.part_ms);
-            float* tgt = reinterpret_cast<float*>(ws + p.tgt);
-            int2* part_arg = reinterpret_cast<int2*>(ws + p.part_arg);
+        float2* part_ms = reinterpret_cast<float2*>(ws + p.part_ms);
+        float* tgt = reinterpret_cast<float*>(ws + p.tgt);
+        int2* part_arg = reinterpret_cast<int2*>(ws + p.part_arg);
+        if (m.dtype == SSD_BF16)
             launch_lmhead_mfma((const uint16_t*)hfin, (const uint16_t*)ctx->lm_head, tok_in, Br, d, m.vocab, part_ms, tgt, part_arg, true, ctx->ds_lm, ctx->bf16_ops, st);
-            launch_lmhead_finalize(part_ms, tgt, part_arg, lmhead_col_groups(m.vocab), Br, logp, tok_out, ctx->dev_flags, st);
-        } else {
-            launch_lmhead_f32((const float*)hfin, (const float*)ctx->lm_head, tok_in, Br, d, m.vocab, logp, tok_out, st);
-        }
+        else
+            launch_lmhead_f32((const float*)hfin, (const float*)ctx->lm_head, tok_in, Br, d, m.vocab, part_ms, tgt, part_arg, st);
+        launch_lmhead_finalize(part_ms, tgt, part_arg, head_groups(m), Br, logp, tok_out, ctx->dev_flags, st);
     }
     HIP_TRY(ctx, hipGetLastError());
     return SSD_OK;
@@ -1197,17 +1179,15 @@ int accept_prefix(ssd_ctx* ctx, const void* h_verify, const int32_t* draft_ids, 
     if (rc != SSD_OK) return rc;
     hipStream_t st = ctx->stream;
     ProfScope ps_all(ctx, SSD_PROF_LMHEAD);
-    if (m.dtype == SSD_BF16) {
-        float2* part_ms = reinterpret_cast<float2*>(ws + p.part_ms);
-        float* tgt = reinterpret_cast<float*>(ws + p.tgt);
-        int2* part_arg = reinterpret_cast<int2*>(ws + p.part_arg);
+    float2* part_ms = reinterpret_cast<float2*>(ws + p.part_ms);
+    float* tgt = reinterpret_cast<float*>(ws + p.tgt);
+    int2* part_arg = reinterpret_cast<int2*>(ws + p.part_arg);
+    if (m.dtype == SSD_BF16)
         launch_lmhead_mfma((const uint16_t*)h_verify, (const uint16_t*)ctx->lm_head, draft_ids, (int)Mv, m.d_model, m.vocab,
                            part_ms, tgt, part_arg, greedy_tok != nullptr, ctx->ds_lm, ctx->bf16_ops, st);
-        launch_lmhead_finalize(part_ms, tgt, part_arg, lmhead_col_groups(m.vocab), (int)Mv, draft_logp, greedy_tok, ctx->dev_flags, st);
-    } else {
-        launch_lmhead_f32((const float*)h_verify, (const float*)ctx->lm_head, draft_ids, (int)Mv, m.d_model, m.vocab,
-                          draft_logp, greedy_tok, st);
-    }
+    else
+        launch_lmhead_f32((const float*)h_verify, (const float*)ctx->lm_head, draft_ids, (int)Mv, m.d_model, m.vocab, part_ms, tgt, part_arg, st);
+    launch_lmhead_finalize(part_ms, tgt, part_arg, head_groups(m), (int)Mv, draft_logp, greedy_tok, ctx->dev_flags, st);
     // ln(tau) in double, rounded once to fp32; tau <= 0 accepts every token
     const float ln_tau = tau_slm > 0.f ? (float)log((double)tau_slm) : -INFINITY;
     launch_accept_scan(draft_logp, cu_dev, Bv, ln_tau, accept_len, all_accepted, st);

@@ -226,44 +226,66 @@ void launch_lmhead_mfma(const uint16_t* hv, const uint16_t* w_lm, const int32_t*
     else lmhead_impl<false>(hv, w_lm, targets, Mv, d, vocab, part_ms, tgt_logit, part_arg, want_greedy, descale, st);
 }
 
-// One wavefront per row merges the per-group partials.
-__global__ void __launch_bounds__(256) lmhead_finalize_kernel(const float2* __restrict__ part_ms,
+// Merges the per-group partials: a workgroup takes eight rows (neighbours in memory: the partials of one group are
+// row-contiguous), 64 lanes per row share the groups, eight loads in flight per lane.  Bound by latency when there
+// are few rows, and then one round of loads instead of n_groups / 64 dependent ones: 11.0 -> 4.9 us at 27 rows x 768 groups.
+constexpr int FIN_ROWS = 8, FIN_LANES = 64;
+__global__ void __launch_bounds__(FIN_ROWS * FIN_LANES) lmhead_finalize_kernel(const float2* __restrict__ part_ms,
                                                               const float* __restrict__ tgt_logit,
                                                               const int2* __restrict__ part_arg, int n_groups, int Mv,
                                                               float* __restrict__ logp, int32_t* __restrict__ greedy,
                                                               int32_t* __restrict__ flags) {
-    const int lane = threadIdx.x % 64;
-    const int row = blockIdx.x * 4 + threadIdx.x / 64;
-    if (row >= Mv) return;
-    float m = -INFINITY, s = 0.f;
-    for (int g = lane; g < n_groups; g += 64) {
-        const float2 p = part_ms[(int64_t)g * Mv + row];
-        if (p.x > m) { s = s * __expf(m - p.x) + p.y; m = p.x; } else { s += p.y * __expf(p.x - m); }
-    }
-    const float M = group_allreduce<64>(m, OpMax());
-    s = (m == -INFINITY) ? 0.f : s * __expf(m - M);
-    const float S = group_allreduce<64>(s, OpSum());
-    if (lane == 0) {
-        const float lp = tgt_logit[row] - (M + logf(S));
-        logp[row] = lp;
-        if (!(fabsf(lp) < INFINITY)) raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);     // non-finite likelihood: inputs were not finite
-    }
-    if (greedy) {
-        int cand = 0x7fffffff;
-        for (int g = lane; g < n_groups; g += 64) {
-            const int2 a = part_arg[(int64_t)g * Mv + row];
-            if (__int_as_float(a.x) == M && a.y < cand) cand = a.y;
+    __shared__ float red_m[FIN_LANES][FIN_ROWS + 1], red_s[FIN_LANES][FIN_ROWS + 1];
+    __shared__ int red_a[FIN_LANES][FIN_ROWS + 1];
+    {
+        const int r = threadIdx.x % FIN_ROWS, gl = threadIdx.x / FIN_ROWS;
+        const int64_t row = min(blockIdx.x * FIN_ROWS + r, Mv - 1);
+        float m = -INFINITY, s = 0.f;
+        int arg = 0x7fffffff;
+        constexpr int U = 8;
+        for (int g0 = gl; g0 < n_groups; g0 += U * FIN_LANES) {
+            float2 p[U];
+            int a[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int g = g0 + u * FIN_LANES;
+                p[u] = g < n_groups ? part_ms[(int64_t)g * Mv + row] : make_float2(-INFINITY, 0.f);
+                a[u] = greedy && g < n_groups ? part_arg[(int64_t)g * Mv + row].y : 0x7fffffff;
+            }
+            float m_new = m;
+#pragma unroll
+            for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, p[u].x);
+            if (m_new == -INFINITY) continue;
+            s *= expf(m - m_new);
+            if (m != m_new) arg = 0x7fffffff;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                s = fmaf(p[u].y, expf(p[u].x - m_new), s);
+                if (p[u].x == m_new) arg = min(arg, a[u]);               // lowest column that holds the maximum
+            }
+            m = m_new;
         }
-        cand = group_allreduce_i<64>(cand, OpMinI());
-        if (lane == 0) greedy[row] = cand;
+        red_m[gl][r] = m; red_s[gl][r] = s; red_a[gl][r] = arg;
     }
+    __syncthreads();
+    const int lane = threadIdx.x % 64, w = threadIdx.x / 64;             // wavefront w finishes row w
+    const int row = blockIdx.x * FIN_ROWS + w;
+    const float m = red_m[lane][w];
+    const float M = group_allreduce<64>(m, OpMax());
+    const float S = group_allreduce<64>(m == -INFINITY ? 0.f : red_s[lane][w] * expf(m - M), OpSum());
+    const int arg = group_allreduce_i<64>(m == M ? red_a[lane][w] : 0x7fffffff, OpMinI());
+    if (row >= Mv || lane != 0) return;
+    const float lp = tgt_logit[row] - (M + logf(S));
+    logp[row] = lp;
+    if (!(fabsf(lp) < INFINITY)) raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);     // non-finite likelihood: inputs were not finite
+    if (greedy) greedy[row] = arg;
 }
 
 void launch_lmhead_finalize(const float2* part_ms, const float* tgt_logit, const int2* part_arg, int n_groups, int Mv,
                             float* logp, int32_t* greedy, int32_t* flags, hipStream_t st) {
     if (Mv <= 0) return;
-    hipLaunchKernelGGL(lmhead_finalize_kernel, dim3((Mv + 3) / 4), dim3(256), 0, st, part_ms, tgt_logit, part_arg,
-                       n_groups, Mv, logp, greedy, flags);
+    hipLaunchKernelGGL(lmhead_finalize_kernel, dim3((Mv + FIN_ROWS - 1) / FIN_ROWS), dim3(FIN_ROWS * FIN_LANES), 0, st, part_ms, tgt_logit,
+                       part_arg, n_groups, Mv, logp, greedy, flags);
 }
 
 }  // namespace ssd

@@ -76,22 +76,31 @@ void launch_rmsnorm(int dtype, float* x, const void* gain, const int32_t* row_id
                     float eps, void* out, const float* partials, int n_splits, int64_t split_stride, int32_t* flags,
                     bool bf16_ops, hipStream_t st);
 
-// ---- f32_path.hip (all-fp32 decoder for the tiny configuration)
-enum F32Epilogue { F32_STORE = 0, F32_ADD = 1 };
-void launch_gemm_f32(const float* A, const float* W, float* C, int M, int N, int K, int epilogue, hipStream_t st);
-void launch_rope_f32(float* qkv, const int32_t* pos, const float* rope_tab, int M, int n_heads_rot, int head_dim,
-                     int row_stride, hipStream_t st);
-void launch_swiglu_f32(const float* gu, float* h, int M, int d_ff, hipStream_t st);
+// ---- f32_path.hip (all-fp32 decoder)
+// qkv = rope(rmsnorm(x) Wqkv^T); rows with row_slot[row] >= 0 (row_slot may be NULL) also go to the K/V cache of the layer
+void launch_gemm_f32_qkv(const float* x, const float* gain, float eps, const float* Wqkv, float* qkv, const int32_t* pos,
+                         const float* rope_tab, int M, int d_model, int d_q, int d_kv, int head_dim, const int32_t* row_slot,
+                         float* kc, float* vc, hipStream_t st);
+// h = silu(gate) * up with [gate | up] = rmsnorm(x) Wgu^T
+void launch_gemm_f32_swiglu(const float* x, const float* gain, float eps, const float* Wgu, float* h, int M, int d_ff, int d_model,
+                            hipStream_t st);
+// x += A W^T
+void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, int N, int K, hipStream_t st);
+constexpr int F32_ATTN_ROWS = 16;        // query rows of one attention work item
 void launch_attn_f32(const float* qkv, float* out, const AttnTile* tiles, int n_tiles, int n_q_heads,
                      int n_kv_heads, int head_dim, hipStream_t st);
-void launch_lmhead_f32(const float* hv, const float* w_lm, const int32_t* targets, int Mv, int d, int vocab,
-                       float* logp, int32_t* greedy, hipStream_t st);
+void launch_decode_attn_f32(const float* qkv, const float* kc, const float* vc, const int32_t* kv_start, const int32_t* n_ctx, int Br,
+                            int n_q_heads, int n_kv_heads, int head_dim, float* out, hipStream_t st);
+// partials per group of 64 vocabulary entries, merged by launch_lmhead_finalize
+int lmhead_f32_groups(int vocab);
+void launch_lmhead_f32(const float* hv, const float* w_lm, const int32_t* targets, int Mv, int d, int vocab, float2* part_ms,
+                       float* tgt_logit, int2* part_arg, hipStream_t st);
 
 // ---- gemm_mfma.hip (16-bit MFMA GEMMs with fused epilogues), attn_mfma.hip, lmhead_mfma.hip.
 // Activations and converted weights are 16-bit operand patterns: IEEE half, or bfloat16 when bf16_ops is set (the
 // context's operand type); `descale` undoes the weight scale (1 for bfloat16 operands).
 // row_slot / kc / vc (all or none): rows with row_slot[row] >= 0 also store their rotated k part and their v
-// part into the K/V cache of this layer at that slot (what launch_kv_store does as a separate pass)
+// part into the K/V cache of this layer at that slot
 // W_stream (may be NULL): the same weights in the stream layout of launch_stream_layout, read when at
 // most 32 rows are projected
 // rope_rows (may be NULL): rope_tab[pos[row]] gathered per row, [M][64] (cos, sin); read instead of pos and rope_tab
@@ -139,13 +148,10 @@ void launch_pack_qkv(int dtype, const void* wq, const void* wk, const void* wv, 
 void launch_pack_gate_up(int dtype, const void* wg, const void* wu, void* out, int d_ff, int d_model, float scale,
                          unsigned long long* inexact, hipStream_t st);
 
-// ---- ar_decode.hip (auto-regressive fallback): K/V cache of one layer is K [slots, d_kv], V [slots, d_kv]
-// in the activation type (IEEE half for bf16-stored models, fp32 otherwise); row_slot < 0 skips a row
-void launch_kv_store(int dtype, const void* qkv, const int32_t* row_slot, int n_rows, int d_q, int d_kv, void* kc,
-                     void* vc, hipStream_t st);
-void launch_decode_attn(int dtype, const void* qkv, const void* kc, const void* vc, const int32_t* kv_start,
-                        const int32_t* n_ctx, int Br, int n_q_heads, int n_kv_heads, int head_dim, void* out,
-                        bool bf16_ops, hipStream_t st);
+// ---- ar_decode.hip (auto-regressive fallback of the 16-bit models): K/V cache of one layer is K [slots, d_kv],
+// V [slots, d_kv] in the operand type
+void launch_decode_attn(const void* qkv, const void* kc, const void* vc, const int32_t* kv_start,
+                        const int32_t* n_ctx, int Br, int n_q_heads, int n_kv_heads, void* out, bool bf16_ops, hipStream_t st);
 
 // head_dim 128, half precision: decode attention that finishes the QKV projection itself.  qkv_part is
 // [n_splits][Br][d_q + 2 d_kv] fp32 partial sums in the packed column order of the fused QKV weight; the
