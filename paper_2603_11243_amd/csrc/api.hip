@@ -1010,7 +1010,7 @@ ArPlan plan_ar(const ssd_model_cfg& c, int64_t Br, int64_t steps) {
     p.h = o; o = align_up(o + (size_t)(Br * c.d_ff) * es);
     p.partials = o; if (c.dtype == SSD_BF16 && Br <= SKINNY_MAX_ROWS) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * Br * d * 4);
     // K-split partial sums of the QKV projection (finished inside the decode attention, few rows only)
-    p.qkv_part = o; if (c.dtype == SSD_BF16 && Br <= 32) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * Br * (dq + 2 * dkv) * 4);
+    p.qkv_part = o; if (c.dtype == SSD_BF16 && Br <= SKINNY_MAX_ROWS) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * Br * (dq + 2 * dkv) * 4);
     p.hfin = o; o = align_up(o + (size_t)(Br * d) * es);
     p.logp = o; o = align_up(o + (size_t)Br * 4);
     const int64_t g = head_groups(c);
@@ -1118,8 +1118,8 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
             if (m.dtype == SSD_BF16) {
                 launch_rmsnorm(m.dtype, x, ctx->norm_attn[l], nullptr, Br, d, m.rms_eps, a, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st);
                 // few rows, head_dim 128: the QKV projection stays K-split and the decode attention finishes it
-                const int qsplits = (Br <= 32 && m.head_dim == 128)
-                    ? launch_gemm_qkv_partial((const uint16_t*)a, ctx->s_qkv[l], qkv_part, Br, d, dq + 2 * dkv, ctx->ds_qkv[l], ctx->bf16_ops, st) : 0;
+                const int qsplits = (Br <= SKINNY_MAX_ROWS && m.head_dim == 128)
+                    ? launch_gemm_qkv_partial((const uint16_t*)a, (const uint16_t*)ctx->wqkv[l], ctx->s_qkv[l], qkv_part, Br, d, dq + 2 * dkv, ctx->ds_qkv[l], ctx->bf16_ops, st) : 0;
                 if (qsplits) {
                     launch_decode_attn_fused(qkv_part, qsplits, ctx->rope_tab, kv_k(ctx, l), kv_v(ctx, l), d_kvs, d_nctx, Br,
                                              m.n_q_heads, m.n_kv_heads, att, ctx->dev_flags, ctx->bf16_ops, st);

@@ -672,6 +672,19 @@ static void launch_stream_cfg(const f16_t* A, const void* Ws, int M, int N, int 
     }
     hipLaunchKernelGGL(kern, dim3((N / 64) * splits), dim3(64 * NW), lds, st, A, static_cast<const u32x4_t*>(Ws), M, N, K, splits, epi);
 }
+template <int R, int NW, int D, class Epi>
+static void launch_stream_rows(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
+    auto kern = gemm_stream_rows_kernel<R, NW, D, Epi::BF, Epi>;
+    constexpr size_t lds = gemm_stream_rows_lds_bytes<R, NW, D>();
+    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        attr_set = true;
+    }
+    const int row_tiles = (M + 32 * R - 1) / (32 * R);
+    hipLaunchKernelGGL(kern, dim3((N / 64) * splits * row_tiles), dim3(64 * NW), lds, st, A, static_cast<const u32x4_t*>(Ws), M, N, K, splits, row_tiles, epi);
+}
 bool stream_layout_supported(int N, int K) { return N > 0 && K > 0 && N % 64 == 0 && K % 256 == 0; }
 static bool stream_shape_ok(int M, int N, int K, int splits) {
     if (M <= 0 || M > STREAM_MAX_ROWS || !stream_layout_supported(N, K) || splits < 1) return false;
@@ -692,6 +705,37 @@ static bool try_launch_stream(const f16_t* A, const void* Ws, int M, int N, int 
 #undef SSD_STREAM_CASE
     return false;
 }
+// 33..128 rows from the stream layout (gemm_stream_rows_kernel), where it is faster than the LDS-ring tiles.  Times in us
+// of one launch with cold weights, stream / ring, at d_model 2048 and 3072:
+//   gate/up, 48 rows 15.5 / 19.9 and 20.9 / 28.1, 70 rows 17.7 / 20.5 and 23.4 / 28.6, 116 rows 19.9 / 21.3 and 28.6 / 29.2
+//   K splits, at most 64 rows: down 9.8 / 12.6 and 12.9 / 16.7, O 5.4 / 5.9 and 7.3 / 8.9, QKV 6.7 / 8.5 and 9.6 / 12.4
+//   K splits, 65..96 rows: down 11.6 / 13.2 and 15.4 / 18.1 (16 and 25 K steps per workgroup), QKV 3072 11.7 / 13.0 (16),
+//     but O 7.2 / 6.3 and 9.2 / 9.4 (4 and 9), QKV 2048 8.9 / 8.7 (8): short K ranges don't pay for adding three row blocks
+//   K splits, 97..128 rows: never faster (O 8.1 / 6.8, down 13.5 / 14.0 and 17.7 / 17.7)
+//   whole QKV sums: the in-workgroup K split is faster (10.4 and 14.8 at 70 rows) while its row tiles of 32 give at most one
+//     workgroup per CU; with 320 of them (116 rows, 5120 columns) 27.5 against 17.5 here with two row tiles of 64
+// Two wavefronts per workgroup rather than four: half of the partial products to be added at the end (O at 48 rows 6.8 -> 5.4).
+template <class Epi>
+static bool try_launch_stream_rows(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
+    if (M <= STREAM_MAX_ROWS || M > SKINNY_MAX_ROWS || !stream_layout_supported(N, K) || (int64_t)N * K * 2 >= (int64_t)1 << 31) return false;
+    const int KT = K / 64;
+    if constexpr (Epi::WANTS_SPLIT) {
+        if (KT < 2 * splits) return false;                   // every wavefront needs a step
+        if (M <= 64) launch_stream_rows<2, 2, 2>(A, Ws, M, N, K, splits, epi, st);
+        else if (M <= 96 && KT >= 12 * splits) launch_stream_rows<3, 2, 3>(A, Ws, M, N, K, splits, epi, st);
+        else return false;
+    } else {
+        if (splits != 1 || KT < 4) return false;
+        if (N / 64 <= 96) {                                  // few column tiles
+            if ((N / 64) * ((M + 31) / 32) <= 256) return false;
+            launch_stream_rows<2, 4, 4>(A, Ws, M, N, K, 1, epi, st);
+        }
+        else if (M <= 64) launch_stream_rows<2, 2, 4>(A, Ws, M, N, K, 1, epi, st);
+        else if (M <= 96) launch_stream_rows<3, 2, 3>(A, Ws, M, N, K, 1, epi, st);
+        else launch_stream_rows<4, 2, 2>(A, Ws, M, N, K, 1, epi, st);
+    }
+    return true;
+}
 void launch_stream_layout(const uint16_t* w, void* out, int N, int K, hipStream_t st) {
     const int64_t units = (int64_t)N * K / 8;
     hipLaunchKernelGGL(stream_layout_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, st,
@@ -703,16 +747,17 @@ void launch_stream_layout(const uint16_t* w, void* out, int N, int K, hipStream_
 // so that the number of tiles wastes as little of the last round over the 256 CUs as possible:
 // cost = rounds * height / efficiency.
 // With at most 128 rows the job is weight streaming and what counts is the number of weight bytes in
-// flight: at most 32 rows go to the register-streaming kernel when the shape divides evenly; otherwise a
-// skinny 128 x 64 tile (four wavefronts, each 32 rows x 64 columns) with a six-stage LDS ring
+// flight: at most 32 rows go to the register-streaming kernel when the shape divides evenly, more to its variant
+// with row blocks where that is faster (try_launch_stream_rows); otherwise a skinny 128 x 64 tile (four wavefronts, each 32 rows x 64 columns) with a six-stage LDS ring
 // (144 KB, five slices in flight), and for at most 32 rows a 32 x 64 tile of one wavefront, six stages
 // of 12 KB, two workgroups per CU.
 template <class Epi>
 static void launch_skinny(const f16_t* A, const f16_t* W, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
     if (try_launch_stream(A, Ws, M, N, K, splits, epi, st)) return;
-    // 33..128 rows: the launch should put a workgroup on every CU.  A projection with few column tiles and no K
-    // split (QKV: 64-80 tiles) is cut into row tiles of 32 or 64 as well; the row tiles of a column slab then
-    // read the same weights, which the L2 serves.
+    if (Ws && try_launch_stream_rows(A, Ws, M, N, K, splits, epi, st)) return;
+    // 33..128 rows through the LDS ring: the launch should put a workgroup on every CU.  A projection with few column
+    // tiles and no K split (QKV: 64-80 tiles) is cut into row tiles of 32 or 64 as well; the row tiles of a column slab
+    // then read the same weights, which the L2 serves.
     const int col_tiles = (N / 64) * splits;
     if constexpr (!Epi::WANTS_SPLIT) {
         // whole sums wanted (no K split across workgroups) and few column tiles: split K inside the workgroup
@@ -763,19 +808,20 @@ void launch_gemm_qkv_rope(const uint16_t* A, const uint16_t* Wqkv_packed, const 
     }
 }
 
-int launch_gemm_qkv_partial(const uint16_t* A, const void* W_stream, float* part, int M, int d_model, int N, float descale,
+int launch_gemm_qkv_partial(const uint16_t* A, const uint16_t* W, const void* W_stream, float* part, int M, int d_model, int N, float descale,
                             bool bf16_ops, hipStream_t st) {
-    if (!W_stream || M > STREAM_MAX_ROWS) return 0;
+    if (!W_stream || M > SKINNY_MAX_ROWS) return 0;
     int splits = 0;
-    for (int s = SKINNY_MAX_SPLITS; s >= 2 && !splits; --s)                 // about one workgroup per CU
-        if (stream_shape_ok(M, N, d_model, s) && (N / 64) * s <= 320) splits = s;
-    if (!splits) return 0;
-    if (bf16_ops) {
-        EpiPartial<true> epi{part, N, (int64_t)M * N, descale};
-        return try_launch_stream(A, W_stream, M, N, d_model, splits, epi, st) ? splits : 0;
+    if (M <= STREAM_MAX_ROWS) {
+        for (int s = SKINNY_MAX_SPLITS; s >= 2 && !splits; --s)             // about one workgroup per CU
+            if (stream_shape_ok(M, N, d_model, s) && (N / 64) * s <= 320) splits = s;
+    } else {
+        splits = min(min(SKINNY_MAX_SPLITS, 256 / (N / 64)), d_model / GEMM_BK / 4);
     }
-    EpiPartial<false> epi{part, N, (int64_t)M * N, descale};
-    return try_launch_stream(A, W_stream, M, N, d_model, splits, epi, st) ? splits : 0;
+    if (splits < 2) return 0;
+    if (bf16_ops) launch_skinny(A, W, W_stream, M, N, d_model, splits, EpiPartial<true>{part, N, (int64_t)M * N, descale}, st);
+    else launch_skinny(A, W, W_stream, M, N, d_model, splits, EpiPartial<false>{part, N, (int64_t)M * N, descale}, st);
+    return splits;
 }
 
 int gemm_residual_splits(int M, int N, int K, bool have_stream) {
@@ -785,9 +831,9 @@ int gemm_residual_splits(int M, int N, int K, bool have_stream) {
         for (int s = SKINNY_MAX_SPLITS; s >= 2; --s)
             if (stream_shape_ok(M, N, K, s) && (N / 64) * s <= 512) return s;
     }
-    int splits = 1;
-    while (splits < SKINNY_MAX_SPLITS && (N / 64) * splits < 256 && K / GEMM_BK / (splits * 2) >= 4) splits *= 2;
-    return splits;
+    // as many as still give every CU at most one workgroup: 3072 columns are 48 tiles, whose 8 splits ran in one and a
+    // half rounds (70 rows: O 13.4 us and down 21.8 us, with 5 splits 9.4 and 18.1)
+    return max(1, min(min(SKINNY_MAX_SPLITS, 256 / (N / 64)), K / GEMM_BK / 4));
 }
 
 // x += A W^T.  With few rows the K range is split over several workgroups per tile to get enough

@@ -136,6 +136,169 @@ gemm_stream_kernel(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, 
         epi.template operator()<1, 2>(out, 0, tile * 64, M, lane);
 }
 
+// The same product for more rows (33..128 and beyond): a workgroup owns 64 columns, 32 R rows and one K split; its NW
+// wavefronts take consecutive pieces of that K range.  W comes from the stream layout straight into the operand
+// registers, A through a wavefront-private ring of D LDS stages (one stage: 32 R rows of one 64-wide K step), and the
+// loads of D steps are in flight per wavefront.  No wavefront waits for another before the partial products are added.
+// The K range need not divide evenly: beyond its end a wavefront issues loads through an empty buffer descriptor
+// (they fetch nothing), so that the number of loads in flight, which the waits count, is the same in every step.
+// Workgroup order: the row tiles of one (column tile, split) read the same weights and get ids 8 apart, i.e. one XCD.
+// buffer descriptor over p, or an empty one (every access out of range: loads return zero and fetch nothing)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_if(const void* p, bool have) {
+    const int bytes = __builtin_amdgcn_readfirstlane(have ? -1 : 0);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4_t buffer_load_16(__amdgpu_buffer_rsrc_t rsrc, int off, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, soff, 0);
+}
+template <int R, int NW, int D>
+constexpr size_t gemm_stream_rows_lds_bytes() { return (size_t)NW * R * (D * 4096 > 8192 ? D * 4096 : 8192); }
+
+template <int R, int NW, int D, bool BF, class Epi>
+__device__ __forceinline__ void gemm_stream_rows(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, int M, int N, int K, int splits,
+                                                 int row_tiles, const Epi& epi, unsigned char* smem_raw) {
+    constexpr int STAGE = R * 4096;
+    constexpr int WAVE_LDS = D * STAGE;
+    constexpr int LOADS = 4 * R + 8;                         // per step
+    static_assert((D - 1) * LOADS <= 63, "vmcnt range");
+    const int lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int x = lane % 32, h = lane / 32;
+    const int units = (N / 64) * splits;
+    int unit, rt;
+    if (units % 8 == 0) {
+        const int chunk = blockIdx.x / (8 * row_tiles), in = blockIdx.x % (8 * row_tiles);
+        unit = chunk * 8 + in % 8;
+        rt = in / 8;
+    } else {
+        unit = blockIdx.x / row_tiles;
+        rt = blockIdx.x % row_tiles;
+    }
+    const int tile = unit / splits, split = unit % splits;
+    const int row0 = rt * 32 * R;
+    const int KT = K / 64, pieces = splits * NW, piece = split * NW + wave;
+    // (said to be uniform: a descriptor or offset in vector registers would turn every load into a loop over the lanes)
+    const int t_first = __builtin_amdgcn_readfirstlane(KT * piece / pieces);
+    const int steps = __builtin_amdgcn_readfirstlane(KT * (piece + 1) / pieces) - t_first;
+    const int w_first = __builtin_amdgcn_readfirstlane((tile * KT + t_first) * (STREAM_STEP_UNITS * 16));
+    unsigned char* my_lds = smem_raw + wave * WAVE_LDS;
+
+    const int lrow = lane / 8, lslot = lane % 8;
+    unsigned a_off[4 * R];
+#pragma unroll
+    for (int q = 0; q < 4 * R; ++q) {
+        const int r = q * 8 + lrow;
+        a_off[q] = (unsigned)min(row0 + r, M - 1) * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
+    }
+    int a_rd[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a_rd[s] = x * GEMM_ROW_BYTES + (((4 * h + s) ^ ((x >> 1) & 7)) * 16);
+
+    f32x16_t acc[R][2];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    u32x4_t w[D][2][4];
+    auto issue = [&](auto dc, int i) {                       // step i of this wavefront into stage d
+        constexpr int d = decltype(dc)::value;
+        const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc_if(A, i < steps), w_rsrc = make_rsrc_if(Ws, i < steps);
+#pragma unroll
+        for (int q = 0; q < 4 * R; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void_t*)(my_lds + d * STAGE + q * 1024), 16, a_off[q], (t_first + i) * GEMM_ROW_BYTES, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                w[d][j][s] = buffer_load_16(w_rsrc, lane * 16 + (j * 4 + s) * 1024, w_first + i * (STREAM_STEP_UNITS * 16));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto compute = [&](auto dc) {
+        constexpr int d = decltype(dc)::value;
+        f16x8_t a[2][R];
+        auto read = [&](int s) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) a[s % 2][i] = as_f16x8(*reinterpret_cast<const uint4*>(my_lds + d * STAGE + i * 4096 + a_rd[s]));
+        };
+        read(0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (s < 3) read(s + 1);
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_32x32x16<BF>(a[s % 2][i], __builtin_bit_cast(f16x8_t, w[d][j][s]), acc[i][j]);
+        }
+    };
+    constexpr int KEEP = (D - 1) * LOADS;
+    auto step = [&](auto dc, int i) {
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (KEEP & 15) | ((KEEP >> 4) << 14));      // step i has landed, the D - 1 younger ones may be out
+        __builtin_amdgcn_sched_barrier(0);
+        if (i < steps) compute(dc);
+        __builtin_amdgcn_s_waitcnt(0xC07F);                  // the fragment reads of this stage are done
+        __builtin_amdgcn_sched_barrier(0);
+        issue(dc, i + D);
+    };
+    auto for_stages = [&](auto f) {
+        f(std::integral_constant<int, 0>());
+        if constexpr (D > 1) f(std::integral_constant<int, 1>());
+        if constexpr (D > 2) f(std::integral_constant<int, 2>());
+        if constexpr (D > 3) f(std::integral_constant<int, 3>());
+        static_assert(D <= 4, "stages");
+    };
+    for_stages([&](auto dc) { issue(dc, decltype(dc)::value); });
+    int i0 = 0;
+    do {                                                     // (a branch here would let the W loads sink below the A loads of later steps)
+        for_stages([&](auto dc) { step(dc, i0 + decltype(dc)::value); });
+        i0 += D;
+    } while (i0 < steps);
+
+    // ---- add the NW partial products in wavefront order: red[wave][row block][j][r/4][lane] float4; row block b is
+    // finished by wavefront b % NW
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    float4* red = reinterpret_cast<float4*>(smem_raw);
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                red[((wave * R + i) * 8 + j * 4 + g) * 64 + lane] = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+    __syncthreads();
+    for (int i = wave; i < R; i += NW) {
+        if (row0 + i * 32 >= M) break;
+        f32x16_t out[1][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) out[0][j][r] = 0.f;
+#pragma unroll 2
+        for (int o = 0; o < NW; ++o)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 v = red[((o * R + i) * 8 + j * 4 + g) * 64 + lane];
+                    out[0][j][4 * g] += v.x; out[0][j][4 * g + 1] += v.y; out[0][j][4 * g + 2] += v.z; out[0][j][4 * g + 3] += v.w;
+                }
+        if constexpr (Epi::WANTS_SPLIT)
+            epi.template operator()<1, 2>(out, row0 + i * 32, tile * 64, M, lane, split);
+        else
+            epi.template operator()<1, 2>(out, row0 + i * 32, tile * 64, M, lane);
+    }
+}
+template <int R, int NW, int D, bool BF, class Epi>
+__global__ void __launch_bounds__(64 * NW)
+gemm_stream_rows_kernel(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, int M, int N, int K, int splits, int row_tiles, Epi epi) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    gemm_stream_rows<R, NW, D, BF>(A, Ws, M, N, K, splits, row_tiles, epi, smem_raw);
+}
+
 // Row-major W[N,K] (f16) -> stream layout; one thread per 16-byte unit.
 __global__ void __launch_bounds__(256) stream_layout_kernel(const u32x4_t* __restrict__ w, u32x4_t* __restrict__ out, int N, int K) {
     const int64_t n_units = (int64_t)N * K / 8;

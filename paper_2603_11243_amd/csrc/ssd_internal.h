@@ -163,7 +163,7 @@ void launch_decode_attn_fused(const float* qkv_part, int n_splits, const float* 
                               void* out, int32_t* flags, bool bf16_ops, hipStream_t st);
 // QKV projection left as K-split partial sums for launch_decode_attn_fused; returns the split count, or 0 if
 // the shape is not served (then nothing was launched)
-int launch_gemm_qkv_partial(const uint16_t* A, const void* W_stream, float* part, int M, int d_model, int N, float descale,
+int launch_gemm_qkv_partial(const uint16_t* A, const uint16_t* W, const void* W_stream, float* part, int M, int d_model, int N, float descale,
                             bool bf16_ops, hipStream_t st);
 
 // threshold grids: outputs are [n_tau][B] / [n_tau][Bv]
