@@ -207,9 +207,6 @@ struct VerifyPlan {
     size_t row_src, pos, vrow, row_slot, tiles, meta_bytes;     // metadata block, uploaded in one copy
     size_t x, a, qkv, attn, h, x_c, attn_c, partials, rope_rows, total;   // activations
 };
-// rows that may go through the few-row GEMM path (split-K scratch): the whole batch, or the
-// verification rows of the last layer
-int64_t skinny_rows(int64_t M, int64_t Mv) { return M <= SKINNY_MAX_ROWS ? M : (Mv <= SKINNY_MAX_ROWS ? Mv : 0); }
 VerifyPlan plan_verify(const ssd_model_cfg& c, int64_t M, int64_t Mv, int64_t utts) {
     VerifyPlan p;
     const size_t es = elem_size(c.dtype);
@@ -231,7 +228,7 @@ VerifyPlan plan_verify(const ssd_model_cfg& c, int64_t M, int64_t Mv, int64_t ut
     p.x_c = o; if (c.dtype == SSD_BF16) o = align_up(o + (size_t)(Mv * d) * 4);
     p.attn_c = o; if (c.dtype == SSD_BF16) o = align_up(o + (size_t)(Mv * dq) * es);
     p.partials = o;
-    if (c.dtype == SSD_BF16) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * skinny_rows(M, Mv) * d * 4);
+    if (c.dtype == SSD_BF16) o = align_up(o + (size_t)residual_partial_floats(M, d) * 4);
     // rotary table rows gathered per decoder row once per forward (the positions are the same in every layer)
     p.rope_rows = o;
     if (c.dtype == SSD_BF16 && M > SKINNY_MAX_ROWS) o = align_up(o + (size_t)M * 64 * sizeof(float2));
@@ -1008,7 +1005,7 @@ ArPlan plan_ar(const ssd_model_cfg& c, int64_t Br, int64_t steps) {
     p.qkv = o; o = align_up(o + (size_t)(Br * (dq + 2 * dkv)) * es);
     p.attn = o; o = align_up(o + (size_t)(Br * dq) * es);
     p.h = o; o = align_up(o + (size_t)(Br * c.d_ff) * es);
-    p.partials = o; if (c.dtype == SSD_BF16 && Br <= SKINNY_MAX_ROWS) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * Br * d * 4);
+    p.partials = o; if (c.dtype == SSD_BF16) o = align_up(o + (size_t)residual_partial_floats(Br, d) * 4);
     // K-split partial sums of the QKV projection (finished inside the decode attention, few rows only)
     p.qkv_part = o; if (c.dtype == SSD_BF16 && Br <= SKINNY_MAX_ROWS) o = align_up(o + (size_t)SKINNY_MAX_SPLITS * Br * (dq + 2 * dkv) * 4);
     p.hfin = o; o = align_up(o + (size_t)(Br * d) * es);

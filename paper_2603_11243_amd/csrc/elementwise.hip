@@ -245,7 +245,7 @@ void launch_rmsnorm(int dtype, float* x, const void* gain, const int32_t* row_id
                     void* out, const float* partials, int n_splits, int64_t split_stride, int32_t* flags, bool bf16_ops,
                     hipStream_t st) {
     if (n_rows <= 0) return;
-    if (n_rows <= 512 && d <= 4096 && n_splits <= SKINNY_MAX_SPLITS) {
+    if ((n_rows <= 512 || n_splits > 1) && d <= 4096 && n_splits <= SKINNY_MAX_SPLITS) {
 #define SSD_RMSNORM_ROW(T, BF) \
         hipLaunchKernelGGL((rmsnorm_row_kernel<T, 4, BF>), dim3(n_rows), dim3(256), 0, st, x, (const T*)gain, row_idx, d, eps, (T*)out, partials, n_splits, split_stride, flags)
         if (dtype == SSD_BF16) { if (bf16_ops) SSD_RMSNORM_ROW(bf16_t, true); else SSD_RMSNORM_ROW(bf16_t, false); }

@@ -11,6 +11,7 @@
 // Three main loops feed these epilogues: big tiles on v_mfma_f32_16x16x32_f16 (gemm_core16.h), skinny
 // LDS-ring tiles for 33..128 rows (gemm_core.h) and the register-streaming kernel for at most 32 rows
 // (gemm_stream.h).
+#include <algorithm>
 #include <type_traits>
 
 #include "gemm_core.h"
@@ -607,15 +608,17 @@ static void launch_gemm_kgroups(const f16_t* A, const f16_t* W, int M, int N, in
     hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * KG), lds, st, A, W, M, N, K, epi);
 }
 
-// Big tiles on v_mfma_f32_16x16x32_f16 (gemm_core16.h): same tile shapes, workgroup order and epilogues.
+// Big tiles on v_mfma_f32_16x16x32_f16 (gemm_core16.h): same tile shapes, workgroup order, K splits and epilogues.
 template <int BM, int BN, int WAVES_M, int WAVES_N, class Epi>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N)
-gemm_mfma16_kernel(const f16_t* __restrict__ A, const f16_t* __restrict__ W, int M, int N, int K, Epi epi) {
+gemm_mfma16_kernel(const f16_t* __restrict__ A, const f16_t* __restrict__ W, int M, int N, int K, int splits, Epi epi) {
     using Tile = GemmTile16<BM, BN, WAVES_M, WAVES_N, Epi::BF, Epi::TRANSPOSE>;   // transposed accumulator blocks where the epilogue gains from them
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
     int tm, tn;
-    tile_of_workgroup(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    const int split = blockIdx.x % splits;
+    tile_of_workgroup(blockIdx.x / splits, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    const int KT = K / GEMM_BK;
     f32x4_t acc[Tile::TM][Tile::TN];
 #pragma unroll
     for (int i = 0; i < Tile::TM; ++i)
@@ -623,12 +626,14 @@ gemm_mfma16_kernel(const f16_t* __restrict__ A, const f16_t* __restrict__ W, int
         for (int j = 0; j < Tile::TN; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-    Tile::run(A, W, M, K, tm * BM, tn * BN, 0, K / GEMM_BK, smem_raw, acc);
+    Tile::run(A, W, M, K, tm * BM, tn * BN, KT * split / splits, KT * (split + 1) / splits, smem_raw, acc);
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     if constexpr (Epi::USES_LDS)
         epi.template run_lds<Tile::TM, Tile::TN>(acc, tm * BM + wm * Tile::WTM, tn * BN + wn * Tile::WTN, M, lane,
                                                  reinterpret_cast<float*>(smem_raw + wave * Epi::template wave_lds_bytes<Tile::TM>()));
+    else if constexpr (Epi::WANTS_SPLIT)
+        epi.template operator()<Tile::TM, Tile::TN, Layout16>(acc, tm * BM + wm * Tile::WTM, tn * BN + wn * Tile::WTN, M, lane, split);
     else if constexpr (Epi::TRANSPOSE)
         epi.template operator()<Tile::TM, Tile::TN, Layout16T>(acc, tm * BM + wm * Tile::WTM, tn * BN + wn * Tile::WTN, M, lane);
     else
@@ -636,7 +641,7 @@ gemm_mfma16_kernel(const f16_t* __restrict__ A, const f16_t* __restrict__ W, int
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, class Epi>
-static void launch_gemm16(const f16_t* A, const f16_t* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
+static void launch_gemm16(const f16_t* A, const f16_t* W, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
     if (M <= 0) return;
     auto kern = gemm_mfma16_kernel<BM, BN, WAVES_M, WAVES_N, Epi>;
     constexpr size_t ring = gemm_lds_bytes<BM, BN, 2>();
@@ -655,7 +660,7 @@ static void launch_gemm16(const f16_t* A, const f16_t* W, int M, int N, int K, c
         attr_set = true;
     }
     const int tiles = ((M + BM - 1) / BM) * (N / BN);
-    hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * WAVES_M * WAVES_N), lds, st, A, W, M, N, K, epi);
+    hipLaunchKernelGGL(kern, dim3(tiles * splits), dim3(64 * WAVES_M * WAVES_N), lds, st, A, W, M, N, K, splits, epi);
 }
 
 // Register-streaming kernel for at most 32 rows (gemm_stream.h); it reads the stream-layout copy of the
@@ -782,13 +787,23 @@ static void launch_big(const f16_t* A, const f16_t* W, int M, int N, int K, cons
         const double cost = (double)((tiles + 255) / 256) * heights[c] / eff[c];
         if (cost < best_cost - 1e-9) { best_cost = cost; best = c; }
     }
-    if (best == 0) launch_gemm16<256, 256, 2, 4>(A, W, M, N, K, epi, st);
-    else if (best == 1) launch_gemm16<192, 256, 2, 4>(A, W, M, N, K, epi, st);
-    else launch_gemm16<128, 256, 2, 4>(A, W, M, N, K, epi, st);
+    if (best == 0) launch_gemm16<256, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
+    else if (best == 1) launch_gemm16<192, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
+    else launch_gemm16<128, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
 }
+// Whole sums (QKV, gate/up, the projector).  Beyond 128 rows the 256-wide tiles leave most of the chip idle until there
+// are about 256 of them, and a workgroup then has its whole K range in front of it whatever the row count (QKV of 136 to
+// 784 rows: 35 us at 2048 x 4096, 60 us at 3072 x 5120).  The narrow LDS-ring tiles are faster while they are at most one
+// workgroup per CU (136 rows: 12.8 and 17.8 us as 64 x 64, 392 rows: 16.4 us as 128 x 64; two rounds of them are not,
+// 392 rows at 3072: 39.3), then 64 x 128 tiles while at most two per CU (784 rows: 27.5 and 56.6 us; gate/up of 136 rows
+// 38.9 -> 30.7 and 61.6 -> 44.7; with 800 of them, 1568 rows, 50.6 against 39.4).
 template <class Epi>
 static void launch_by_shape(const f16_t* A, const f16_t* W, const void* Ws, int M, int N, int K, const Epi& epi, hipStream_t st) {
+    auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * (N / bn); };
     if (M <= SKINNY_MAX_ROWS) launch_skinny(A, W, Ws, M, N, K, 1, epi, st);
+    else if (tiles(64, 64) <= 256) launch_gemm<64, 64, 2, 1, 6>(A, W, M, N, K, 1, epi, st);
+    else if (tiles(128, 64) <= 256) launch_gemm<128, 64, 4, 1, 6>(A, W, M, N, K, 1, epi, st);
+    else if (tiles(64, 128) <= 512) launch_gemm16<64, 128, 2, 2>(A, W, M, N, K, 1, epi, st);
     else launch_big(A, W, M, N, K, epi, st);
 }
 
@@ -824,8 +839,22 @@ int launch_gemm_qkv_partial(const uint16_t* A, const uint16_t* W, const void* W_
     return splits;
 }
 
+// Residual projections of more than 128 rows: as many K splits of 128 x 256 tiles as one round over the CUs takes, or of
+// 128 x 64 LDS-ring tiles if those use more CUs.  Unsplit, a workgroup walks the whole K range (down, K = 8192, of 136 to
+// 1568 rows: 132-136 us); with splits, at 2048 and 3072 columns: 136 rows 16.4 and 23.5 us, 392 rows 25.0 and 35.5, 784 rows
+// 41.3 and 57.0, 1176 rows 54.8 and 78.0; O projection of 784 rows 36.4 -> 14.4 and 54.4 -> 24.3.  From 129 tiles on
+// (2049 rows at 2048 columns, 1281 at 3072) there is no second split and the projection adds to x in place.
+struct ResidualSplit { int splits; bool narrow; };
+static ResidualSplit mid_residual_split(int M, int N, int K) {
+    const int64_t wide = (int64_t)((M + 127) / 128) * (N / 256), narrow = 4 * wide;
+    const int most = max(1, min(SKINNY_MAX_SPLITS, K / GEMM_BK / 4));
+    const int sw = (int)std::min<int64_t>(most, 256 / wide), sn = (int)std::min<int64_t>(most, 256 / narrow);
+    if (sn >= 2 && narrow * sn > wide * sw) return {sn, true};
+    return {max(1, sw), false};
+}
+
 int gemm_residual_splits(int M, int N, int K, bool have_stream) {
-    if (M > SKINNY_MAX_ROWS) return 1;
+    if (M > SKINNY_MAX_ROWS) return mid_residual_split(M, N, K).splits;
     if (have_stream && M <= STREAM_MAX_ROWS) {
         // register-streaming kernel: the most splits (workgroups) whose K range still divides over 4 wavefronts
         for (int s = SKINNY_MAX_SPLITS; s >= 2; --s)
@@ -836,7 +865,7 @@ int gemm_residual_splits(int M, int N, int K, bool have_stream) {
     return max(1, min(min(SKINNY_MAX_SPLITS, 256 / (N / 64)), K / GEMM_BK / 4));
 }
 
-// x += A W^T.  With few rows the K range is split over several workgroups per tile to get enough
+// x += A W^T.  Where a launch would leave CUs idle the K range is split over several workgroups per tile to get enough
 // of them for weight streaming; the splits land in `partials` ([splits][M][N] fp32) and the caller
 // hands them to the next RMSNorm, which adds them to x in a fixed order.  Returns the split count
 // (1: x has been updated in place).
@@ -846,7 +875,9 @@ static int gemm_residual_impl(const uint16_t* A, const uint16_t* W, const void* 
     const int splits = gemm_residual_splits(M, N, K, W_stream != nullptr);
     if (splits > 1) {
         EpiPartial<BF> epi{partials, N, (int64_t)M * N, descale};
-        launch_skinny(A, W, W_stream, M, N, K, splits, epi, st);
+        if (M <= SKINNY_MAX_ROWS) launch_skinny(A, W, W_stream, M, N, K, splits, epi, st);
+        else if (mid_residual_split(M, N, K).narrow) launch_gemm<128, 64, 4, 1, 6>(A, W, M, N, K, splits, epi, st);
+        else launch_gemm16<128, 256, 2, 4>(A, W, M, N, K, splits, epi, st);
         return splits;
     }
     if (M > SKINNY_MAX_ROWS) launch_big(A, W, M, N, K, EpiResidualLds<BF>{x, N, descale}, st);

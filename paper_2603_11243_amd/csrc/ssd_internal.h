@@ -111,6 +111,12 @@ void launch_gemm_qkv_rope(const uint16_t* A, const uint16_t* Wqkv_packed, const 
 constexpr int SKINNY_MAX_ROWS = 128;     // at most this many decoder rows: weight-streaming GEMM variants
 constexpr int SKINNY_MAX_SPLITS = 8;
 int gemm_residual_splits(int M, int N, int K, bool have_stream);
+// fp32 values the partial sums of a residual projection of at most `rows` rows and d columns need: SKINNY_MAX_SPLITS sums
+// per value, but no more than one round of 128 x 256 tiles over 256 CUs (which covers 128 rows of up to 8192 columns)
+inline int64_t residual_partial_floats(int64_t rows, int64_t d) {
+    const int64_t all = SKINNY_MAX_SPLITS * rows * d, round = (int64_t)128 * 256 * 256;
+    return all < round ? all : round;
+}
 // returns the number of K splits written to `partials` ([splits][M][N] fp32), or 1 if x was updated in place
 int launch_gemm_residual(const uint16_t* A, const uint16_t* W, const void* W_stream, float* x, float* partials, int M, int N, int K,
                          float descale, bool bf16_ops, hipStream_t st);

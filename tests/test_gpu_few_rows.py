@@ -60,3 +60,15 @@ def test_fallback_row_blocks(Br):
     res = _run_chain(wl, w, vi, 0.5, 2)
     assert len(res[1]) == Br
     _check_against_oracle(wl, w, vi, 0.5, 2, *res, sample=range(0, Br, 8))
+
+
+# 768 columns are 3 (12) tiles per 128 rows: K splits of 128 x 64 tiles while they use more CUs, then of 128 x 256 tiles,
+# over 12 and 50 K steps; QKV and gate/up pass from 64 x 64 over 128 x 64 and 64 x 128 to the 256-wide tiles
+@pytest.mark.parametrize("M", [129, 256, 257, 500, 641, 1100, 1700])
+def test_verify_mid_rows(M):
+    m = ModelCfg(2, 768, 6, 2, 128, 3200, 512, dtype="bf16")
+    wl = replace(WORKLOADS["cfg3_1b_ragged64"], model=m)
+    w = make_model_weights(m, 80 + M)
+    vi = _inputs(m, [(M // 2 - 40, 3, 37), (M - M // 2 - 9, 4, 5)], M)
+    tau = 1.0 / m.vocab
+    _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
