@@ -50,6 +50,16 @@ struct Layout32 {
     static __device__ __forceinline__ int col(int j, int lane) { return acc_col(j, lane); }
 };
 
+// Registers 4 q .. 4 q + 3 of a 32x32 block: rows 8 q + 4 (lane / 32) + r; the caller adds 8 q to the first row.  For epilogues
+// that share a block among four wavefronts.
+struct Layout32Quarter {
+    static constexpr bool TRANSPOSED = false;
+    static constexpr int BLOCK = 32, REGS = 4, PAIR = 1;
+    typedef f32x4_t vec_t;
+    static __device__ __forceinline__ int row(int i, int r, int lane) { return 4 * (lane / 32) + r; }
+    static __device__ __forceinline__ int col(int j, int lane) { return acc_col(j, lane); }
+};
+
 // SWAP: issue the MFMA with the W fragment as the row operand, which transposes every accumulator block
 // (Layout16T instead of Layout16); the loop, the fragments and their reads are the same.
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool BF16 = false, bool SWAP = false>

@@ -544,7 +544,7 @@ static void launch_gemm(const f16_t* A, const f16_t* W, int M, int N, int K, int
 }
 
 // One-wavefront tile with the K range split over KG wavefronts of the workgroup, each with its own LDS ring; the
-// partial accumulators are added through LDS in group order (deterministic) and group 0 runs the epilogue.  For
+// partial accumulators are added through LDS in group order (deterministic), a quarter of the tile per group, with the epilogue.  For
 // projections with few rows, few column tiles and an epilogue that needs whole sums (QKV + RoPE at 33-128 rows): a
 // CU then keeps KG rings of weight and activation slices in flight instead of one.
 template <int BM, int BN, int NSTAGE, int KG, class Epi>
@@ -569,28 +569,10 @@ gemm_mfma_kgroups_kernel(const f16_t* __restrict__ A, const f16_t* __restrict__ 
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     Tile::run(A, W, M, K, tm * BM, tn * BN, g * per, (g + 1) * per, smem_raw + g * RING, acc);
     // a group's ring is read by that group only and all its reads have completed: it may hold the partial tile
-    float* mine = reinterpret_cast<float*>(smem_raw + g * RING);
-    if (g > 0) {
-#pragma unroll
-        for (int i = 0; i < Tile::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < Tile::TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mine[((i * Tile::TN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
-    }
+    static_assert(Tile::TM == 1 && Tile::TN == 2, "finish_quarter takes 32 x 64 blocks");
+    store_partial(reinterpret_cast<float4*>(smem_raw + g * RING), acc[0], lane);
     __syncthreads();
-    if (g == 0) {
-        for (int o = 1; o < KG; ++o) {
-            const float* theirs = reinterpret_cast<const float*>(smem_raw + o * RING);
-#pragma unroll
-            for (int i = 0; i < Tile::TM; ++i)
-#pragma unroll
-                for (int j = 0; j < Tile::TN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[i][j][r] += theirs[((i * Tile::TN + j) * 16 + r) * 64 + lane];
-        }
-        epi.template operator()<Tile::TM, Tile::TN>(acc, tm * BM, tn * BN, M, lane);
-    }
+    for (int q = g; q < 4; q += KG) finish_quarter<KG>(reinterpret_cast<const float4*>(smem_raw), RING / 16, q, tm * BM, tn * BN, M, lane, 0, epi);
 }
 
 template <int BM, int BN, int NSTAGE, int KG, class Epi>

@@ -17,13 +17,13 @@
 //
 // Work split: a workgroup owns 64 output columns and the K range of one split; its NW wavefronts take
 // consecutive, equally long pieces of that range and each accumulates a full 32 x 64 partial product;
-// the partial products are added through LDS in a fixed order (deterministic) by wavefront 0, which
-// applies the epilogue.  A (a few KB per wavefront, L2 resident) is staged in a wavefront-private LDS
+// the partial products are added through LDS in a fixed order (deterministic) by four wavefronts, a
+// quarter of the block each, which apply the epilogue.  A (a few KB per wavefront, L2 resident) is staged in a wavefront-private LDS
 // region with the same swizzled row layout as the big GEMM (gemm_core.h), so no workgroup barrier is
 // needed before the reduction.
 // Requirements: (K / 64) % (splits * NW) == 0, A and W 16-byte aligned, A smaller than 4 GiB.
 #pragma once
-#include "gemm_core.h"
+#include "gemm_core16.h"
 
 namespace ssd {
 
@@ -34,6 +34,35 @@ constexpr int STREAM_STEP_UNITS = 8 * 64;          // 16-byte units of one (colu
 template <int NW, int DEPTH>
 constexpr size_t gemm_stream_lds_bytes() {
     return (size_t)NW * (DEPTH * 4096 > 8192 ? DEPTH * 4096 : 8192);
+}
+
+// The end of a workgroup whose wavefronts hold partial products of the same 32 x 64 block: each stores its own to LDS as
+// [j][r / 4][lane] float4 (512 of them), then the quarters r / 4 are summed in wavefront order and finished by different
+// wavefronts.  (One wavefront doing all of it was up to 2 us of a launch: 16 greedy steps at 27 rows 23.8 -> 22.3 ms,
+// verification of 116 rows 1.86 -> 1.76 ms.)
+__device__ __forceinline__ void store_partial(float4* dst, const f32x16_t (&acc)[2], int lane) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            dst[(j * 4 + g) * 64 + lane] = make_float4(acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]);
+}
+template <int NW, class Epi>
+__device__ __forceinline__ void finish_quarter(const float4* red, int stride, int q, int row0, int col0, int M, int lane, int split, const Epi& epi) {
+    f32x4_t out[1][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        float4 v[NW];
+#pragma unroll
+        for (int o = 0; o < NW; ++o) v[o] = red[o * stride + (j * 4 + q) * 64 + lane];
+        out[0][j] = (f32x4_t){v[0].x, v[0].y, v[0].z, v[0].w};
+#pragma unroll
+        for (int o = 1; o < NW; ++o) out[0][j] += (f32x4_t){v[o].x, v[o].y, v[o].z, v[o].w};
+    }
+    if constexpr (Epi::WANTS_SPLIT)
+        epi.template operator()<1, 2, Layout32Quarter>(out, row0 + 8 * q, col0, M, lane, split);
+    else
+        epi.template operator()<1, 2, Layout32Quarter>(out, row0 + 8 * q, col0, M, lane);
 }
 
 template <int NW, int DEPTH, bool BF, class Epi>
@@ -105,35 +134,11 @@ gemm_stream_kernel(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, 
             }
     }
 
-    // ---- add the NW partial products in wavefront order: red[wave][j][r/4][lane] float4
+    // ---- add the NW partial products in wavefront order
     __syncthreads();                                         // every wavefront is done with its A region
-    float4* red = reinterpret_cast<float4*>(smem_raw);
-    if (wave != 0) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                red[(wave * 8 + j * 4 + g) * 64 + lane] = make_float4(acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]);
-    }
+    store_partial(reinterpret_cast<float4*>(smem_raw) + wave * 512, acc, lane);
     __syncthreads();
-    if (wave != 0) return;
-    f32x16_t out[1][2];
-    out[0][0] = acc[0];
-    out[0][1] = acc[1];
-#pragma unroll 2
-    for (int w = 1; w < NW; ++w) {                           // few at a time: the reads of one w are 32 registers
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 v = red[(w * 8 + j * 4 + g) * 64 + lane];
-                out[0][j][4 * g] += v.x; out[0][j][4 * g + 1] += v.y; out[0][j][4 * g + 2] += v.z; out[0][j][4 * g + 3] += v.w;
-            }
-    }
-    if constexpr (Epi::WANTS_SPLIT)
-        epi.template operator()<1, 2>(out, 0, tile * 64, M, lane, split);
-    else
-        epi.template operator()<1, 2>(out, 0, tile * 64, M, lane);
+    for (int q = wave; q < 4; q += NW) finish_quarter<NW>(reinterpret_cast<const float4*>(smem_raw), 512, q, 0, tile * 64, M, lane, split, epi);
 }
 
 // The same product for more rows (33..128 and beyond): a workgroup owns 64 columns, 32 R rows and one K split; its NW
@@ -257,39 +262,15 @@ __device__ __forceinline__ void gemm_stream_rows(const f16_t* __restrict__ A, co
         i0 += D;
     } while (i0 < steps);
 
-    // ---- add the NW partial products in wavefront order: red[wave][row block][j][r/4][lane] float4; row block b is
-    // finished by wavefront b % NW
+    // ---- add the NW partial products in wavefront order; the wavefronts share the quarters of the row blocks
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    float4* red = reinterpret_cast<float4*>(smem_raw);
 #pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                red[((wave * R + i) * 8 + j * 4 + g) * 64 + lane] = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+    for (int i = 0; i < R; ++i) store_partial(reinterpret_cast<float4*>(smem_raw) + (wave * R + i) * 512, acc[i], lane);
     __syncthreads();
-    for (int i = wave; i < R; i += NW) {
-        if (row0 + i * 32 >= M) break;
-        f32x16_t out[1][2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) out[0][j][r] = 0.f;
-#pragma unroll 2
-        for (int o = 0; o < NW; ++o)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float4 v = red[((o * R + i) * 8 + j * 4 + g) * 64 + lane];
-                    out[0][j][4 * g] += v.x; out[0][j][4 * g + 1] += v.y; out[0][j][4 * g + 2] += v.z; out[0][j][4 * g + 3] += v.w;
-                }
-        if constexpr (Epi::WANTS_SPLIT)
-            epi.template operator()<1, 2>(out, row0 + i * 32, tile * 64, M, lane, split);
-        else
-            epi.template operator()<1, 2>(out, row0 + i * 32, tile * 64, M, lane);
+    for (int q = wave; q < 4 * R; q += NW) {
+        if (row0 + q * 8 >= M) break;
+        finish_quarter<NW>(reinterpret_cast<const float4*>(smem_raw) + (q / 4) * 512, R * 512, q % 4, row0 + (q / 4) * 32, tile * 64, M, lane, split, epi);
     }
 }
 template <int R, int NW, int D, bool BF, class Epi>
