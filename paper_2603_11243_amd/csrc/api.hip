@@ -690,12 +690,16 @@ int ctc_gate(ssd_ctx* ctx, const void* logits, int dtype, const int32_t* cu_fram
     float* H = frame_entropy ? frame_entropy : reinterpret_cast<float*>(ws + p.H);
     int32_t* arg = frame_argmax ? frame_argmax : reinterpret_cast<int32_t*>(ws + p.arg);
     int32_t* cu_dev = reinterpret_cast<int32_t*>(ws + p.cu);
-    int rc = upload(ctx, cu_frames, cu_dev, (size_t)(B + 1) * 4);
-    if (rc != SSD_OK) return rc;
+    const bool as_args = B <= GATE_MAX_ARG_UTTS;
+    if (!as_args) {
+        const int rc = upload(ctx, cu_frames, cu_dev, (size_t)(B + 1) * 4);
+        if (rc != SSD_OK) return rc;
+    }
     {
         ProfScope ps(ctx, SSD_PROF_GATE);
-        launch_gate(logits, dtype, n_rows, V_ctc, cu_dev, B, blank_id, tau_ctc, H, arg, max_entropy, gate_pass, draft_ctc,
-                    draft_len, ctx->stream);
+        launch_gate_frames(logits, dtype, n_rows, V_ctc, H, arg, ctx->stream);
+        if (as_args) launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
+        else launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
     }
     HIP_TRY(ctx, hipGetLastError());
     return SSD_OK;

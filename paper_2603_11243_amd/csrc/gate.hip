@@ -307,16 +307,26 @@ __global__ void __launch_bounds__(256) gate_frames_generic(const T* __restrict__
 
 // One workgroup (256 threads) per utterance.  The frame range of an utterance is clamped into
 // [0, n_rows], so that prefix sums that were never seen by the host cannot lead outside H / arg / draft.
+// CU: the prefix sums, in device memory (CuArray) or among the kernel's arguments (CuArgs).
+struct CuArray {
+    const int32_t* cu;
+    __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
+};
+struct CuArgs {
+    int32_t cu[GATE_MAX_ARG_UTTS + 1];
+    __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
+};
+template <class CU>
 __global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__ H,
                                                        const int32_t* __restrict__ arg,
-                                                       const int32_t* __restrict__ cu_frames, int n_rows, int blank,
+                                                       const CU cu_frames, int n_rows, int blank,
                                                        float tau, float* __restrict__ max_entropy,
                                                        uint8_t* __restrict__ gate_pass,
                                                        int32_t* __restrict__ draft, int32_t* __restrict__ draft_len) {
     __shared__ int wave_cnt[4];
     __shared__ float wave_max[4];
     const int b = blockIdx.x;
-    const int lo = min(max(cu_frames[b], 0), n_rows), hi = min(max(cu_frames[b + 1], lo), n_rows);
+    const int lo = min(max(cu_frames(b), 0), n_rows), hi = min(max(cu_frames(b + 1), lo), n_rows);
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     float mx = -INFINITY;
     int written = 0;                                   // same value in every thread
@@ -358,7 +368,16 @@ __global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__
 void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* cu_frames_dev, int64_t n_rows, int B, int blank,
                             float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                             hipStream_t st) {
-    hipLaunchKernelGGL(gate_utterances, dim3(B), dim3(256), 0, st, H, arg, cu_frames_dev, (int)n_rows, blank, tau,
+    hipLaunchKernelGGL(gate_utterances<CuArray>, dim3(B), dim3(256), 0, st, H, arg, CuArray{cu_frames_dev}, (int)n_rows, blank, tau,
+                       max_entropy, gate_pass, draft, draft_len);
+}
+
+void launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
+                                 float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
+                                 hipStream_t st) {
+    CuArgs cu;
+    for (int b = 0; b <= B; ++b) cu.cu[b] = cu_frames[b];
+    hipLaunchKernelGGL(gate_utterances<CuArgs>, dim3(B), dim3(256), 0, st, H, arg, cu, (int)n_rows, blank, tau,
                        max_entropy, gate_pass, draft, draft_len);
 }
 
@@ -384,6 +403,7 @@ static void launch_vec(const T* logits, int64_t n_rows, int V, float* H, int32_t
     }
     if (nch <= 1) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 1>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
     else if (nch <= 2) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 2>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
+    else if (nch == 6) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 6>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
     else if (nch <= 4) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 4>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
     else hipLaunchKernelGGL((gate_frames_vec<T, LPR, 8>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
 }
@@ -393,7 +413,10 @@ static void launch_frames(const T* logits, int64_t n_rows, int V, float* H, int3
     constexpr int EPC = Chunk<T>::N;
     const bool vec_ok = (V % EPC == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
     if (vec_ok && V <= 16 * 8 * EPC && V > 0) {
-        if (V <= 16 * 4 * EPC || V > 64 * 4 * EPC / 2) launch_vec<T, 16>(logits, n_rows, V, H, arg, st);
+        // fp32 rows of 321 to 384 scores are six chunks of 16 lanes, at least five sixths of them in use, with every reduction
+        // inside a DPP row; as two chunks of 64 lanes 87 of 128 were (348 scores, 17.6 K frames: the whole gate 17.6 -> 10.8 us
+        // together with the prefix sums as kernel arguments)
+        if (V <= 16 * 4 * EPC || V > 64 * 4 * EPC / 2 || (sizeof(T) == 4 && V > 16 * 5 * EPC && V <= 16 * 6 * EPC)) launch_vec<T, 16>(logits, n_rows, V, H, arg, st);
         else launch_vec<T, 64>(logits, n_rows, V, H, arg, st);
     } else if (vec_ok && V <= 64 * 8 * EPC) {
         launch_vec<T, 64>(logits, n_rows, V, H, arg, st);
@@ -403,12 +426,9 @@ static void launch_frames(const T* logits, int64_t n_rows, int V, float* H, int3
     }
 }
 
-void launch_gate(const void* logits, int dtype, int64_t n_rows, int V, const int32_t* cu_frames_dev, int B,
-                 int blank, float tau, float* H, int32_t* arg, float* max_entropy, uint8_t* gate_pass,
-                 int32_t* draft, int32_t* draft_len, hipStream_t st) {
+void launch_gate_frames(const void* logits, int dtype, int64_t n_rows, int V, float* H, int32_t* arg, hipStream_t st) {
     if (dtype == SSD_BF16) launch_frames<bf16_t>(static_cast<const bf16_t*>(logits), n_rows, V, H, arg, st);
     else launch_frames<float>(static_cast<const float*>(logits), n_rows, V, H, arg, st);
-    launch_gate_utterances(H, arg, cu_frames_dev, n_rows, B, blank, tau, max_entropy, gate_pass, draft, draft_len, st);
 }
 
 }  // namespace ssd

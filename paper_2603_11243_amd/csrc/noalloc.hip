@@ -76,8 +76,9 @@ extern "C" int ctc_gate_noalloc(void* hip_stream, const void* logits, int dtype,
     int32_t* arg = reinterpret_cast<int32_t*>(static_cast<unsigned char*>(base) + (size_t)SSD_NOALLOC_MAX_FRAMES * 4);
     // Both scratch halves are written for every frame below n_frames before they are read (the second
     // kernel reads frames inside [0, n_frames) only), so nothing has to be cleared between calls.
-    ssd::launch_gate(logits, dtype, n_frames, V_ctc, cu_frames_dev, B, blank_id, tau_ctc, H, arg, max_entropy, gate_pass,
-                     draft_ctc, draft_len, static_cast<hipStream_t>(hip_stream));
+    const hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    ssd::launch_gate_frames(logits, dtype, n_frames, V_ctc, H, arg, st);
+    ssd::launch_gate_utterances(H, arg, cu_frames_dev, n_frames, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, st);
     e = hipGetLastError();
     if (e != hipSuccess) return report(err, err_len, SSD_EHIP, "ctc_gate_noalloc: launch: %s", hipGetErrorString(e));
     return SSD_OK;

@@ -11,15 +11,21 @@
 namespace ssd {
 
 // ---- gate.hip
-void launch_gate(const void* logits, int dtype, int64_t n_rows, int V, const int32_t* cu_frames_dev, int B,
-                 int blank, float tau, float* H, int32_t* arg, float* max_entropy, uint8_t* gate_pass,
-                 int32_t* draft, int32_t* draft_len, hipStream_t st);
+// first half of the gate: frame entropies and greedy labels
+void launch_gate_frames(const void* logits, int dtype, int64_t n_rows, int V, float* H, int32_t* arg, hipStream_t st);
 
 // second half of the gate on its own: per-utterance max entropy, threshold test and collapse
 // (frame ranges are clamped into [0, n_rows] on the device)
 void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* cu_frames_dev, int64_t n_rows, int B, int blank,
                             float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                             hipStream_t st);
+
+// The same with the prefix sums in host memory, B <= GATE_MAX_ARG_UTTS: they travel as kernel arguments (1 KB), which spares
+// a small batch its upload (one ten-second utterance: copy 3 us of 12.6 us).
+constexpr int GATE_MAX_ARG_UTTS = 256;
+void launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
+                                 float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
+                                 hipStream_t st);
 
 // ---- ctc_head.hip: output layer of the CTC encoder fused with the frame statistics of the gate
 int ctc_head_groups(int V);      // groups of 64 symbols that hold at least one real symbol
