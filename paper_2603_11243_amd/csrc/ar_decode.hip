@@ -24,7 +24,8 @@ __device__ __forceinline__ void unpack8(const uint4& w, float (&v)[8]) {
 
 // head_dim 128: a workgroup is DEC_WAVES wavefronts and serves one (utterance, G query heads of one K/V head): every
 // cached row is read once for its G heads (one workgroup per query head read each row G times, from whichever XCD it
-// ran on: 21.6 us per launch at 70 utterances of 24 heads over 8, against 8 us for the bytes).  Lane = (key group kg
+// ran on).  Per launch, before and after: 13.2 -> 9.8 us at 27 utterances of 16 heads over 8; at 70 utterances of 24 over 8
+// 21.6 -> 20.7 us, the QKV splits now added here included (206 registers: two workgroups per CU, 560 of them).  Lane = (key group kg
 // of 4, chunk dc of 8 dims).  A block of DEC_KEYS keys is 8 loads of K and 8 of V per lane (the rows are 256 bytes, a
 // 16-lane group reads one row); a score is a 16-lane reduction, the softmax statistics are reduced over the four key
 // groups, and P.V accumulates in the lane, reduced over the key groups at the end.  The wavefronts take the blocks of

@@ -8,9 +8,9 @@
 // The fused weight layouts are produced by pack_qkv_kernel / pack_gate_up_kernel: a column and the
 // column it must be combined with sit 32 packed columns apart inside a group of 64, i.e. in two
 // accumulator blocks of the same lane.
-// Three main loops feed these epilogues: big tiles on v_mfma_f32_16x16x32_f16 (gemm_core16.h), skinny
-// LDS-ring tiles for 33..128 rows (gemm_core.h) and the register-streaming kernel for at most 32 rows
-// (gemm_stream.h).
+// Four main loops feed these epilogues: big tiles on v_mfma_f32_16x16x32_f16 (gemm_core16.h), skinny
+// LDS-ring tiles from 33 rows on (gemm_core.h) and, from the stream layout of the weights, the
+// register-streaming kernels for at most 32 and for 33..128 rows (gemm_stream.h).
 #include <algorithm>
 #include <type_traits>
 

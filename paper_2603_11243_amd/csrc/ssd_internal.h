@@ -108,7 +108,7 @@ void launch_lmhead_f32(const float* hv, const float* w_lm, const int32_t* target
 // row_slot / kc / vc (all or none): rows with row_slot[row] >= 0 also store their rotated k part and their v
 // part into the K/V cache of this layer at that slot
 // W_stream (may be NULL): the same weights in the stream layout of launch_stream_layout, read when at
-// most 32 rows are projected
+// most 128 rows are projected (the rule is in gemm_mfma.hip)
 // rope_rows (may be NULL): rope_tab[pos[row]] gathered per row, [M][64] (cos, sin); read instead of pos and rope_tab
 void launch_gemm_qkv_rope(const uint16_t* A, const uint16_t* Wqkv_packed, const void* W_stream, uint16_t* qkv, const int32_t* pos,
                           const float* rope_tab, int M, int d_model, int d_q, int d_kv, float descale,
