@@ -271,11 +271,36 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(const float* __restrict__
         l = l * alpha + ps;
         m = m_new;
 #pragma unroll
-        for (int c = 0; c < NDB; ++c) {
+        for (int c = 0; c < NDB; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) o[c][r] *= alpha;
+        // In the block of the diagonal the matrix product multiplies values a query must not see by probabilities of 0,
+        // which is only nothing while they are finite.
+        float zero_sum = 0.f;
+        if (kb * 16 >= t.q_start) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][r], p[r], o[c], 0, 0, 0);
+            for (int c = 0; c < NDB; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) zero_sum = fmaf(vf[c][r], 0.f, zero_sum);
+        }
+        if (__any(zero_sum != 0.f)) {                         // an infinite or NaN value: visible keys only, one at a time
+            for (int j = 0; j < 16; ++j) {                    // in the order of the matrix product
+                const int r = j / 4, q = j % 4, key = kb * 16 + 4 * q + r;
+                const float pj = __shfl(r == 0 ? p[0] : r == 1 ? p[1] : r == 2 ? p[2] : p[3], 16 * q + x);
+                if (key > qpos) continue;
+                const float* vr = vbase + (int64_t)min(key, n - 1) * stride + 4 * kq;
+#pragma unroll
+                for (int c = 0; c < NDB; ++c) {
+                    if (16 * c + 4 * kq >= head_dim) continue;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[c][e] = fmaf(pj, vr[16 * c + e], o[c][e]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < NDB; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][r], p[r], o[c], 0, 0, 0);
         }
     }
 #pragma unroll

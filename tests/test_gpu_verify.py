@@ -176,6 +176,43 @@ def test_tiny_f32_causality_and_batch_isolation():
     assert np.array_equal(mod["draft_logp"][:lo], base["draft_logp"][:lo])
 
 
+# draft lengths and poisoned draft positions: the poisoned row is the first, second, ninth and last of a 16-row attention
+# tile, in the first tile and in later ones
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_tiny_f32_non_finite_rows_do_not_reach_earlier_positions(value, head_dim):
+    from workloads.synth import VerifyInputs
+    wl = WORKLOADS["cfg1_tiny_f32"]
+    wl = replace(wl, model=replace(wl.model, head_dim=head_dim))
+    S, P, U, at = [1, 9, 20, 30, 40, 5], [4] * 6, [20, 30, 40, 24, 30, 8], [0, 3, 9, 13, 27, None]
+    rows = [(s + p + a) % 16 for s, p, a in zip(S, P, at) if a is not None]
+    assert rows == [5, 0, 1, 15, 7]
+    cu = lambda a: np.concatenate([[0], np.cumsum(a)]).astype(np.int32)
+    r, poison = np.random.default_rng(3), 5
+    ids = lambda n: r.integers(poison + 1, wl.model.vocab, n).astype(np.int32)
+    vi = VerifyInputs(torch.randn(sum(S), wl.model.d_model, generator=torch.Generator().manual_seed(3)) * 0.02, cu(S), ids(sum(P)),
+                      cu(P), ids(sum(U)), cu(U))
+    w = make_model_weights(wl.model, wl.seed)
+    w["embed"][poison] = value
+    base = _run_gpu(wl, w, vi, 1e-30)
+    assert np.isfinite(base["draft_logp"]).all()
+    for b, a in enumerate(at):
+        if a is not None:
+            vi.draft_ids[vi.cu_draft[b] + a] = poison
+    mod = _run_gpu(wl, w, vi, 1e-30)
+    for b, a in enumerate(at):
+        lo, hi = vi.cu_draft[b], vi.cu_draft[b + 1]
+        end = hi if a is None else lo + a
+        assert np.array_equal(mod["draft_logp"][lo:end], base["draft_logp"][lo:end]), f"utterance {b}"
+        assert np.array_equal(mod["greedy_tok"][lo:end], base["greedy_tok"][lo:end])
+        if a is None:
+            assert mod["accept_len"][b] == U[b]
+            continue
+        assert np.isfinite(mod["draft_logp"][end])               # the poisoned token is scored by the row before it
+        assert not np.isfinite(mod["draft_logp"][end + 1:hi]).any()
+        assert mod["accept_len"][b] == a + 1
+
+
 # ------------------------------------------------------------------ bf16, reduced depth, whole batch
 
 @pytest.mark.parametrize("name,layers,B", [("cfg3_1b_ragged64", 2, 12), ("cfg5_3b_ragged128", 1, 10),
