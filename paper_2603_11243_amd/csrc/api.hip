@@ -202,6 +202,8 @@ QformerPlan plan_qformer(int64_t frames, int64_t utts, int window, int n_q, int 
 
 int attn_tile_rows(int dtype) { return dtype == SSD_BF16 ? 64 : F32_ATTN_ROWS; }
 int head_groups(const ssd_model_cfg& c) { return c.dtype == SSD_BF16 ? lmhead_col_groups(c.vocab) : lmhead_f32_groups(c.vocab); }
+// SSD_FLAG_ACT_OVERFLOW is about the 16-bit operand types: fp32 models raise it nowhere
+int32_t* head_flags(const ssd_ctx* c) { return c->cfg.dtype == SSD_BF16 ? c->dev_flags : nullptr; }
 
 struct VerifyPlan {
     size_t row_src, pos, vrow, row_slot, tiles, meta_bytes;     // metadata block, uploaded in one copy
@@ -1152,7 +1154,7 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
             launch_lmhead_mfma((const uint16_t*)hfin, (const uint16_t*)ctx->lm_head, tok_in, Br, d, m.vocab, part_ms, tgt, part_arg, true, ctx->ds_lm, ctx->bf16_ops, st);
         else
             launch_lmhead_f32((const float*)hfin, (const float*)ctx->lm_head, tok_in, Br, d, m.vocab, part_ms, tgt, part_arg, st);
-        launch_lmhead_finalize(part_ms, tgt, part_arg, head_groups(m), Br, logp, tok_out, ctx->dev_flags, st);
+        launch_lmhead_finalize(part_ms, tgt, part_arg, head_groups(m), Br, logp, tok_out, head_flags(ctx), st);
     }
     HIP_TRY(ctx, hipGetLastError());
     return SSD_OK;
@@ -1188,7 +1190,7 @@ int accept_prefix(ssd_ctx* ctx, const void* h_verify, const int32_t* draft_ids, 
                            part_ms, tgt, part_arg, greedy_tok != nullptr, ctx->ds_lm, ctx->bf16_ops, st);
     else
         launch_lmhead_f32((const float*)h_verify, (const float*)ctx->lm_head, draft_ids, (int)Mv, m.d_model, m.vocab, part_ms, tgt, part_arg, st);
-    launch_lmhead_finalize(part_ms, tgt, part_arg, head_groups(m), (int)Mv, draft_logp, greedy_tok, ctx->dev_flags, st);
+    launch_lmhead_finalize(part_ms, tgt, part_arg, head_groups(m), (int)Mv, draft_logp, greedy_tok, head_flags(ctx), st);
     // ln(tau) in double, rounded once to fp32; tau <= 0 accepts every token
     const float ln_tau = tau_slm > 0.f ? (float)log((double)tau_slm) : -INFINITY;
     launch_accept_scan(draft_logp, cu_dev, Bv, ln_tau, accept_len, all_accepted, st);

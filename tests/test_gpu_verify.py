@@ -213,6 +213,27 @@ def test_tiny_f32_non_finite_rows_do_not_reach_earlier_positions(value, head_dim
         assert mod["accept_len"][b] == a + 1
 
 
+def test_tiny_f32_does_not_raise_the_operand_overflow_flag():
+    """fp32 models have no matrix-core operand type to leave: a likelihood that is not finite is returned as it is."""
+    from paper_2603_11243_amd.binding import Context
+    wl = WORKLOADS["cfg1_tiny_f32"]
+    w = make_model_weights(wl.model, wl.seed)
+    ctx = Context(wl.model, w)
+    try:
+        ctx.reserve(max_tokens=8, max_verify_rows=4, max_utts=1, ar_utts=1, ar_steps=1)
+        ctx.set_kv_cache(16)
+        speech = torch.zeros(3, wl.model.d_model)
+        speech[1] = float("nan")
+        d_ids = _dev([5, 6])
+        hv = ctx.verify_forward(speech.cuda(), [0, 3], _dev([1]), [0, 1], d_ids, [0, 2], kv_start=[0])
+        acc = ctx.accept_prefix(hv, d_ids, [0, 2], 0.1)
+        ctx.ar_fallback([0], [4], _dev([7]), 1)
+        assert not torch.isfinite(acc["draft_logp"]).any()
+        assert ctx.device_flags() == 0
+    finally:
+        ctx.close()
+
+
 # ------------------------------------------------------------------ bf16, reduced depth, whole batch
 
 @pytest.mark.parametrize("name,layers,B", [("cfg3_1b_ragged64", 2, 12), ("cfg5_3b_ragged128", 1, 10),
