@@ -1059,7 +1059,9 @@ int ssd_set_kv_cache(ssd_ctx* ctx, void* dev_ptr, size_t bytes, int64_t slots) {
 
 size_t ssd_ar_workspace_bytes(const ssd_ctx* ctx, int max_utts, int max_steps) {
     if (!ctx || !ctx->has_model || max_utts <= 0 || max_steps <= 0) return 0;
-    return plan_ar(ctx->cfg, max_utts, max_steps).total + 256;
+    // up to SKINNY_MAX_ROWS utterances the plan holds K-split sums of the QKV projection, which a larger one does not
+    const int few = std::min(max_utts, SKINNY_MAX_ROWS);
+    return std::max(plan_ar(ctx->cfg, max_utts, max_steps).total, plan_ar(ctx->cfg, few, max_steps).total) + 256;
 }
 
 int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ctx_len, const int32_t* first_tok,

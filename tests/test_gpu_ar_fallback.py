@@ -10,7 +10,7 @@ from oracle import ssd_oracle as O
 from tests.parity import TOL_LOGP, check_accept_len
 from tests.test_gpu_verify import _dev, _gate_drafts, _tau_for
 from workloads import WORKLOADS, make_ctc_batch, make_model_weights, make_verify_inputs
-from workloads.configs import scaled_down
+from workloads.configs import ModelCfg, scaled_down
 
 pytestmark = pytest.mark.gpu
 
@@ -173,3 +173,28 @@ def test_ar_fallback_bfloat16_operands():
     n_exact = _check_against_oracle(wl, w, vi, tau, n_steps, *res, tol=10 * TOL_LOGP["bf16"])
     print(f"{wl.name}, bfloat16 operands: {n_exact} of {(n_steps + 1) * len(res[1])} generated tokens identical to the oracle's")
     assert n_exact >= (n_steps + 1) * len(res[1]) // 2
+
+
+# The plan for fewer utterances may need more scratch than the one for many (split partial sums), by how much depends on the
+# widths: a workspace of the size reported for `most` has to serve every smaller batch.
+@pytest.mark.parametrize("m", [ModelCfg(1, 256, 2, 1, 128, 256, 512), ModelCfg(1, 512, 4, 1, 128, 256, 512),
+                               ModelCfg(1, 2048, 16, 8, 128, 256, 512), ModelCfg(1, 64, 2, 1, 32, 64, 512, dtype="f32")])
+def test_ar_workspace_covers_smaller_batches(m):
+    from paper_2603_11243_amd.binding import Context
+    w = make_model_weights(m, 90, device="cuda")
+    ctx = Context(m, w)
+    size = lambda n, steps=3: int(ctx._lib.ssd_ar_workspace_bytes(ctx._h, n, steps))
+    sizes = [size(n) for n in range(1, 400)]
+    ctx.set_kv_cache(160 * 8)
+    ctx._kv.zero_()
+
+    def run(Br, bytes_):
+        ctx.set_workspace(torch.empty(bytes_, dtype=torch.uint8, device="cuda"))
+        first = torch.arange(Br, dtype=torch.int32, device="cuda")
+        return ctx.ar_fallback(np.arange(Br) * 8, np.full(Br, 2), first, 3).cpu().numpy()
+
+    for most, Br in [(129, 66), (160, 128), (160, 120), (160, 33), (129, 128), (33, 32)]:
+        got = run(Br, size(most))
+        assert np.array_equal(got, run(Br, 1 << 28))
+    ctx.close()
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
