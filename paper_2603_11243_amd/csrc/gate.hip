@@ -403,8 +403,9 @@ static void launch_vec(const T* logits, int64_t n_rows, int V, float* H, int32_t
     }
     if (nch <= 1) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 1>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
     else if (nch <= 2) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 2>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
-    else if (nch == 6) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 6>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
     else if (nch <= 4) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 4>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
+    // (1028 / 1536 scores, 17.6 K frames, as eight chunks of 64 lanes and as six: 20.0 / 20.4 and 17.1 / 17.4 us)
+    else if (nch <= 6) hipLaunchKernelGGL((gate_frames_vec<T, LPR, 6>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
     else hipLaunchKernelGGL((gate_frames_vec<T, LPR, 8>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
 }
 
@@ -413,10 +414,14 @@ static void launch_frames(const T* logits, int64_t n_rows, int V, float* H, int3
     constexpr int EPC = Chunk<T>::N;
     const bool vec_ok = (V % EPC == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
     if (vec_ok && V <= 16 * 8 * EPC && V > 0) {
-        // fp32 rows of 321 to 384 scores are six chunks of 16 lanes, at least five sixths of them in use, with every reduction
-        // inside a DPP row; as two chunks of 64 lanes 87 of 128 were (348 scores, 17.6 K frames: the whole gate 17.6 -> 10.8 us
-        // together with the prefix sums as kernel arguments)
-        if (V <= 16 * 4 * EPC || V > 64 * 4 * EPC / 2 || (sizeof(T) == 4 && V > 16 * 5 * EPC && V <= 16 * 6 * EPC)) launch_vec<T, 16>(logits, n_rows, V, H, arg, st);
+        // fp32 rows of 257 to 512 scores: as two chunks of 64 lanes up to half of the slots are empty and every reduction
+        // crosses DPP rows, but a lane has little to do and the few rows of a small batch spread over more wavefronts; as six or
+        // eight chunks of 16 lanes four rows share a wavefront.  64 / 16 lanes in us, 260, 348, 384 scores: 250 frames 2.9 / 3.2, 2.9 / 3.2,
+        // 2.9 / 3.0; 2000 frames even; 4000 frames 4.1 / 3.6, 4.3 / 3.7, 4.2 / 3.5; 17.6 K 8.9 / 7.0, 8.9 / 7.3, 9.0 / 6.0; 200 K 62 / 37,
+        // 62 / 42, 64 / 45.  388, 448, 512 scores: 250 frames 2.8 / 3.4, 2.8 / 3.4, 2.7 / 3.2; 8000 frames even; 17.6 K 8.8 / 8.4, 8.9 / 8.1,
+        // 7.7 / 7.3; 200 K 66 / 54, 63 / 51, 60 / 61.
+        const int64_t few = V <= 16 * 6 * EPC ? 2048 : 8192;
+        if (V <= 16 * 4 * EPC || (sizeof(T) == 4 && n_rows > few)) launch_vec<T, 16>(logits, n_rows, V, H, arg, st);
         else launch_vec<T, 64>(logits, n_rows, V, H, arg, st);
     } else if (vec_ok && V <= 64 * 8 * EPC) {
         launch_vec<T, 64>(logits, n_rows, V, H, arg, st);
