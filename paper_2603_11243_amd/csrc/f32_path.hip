@@ -437,6 +437,12 @@ void launch_decode_attn_f32(const float* qkv, const float* kc, const float* vc, 
 // in LDS.  Vocabulary and row count are arbitrary, d a multiple of 16.
 // 1194 -> 9.0 us at 125 rows x 4096 entries: a workgroup per row walked the whole vocabulary with a six-step
 // cross-lane sum per logit, i.e. 125 workgroups with 1024 dependent reductions each.
+// Hidden rows and head are the caller's own buffers and may start at any float: 16-byte loads that are aligned to 4.
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4_unaligned(const float* p) {
+    const f32x4u_t v = *reinterpret_cast<const f32x4u_t*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
 int lmhead_f32_groups(int vocab) { return (vocab + 63) / 64; }
 __global__ void __launch_bounds__(256) lmhead_f32_kernel(const float* __restrict__ hv, const float* __restrict__ w_lm,
                                                          const int32_t* __restrict__ targets, int Mv, int d, int vocab,
@@ -460,9 +466,9 @@ __global__ void __launch_bounds__(256) lmhead_f32_kernel(const float* __restrict
         for (int u = 0; u < U; ++u) {
             const int64_t k = 16 * min(t + u, t1 - 1);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[u][i] = *reinterpret_cast<const float4*>(a_row[i] + k);
+            for (int i = 0; i < 2; ++i) a[u][i] = load4_unaligned(a_row[i] + k);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[u][j] = *reinterpret_cast<const float4*>(w_row[j] + k);
+            for (int j = 0; j < 4; ++j) w[u][j] = load4_unaligned(w_row[j] + k);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {

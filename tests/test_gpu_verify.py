@@ -213,6 +213,35 @@ def test_tiny_f32_non_finite_rows_do_not_reach_earlier_positions(value, head_dim
         assert mod["accept_len"][b] == a + 1
 
 
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_tiny_f32_head_and_hidden_rows_at_any_float(shift):
+    """accept_prefix reads the caller's hidden rows and head in place: neither has to start at a multiple of 16 bytes."""
+    from paper_2603_11243_amd.binding import Context
+    wl = WORKLOADS["cfg1_tiny_f32"]
+    d, n = wl.model.d_model, 37
+    w = make_model_weights(wl.model, wl.seed)
+    h = torch.randn(n, d, generator=torch.Generator().manual_seed(1))
+    ids = _dev(np.arange(n))
+
+    def shifted(t, by):
+        buf = torch.empty(t.numel() + by, device="cuda")
+        return buf[by:].view(t.shape).copy_(t)
+
+    def accept(by):
+        ctx = Context(wl.model, dict(w, lm_head=shifted(w["lm_head"], by)))
+        assert ctx._keep[1].data_ptr() % 16 == 4 * by
+        ctx.reserve(max_tokens=n, max_verify_rows=n, max_utts=1)
+        res = ctx.accept_prefix(shifted(h, by), ids, [0, n], 0.1)
+        res = {k: v.cpu() for k, v in res.items()}
+        ctx.close()
+        return res
+
+    want, got = accept(0), accept(shift)
+    assert torch.isfinite(want["draft_logp"]).all()
+    for k in want:
+        assert torch.equal(want[k], got[k])
+
+
 def test_tiny_f32_does_not_raise_the_operand_overflow_flag():
     """fp32 models have no matrix-core operand type to leave: a likelihood that is not finite is returned as it is."""
     from paper_2603_11243_amd.binding import Context
