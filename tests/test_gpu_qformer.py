@@ -53,6 +53,28 @@ def test_qformer_pool_matches_oracle(name, B, d_out):
     print(f"{wl.name}: {int(hb.cu_frames[-1])} frames -> {int(cu_s[-1])} rows, worst relative row error {worst:.2e}")
 
 
+# 20 column tiles of 64 for scores and values, 48 for the output: both projections pass from the few-row kernels over 64 x 64,
+# 128 x 64 and 64 x 128 tiles to the 256-wide ones, at 128, 768, 1536 and 3264 frames and at 128, 320, 640 and 1344 rows
+@pytest.mark.parametrize("frames", [128, 129, 768, 769, 1536, 1537, 3264, 3265, 6730])
+def test_qformer_pool_frame_counts(frames):
+    from paper_2603_11243_amd.binding import Context
+    g = torch.Generator().manual_seed(frames)
+    h = torch.randn(frames, 1024, generator=g).bfloat16()
+    qw = make_qformer_weights(frames, d_out=3072)
+    cu = np.array([0, 16, frames // 2, frames], dtype=np.int32)
+    ctx = Context()
+    try:
+        ctx.set_qformer(*(qw[k].cuda() for k in ("q_proj", "w_k", "w_v", "w_o")), n_heads=16, window=15)
+        ctx.reserve(max_frames=frames, max_utts=3)
+        got, cu_s = ctx.qformer_pool(h.cuda(), cu)
+        got = got.float().cpu().numpy()
+    finally:
+        ctx.close()
+    ref, cu_ref = O.qformer_window_pool(h, cu, qw["q_proj"], qw["w_k"], qw["w_v"], qw["w_o"], 16, 15)
+    assert np.array_equal(cu_s, cu_ref)
+    _check(got, ref)
+
+
 def test_qformer_pool_argument_errors():
     from paper_2603_11243_amd.binding import Context, SsdError
     ctx = Context()
