@@ -308,7 +308,8 @@ int ssd_set_kv_cache(ssd_ctx *ctx, void *dev_ptr, size_t bytes, int64_t slots);
  * Step t = 0..n_steps-1 feeds token u_t (u_0 = first_tok) at position ctx_len + t, appends its keys and
  * values to the cache and writes u_{t+1} = lowest-index argmax of the next-token distribution to
  * out_tokens[t * Br + b] (dev, [n_steps, Br]).  Stopping at an end-of-sequence token is the caller's
- * business (truncate the row).  Needs ssd_ar_workspace_bytes(ctx, Br, n_steps) bytes of workspace.
+ * business (truncate the row).  Needs ssd_ar_workspace_bytes(ctx, Br, n_steps) bytes of workspace; the size for
+ * max_utts utterances serves every smaller batch.
  * head_dim must be a multiple of 8 (SSD_ESHAPE otherwise). */
 size_t ssd_ar_workspace_bytes(const ssd_ctx *ctx, int max_utts, int max_steps);
 int ar_fallback(ssd_ctx *ctx, int Br, const int32_t *kv_start /*host [Br]*/, const int32_t *ctx_len /*host [Br]*/,

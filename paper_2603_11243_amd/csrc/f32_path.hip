@@ -214,7 +214,8 @@ void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, i
 // S^T = K Q^T leaves a lane with query x and keys 4 kq + r, which is the operand that O^T += V^T P^T wants: the
 // probabilities go from one product to the next in registers.
 // qkv rows: [q heads | k heads | v heads]; head_dim <= 16 NDB and a multiple of 4.
-// 20.4 -> 6.8 us at 285 rows (a wavefront per query read each key row from one lane and the values one key at a time).
+// 20.4 -> 6.8 us at 285 rows (a wavefront per query read each key row from one lane and the values one key at a time);
+// the look at the diagonal block's values is 0.1 us of that launch.
 template <int NDB>
 __global__ void __launch_bounds__(256) attn_f32_kernel(const float* __restrict__ qkv, float* __restrict__ out,
                                                        const AttnTile* __restrict__ tiles, int n_q_heads,

@@ -21,7 +21,7 @@ void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* c
                             hipStream_t st);
 
 // The same with the prefix sums in host memory, B <= GATE_MAX_ARG_UTTS: they travel as kernel arguments (1 KB), which spares
-// a small batch its upload (one ten-second utterance: copy 3 us of 12.6 us).
+// a small batch its upload (one ten-second utterance: 15.2 -> 10.7 us a call).
 constexpr int GATE_MAX_ARG_UTTS = 256;
 void launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
                                  float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
