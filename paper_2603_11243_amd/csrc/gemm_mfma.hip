@@ -701,6 +701,7 @@ static bool try_launch_stream(const f16_t* A, const void* Ws, int M, int N, int 
 //   K splits, 97..128 rows: never faster (O 8.1 / 6.8, down 13.5 / 14.0 and 17.7 / 17.7)
 //   whole QKV sums: the in-workgroup K split is faster (10.4 and 14.8 at 70 rows) while its row tiles of 32 give at most one
 //     workgroup per CU; with 320 of them (116 rows, 5120 columns) 27.5 against 17.5 here with two row tiles of 64
+// (The limits of 12 K steps and 96 column tiles lie between these two widths' figures; no other width was measured.)
 // Two wavefronts per workgroup rather than four: half of the partial products to be added at the end (O at 48 rows 6.8 -> 5.4).
 template <class Epi>
 static bool try_launch_stream_rows(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
