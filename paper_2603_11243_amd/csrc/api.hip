@@ -102,6 +102,8 @@ struct ssd_ctx {
     // projector windows (ssd_set_qformer): fused [scores | values] weight and the output projection, both bf16
     uint16_t* qf_wcat = nullptr;
     uint16_t* qf_wo = nullptr;
+    float qf_ds = 1.f;                       // undoes the scale of qf_wfrag
+    uint16_t* qf_wfrag = nullptr;            // w_v for the projection after the pooling (NULL: shape not served)
     int qf_nq = 0, qf_heads = 0, qf_dh = 0, qf_denc = 0, qf_dout = 0, qf_window = 0;
     void* kv = nullptr;                      // caller-owned K/V cache: [layer][K|V][slots][d_kv] in the activation type
     int64_t kv_slots = 0;
@@ -202,6 +204,10 @@ QformerPlan plan_qformer(int64_t frames, int64_t utts, int window, int n_q, int 
 
 int attn_tile_rows(int dtype) { return dtype == SSD_BF16 ? 64 : F32_ATTN_ROWS; }
 int head_groups(const ssd_model_cfg& c) { return c.dtype == SSD_BF16 ? lmhead_col_groups(c.vocab) : lmhead_f32_groups(c.vocab); }
+// Windows from which the projector's values are projected after the pooling (qformer_values.hip): a workgroup takes 16 of them and some
+// 45 us, however few there are.  us a call, projected before / after, d_out 2048 and 3072: 768 windows 65 / 77 and 66 / 79, 1024 windows
+// 82 / 79 and 87 / 84, 1536 windows 103 / 86 and 111 / 94, 4096 windows 271 / 151 and 297 / 181, 8192 windows 503 / 303 and 566 / 363.
+constexpr int QF_VALUES_MIN_WINDOWS = 1024;
 // SSD_FLAG_ACT_OVERFLOW is about the 16-bit operand types: fp32 models raise it nowhere
 int32_t* head_flags(const ssd_ctx* c) { return c->cfg.dtype == SSD_BF16 ? c->dev_flags : nullptr; }
 
@@ -249,6 +255,14 @@ AcceptPlan plan_accept(const ssd_model_cfg& c, int64_t Mv, int64_t utts) {
     p.part_arg = o; o = align_up(o + (size_t)(g * Mv) * sizeof(int2));
     p.total = o;
     return p;
+}
+
+// the power of two that brings a weight group of largest magnitude mx below 2^14
+float weight_scale(float mx) {
+    if (!(mx > 0.f) || !std::isfinite(mx)) return 1.0f;
+    int ex;
+    frexpf(mx, &ex);                                          // mx < 2^ex
+    return ldexpf(1.0f, std::max(-60, std::min(60, 14 - ex)));
 }
 
 int check_model(ssd_ctx* c, const ssd_model_cfg& m) {
@@ -341,12 +355,7 @@ int ssd_create(ssd_ctx** out, const ssd_model_cfg* cfg, const ssd_weights* w, vo
         if ((e = hipMemcpyAsync(mx.data(), d_max, (size_t)n_groups * 4, hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
             return bail(e, "hipMemcpyAsync(absmax)");
         if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return bail(e, "absmax");
-        for (int g = 0; g < n_groups; ++g) {
-            if (!(mx[g] > 0.f) || !std::isfinite(mx[g])) continue;
-            int ex;
-            frexpf(mx[g], &ex);                               // mx < 2^ex
-            scale[g] = ldexpf(1.0f, std::max(-60, std::min(60, 14 - ex)));   // largest value lands below 2^14
-        }
+        for (int g = 0; g < n_groups; ++g) scale[g] = weight_scale(mx[g]);
     }
     // values that the conversion to half cannot hold exactly are counted (ssd_inexact_weights)
     unsigned long long* d_inexact = nullptr;
@@ -751,9 +760,22 @@ int ssd_set_qformer(ssd_ctx* ctx, const void* q_proj, const void* w_k, const voi
         for (auto& q : ctx->owned) if (q == p) q = nullptr;
         (void)hipFree(p);
     };
-    drop(ctx->qf_wcat); drop(ctx->qf_wo);
-    ctx->qf_wcat = ctx->qf_wo = nullptr; ctx->qf_nq = 0;
-    void *wc = nullptr, *wo = nullptr;
+    drop(ctx->qf_wcat); drop(ctx->qf_wo); drop(ctx->qf_wfrag);
+    ctx->qf_wcat = ctx->qf_wo = ctx->qf_wfrag = nullptr; ctx->qf_nq = 0;
+    void *wc = nullptr, *wo = nullptr, *wf = nullptr;
+    if (qformer_values_supported(n_q, n_heads, d_h, d_enc, window)) {
+        HIP_TRY(ctx, hipMalloc(&wf, (size_t)d_h * d_enc * 2));
+        ctx->owned.push_back(wf);
+        // largest magnitude -> exact power-of-two scale into the range of half, as for the decoder's matrices
+        float mx = 0.f;
+        HIP_TRY(ctx, hipMemsetAsync(wf, 0, 4, ctx->stream));
+        launch_absmax(SSD_BF16, w_v, (int64_t)d_h * d_enc, static_cast<unsigned*>(wf), ctx->stream);
+        HIP_TRY(ctx, hipMemcpyAsync(&mx, wf, 4, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        const float scale = weight_scale(mx);
+        ctx->qf_ds = 1.0f / scale;
+        launch_qformer_value_fragments(static_cast<const uint16_t*>(w_v), d_enc, scale, static_cast<uint16_t*>(wf), ctx->stream);
+    }
     HIP_TRY(ctx, hipMalloc(&wc, (size_t)qformer_cat_rows(d_h) * d_enc * 2));
     ctx->owned.push_back(wc);
     HIP_TRY(ctx, hipMalloc(&wo, (size_t)d_out * d_h * 2));
@@ -763,7 +785,7 @@ int ssd_set_qformer(ssd_ctx* ctx, const void* q_proj, const void* w_k, const voi
     HIP_TRY(ctx, hipMemcpyAsync(wo, w_o, (size_t)d_out * d_h * 2, hipMemcpyDeviceToDevice, ctx->stream));
     HIP_TRY(ctx, hipGetLastError());
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));     // the caller may release its copies on return
-    ctx->qf_wcat = static_cast<uint16_t*>(wc); ctx->qf_wo = static_cast<uint16_t*>(wo);
+    ctx->qf_wcat = static_cast<uint16_t*>(wc); ctx->qf_wo = static_cast<uint16_t*>(wo); ctx->qf_wfrag = static_cast<uint16_t*>(wf);
     ctx->qf_nq = n_q; ctx->qf_heads = n_heads; ctx->qf_dh = d_h; ctx->qf_denc = d_enc; ctx->qf_dout = d_out; ctx->qf_window = window;
     return SSD_OK;
 }
@@ -800,9 +822,15 @@ int qformer_pool(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int 
     const int n_cat = qformer_cat_rows(d_h);
     {
         ProfScope ps(ctx, SSD_PROF_QFORMER);
-        launch_gemm_scores_values(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, vals, (int)n_rows, n_cat, d_enc, d_h,
-                                  ctx->dev_flags, true, ctx->stream);
-        launch_qformer_pool(scores, vals, reinterpret_cast<const QWindow*>(ws + p.wins), n_windows, n_q, ctx->qf_heads, d_h, o, ctx->stream);
+        const QWindow* d_wins = reinterpret_cast<const QWindow*>(ws + p.wins);
+        if (ctx->qf_wfrag && n_windows >= QF_VALUES_MIN_WINDOWS) {
+            launch_gemm_scores(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, (int)n_rows, d_enc, ctx->stream);
+            launch_qformer_values(static_cast<const uint16_t*>(enc_h), scores, ctx->qf_wfrag, ctx->qf_ds, d_wins, n_windows, n_q, d_enc, o, ctx->dev_flags, ctx->stream);
+        } else {
+            launch_gemm_scores_values(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, vals, (int)n_rows, n_cat, d_enc, d_h,
+                                      ctx->dev_flags, true, ctx->stream);
+            launch_qformer_pool(scores, vals, d_wins, n_windows, n_q, ctx->qf_heads, d_h, o, ctx->stream);
+        }
         launch_gemm_store_16(o, ctx->qf_wo, static_cast<uint16_t*>(speech_emb), n_windows * n_q, ctx->qf_dout, d_h, true, ctx->stream);
     }
     HIP_TRY(ctx, hipGetLastError());

@@ -878,6 +878,9 @@ void launch_gemm_scores_values(const uint16_t* A, const uint16_t* W, float* scor
     if (bf16_ops) launch_by_shape(A, W, nullptr, M, N, K, EpiScoresValues<true>{scores, vals, d_h, flags}, st);
     else launch_by_shape(A, W, nullptr, M, N, K, EpiScoresValues<false>{scores, vals, d_h, flags}, st);
 }
+void launch_gemm_scores(const uint16_t* A, const uint16_t* W, float* scores, int M, int K, hipStream_t st) {
+    launch_gemm<128, 64, 4, 1, 3>(A, W, M, QF_SCORE_COLS, K, 1, EpiScoresValues<true>{scores, nullptr, 0, nullptr}, st);
+}
 void launch_gemm_store_16(const uint16_t* A, const uint16_t* W, uint16_t* C, int M, int N, int K, bool bf16_ops, hipStream_t st) {
     if (bf16_ops) launch_by_shape(A, W, nullptr, M, N, K, EpiStore16<true>{C, N}, st);
     else launch_by_shape(A, W, nullptr, M, N, K, EpiStore16<false>{C, N}, st);

@@ -10,6 +10,8 @@
 //                                                         values [frames, d_h] IEEE half
 //   2. per window: softmax over its frames of each score column, weighted sum of the value columns   (here)
 //   3. g [3 windows, d_out] = o w_o^T                      one MFMA GEMM, stored in the storage type of speech_emb
+// Large batches of the usual shape skip the value columns of the product and project the values after the pooling instead
+// (qformer_values.hip; the rule is QF_VALUES_MIN_WINDOWS in api.hip).
 // Windows never cross an utterance; the last window of an utterance may hold fewer frames.
 #include "device_utils.h"
 #include "ssd_internal.h"

@@ -51,6 +51,13 @@ void launch_qformer_fold(const uint16_t* q_proj, const uint16_t* w_k, const uint
 void launch_qformer_pool(const float* scores, const uint16_t* vals, const QWindow* wins, int n_windows, int n_q, int n_heads,
                          int d_h, uint16_t* o, hipStream_t st);
 
+// ---- qformer_values.hip: the same with the values projected after the pooling; for 16 heads of 64 dims, at most 3 queries and
+// windows of at most 16 frames.  w_frag: fragment-ordered copy of w_v [d_h, d_enc] as IEEE half times `scale`, a power of two.
+bool qformer_values_supported(int n_q, int n_heads, int d_h, int d_enc, int window);
+void launch_qformer_value_fragments(const uint16_t* w_v, int d_enc, float scale, uint16_t* w_frag, hipStream_t st);
+void launch_qformer_values(const uint16_t* enc_h, const float* scores, const uint16_t* w_frag, float descale, const QWindow* wins, int n_windows, int n_q,
+                           int d_enc, uint16_t* o, int32_t* flags, hipStream_t st);
+
 // ---- row metadata built on the host for one verify_forward call
 // src code of a decoder row: speech rows hold the speech_emb row index; token rows hold
 // SRC_PROMPT | index into prompt_ids or SRC_DRAFT | index into draft_ids.
@@ -133,6 +140,8 @@ void launch_gemm_swiglu(const uint16_t* A, const uint16_t* Wgu_packed, const voi
 // C = A W^T with W = [64 score rows | d_h value rows | zero rows up to N]: scores [M, 64] fp32, vals [M, d_h] IEEE half (saturating)
 void launch_gemm_scores_values(const uint16_t* A, const uint16_t* W, float* scores, uint16_t* vals, int M, int N, int K, int d_h,
                                int32_t* flags, bool bf16_ops, hipStream_t st);
+// the score rows of the same W alone: scores [M, 64] fp32 (bfloat16 operands)
+void launch_gemm_scores(const uint16_t* A, const uint16_t* W, float* scores, int M, int K, hipStream_t st);
 void launch_gemm_store_16(const uint16_t* A, const uint16_t* W, uint16_t* C, int M, int N, int K, bool bf16_ops, hipStream_t st);
 // second copy of an f16 weight matrix W[N,K] for the few-row kernel (N % 64 == 0, K % 256 == 0)
 bool stream_layout_supported(int N, int K);

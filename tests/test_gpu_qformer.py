@@ -94,3 +94,28 @@ def test_qformer_pool_argument_errors():
             ctx.qformer_pool(h, [0, 30, 30])
     finally:
         ctx.close()
+
+
+# From 1024 windows on the values are projected after the pooling, 16 windows to a workgroup: a last workgroup of 1 and of 15, windows
+# of one and of 16 frames, every query count, encoder widths of one and several steps.  Fewer windows take the other order.
+@pytest.mark.parametrize("n_q,d_enc,window,windows", [(3, 1024, 15, 1025), (3, 64, 15, 1039), (2, 192, 16, 1024), (1, 128, 1, 1040), (3, 128, 4, 1023)])
+def test_qformer_pool_values_after_pooling(n_q, d_enc, window, windows):
+    from paper_2603_11243_amd.binding import Context
+    g = torch.Generator().manual_seed(windows)
+    r = lambda *s: (torch.randn(*s, generator=g) * s[-1] ** -0.5).bfloat16()
+    last = max(1, window // 2)
+    lengths = [window] * 5 + [1] + [window * (windows - 7) + last]      # whole windows, a one-frame window, a short last one
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    h = torch.randn(int(cu[-1]), d_enc, generator=g).bfloat16()
+    q, w_k, w_v, w_o = torch.randn(n_q, 1024, generator=g).bfloat16(), r(1024, d_enc), r(1024, d_enc), r(256, 1024)
+    ctx = Context()
+    try:
+        ctx.set_qformer(q.cuda(), w_k.cuda(), w_v.cuda(), w_o.cuda(), n_heads=16, window=window)
+        ctx.reserve(max_frames=int(cu[-1]), max_utts=len(lengths))
+        got, cu_s = ctx.qformer_pool(h.cuda(), cu)
+        got = got.float().cpu().numpy()
+    finally:
+        ctx.close()
+    ref, cu_ref = O.qformer_window_pool(h, cu, q, w_k, w_v, w_o, 16, window)
+    assert cu_s[-1] == n_q * windows and np.array_equal(cu_s, cu_ref)
+    _check(got, ref)
