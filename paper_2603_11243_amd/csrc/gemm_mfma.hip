@@ -733,7 +733,9 @@ void launch_stream_layout(const uint16_t* w, void* out, int N, int K, hipStream_
 // Tile choice.  All candidates use eight wavefronts as 2 x 4 and a 256-wide tile (N is a multiple
 // of 256 for every GEMM here) on the 16x16x32 matrix instruction; the tile height is picked per launch
 // so that the number of tiles wastes as little of the last round over the 256 CUs as possible:
-// cost = rounds * height / efficiency.
+// cost = rounds * (height * K / efficiency + what a round costs beside its K loop: first loads, epilogue, the burst of stores).
+// The last term is TILE_OVERHEAD row-slices, about eleven slices of the highest tile: 40 K x 3072 outputs of K = 1024 take 290 us
+// in ten rounds of 192 rows and 268 us in eight of 256.
 // With at most 128 rows the job is weight streaming and what counts is the number of weight bytes in
 // flight: at most 32 rows go to the register-streaming kernel when the shape divides evenly, more to its variant
 // with row blocks where that is faster (try_launch_stream_rows); otherwise a skinny 128 x 64 tile (four wavefronts, each 32 rows x 64 columns) with a six-stage LDS ring
@@ -763,11 +765,12 @@ template <class Epi>
 static void launch_big(const f16_t* A, const f16_t* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
     const int heights[3] = {256, 192, 128};
     const double eff[3] = {1.0, 0.97, 0.90};
+    constexpr double TILE_OVERHEAD = 2800;
     int best = 0;
     double best_cost = 1e30;
     for (int c = 0; c < 3; ++c) {
         const long tiles = (long)((M + heights[c] - 1) / heights[c]) * (N / 256);
-        const double cost = (double)((tiles + 255) / 256) * heights[c] / eff[c];
+        const double cost = (double)((tiles + 255) / 256) * (heights[c] / eff[c] * (K / GEMM_BK) + TILE_OVERHEAD);
         if (cost < best_cost - 1e-9) { best_cost = cost; best = c; }
     }
     if (best == 0) launch_gemm16<256, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
