@@ -93,6 +93,7 @@ struct ssd_ctx {
     std::vector<float> ds_qkv, ds_o, ds_gu, ds_down;
     float ds_lm = 1.f;
     float* rope_tab = nullptr;               // [max_positions][head_dim/2] (cos, sin) pairs
+    unsigned* gate_arrived = nullptr;        // rows done per utterance, all zero between calls (launch_gate_fused)
     int32_t* dev_flags = nullptr;            // sticky data-dependent conditions seen by kernels (ssd_device_flags)
     void* ws = nullptr;
     size_t ws_bytes = 0;
@@ -290,6 +291,26 @@ int check_model(ssd_ctx* c, const ssd_model_cfg& m) {
     return SSD_OK;
 }
 
+// Without the counters the gate takes two launches: a failure is none of the caller's, and a stream under capture is left alone.
+void alloc_gate_counters(ssd_ctx* c) {
+    hipStreamCaptureStatus capture;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;       // captures of other streams go on
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    void* p = nullptr;
+    if (hipMalloc(&p, GATE_ARRIVED_BYTES) == hipSuccess && hipMemsetAsync(p, 0, GATE_ARRIVED_BYTES, c->stream) == hipSuccess) {
+        c->owned.push_back(p);
+        c->gate_arrived = static_cast<unsigned*>(p);
+    } else {
+        if (p) (void)hipFree(p);
+        (void)hipGetLastError();
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
+
 }  // namespace
 
 extern "C" {
@@ -464,6 +485,7 @@ int ssd_set_workspace(ssd_ctx* ctx, void* dev_ptr, size_t bytes) {
     if (reinterpret_cast<uintptr_t>(dev_ptr) & 255) return fail(ctx, SSD_EINVAL, "workspace must be 256-byte aligned");
     ctx->ws = dev_ptr;
     ctx->ws_bytes = bytes;
+    if (dev_ptr && !ctx->gate_arrived) alloc_gate_counters(ctx);
     return SSD_OK;
 }
 
@@ -705,9 +727,12 @@ int ctc_gate(ssd_ctx* ctx, const void* logits, int dtype, const int32_t* cu_fram
     }
     {
         ProfScope ps(ctx, SSD_PROF_GATE);
-        launch_gate_frames(logits, dtype, n_rows, V_ctc, H, arg, ctx->stream);
-        if (as_args) launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
-        else launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
+        if (!launch_gate_fused(logits, dtype, cu_frames, n_rows, B, V_ctc, blank_id, tau_ctc, H, arg, max_entropy, gate_pass, draft_ctc, draft_len,
+                               ctx->gate_arrived, ctx->stream)) {
+            launch_gate_frames(logits, dtype, n_rows, V_ctc, H, arg, ctx->stream);
+            if (as_args) launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
+            else launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
+        }
     }
     HIP_TRY(ctx, hipGetLastError());
     return SSD_OK;

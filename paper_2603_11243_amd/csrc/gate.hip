@@ -9,6 +9,8 @@
 //
 // Kernel 2 (gate_utterances): one workgroup per utterance: max_t H_t, threshold test, and a
 // stable compaction of the frames kept by B (not blank, and different from the previous frame).
+//
+// Batches that do not fill the device take both steps in one launch (gate_fused).
 #include "device_utils.h"
 #include "ssd_internal.h"
 
@@ -34,14 +36,11 @@ template <> struct Chunk<bf16_t> {
 
 // Rows are V scores with V*sizeof(T) a multiple of 16; a row has n_chunks <= LPR*NCH chunks.
 // Lane g of a group owns chunks g, g+LPR, g+2*LPR, ...
-template <typename T, int LPR, int NCH>
-__global__ void __launch_bounds__(256) gate_frames_vec(const T* __restrict__ logits, int64_t n_rows,
-                                                       int V, float* __restrict__ H_out,
-                                                       int32_t* __restrict__ arg_out) {
+// out(row, H, arg) is called by one lane per row.
+template <typename T, int LPR, int NCH, class Out>
+__device__ __forceinline__ void frame_vec(const T* __restrict__ logits, int64_t row, int64_t n_rows, int V, Out out) {
     constexpr int EPC = Chunk<T>::N;
-    constexpr int ROWS_PER_BLOCK = 256 / LPR;
     const int g = threadIdx.x % LPR;
-    int64_t row = (int64_t)blockIdx.x * ROWS_PER_BLOCK + threadIdx.x / LPR;
     const bool live = row < n_rows;
     if (!live) row = n_rows - 1;                      // keep the lane group whole for the reductions
     const int n_chunks = V / EPC;
@@ -103,10 +102,14 @@ __global__ void __launch_bounds__(256) gate_frames_vec(const T* __restrict__ log
     S = group_allreduce<LPR>(S, OpSum());
     W = group_allreduce<LPR>(W, OpSum());
     arg = group_allreduce_i<LPR>(arg, OpMinI());
-    if (live && g == 0) {
-        H_out[row] = __logf(S) - W / S;
-        arg_out[row] = arg;
-    }
+    if (live && g == 0) out(row, __logf(S) - W / S, arg);
+}
+template <typename T, int LPR, int NCH>
+__global__ void __launch_bounds__(256) gate_frames_vec(const T* __restrict__ logits, int64_t n_rows,
+                                                       int V, float* __restrict__ H_out,
+                                                       int32_t* __restrict__ arg_out) {
+    frame_vec<T, LPR, NCH>(logits, (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR, n_rows, V,
+                           [&](int64_t row, float H, int arg) { H_out[row] = H; arg_out[row] = arg; });
 }
 
 // bf16 fast path.  A bf16 score widened to fp32 has 16 zero bits at the bottom; the complement of
@@ -143,9 +146,9 @@ __device__ __forceinline__ float group_max_bits(float v) {
     return v;
 }
 
-template <int LPR, int NCH, bool FULL>     // FULL: the row has exactly LPR*NCH chunks (no chunk predicate)
-__global__ void __launch_bounds__(256) gate_frames_bf16_keyed(const bf16_t* __restrict__ logits, int64_t n_rows, int V,
-                                                              float* __restrict__ H_out, int32_t* __restrict__ arg_out) {
+// Row blocks first, first + stride, ... (ONE: the first alone, with no second set of registers); FULL: the row has exactly LPR*NCH chunks (no chunk predicate)
+template <int LPR, int NCH, bool FULL, bool ONE, class Out>
+__device__ __forceinline__ void frames_bf16_keyed(const bf16_t* __restrict__ logits, int64_t n_rows, int V, int64_t first, int64_t stride, Out out) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int ROWS_PER_BLOCK = 256 / LPR;
     constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
@@ -172,17 +175,17 @@ __global__ void __launch_bounds__(256) gate_frames_bf16_keyed(const bf16_t* __re
     };
 
     u32x4 buf0[NCH], buf1[NCH];
-    if ((int64_t)blockIdx.x < n_blocks) load_block(blockIdx.x, buf0);
+    if (first < n_blocks) load_block(first, buf0);
     // two row blocks per trip so that the register sets swap roles without copies
-    for (int64_t blk0 = blockIdx.x; blk0 < n_blocks; blk0 += 2 * (int64_t)gridDim.x) {
+    for (int64_t blk0 = first; blk0 < n_blocks; blk0 += 2 * stride) {
       #pragma unroll
       for (int half = 0; half < 2; ++half) {
-        const int64_t blk = blk0 + half * (int64_t)gridDim.x;
+        const int64_t blk = blk0 + half * stride;
         if (blk >= n_blocks) break;
         u32x4 (&cur)[NCH] = half ? buf1 : buf0;
         u32x4 (&nxt)[NCH] = half ? buf0 : buf1;
-        const int64_t nblk = blk + gridDim.x;
-        if (nblk < n_blocks) load_block(nblk, nxt);
+        const int64_t nblk = blk + stride;
+        if (!ONE && nblk < n_blocks) load_block(nblk, nxt);
         const int64_t row = blk * ROWS_PER_BLOCK + threadIdx.x / LPR;
         const bool live = row < n_rows;
 
@@ -262,12 +265,16 @@ __global__ void __launch_bounds__(256) gate_frames_bf16_keyed(const bf16_t* __re
         }
         S = group_allreduce<LPR>(S, OpSum());
         W2 = group_allreduce<LPR>(W2, OpSum());
-        if (live && g == 0) {
-            H_out[row] = LN2 * (__builtin_amdgcn_logf(S) - W2 / S);
-            arg_out[row] = arg;
-        }
+        if (live && g == 0) out(row, LN2 * (__builtin_amdgcn_logf(S) - W2 / S), arg);
+        if (ONE) return;
       }
     }
+}
+template <int LPR, int NCH, bool FULL>
+__global__ void __launch_bounds__(256) gate_frames_bf16_keyed(const bf16_t* __restrict__ logits, int64_t n_rows, int V,
+                                                              float* __restrict__ H_out, int32_t* __restrict__ arg_out) {
+    frames_bf16_keyed<LPR, NCH, FULL, false>(logits, n_rows, V, blockIdx.x, gridDim.x,
+                                           [&](int64_t row, float H, int arg) { H_out[row] = H; arg_out[row] = arg; });
 }
 
 // Any V, any alignment: one wavefront per row, two passes over memory (second pass hits cache).
@@ -316,42 +323,52 @@ struct CuArgs {
     int32_t cu[GATE_MAX_ARG_UTTS + 1];
     __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
 };
-template <class CU>
-__global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__ H,
-                                                       const int32_t* __restrict__ arg,
-                                                       const CU cu_frames, int n_rows, int blank,
-                                                       float tau, float* __restrict__ max_entropy,
-                                                       uint8_t* __restrict__ gate_pass,
-                                                       int32_t* __restrict__ draft, int32_t* __restrict__ draft_len) {
-    __shared__ int wave_cnt[4];
+// The decision about one utterance and its collapsed path, by 256 threads.  frame(t, H, arg) and symbol(t) read frame t's statistics.
+// 1024 frames a trip: every trip waits for memory once and for the other wavefronts twice (with 256 a trip, 1500 frames were six waits).
+template <class Frame, class Symbol>
+__device__ __forceinline__ void gate_utterance(int b, int lo, int hi, int blank, float tau, float* __restrict__ max_entropy, uint8_t* __restrict__ gate_pass,
+                                               int32_t* __restrict__ draft, int32_t* __restrict__ draft_len, Frame frame, Symbol symbol) {
+    constexpr int AHEAD = 4;
+    __shared__ int wave_cnt[AHEAD][4];
     __shared__ float wave_max[4];
-    const int b = blockIdx.x;
-    const int lo = min(max(cu_frames(b), 0), n_rows), hi = min(max(cu_frames(b + 1), lo), n_rows);
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     float mx = -INFINITY;
     int written = 0;                                   // same value in every thread
-    for (int t0 = lo; t0 < hi; t0 += 256) {
-        const int t = t0 + threadIdx.x;
-        bool keep = false;
-        int a = 0;
-        if (t < hi) {
-            a = arg[t];
-            mx = fmaxf(mx, H[t]);
-            keep = (a != blank) && (t == lo || a != arg[t - 1]);
-        }
-        const unsigned long long mask = __ballot(keep);
-        const int before = __popcll(mask & ((1ull << lane) - 1ull));
-        if (lane == 0) wave_cnt[wave] = __popcll(mask);
-        __syncthreads();
-        int wave_off = 0, total = 0;
+    for (int t0 = lo; t0 < hi; t0 += 256 * AHEAD) {
+        int a[AHEAD], prev[AHEAD];
+        float H[AHEAD];
+        unsigned long long mask[AHEAD];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int c = wave_cnt[w];
-            if (w < wave) wave_off += c;
-            total += c;
+        for (int u = 0; u < AHEAD; ++u) {
+            const int t = min(t0 + u * 256 + (int)threadIdx.x, hi - 1);
+            frame(t, H[u], a[u]);
+            prev[u] = symbol(max(t - 1, lo));
         }
-        if (keep) draft[lo + written + wave_off + before] = a;
-        written += total;
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int t = t0 + u * 256 + threadIdx.x;
+            bool keep = false;
+            if (t < hi) {
+                mx = fmaxf(mx, H[u]);
+                keep = (a[u] != blank) && (t == lo || a[u] != prev[u]);
+            }
+            mask[u] = __ballot(keep);
+            if (lane == 0) wave_cnt[u][wave] = __popcll(mask[u]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            int wave_off = 0, total = 0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int c = wave_cnt[u][w];
+                if (w < wave) wave_off += c;
+                total += c;
+            }
+            const unsigned long long below = (1ull << lane) - 1ull;
+            if (mask[u] >> lane & 1) draft[lo + written + wave_off + __popcll(mask[u] & below)] = a[u];
+            written += total;
+        }
         __syncthreads();
     }
     mx = group_allreduce<64>(mx, OpMax());
@@ -363,6 +380,83 @@ __global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__
         gate_pass[b] = (m < tau) ? 1 : 0;
         draft_len[b] = written;
     }
+}
+template <class CU>
+__global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__ H,
+                                                       const int32_t* __restrict__ arg,
+                                                       const CU cu_frames, int n_rows, int blank,
+                                                       float tau, float* __restrict__ max_entropy,
+                                                       uint8_t* __restrict__ gate_pass,
+                                                       int32_t* __restrict__ draft, int32_t* __restrict__ draft_len) {
+    const int b = blockIdx.x;
+    const int lo = min(max(cu_frames(b), 0), n_rows), hi = min(max(cu_frames(b + 1), lo), n_rows);
+    gate_utterance(b, lo, hi, blank, tau, max_entropy, gate_pass, draft, draft_len,
+                        [&](int t, float& h, int& a) { a = arg[t]; h = H[t]; }, [&](int t) { return arg[t]; });
+}
+
+// ---- Both steps in one launch: the workgroup whose rows complete an utterance finishes it.
+// A small call is bound by the host's two launches (8.8 us; of one, 6.5), not by what they do.  Every workgroup does one block of
+// rows, stores the frames' statistics write-through, waits for the stores, and adds the rows it did to a count per utterance; whoever
+// brings a count to the utterance's length reads the statistics past L1 and L2, decides, compacts, and clears the count for the
+// next call.  Nobody waits for anybody.  (No agent-scope fences: they write back and invalidate a whole L2.)
+// us a call, two launches / one: one utterance of 250 frames of 512 bf16 scores 9.9 / 7.0, 64 of 100 10.3 / 7.1, 32 of 500 9.9 / 7.2,
+// 64 of 250 frames of 348 fp32 scores 10.0 / 8.3.
+// Where the one launch stays the faster: up to 24 MiB of scores, because a row block pays for its stores and the count with waits
+// that only pay off while the device waits for the host (two / one launch in us: 512 bf16 scores 64 x 250 frames 9.9 / 7.3, 64 x 400
+// [25 MiB] 9.9 / 8.4, 128 x 250 [31 MiB] 10.5 / 10.2; 348 fp32 scores 32 x 500 [21 MiB] 10.0 / 8.1, 32 x 750 [31 MiB] 11.0 / 10.5,
+// 256 x 100 [33 MiB] 10.4 / 12.3); up to 192 workgroups an utterance, because additions to one count go one after the other (512 fp32
+// scores, four frames a workgroup: 2 x 750 frames 9.8 / 7.3, 8 x 750 9.8 / 9.1, 8 x 1000 9.9 / 11.0, 1 x 3000 11.5 / 14.9); and as many
+// workgroups as have a place in the arguments.
+constexpr int64_t GATE_FUSED_MAX_BYTES = (int64_t)24 << 20;
+constexpr int GATE_FUSED_MAX_BLOCKS = 2048, GATE_FUSED_MAX_UTT_BLOCKS = 192;
+constexpr int ARRIVED_STRIDE = GATE_ARRIVED_BYTES / GATE_MAX_ARG_UTTS / 4;
+struct GateTail {
+    uint8_t first[GATE_FUSED_MAX_BLOCKS];      // the utterance of a workgroup's first row.  No utterance has fewer rows than a workgroup, which so has rows of two at most
+    int32_t cu[GATE_MAX_ARG_UTTS + 1];
+    int blank;
+    float tau;
+    float* max_entropy; uint8_t* gate_pass; int32_t* draft; int32_t* draft_len;
+    unsigned* arrived;
+};
+template <class V> __device__ __forceinline__ void store_shared(V* p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class V> __device__ __forceinline__ V load_shared(const V* p) { return __hip_atomic_load(const_cast<V*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T, int LPR, int NCH>
+__global__ void __launch_bounds__(256) gate_fused(const T* __restrict__ logits, int n_rows, int V, float* H, int32_t* arg, const GateTail g) {
+    constexpr int ROWS = 256 / LPR;
+    const int row0 = blockIdx.x * ROWS, end = min(row0 + ROWS, n_rows);
+    const int b0 = g.first[blockIdx.x], lo = g.cu[b0], mid = g.cu[b0 + 1];
+    auto out = [&](int64_t row, float h, int a) {
+        store_shared(H + row, h);
+        store_shared(arg + row, (int32_t)a);
+    };
+    if constexpr (sizeof(T) == 2) {
+        if (V / 8 == LPR * NCH) frames_bf16_keyed<LPR, NCH, true, true>(logits, n_rows, V, blockIdx.x, gridDim.x, out);
+        else frames_bf16_keyed<LPR, NCH, false, true>(logits, n_rows, V, blockIdx.x, gridDim.x, out);
+    } else {
+        frame_vec<T, LPR, NCH>(logits, row0 + threadIdx.x / LPR, n_rows, V, out);
+    }
+
+    __shared__ int complete_s[2];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // stored
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const bool second = threadIdx.x == 1;
+        const int mine = second ? end - mid : min(mid, end) - row0;
+        bool complete = false;
+        if (mine > 0) {
+            unsigned* n = g.arrived + (b0 + second) * ARRIVED_STRIDE;
+            const int length = second ? g.cu[b0 + 2] - mid : mid - lo;
+            complete = __hip_atomic_fetch_add(n, (unsigned)mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine == (unsigned)length;
+            if (complete) store_shared(n, 0u);
+        }
+        complete_s[threadIdx.x] = complete;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int u = 0; u < 2; ++u)
+        if (__builtin_amdgcn_readfirstlane(complete_s[u]))
+            gate_utterance(b0 + u, g.cu[b0 + u], g.cu[b0 + u + 1], g.blank, g.tau, g.max_entropy, g.gate_pass, g.draft, g.draft_len,
+                           [&](int t, float& h, int& a) { a = load_shared(arg + t); h = load_shared(H + t); }, [&](int t) { return load_shared(arg + t); });
 }
 
 void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* cu_frames_dev, int64_t n_rows, int B, int blank,
@@ -409,23 +503,27 @@ static void launch_vec(const T* logits, int64_t n_rows, int V, float* H, int32_t
     else hipLaunchKernelGGL((gate_frames_vec<T, LPR, 8>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
 }
 
+// Lanes that share a row in the vectorised kernels, 16 or 64; 0: the row length or the alignment takes the general one.
+template <typename T>
+static int vec_lanes(const T* logits, int64_t n_rows, int V) {
+    constexpr int EPC = Chunk<T>::N;
+    if (V <= 0 || V % EPC || (reinterpret_cast<uintptr_t>(logits) & 15) || V > 64 * 8 * EPC) return 0;
+    if (V > 16 * 8 * EPC) return 64;
+    // fp32 rows of 257 to 512 scores: as two chunks of 64 lanes up to half of the slots are empty and every reduction
+    // crosses DPP rows, but a lane has little to do and the few rows of a small batch spread over more wavefronts; as six or
+    // eight chunks of 16 lanes four rows share a wavefront.  64 / 16 lanes in us, 260, 348, 384 scores: 250 frames 2.9 / 3.2, 2.9 / 3.2,
+    // 2.9 / 3.0; 2000 frames even; 4000 frames 4.1 / 3.6, 4.3 / 3.7, 4.2 / 3.5; 17.6 K 8.9 / 7.0, 8.9 / 7.3, 9.0 / 6.0; 200 K 62 / 37,
+    // 62 / 42, 64 / 45.  388, 448, 512 scores: 250 frames 2.8 / 3.4, 2.8 / 3.4, 2.7 / 3.2; 8000 frames even; 17.6 K 8.8 / 8.4, 8.9 / 8.1,
+    // 7.7 / 7.3; 200 K 66 / 54, 63 / 51, 60 / 61.
+    const int64_t few = V <= 16 * 6 * EPC ? 2048 : 8192;
+    return V <= 16 * 4 * EPC || (sizeof(T) == 4 && n_rows > few) ? 16 : 64;
+}
 template <typename T>
 static void launch_frames(const T* logits, int64_t n_rows, int V, float* H, int32_t* arg, hipStream_t st) {
-    constexpr int EPC = Chunk<T>::N;
-    const bool vec_ok = (V % EPC == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
-    if (vec_ok && V <= 16 * 8 * EPC && V > 0) {
-        // fp32 rows of 257 to 512 scores: as two chunks of 64 lanes up to half of the slots are empty and every reduction
-        // crosses DPP rows, but a lane has little to do and the few rows of a small batch spread over more wavefronts; as six or
-        // eight chunks of 16 lanes four rows share a wavefront.  64 / 16 lanes in us, 260, 348, 384 scores: 250 frames 2.9 / 3.2, 2.9 / 3.2,
-        // 2.9 / 3.0; 2000 frames even; 4000 frames 4.1 / 3.6, 4.3 / 3.7, 4.2 / 3.5; 17.6 K 8.9 / 7.0, 8.9 / 7.3, 9.0 / 6.0; 200 K 62 / 37,
-        // 62 / 42, 64 / 45.  388, 448, 512 scores: 250 frames 2.8 / 3.4, 2.8 / 3.4, 2.7 / 3.2; 8000 frames even; 17.6 K 8.8 / 8.4, 8.9 / 8.1,
-        // 7.7 / 7.3; 200 K 66 / 54, 63 / 51, 60 / 61.
-        const int64_t few = V <= 16 * 6 * EPC ? 2048 : 8192;
-        if (V <= 16 * 4 * EPC || (sizeof(T) == 4 && n_rows > few)) launch_vec<T, 16>(logits, n_rows, V, H, arg, st);
-        else launch_vec<T, 64>(logits, n_rows, V, H, arg, st);
-    } else if (vec_ok && V <= 64 * 8 * EPC) {
-        launch_vec<T, 64>(logits, n_rows, V, H, arg, st);
-    } else {
+    const int lanes = vec_lanes(logits, n_rows, V);
+    if (lanes == 16) launch_vec<T, 16>(logits, n_rows, V, H, arg, st);
+    else if (lanes == 64) launch_vec<T, 64>(logits, n_rows, V, H, arg, st);
+    else {
         const unsigned grid = (unsigned)((n_rows + 3) / 4);
         hipLaunchKernelGGL((gate_frames_generic<T>), dim3(grid), dim3(256), 0, st, logits, n_rows, V, H, arg);
     }
@@ -434,6 +532,49 @@ static void launch_frames(const T* logits, int64_t n_rows, int V, float* H, int3
 void launch_gate_frames(const void* logits, int dtype, int64_t n_rows, int V, float* H, int32_t* arg, hipStream_t st) {
     if (dtype == SSD_BF16) launch_frames<bf16_t>(static_cast<const bf16_t*>(logits), n_rows, V, H, arg, st);
     else launch_frames<float>(static_cast<const float*>(logits), n_rows, V, H, arg, st);
+}
+
+template <typename T, int LPR>
+static void launch_fused(const T* logits, int64_t n_rows, int V, float* H, int32_t* arg, const GateTail& tail, hipStream_t st) {
+    const int nch = (V / Chunk<T>::N + LPR - 1) / LPR;
+    const unsigned grid = (unsigned)((n_rows + (256 / LPR) - 1) / (256 / LPR));
+#define SSD_FUSED(NCH_) hipLaunchKernelGGL((gate_fused<T, LPR, NCH_>), dim3(grid), dim3(256), 0, st, logits, (int)n_rows, V, H, arg, tail)
+    if (nch <= 1) SSD_FUSED(1);
+    else if (nch <= 2) SSD_FUSED(2);
+    else if (nch <= 4) SSD_FUSED(4);
+    else {
+        if constexpr (sizeof(T) == 4) {
+            if (nch <= 6) { SSD_FUSED(6); return; }
+        }
+        SSD_FUSED(8);
+    }
+#undef SSD_FUSED
+}
+bool launch_gate_fused(const void* logits, int dtype, const int32_t* cu_frames, int64_t n_rows, int B, int V, int blank, float tau, float* H, int32_t* arg,
+                       float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len, unsigned* arrived, hipStream_t st) {
+    const int lanes = dtype == SSD_BF16 ? vec_lanes(static_cast<const bf16_t*>(logits), n_rows, V) : vec_lanes(static_cast<const float*>(logits), n_rows, V);
+    if (!arrived || B > GATE_MAX_ARG_UTTS || !lanes) return false;
+    const int rows = 256 / lanes;
+    if (n_rows > (int64_t)rows * GATE_FUSED_MAX_BLOCKS || n_rows * V * (dtype == SSD_BF16 ? 2 : 4) > GATE_FUSED_MAX_BYTES) return false;
+    GateTail tail;
+    int block = 0;
+    tail.cu[0] = 0;
+    for (int b = 0; b < B; ++b) {
+        const int length = cu_frames[b + 1] - cu_frames[b];
+        if (length < rows || length > rows * GATE_FUSED_MAX_UTT_BLOCKS) return false;
+        tail.cu[b + 1] = cu_frames[b + 1];
+        for (; block * rows < cu_frames[b + 1]; ++block) tail.first[block] = (uint8_t)b;
+    }
+    tail.blank = blank; tail.tau = tau;
+    tail.max_entropy = max_entropy; tail.gate_pass = gate_pass; tail.draft = draft; tail.draft_len = draft_len; tail.arrived = arrived;
+    if (dtype == SSD_BF16) {
+        if (lanes == 16) launch_fused<bf16_t, 16>(static_cast<const bf16_t*>(logits), n_rows, V, H, arg, tail, st);
+        else launch_fused<bf16_t, 64>(static_cast<const bf16_t*>(logits), n_rows, V, H, arg, tail, st);
+    } else {
+        if (lanes == 16) launch_fused<float, 16>(static_cast<const float*>(logits), n_rows, V, H, arg, tail, st);
+        else launch_fused<float, 64>(static_cast<const float*>(logits), n_rows, V, H, arg, tail, st);
+    }
+    return true;
 }
 
 }  // namespace ssd

@@ -27,6 +27,12 @@ void launch_gate_utterances_host(const float* H, const int32_t* arg, const int32
                                  float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                                  hipStream_t st);
 
+// Frames and utterances in one launch for batches of few enough frames; false: not served, nothing was launched.  arrived:
+// GATE_ARRIVED_BYTES of zeros, which the call leaves as zeros.
+constexpr int GATE_ARRIVED_BYTES = GATE_MAX_ARG_UTTS * 64;
+bool launch_gate_fused(const void* logits, int dtype, const int32_t* cu_frames, int64_t n_rows, int B, int V, int blank, float tau, float* H, int32_t* arg,
+                       float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len, unsigned* arrived, hipStream_t st);
+
 // ---- ctc_head.hip: output layer of the CTC encoder fused with the frame statistics of the gate
 int ctc_head_groups(int V);      // groups of 64 symbols that hold at least one real symbol
 int ctc_head_padded(int V);      // symbol count after padding

@@ -28,3 +28,66 @@ def test_fp32_rows_around_chunk_counts(ctx, V, n):  # noqa: F811
     logits[6] = torch.round(logits[6])                      # ties
     logits[n - 1, V - 1] = logits[n - 2, V - 1] = 20        # the last score of the last rows
     _run_and_compare(ctx, logits, [0, 1, 17, n], 0, 3.0)
+
+
+# one launch for both steps: utterances around a workgroup's 16 or 4 rows (one row fewer takes two launches), around the 192
+# workgroups an utterance may have and the 2048 of a call, around 24 MiB, and through the 1024 frames a trip of the collapse.  Long
+# and short ones in turn, so that every call finds the counts as the one before left them.
+@pytest.mark.parametrize("dtype,V,rows", [("bfloat16", 512, 16), ("bfloat16", 40, 16), ("bfloat16", 1024, 4), ("float32", 256, 16), ("float32", 348, 4)])
+def test_one_launch_around_its_limits(ctx, dtype, V, rows):  # noqa: F811
+    long = rows * 192                                       # 1024 frames are more than that at four rows
+    for T in ([rows], [rows - 1, rows], [rows, rows + 1, 2 * rows - 1, 2 * rows], [long, rows], [long + 1, rows], [1023, 1024, 1025],
+              [rows] * 256, [rows + 3] * 257, [rows * 8] * 256, [rows * 8] * 255 + [rows * 8 + 1]):
+        cu = np.concatenate([[0], np.cumsum(T)])
+        g = torch.Generator().manual_seed(len(T) + T[0])
+        z = torch.randn(int(cu[-1]), V, generator=g) * 3
+        lab = torch.randint(0, V, (len(z) // 3 + 1,), generator=g).repeat_interleave(3)[: len(z)]
+        lab[torch.rand(len(z), generator=g) < 0.4] = 7
+        z[torch.arange(len(z)), lab] += 12
+        z = z.to(getattr(torch, dtype))
+        z[len(z) // 2] = -float("inf")
+        z[len(z) // 2, V - 1] = 0
+        _run_and_compare(ctx, z, cu, 7, 0.7)
+
+
+@pytest.mark.parametrize("n", [24576 - 16, 24576, 24576 + 16])
+def test_one_launch_around_its_bytes(ctx, n):  # noqa: F811
+    z = torch.randn(n, 512, generator=torch.Generator().manual_seed(n)) * 3
+    _run_and_compare(ctx, z.to(torch.bfloat16), np.linspace(0, n, 65).astype(np.int32), 0, 2.0)
+
+
+def test_one_launch_in_a_graph(ctx):  # noqa: F811
+    """Replays next to eager calls of other sizes that use the same counts."""
+    T = [40, 300, 16, 700]
+    cu = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
+    g = torch.Generator().manual_seed(5)
+    z = (torch.randn(int(cu[-1]), 348, generator=g) * 3).cuda()
+    other = (torch.randn(640, 348, generator=g) * 3).cuda()
+    ctx.reserve(max_frames=4096, max_utts=64)
+    want = {k: v.clone() for k, v in ctx.ctc_gate(z, cu, 0, 2.0, want_frames=True).items()}
+    out = {k: torch.zeros_like(v) for k, v in want.items()}
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    from paper_2603_11243_amd.binding import Context
+    c = Context(stream=side)
+    try:
+        c.reserve(max_frames=4096, max_utts=64)
+        with torch.cuda.graph(graph, stream=side):
+            c.ctc_gate(z, cu, 0, 2.0, out=out)
+        for i in range(4):
+            for v in out.values():
+                v.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for u in range(len(T)):
+                n = int(want["draft_len"][u])
+                assert torch.equal(out["draft_ctc"][cu[u]:cu[u] + n], want["draft_ctc"][cu[u]:cu[u] + n]), (i, u)
+            for k in want:
+                if k != "draft_ctc":
+                    assert torch.equal(out[k], want[k]), (i, k)
+            c.ctc_gate(other, np.arange(0, 641, 64 >> (i % 2)).astype(np.int32), 0, 2.0)
+            torch.cuda.synchronize()
+    finally:
+        c.close()
