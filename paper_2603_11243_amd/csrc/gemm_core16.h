@@ -13,7 +13,8 @@
 // block it holds column l % 16 and rows 4 (l / 16) + r in register r = 0..3.
 // A 64-wide K slice is two such steps.  A wavefront tile of WTM x WTN is (WTM/16) x (WTN/16) blocks; the
 // A fragments of a step are read in two halves (upper and lower row blocks), so that the pipeline has
-// four phases per slice like the 32x32x16 loop and 16 fragments live at a time:
+// four phases per slice like the 32x32x16 loop and 16 fragments live at a time (an odd number of row blocks leaves the
+// upper half one short):
 //   phase (s, lower): MFMAs of the lower row blocks of step s   | reads: upper A fragments of step s
 //   phase (s, upper): MFMAs of the upper row blocks of step s   | reads: lower A and all W fragments of step s+1
 // The barrier that ends a slice sits before the last phase, which also issues the refill loads.
@@ -68,15 +69,17 @@ struct GemmTile16 {
     static constexpr int WAVES = WAVES_M * WAVES_N;
     static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
     static constexpr int TM = WTM / 16, TN = WTN / 16;
-    static constexpr int TH = TM / 2;                        // row blocks per half
-    static constexpr int A_LOADS = BM / (8 * WAVES);         // 1 KB (8 rows) per wavefront load instruction
+    static constexpr int TH0 = (TM + 1) / 2, TH1 = TM / 2;   // row blocks of the lower and the upper half
+    static constexpr int A_LOADS = (BM + 8 * WAVES - 1) / (8 * WAVES);    // 1 KB (8 rows) per wavefront load instruction
     static constexpr int B_LOADS = BN / (8 * WAVES);
-    static constexpr int A_BYTES = BM * GEMM_ROW_BYTES, B_BYTES = BN * GEMM_ROW_BYTES;
+    static constexpr int A_ROWS = A_LOADS * 8 * WAVES;       // rows of LDS: every wavefront issues the same number of loads, whatever BM
+    static constexpr int A_BYTES = A_ROWS * GEMM_ROW_BYTES, B_BYTES = BN * GEMM_ROW_BYTES;
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-    static_assert(BM % (8 * WAVES) == 0 && BN % (8 * WAVES) == 0, "tile/thread mismatch");
-    static_assert(WTM % 32 == 0 && WTN % 16 == 0, "wave tile: an even number of 16-row blocks, 16-column blocks");
+    static constexpr size_t LDS_BYTES = (size_t)NSTAGE * STAGE_BYTES;
+    static_assert(BN % (8 * WAVES) == 0, "tile/thread mismatch");
+    static_assert(WTM % 16 == 0 && WTN % 16 == 0 && TH1 >= 1, "wave tile: at least two 16-row blocks, 16-column blocks");
 
-    // acc is accumulated onto.  smem: gemm_lds_bytes<BM,BN,2>() bytes, 16-byte aligned.  K slices kt0 <= kt < kt1.
+    // acc is accumulated onto.  smem: LDS_BYTES bytes, 16-byte aligned.  K slices kt0 <= kt < kt1.
     static __device__ __forceinline__ void run(const f16_t* __restrict__ A, const f16_t* __restrict__ W, int M, int K,
                                                int m0, int n0, int kt0, int kt1, unsigned char* smem,
                                                f32x4_t (&acc)[TM][TN]) {
@@ -91,7 +94,9 @@ struct GemmTile16 {
 #pragma unroll
         for (int i = 0; i < A_LOADS; ++i) {
             const int r = (i * WAVES + wave) * 8 + lrow;
-            a_off[i] = (unsigned)min(m0 + r, M - 1) * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
+            // rows of LDS beyond the tile are read by nobody: one cache line fills them
+            a_off[i] = A_ROWS == BM || r < BM ? (unsigned)min(m0 + r, M - 1) * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16)
+                                              : (unsigned)min(m0, M - 1) * (unsigned)K * 2u + (unsigned)(lslot * 16);
         }
 #pragma unroll
         for (int i = 0; i < B_LOADS; ++i) {
@@ -119,30 +124,32 @@ struct GemmTile16 {
             a_rd[s] = (wm * WTM + lane % 16) * GEMM_ROW_BYTES + slot * 16;
             b_rd[s] = A_BYTES + (wn * WTN + lane % 16) * GEMM_ROW_BYTES + slot * 16;
         }
-        auto read_a = [&](int stage, int s, int half, f16x8_t (&a)[TH]) {
-            const unsigned char* sbase = smem + stage * STAGE_BYTES + a_rd[s] + half * TH * 16 * GEMM_ROW_BYTES;
+        auto read_a = [&](int stage, int s, auto half, auto& a) {
+            const unsigned char* sbase = smem + stage * STAGE_BYTES + a_rd[s] + half * TH0 * 16 * GEMM_ROW_BYTES;
 #pragma unroll
-            for (int i = 0; i < TH; ++i) a[i] = as_f16x8(*reinterpret_cast<const uint4*>(sbase + i * 16 * GEMM_ROW_BYTES));
+            for (int i = 0; i < (half ? TH1 : TH0); ++i) a[i] = as_f16x8(*reinterpret_cast<const uint4*>(sbase + i * 16 * GEMM_ROW_BYTES));
         };
         auto read_b = [&](int stage, int s, f16x8_t (&b)[TN]) {
             const unsigned char* sbase = smem + stage * STAGE_BYTES + b_rd[s];
 #pragma unroll
             for (int j = 0; j < TN; ++j) b[j] = as_f16x8(*reinterpret_cast<const uint4*>(sbase + j * 16 * GEMM_ROW_BYTES));
         };
-        auto mfma_half = [&](int half, const f16x8_t (&a)[TH], const f16x8_t (&b)[TN]) {
+        auto mfma_half = [&](auto half, const auto& a, const f16x8_t (&b)[TN]) {
 #pragma unroll
-            for (int i = 0; i < TH; ++i)
+            for (int i = 0; i < (half ? TH1 : TH0); ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    acc[half * TH + i][j] = SWAP ? mfma_16x16x32<BF16>(b[j], a[i], acc[half * TH + i][j])
-                                                 : mfma_16x16x32<BF16>(a[i], b[j], acc[half * TH + i][j]);
+                    acc[half * TH0 + i][j] = SWAP ? mfma_16x16x32<BF16>(b[j], a[i], acc[half * TH0 + i][j])
+                                                  : mfma_16x16x32<BF16>(a[i], b[j], acc[half * TH0 + i][j]);
         };
+        const std::integral_constant<int, 0> lower;
+        const std::integral_constant<int, 1> upper;
         // scheduling patterns: one MFMA, one LDS read, for the first n_reads MFMAs of a phase
-        constexpr int PH = TH * TN;                          // MFMAs per phase
-        auto interleave_reads = [&](auto n_reads_c) {
+        constexpr int PH = TH1 * TN;                         // MFMAs of an upper phase
+        auto interleave_reads = [&](auto half, auto n_reads_c) {
             constexpr int NR = decltype(n_reads_c)::value;
 #pragma unroll
-            for (int q = 0; q < PH; ++q) {
+            for (int q = 0; q < (half ? TH1 : TH0) * TN; ++q) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (q < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
@@ -150,34 +157,34 @@ struct GemmTile16 {
         constexpr int NL = A_LOADS + B_LOADS;
         constexpr int HALF = PH / 2;
         constexpr int LOADS_PER_MFMA = (NL + HALF - 1) / HALF;
-        constexpr int READS_PER_MFMA = (TH + TN + HALF - 1) / HALF;
+        constexpr int READS_PER_MFMA = (TH0 + TN + HALF - 1) / HALF;
 
         const int n = kt1 - kt0;
-        f16x8_t alo[TH], ahi[TH], b0[TN], b1[TN];
+        f16x8_t alo[TH0], ahi[TH1], b0[TN], b1[TN];
 #pragma unroll
         for (int s = 0; s < NSTAGE; ++s)
             if (s < n) issue_loads(kt0 + s, s);
         if (n >= NSTAGE) __builtin_amdgcn_s_waitcnt(0x0F70 | (NL & 15) | ((NL >> 4) << 14)); else __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
-        read_a(0, 0, 0, alo);
+        read_a(0, 0, lower, alo);
         read_b(0, 0, b0);
 
         int stage = 0;
         auto slice = [&](auto steady, int i) {
             constexpr bool STEADY = decltype(steady)::value;
             __builtin_amdgcn_sched_barrier(0);
-            read_a(stage, 0, 1, ahi);                        // phase (0, lower)
-            mfma_half(0, alo, b0);
-            interleave_reads(std::integral_constant<int, TH>());
+            read_a(stage, 0, upper, ahi);                        // phase (0, lower)
+            mfma_half(lower, alo, b0);
+            interleave_reads(lower, std::integral_constant<int, TH1>());
             __builtin_amdgcn_sched_barrier(0);
-            read_a(stage, 1, 0, alo);                        // phase (0, upper)
+            read_a(stage, 1, lower, alo);                        // phase (0, upper)
             read_b(stage, 1, b1);
-            mfma_half(1, ahi, b0);
-            interleave_reads(std::integral_constant<int, TH + TN>());
+            mfma_half(upper, ahi, b0);
+            interleave_reads(upper, std::integral_constant<int, TH0 + TN>());
             __builtin_amdgcn_sched_barrier(0);
-            read_a(stage, 1, 1, ahi);                        // phase (1, lower)
-            mfma_half(0, alo, b1);
-            interleave_reads(std::integral_constant<int, TH>());
+            read_a(stage, 1, upper, ahi);                        // phase (1, lower)
+            mfma_half(lower, alo, b1);
+            interleave_reads(lower, std::integral_constant<int, TH1>());
             __builtin_amdgcn_sched_barrier(0);
             // all reads of `stage` are issued; wait for them and for slice i+1 (its loads are the oldest)
             const int next = 1 - stage;
@@ -185,9 +192,9 @@ struct GemmTile16 {
             __syncthreads();
             if constexpr (STEADY) {                          // phase (1, upper) with the refill and the next slice's first reads
                 issue_loads(kt0 + i + NSTAGE, stage);
-                read_a(next, 0, 0, alo);
+                read_a(next, 0, lower, alo);
                 read_b(next, 0, b0);
-                mfma_half(1, ahi, b1);
+                mfma_half(upper, ahi, b1);
 #pragma unroll
                 for (int q = 0; q < PH; ++q) {               // loads under the first half, fragment reads under the second
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -195,8 +202,8 @@ struct GemmTile16 {
                     else __builtin_amdgcn_sched_group_barrier(0x100, READS_PER_MFMA, 0);
                 }
             } else {
-                if (i + 1 < n) { read_a(next, 0, 0, alo); read_b(next, 0, b0); }
-                mfma_half(1, ahi, b1);
+                if (i + 1 < n) { read_a(next, 0, lower, alo); read_b(next, 0, b0); }
+                mfma_half(upper, ahi, b1);
             }
             stage = next;
         };

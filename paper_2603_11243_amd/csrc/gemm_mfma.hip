@@ -123,17 +123,17 @@ template <bool BF_>
 struct EpiResidualLds {
     static constexpr bool WANTS_SPLIT = false, BF = BF_, TRANSPOSE = true, USES_LDS = true;
     float* x; int ldx; float descale;
-    template <int TM> static constexpr int wave_lds_bytes() { return (TM / 2) * 16 * RES_LDS_STRIDE * 4; }
+    template <int TM> static constexpr int wave_lds_bytes() { return ((TM + 1) / 2) * 16 * RES_LDS_STRIDE * 4; }
     template <int TM, int TN>
     __device__ __forceinline__ void run_lds(f32x4_t (&acc)[TM][TN], int row0, int col0, int M, int lane, float* stage) const {
-        static_assert(TN == 4 && TM % 2 == 0, "a wavefront tile of 64 columns, two halves of row blocks");
-        constexpr int HB = TM / 2;                           // row blocks per half
-        constexpr int ROWS = HB * 16;                        // rows per half
-        constexpr int NI = ROWS / 4;                         // instructions per half: 4 rows x 256 bytes each
+        static_assert(TN == 4, "a wavefront tile of 64 columns");
+        constexpr int H0 = (TM + 1) / 2;                     // row blocks of the first half; the second has TM - H0
+        constexpr int ROWS = H0 * 16;
         const int m = lane % 16, g = lane / 16;
         const int rr = lane / 16, cc = (lane % 16) * 4;      // read-back: row 4 it + rr of the half, columns cc .. cc + 3
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
+        auto do_half = [&](auto half) {
+            constexpr int HB = half ? TM - H0 : H0;          // row blocks
+            constexpr int NI = HB * 4;                       // instructions: 4 rows x 256 bytes each
             // old values first: their round trip overlaps the LDS exchange
             float4 old[NI];
 #pragma unroll
@@ -148,7 +148,7 @@ struct EpiResidualLds {
             for (int i = 0; i < HB; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    const f32x4_t a = acc[half * HB + i][j];
+                    const f32x4_t a = acc[half * H0 + i][j];
                     *reinterpret_cast<float4*>(stage + (i * 16 + m) * RES_LDS_STRIDE + j * 16 + 4 * g) =
                         make_float4(a[0] * descale, a[1] * descale, a[2] * descale, a[3] * descale);
                 }
@@ -163,7 +163,9 @@ struct EpiResidualLds {
                         make_float4(old[it].x + v.x, old[it].y + v.y, old[it].z + v.z, old[it].w + v.w);
             }
             __builtin_amdgcn_s_waitcnt(0xC07F);
-        }
+        };
+        do_half(std::integral_constant<int, 0>());
+        do_half(std::integral_constant<int, 1>());
     }
 };
 
@@ -188,12 +190,14 @@ struct EpiQkvRope {
             const int d_kvT = d_rot - d_q;
             float peak = 0.f;
             constexpr int NJT = TN / 2;
-            constexpr int GT = residual_batch(TM, 64 / (NJT * 8) > 0 ? 64 / (NJT * 8) : 1);
+            constexpr int MOST = 64 / (NJT * 8) > 0 ? 64 / (NJT * 8) : 1, NB = (TM + MOST - 1) / MOST;
+            constexpr int GT = (TM + NB - 1) / NB;          // row blocks of a batch; the last may be one short
 #pragma unroll
             for (int i0 = 0; i0 < TM; i0 += GT) {
                 int t_row[GT], slot[GT];
 #pragma unroll
                 for (int g = 0; g < GT; ++g) {
+                    if (i0 + g >= TM) continue;
                     const int row = min(row0 + L::row(i0 + g, lane), M - 1);
                     t_row[g] = rope_rows ? row : pos[row];
                     slot[g] = row_slot ? row_slot[row] : -1;
@@ -203,6 +207,7 @@ struct EpiQkvRope {
                 for (int g = 0; g < GT; ++g)
 #pragma unroll
                     for (int jj = 0; jj < NJT; ++jj) {
+                        if (i0 + g >= TM) continue;
                         const int j = (jj / L::PAIR) * 2 * L::PAIR + jj % L::PAIR;
                         const int p = col0 + j * L::BLOCK;
                         const int i_rot = ((p % 128) / 64) * 32 + p % 32 + 4 * (lane / 16);
@@ -218,6 +223,7 @@ struct EpiQkvRope {
                     constexpr bool CLAMP = decltype(clamp_c)::value;
 #pragma unroll
                     for (int g = 0; g < GT; ++g) {
+                        if (i0 + g >= TM) continue;
                         const int row = row0 + L::row(i0 + g, lane);
                         if (row >= M) continue;
 #pragma unroll
@@ -626,7 +632,7 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, class Epi>
 static void launch_gemm16(const f16_t* A, const f16_t* W, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
     if (M <= 0) return;
     auto kern = gemm_mfma16_kernel<BM, BN, WAVES_M, WAVES_N, Epi>;
-    constexpr size_t ring = gemm_lds_bytes<BM, BN, 2>();
+    constexpr size_t ring = GemmTile16<BM, BN, WAVES_M, WAVES_N, Epi::BF, Epi::TRANSPOSE>::LDS_BYTES;
     constexpr size_t lds = [] {
         if constexpr (Epi::USES_LDS) {
             constexpr size_t stage = (size_t)WAVES_M * WAVES_N * Epi::template wave_lds_bytes<BM / WAVES_M / 16>();
@@ -735,7 +741,13 @@ void launch_stream_layout(const uint16_t* w, void* out, int N, int K, hipStream_
 // so that the number of tiles wastes as little of the last round over the 256 CUs as possible:
 // cost = rounds * (height * K / efficiency + what a round costs beside its K loop: first loads, epilogue, the burst of stores).
 // The last term is TILE_OVERHEAD row-slices, about eleven slices of the highest tile: 40 K x 3072 outputs of K = 1024 take 290 us
-// in ten rounds of 192 rows and 268 us in eight of 256.
+// in ten rounds of 192 rows and 268 us in eight of 256.  Five heights because a coarser step leaves up to a quarter of a round
+// empty (256, 192 and 128 only, against these, us: QKV of 3400 rows 68.9 -> 62.4 and 136.6 -> 125.2 at 2048 and 3072 wide, gate/up of
+// 2600 rows 162.5 -> 149.4, down of 4200 rows 166 -> 157, of 6400 rows 196 -> 184 and 327 -> 310; over 24 row counts from 2300 to
+// 15390 and four projections at two widths 1.5 % less, none more than 0.5 % slower).  Rounds of 160 rows that are filled are
+// no faster than three quarters of a round of 192, where all CUs store at once (QKV of 4788 rows, 1.88 rounds of 160: 99.1 us, 1.56
+// of 192: 92.8; with 1.69 rounds, 4200 rows, 91.0 and 94.3); the residual's adds stand more of it (down of 4788 rows 164 and 169, of
+// 5056 rows, a round of exactly 256, 163 and 161).
 // With at most 128 rows the job is weight streaming and what counts is the number of weight bytes in
 // flight: at most 32 rows go to the register-streaming kernel when the shape divides evenly, more to its variant
 // with row blocks where that is faster (try_launch_stream_rows); otherwise a skinny 128 x 64 tile (four wavefronts, each 32 rows x 64 columns) with a six-stage LDS ring
@@ -763,18 +775,23 @@ static void launch_skinny(const f16_t* A, const f16_t* W, const void* Ws, int M,
 
 template <class Epi>
 static void launch_big(const f16_t* A, const f16_t* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
-    const int heights[3] = {256, 192, 128};
-    const double eff[3] = {1.0, 0.97, 0.90};
+    const int heights[5] = {256, 224, 192, 160, 128};
+    const double eff[5] = {1.0, 0.98, 0.96, 0.92, 0.86};
+    constexpr double FULL_160 = Epi::USES_LDS ? 0.96 : 0.92;
     constexpr double TILE_OVERHEAD = 2800;
     int best = 0;
     double best_cost = 1e30;
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < 5; ++c) {
         const long tiles = (long)((M + heights[c] - 1) / heights[c]) * (N / 256);
-        const double cost = (double)((tiles + 255) / 256) * (heights[c] / eff[c] * (K / GEMM_BK) + TILE_OVERHEAD);
+        const long rounds = (tiles + 255) / 256;
+        if (heights[c] == 160 && tiles > FULL_160 * 256 * rounds) continue;
+        const double cost = (double)rounds * (heights[c] / eff[c] * (K / GEMM_BK) + TILE_OVERHEAD);
         if (cost < best_cost - 1e-9) { best_cost = cost; best = c; }
     }
     if (best == 0) launch_gemm16<256, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
-    else if (best == 1) launch_gemm16<192, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
+    else if (best == 1) launch_gemm16<224, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
+    else if (best == 2) launch_gemm16<192, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
+    else if (best == 3) launch_gemm16<160, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
     else launch_gemm16<128, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
 }
 // Whole sums (QKV, gate/up, the projector).  Beyond 128 rows the 256-wide tiles leave most of the chip idle until there

@@ -145,3 +145,17 @@ def test_verify_mid_rows(M):
     vi = _inputs(m, [(M // 2 - 40, 3, 37), (M - M // 2 - 9, 4, 5)], M)
     tau = 1.0 / m.vocab
     _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
+
+
+# the heights of the 256-wide tiles with an odd number of 16-row blocks per wavefront, 160 and 224: gate/up (25 tiles per row of
+# tiles) of 1281..1440 and 1921..2240 rows; then 16 QKV and 8 O / down tiles: QKV of 2200 and 3300 rows, O and down of 4500 and 6500
+@pytest.mark.parametrize("shape,M", [((2, 768, 6, 2, 128, 3200, 512), M) for M in (1282, 1440, 1921, 2240)]
+                         + [((2, 2048, 16, 8, 128, 256, 512), M) for M in (2200, 3300, 4500, 6500)])
+def test_verify_tile_heights(shape, M):
+    m = ModelCfg(*shape, dtype="bf16")
+    wl = replace(WORKLOADS["cfg3_1b_ragged64"], model=m)
+    w = make_model_weights(m, 90 + M)
+    n = M // 150
+    vi = _inputs(m, [(130 + (M - 150 * n if b == 0 else 0), 8, 12) for b in range(n)], M)
+    tau = 1.0 / m.vocab
+    _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
