@@ -1230,8 +1230,11 @@ int accept_prefix(ssd_ctx* ctx, const void* h_verify, const int32_t* draft_ids, 
         return fail(ctx, SSD_EWORKSPACE, "accept_prefix: workspace of %zu bytes needed, %zu set", p.total, ctx->ws_bytes);
     char* ws = static_cast<char*>(ctx->ws);
     int32_t* cu_dev = reinterpret_cast<int32_t*>(ws + p.cu);
-    int rc = upload(ctx, cu_draft, cu_dev, (size_t)(Bv + 1) * 4);
-    if (rc != SSD_OK) return rc;
+    const bool as_args = Bv <= GATE_MAX_ARG_UTTS;
+    if (!as_args) {
+        const int rc = upload(ctx, cu_draft, cu_dev, (size_t)(Bv + 1) * 4);
+        if (rc != SSD_OK) return rc;
+    }
     hipStream_t st = ctx->stream;
     ProfScope ps_all(ctx, SSD_PROF_LMHEAD);
     float2* part_ms = reinterpret_cast<float2*>(ws + p.part_ms);
@@ -1245,7 +1248,8 @@ int accept_prefix(ssd_ctx* ctx, const void* h_verify, const int32_t* draft_ids, 
     launch_lmhead_finalize(part_ms, tgt, part_arg, head_groups(m), (int)Mv, draft_logp, greedy_tok, head_flags(ctx), st);
     // ln(tau) in double, rounded once to fp32; tau <= 0 accepts every token
     const float ln_tau = tau_slm > 0.f ? (float)log((double)tau_slm) : -INFINITY;
-    launch_accept_scan(draft_logp, cu_dev, Bv, ln_tau, accept_len, all_accepted, st);
+    if (as_args) launch_accept_scan_host(draft_logp, cu_draft, Bv, ln_tau, accept_len, all_accepted, st);
+    else launch_accept_scan(draft_logp, cu_dev, Bv, ln_tau, accept_len, all_accepted, st);
     HIP_TRY(ctx, hipGetLastError());
     return SSD_OK;
 }

@@ -403,12 +403,13 @@ void launch_pack_gate_up(int dtype, const void* wg, const void* wu, void* out, i
 // Acceptance (Eq. 5 and the definition of j in Sec. 2.3): token i passes iff logp_i > ln(tau);
 // accept_len = (index of the first failing token) - 1, or U when none fails.
 // One wavefront per utterance.
+template <class CU>
 __global__ void __launch_bounds__(64) accept_scan_kernel(const float* __restrict__ logp,
-                                                         const int32_t* __restrict__ cu_draft, float ln_tau,
+                                                         const CU cu_draft, float ln_tau,
                                                          int32_t* __restrict__ accept_len,
                                                          uint8_t* __restrict__ all_accepted) {
     const int b = blockIdx.x;
-    const int lo = cu_draft[b], hi = cu_draft[b + 1];
+    const int lo = cu_draft(b), hi = cu_draft(b + 1);
     const int U = hi - lo;
     int first_fail = U;                                  // 0-based index of the first failing token
     for (int i = threadIdx.x; i < U; i += 64) {
@@ -459,7 +460,14 @@ void launch_accept_grid(const float* logp, const int32_t* cu_draft_dev, int Bv, 
 void launch_accept_scan(const float* logp, const int32_t* cu_draft_dev, int Bv, float ln_tau, int32_t* accept_len,
                         uint8_t* all_accepted, hipStream_t st) {
     if (Bv <= 0) return;
-    hipLaunchKernelGGL(accept_scan_kernel, dim3(Bv), dim3(64), 0, st, logp, cu_draft_dev, ln_tau, accept_len, all_accepted);
+    hipLaunchKernelGGL(accept_scan_kernel<CuArray>, dim3(Bv), dim3(64), 0, st, logp, CuArray{cu_draft_dev}, ln_tau, accept_len, all_accepted);
+}
+void launch_accept_scan_host(const float* logp, const int32_t* cu_draft, int Bv, float ln_tau, int32_t* accept_len,
+                             uint8_t* all_accepted, hipStream_t st) {
+    if (Bv <= 0) return;
+    CuArgs cu;
+    for (int b = 0; b <= Bv; ++b) cu.cu[b] = cu_draft[b];
+    hipLaunchKernelGGL(accept_scan_kernel<CuArgs>, dim3(Bv), dim3(64), 0, st, logp, cu, ln_tau, accept_len, all_accepted);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -314,15 +314,6 @@ __global__ void __launch_bounds__(256) gate_frames_generic(const T* __restrict__
 
 // One workgroup (256 threads) per utterance.  The frame range of an utterance is clamped into
 // [0, n_rows], so that prefix sums that were never seen by the host cannot lead outside H / arg / draft.
-// CU: the prefix sums, in device memory (CuArray) or among the kernel's arguments (CuArgs).
-struct CuArray {
-    const int32_t* cu;
-    __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
-};
-struct CuArgs {
-    int32_t cu[GATE_MAX_ARG_UTTS + 1];
-    __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
-};
 // The decision about one utterance and its collapsed path, by 256 threads.  frame(t, H, arg) and symbol(t) read frame t's statistics.
 // 1024 frames a trip: every trip waits for memory once and for the other wavefronts twice (with 256 a trip, 1500 frames were six waits).
 template <class Frame, class Symbol>

@@ -23,6 +23,14 @@ void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* c
 // The same with the prefix sums in host memory, B <= GATE_MAX_ARG_UTTS: they travel as kernel arguments (1 KB), which spares
 // a small batch its upload (one ten-second utterance: 15.2 -> 10.7 us a call).
 constexpr int GATE_MAX_ARG_UTTS = 256;
+struct CuArray {                             // prefix sums in device memory
+    const int32_t* cu;
+    __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
+};
+struct CuArgs {                              // among the kernel's arguments
+    int32_t cu[GATE_MAX_ARG_UTTS + 1];
+    __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
+};
 void launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
                                  float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                                  hipStream_t st);
@@ -206,5 +214,9 @@ void launch_mfma_ceiling(float* sink, long long* clocks, int n_workgroups, int i
 // ---- accept (shared by both dtypes): first failing token per utterance
 void launch_accept_scan(const float* logp, const int32_t* cu_draft_dev, int Bv, float ln_tau, int32_t* accept_len,
                         uint8_t* all_accepted, hipStream_t st);
+// the prefix sums in host memory, Bv <= GATE_MAX_ARG_UTTS, as kernel arguments: an upload is a copy kernel of 2.4 us and a gap
+// (four short utterances of the small fp32 decoder, verification and acceptance: 107.4 -> 101.9 us)
+void launch_accept_scan_host(const float* logp, const int32_t* cu_draft, int Bv, float ln_tau, int32_t* accept_len,
+                             uint8_t* all_accepted, hipStream_t st);
 
 }  // namespace ssd

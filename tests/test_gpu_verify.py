@@ -619,3 +619,27 @@ def test_operand_types_against_oracle(name, layers, B):
     print(f"{wl.name}: worst |dlogp| half {worst['f16']:.3e}, bfloat16 {worst['bf16']:.3e}; worst relative error of a "
           f"hidden row half {hidden['f16']:.2e}, bfloat16 {hidden['bf16']:.2e}")
     assert hidden["bf16"] > 2 * hidden["f16"]          # three mantissa bits fewer at every contraction input
+
+
+@pytest.mark.parametrize("Bv", [1, 255, 256, 257])
+def test_accept_prefix_with_prefix_sums_as_arguments(Bv):
+    """Up to 256 utterances the prefix sums are kernel arguments, beyond they are uploaded: the decision follows from the stored
+    likelihoods exactly, with empty drafts and the lowest and highest utterance among them."""
+    from paper_2603_11243_amd.binding import Context
+    wl = WORKLOADS["cfg1_tiny_f32"]
+    ctx = Context(wl.model, make_model_weights(wl.model, 5))
+    U = np.arange(Bv) * 5 % 4 + (Bv == 1)
+    cu = np.concatenate([[0], np.cumsum(U)]).astype(np.int32)
+    n = int(cu[-1])
+    g = torch.Generator(device="cuda").manual_seed(Bv)
+    h = torch.randn(n, wl.model.d_model, generator=g, device="cuda")
+    ids = torch.randint(0, wl.model.vocab, (n,), generator=g, device="cuda", dtype=torch.int32)
+    ctx.reserve(max_tokens=n, max_verify_rows=n, max_utts=Bv)
+    tau = float(torch.exp(ctx.accept_prefix(h, ids, cu, 0.5)["draft_logp"]).median())
+    out = {k: v.cpu().numpy() for k, v in ctx.accept_prefix(h, ids, cu, tau).items()}
+    ctx.close()
+    ok = out["draft_logp"] > np.float32(np.log(np.float64(np.float32(tau))))
+    for b in range(Bv):
+        bad = np.flatnonzero(~ok[cu[b]:cu[b + 1]])
+        want = bad[0] if len(bad) else U[b]
+        assert out["accept_len"][b] == want and out["all_accepted"][b] == (want == U[b])
