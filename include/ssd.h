@@ -118,9 +118,9 @@ const char *ssd_last_error(const ssd_ctx *ctx);
  * kernels repair them and raise a sticky flag.  ssd_device_flags waits for the stream, writes the flags
  * raised since the last call to *flags (host) and clears them.
  *   SSD_FLAG_TOKEN_CLAMPED  a prompt, draft or first_tok id outside [0, vocab) was clamped into range
- *   SSD_FLAG_ACT_OVERFLOW   SSD_BF16 models: an activation left the range of the matrix-core operand type
+ *   SSD_FLAG_ACT_OVERFLOW   SSD_BF16 models and qformer_pool: an activation left the range of the matrix-core operand type
  *                           (|v| > 65504 for IEEE half, or NaN) at one of the points where the fp32 pipeline
- *                           rounds to it (RMSNorm output, rotated q / k and v, SiLU(gate)*up, K/V-cache rows) and
+ *                           rounds to it (RMSNorm output, rotated q / k and v, SiLU(gate)*up, K/V-cache rows, the projector's values) and
  *                           was stored saturated to +-65504, or a log-likelihood came out non-finite.  Results of
  *                           calls since the last read are then not the model's: re-run in fp32 or rescale. */
 enum ssd_device_flag { SSD_FLAG_TOKEN_CLAMPED = 1, SSD_FLAG_ACT_OVERFLOW = 2 };
@@ -229,9 +229,12 @@ int ctc_head_gate(ssd_ctx *ctx, const void *enc_h, const int32_t *cu_frames /*ho
  *
  * qformer_pool: for every utterance b and window w of its frames (the last one may be shorter and attends over
  * the frames it has), query j: p = softmax over the window's frames of the head-wise scores, o = sum_t p_t w_v h_t,
- * g = w_o o, written as bf16 to speech_emb row cu_speech[b] + n_q * w + j (the projected values w_v h_t pass through
- * IEEE half on the way: one beyond 65504 is clamped and raises SSD_FLAG_ACT_OVERFLOW); cu_speech (host, B + 1 entries) is
- * filled with the prefix sums S_b = n_q * ceil(T_b / window) that verify_forward takes.  The rest of a q-former
+ * g = w_o o, written as bf16 to speech_emb row cu_speech[b] + n_q * w + j; cu_speech (host, B + 1 entries) is
+ * filled with the prefix sums S_b = n_q * ceil(T_b / window) that verify_forward takes.  In small calls, and for other shapes than 16
+ * heads of 64 dims with n_q <= 3 and window <= 16, the projected values w_v h_t pass through IEEE half: one beyond 65504
+ * is clamped and raises SSD_FLAG_ACT_OVERFLOW.  Large calls pool the states first and project the sums, o = w_v sum_t p_t h_t, in at least 16
+ * significant bits and the range of fp32: nothing is clamped.  A state that is not finite makes the rows of its window NaN and
+ * raises the flag in both.  The rest of a q-former
  * layer (self-attention among the queries, feed-forward block, normalisation, second layer) is not described in
  * the paper and not part of this call.
  * enc_h: dev [cu_frames[B], d_enc] bf16 packed rows; speech_emb: dev [n_q * (frames / window + B), d_out] is enough.

@@ -103,7 +103,6 @@ struct ssd_ctx {
     // projector windows (ssd_set_qformer): fused [scores | values] weight and the output projection, both bf16
     uint16_t* qf_wcat = nullptr;
     uint16_t* qf_wo = nullptr;
-    float qf_ds = 1.f;                       // undoes the scale of qf_wfrag
     uint16_t* qf_wfrag = nullptr;            // w_v for the projection after the pooling (NULL: shape not served)
     int qf_nq = 0, qf_heads = 0, qf_dh = 0, qf_denc = 0, qf_dout = 0, qf_window = 0;
     void* kv = nullptr;                      // caller-owned K/V cache: [layer][K|V][slots][d_kv] in the activation type
@@ -791,15 +790,7 @@ int ssd_set_qformer(ssd_ctx* ctx, const void* q_proj, const void* w_k, const voi
     if (qformer_values_supported(n_q, n_heads, d_h, d_enc, window)) {
         HIP_TRY(ctx, hipMalloc(&wf, (size_t)d_h * d_enc * 2));
         ctx->owned.push_back(wf);
-        // largest magnitude -> exact power-of-two scale into the range of half, as for the decoder's matrices
-        float mx = 0.f;
-        HIP_TRY(ctx, hipMemsetAsync(wf, 0, 4, ctx->stream));
-        launch_absmax(SSD_BF16, w_v, (int64_t)d_h * d_enc, static_cast<unsigned*>(wf), ctx->stream);
-        HIP_TRY(ctx, hipMemcpyAsync(&mx, wf, 4, hipMemcpyDeviceToHost, ctx->stream));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        const float scale = weight_scale(mx);
-        ctx->qf_ds = 1.0f / scale;
-        launch_qformer_value_fragments(static_cast<const uint16_t*>(w_v), d_enc, scale, static_cast<uint16_t*>(wf), ctx->stream);
+        launch_qformer_value_fragments(static_cast<const uint16_t*>(w_v), d_enc, static_cast<uint16_t*>(wf), ctx->stream);
     }
     HIP_TRY(ctx, hipMalloc(&wc, (size_t)qformer_cat_rows(d_h) * d_enc * 2));
     ctx->owned.push_back(wc);
@@ -850,7 +841,7 @@ int qformer_pool(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int 
         const QWindow* d_wins = reinterpret_cast<const QWindow*>(ws + p.wins);
         if (ctx->qf_wfrag && n_windows >= QF_VALUES_MIN_WINDOWS) {
             launch_gemm_scores(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, (int)n_rows, d_enc, ctx->stream);
-            launch_qformer_values(static_cast<const uint16_t*>(enc_h), scores, ctx->qf_wfrag, ctx->qf_ds, d_wins, n_windows, n_q, d_enc, o, ctx->dev_flags, ctx->stream);
+            launch_qformer_values(static_cast<const uint16_t*>(enc_h), scores, ctx->qf_wfrag, d_wins, n_windows, n_q, d_enc, o, ctx->dev_flags, ctx->stream);
         } else {
             launch_gemm_scores_values(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, vals, (int)n_rows, n_cat, d_enc, d_h,
                                       ctx->dev_flags, true, ctx->stream);

@@ -6,30 +6,31 @@
 // states of 16 windows would be 1.5 MB, so they go from one product to the next through LDS.
 //
 // A workgroup takes 16 windows; its eight wavefronts each pool two windows for all heads and project two heads for all windows,
-// in steps of 32 state columns:
-//   pool     D[cols, heads] = H^T P^T over the frames of a window, per query.  A product takes 32 k and a window has at most 16 frames:
-//            the probabilities are bf16 pairs hi + lo (16 significant bits), hi against k 0..15 and lo against k 16..31 of twice the
-//            same frames (bf16 as stored).  H^T fragments come from the transposing LDS read.
-//   exchange the sums, rounded to IEEE half as the values are in the other order (saturating, SSD_FLAG_ACT_OVERFLOW), go to LDS in
-//            fragment order: a lane that held one head then reads one window
-//   project  O[dims, windows] += w_v[h] D, w_v as half times a power of two in a fragment-ordered copy, straight from the L2
-// Relative error of g against 64 bits (1300 windows, states of unit spread, four times and a twentieth of it): 2.726e-3, 3.580e-3 and
-// 2.353e-3; the other order 2.725e-3, 3.581e-3 and 2.352e-3.
-// What bounds it: nothing alone.  A step is 36 products a wavefront (1152 cycles of the matrix cores), 96 conversions, 64 KB of
-// weights (1024 cycles of the address path) and 98 KB through LDS, and takes 2400 cycles; first loads, scores and the way out are a
-// fifth of a workgroup's life; 842 workgroups are 3.3 rounds over the CUs.  At 198 K frames 285 us and 88 us for the scores, against
-// 578 us for scores and values in one product and 114 us for the pooling.
+// in units of 32 state columns and a query:
+//   pool     D[cols, heads] = H^T P^T over the frames of a window.  A product takes 32 k and a window has at most 16 frames: the
+//            probabilities are bf16 pairs hi + lo, hi against k 0..15 and lo against k 16..31 of twice the same frames (bf16 as
+//            stored).  H^T fragments come from the transposing LDS read.
+//   exchange the sums, again as bf16 pairs hi + lo, go to LDS in fragment order: a lane that held one head then reads one window
+//   project  O[dims, windows] += w_v[h] (hi + lo), w_v as stored in a fragment-ordered copy, straight from the L2
+// A pair has 16 significant bits and the range of fp32, where the other order rounds the values to IEEE half (11 bits, 65504): nothing
+// is clamped here, whatever the scales of states and w_v, and NaN stays NaN.  Relative error of g against 64 bits (1300 windows, states of
+// unit spread, four times and a twentieth of it): 2.717e-3, 3.574e-3 and 2.343e-3; the other order 2.725e-3, 3.581e-3 and 2.352e-3
+// (bf16 results and score rows: 2.7e-3, 3.6e-3 and 2.3e-3 of each).
+// What bounds it: nothing alone.  32 columns are 60 products a wavefront (1920 cycles of the matrix cores), 64 KB of weights (1024
+// cycles of the address path), 225 KB through LDS (1760 cycles) and 336 conversions; the parts overlap in half.  Sums as half values
+// (36 products, 130 KB) are 75 us faster at 198 K frames, but lose what is outside their range.
 #include "gemm_core.h"
 #include "ssd_internal.h"
 
 namespace ssd {
 
 constexpr int QV_WINDOWS = 16, QV_WAVES = 8, QV_HEADS = 16, QV_DIM = 64;
-constexpr int QV_HEAD_BYTES = 1024 + 16;                   // one head and query: 16 windows x 32 columns; padded for the writes
-constexpr int QV_QUERY_BYTES = QV_HEADS * QV_HEAD_BYTES;
+constexpr int QV_HEAD_BYTES = 2048 + 16;                   // hi | lo of one head: 16 windows x 32 columns each; padded for the writes
+constexpr int QV_SLOT_BYTES = QV_HEADS * QV_HEAD_BYTES;    // the sums of one query and 32 columns
+constexpr int QV_SLOTS = 4;                                // two are read while the other two are written
 constexpr int QV_H_BYTES = 2 * 16 * 64;                    // two windows x 16 frames x 32 state columns of one wavefront
 template <int NQ> constexpr int qv_lds_bytes() {
-    constexpr int loop = 2 * NQ * QV_QUERY_BYTES + QV_WAVES * QV_H_BYTES, out = QV_WINDOWS * (NQ * QV_HEADS * QV_DIM * 2 + 16);
+    constexpr int loop = QV_SLOTS * QV_SLOT_BYTES + QV_WAVES * QV_H_BYTES, out = QV_WINDOWS * (NQ * QV_HEADS * QV_DIM * 2 + 16);
     return loop > out ? loop : out;
 }
 
@@ -44,43 +45,39 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) v4i16_t lds_v4i16_t;
 
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t)); }
-typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t cvt_pk_f16_sat(float a, float b) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){__builtin_amdgcn_fmed3f(a, -F16_MAX, F16_MAX), __builtin_amdgcn_fmed3f(b, -F16_MAX, F16_MAX)}, f16x2_t));
-}
 // a pair of values as bf16 pairs: hi, and lo = what hi left out
 __device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint32_t& lo) {
     hi = cvt_pk_bf16(a, b);
     lo = cvt_pk_bf16(a - bf16_lo(hi), b - bf16_hi(hi));
 }
 
-// w_v [d_h, d_enc] -> operand fragments in IEEE half times `scale`: unit ((c * 16 + head) * 4 + n) * 64 + lane holds
+// w_v [d_h, d_enc] in the order of the operand fragments: unit ((c * 16 + head) * 4 + n) * 64 + lane holds
 // w_v[64 head + 16 n + lane % 16][32 c + 8 (lane / 16) .. + 7]
-__global__ void __launch_bounds__(256) qformer_value_fragments_kernel(const bf16_t* __restrict__ w_v, int d_enc, float scale, uint4* __restrict__ out) {
+__global__ void __launch_bounds__(256) qformer_value_fragments_kernel(const bf16_t* __restrict__ w_v, int d_enc, uint4* __restrict__ out) {
     const int u = blockIdx.x * 256 + threadIdx.x;
     if (u >= QV_HEADS * QV_DIM * (d_enc / 8)) return;
     const int lane = u % 64, n = (u / 64) % 4, head = (u / 256) % QV_HEADS, c = u / (256 * QV_HEADS);
     const bf16_t* src = w_v + (int64_t)(head * QV_DIM + n * 16 + lane % 16) * d_enc + 32 * c + 8 * (lane / 16);
     uint32_t v[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = pack_f16x2(bf16_to_f32(src[2 * e]) * scale, bf16_to_f32(src[2 * e + 1]) * scale);
+    for (int e = 0; e < 4; ++e) v[e] = (uint32_t)src[2 * e] | ((uint32_t)src[2 * e + 1] << 16);
     out[u] = make_uint4(v[0], v[1], v[2], v[3]);
 }
-void launch_qformer_value_fragments(const uint16_t* w_v, int d_enc, float scale, uint16_t* out, hipStream_t st) {
+void launch_qformer_value_fragments(const uint16_t* w_v, int d_enc, uint16_t* out, hipStream_t st) {
     const int units = QV_HEADS * QV_DIM * (d_enc / 8);
-    hipLaunchKernelGGL(qformer_value_fragments_kernel, dim3((units + 255) / 256), dim3(256), 0, st, w_v, d_enc, scale, reinterpret_cast<uint4*>(out));
+    hipLaunchKernelGGL(qformer_value_fragments_kernel, dim3((units + 255) / 256), dim3(256), 0, st, w_v, d_enc, reinterpret_cast<uint4*>(out));
 }
 
 template <int NQ>
 __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf16_t* __restrict__ enc_h, const float* __restrict__ scores,
                                                                      const bf16_t* __restrict__ w_frag, const QWindow* __restrict__ wins, int n_windows,
-                                                                     int d_enc, float descale, bf16_t* __restrict__ o, int32_t* __restrict__ flags) {
+                                                                     int d_enc, bf16_t* __restrict__ o, int32_t* __restrict__ flags) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* x_lds = smem;
     const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const int m = lane % 16, g = lane / 16;
     const int w0 = blockIdx.x * QV_WINDOWS;
-    unsigned char* h_lds = smem + 2 * NQ * QV_QUERY_BYTES + wave * QV_H_BYTES;
+    unsigned char* h_lds = smem + QV_SLOTS * QV_SLOT_BYTES + wave * QV_H_BYTES;
     QWindow win[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -172,7 +169,6 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
             }
     };
     unsigned char* x_wr = x_lds + m * QV_HEAD_BYTES + (g / 2) * 256 + (g % 2) * 8 + 2 * wave * 16;
-    float peak = 0.f;                                        // largest magnitude of a sum
     f32x4_t sums[2][2];                                      // lane: head m, state columns 16 n + 4 g .. + 3
     auto pool = [&](int j) {
 #pragma unroll
@@ -180,15 +176,17 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
 #pragma unroll
             for (int n = 0; n < 2; ++n) sums[i][n] = mfma_16x16x32<true>(h_frag[i][n], p_frag[i][j], (f32x4_t){0.f, 0.f, 0.f, 0.f});
     };
-    auto store_sums = [&](int j, int buf) {
+    auto store_sums = [&](int slot) {                        // slot: byte offset
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int n = 0; n < 2; ++n) {
                 const f32x4_t d = sums[i][n];
-                peak = fmaxf(fmaxf(peak, fabsf(d[0])), fabsf(d[1]));
-                peak = fmaxf(fmaxf(peak, fabsf(d[2])), fabsf(d[3]));
-                *reinterpret_cast<uint2*>(x_wr + (buf * NQ + j) * QV_QUERY_BYTES + n * 512 + i * 16) = make_uint2(cvt_pk_f16_sat(d[0], d[1]), cvt_pk_f16_sat(d[2], d[3]));
+                uint2 hi, lo;
+                split_bf16(d[0], d[1], hi.x, lo.x);
+                split_bf16(d[2], d[3], hi.y, lo.y);
+                *reinterpret_cast<uint2*>(x_wr + slot + n * 512 + i * 16) = hi;
+                *reinterpret_cast<uint2*>(x_wr + slot + n * 512 + i * 16 + 1024) = lo;
             }
     };
 
@@ -206,64 +204,70 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
 #pragma unroll
         for (int n = 0; n < 4; ++n) w[h][n] = __builtin_bit_cast(f16x8_t, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16 + (h * 4 + n) * 1024, base, 0));
     };
-    f16x8_t x[2][NQ];
+    f16x8_t x[2][2];                                         // head, hi | lo
     const unsigned char* x_rd = x_lds + 2 * wave * QV_HEAD_BYTES + lane * 16;
-    auto read_x = [&](int buf, int b) {                      // block b: head b / NQ, query b % NQ
-        x[b / NQ][b % NQ] = as_f16x8(*reinterpret_cast<const uint4*>(x_rd + (buf * NQ + b % NQ) * QV_QUERY_BYTES + b / NQ * QV_HEAD_BYTES));
+    auto read_x = [&](int h, int slot) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) x[h][e] = as_f16x8(*reinterpret_cast<const uint4*>(x_rd + slot + h * QV_HEAD_BYTES + e * 1024));
     };
     auto project = [&](int h, int j) {
 #pragma unroll
-        for (int n = 0; n < 4; ++n) acc[h][j][n] = mfma_16x16x32<false>(w[h][n], x[h][j], acc[h][j][n]);
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int n = 0; n < 4; ++n) acc[h][j][n] = mfma_16x16x32<true>(w[h][n], x[h][e], acc[h][j][n]);
     };
 
-    // Step c: project columns c; request their successor's weights; pool columns c + 1, whose fragments are in registers; make
-    // the fragments of c + 2 and request the frames of c + 4.
+    // Unit u: 32 columns c = u / NQ and a query j = u % NQ.  It projects the sums of u from one slot, forms those of u + 2 and puts
+    // them into another; two units a barrier.  (The last units form sums of columns that they repeat; nobody reads them.)
+    auto frames = [&](int c, int odd) {                      // fragments of columns c; request of c + 2
+        read_h(h_reg[odd]);
+        load_h(c + 2, h_reg[odd]);
+    };
     load_w(0, 0);
     load_w(0, 1);
-    read_h(h_reg[0]);
-    load_h(2, h_reg[0]);
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) {
-        pool(j);
-        store_sums(j, 0);
+    for (int t = 0; t < 2; ++t) {
+        if (t % NQ == 0) frames(t / NQ, t / NQ % 2);
+        pool(t % NQ);
+        store_sums(t * QV_SLOT_BYTES);
     }
-    read_h(h_reg[1]);
-    load_h(3, h_reg[1]);
     __syncthreads();
-    for (int c0 = 0; c0 < n32; c0 += 2) {
+    if (2 % NQ == 0) frames(2 / NQ, 2 / NQ % 2);
+    int rd = 0, wr = 2 * QV_SLOT_BYTES;                      // slots of the units being projected and being formed
+    read_x(0, 0);
+    read_x(1, 0);
+    for (int c0 = 0; c0 < n32; c0 += 2) {                    // (n32 is even)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {                        // (n32 is even)
-            const int c = c0 + k;
-            read_x(k, 0);
-            read_x(k, 1);
-            // The sums of a query are formed, then converted under two of the 2 NQ blocks of projection products (the last step's
-            // are of columns that it repeats; nobody reads them).
+        for (int u = 0; u < 2 * NQ; ++u) {
+            const int j = u % NQ, t = u + 2, k = u % 2;
+            __builtin_amdgcn_sched_barrier(0);
+            pool(t % NQ);
+            __builtin_amdgcn_sched_barrier(0);
+            project(0, j);
+            if (k == 0) read_x(0, rd + QV_SLOT_BYTES);
+            if (j == NQ - 1) load_w(c0 + u / NQ + 1, 0);
+            project(1, j);
+            store_sums(wr + k * QV_SLOT_BYTES);
 #pragma unroll
-            for (int j = 0; j < NQ; ++j) {
-                __builtin_amdgcn_sched_barrier(0);
-                pool(j);
-                if (j + 1 < NQ) {
-                    read_x(k, 2 * j + 2);
-                    read_x(k, 2 * j + 3);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int b = 2 * j; b < 2 * j + 2; ++b) project(b / NQ, b % NQ);
-                store_sums(j, 1 - k);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (2 * j + 2 >= NQ && 2 * j < NQ) load_w(c + 1, 0);     // the first head's products are done
+            for (int q = 0; q < 16; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
             }
-            load_w(c + 1, 1);
-            read_h(h_reg[k]);
-            load_h(c + 4, h_reg[k]);
-            __syncthreads();
+            __builtin_amdgcn_sched_barrier(0);
+            if (k == 0) read_x(1, rd + QV_SLOT_BYTES);
+            if (j == NQ - 1) load_w(c0 + u / NQ + 1, 1);
+            if ((t + 1) % NQ == 0) frames(c0 + (t + 1) / NQ, (t + 1) / NQ % 2);
+            if (k == 1) {
+                __syncthreads();
+                const int was = rd;
+                rd = wr;
+                wr = was;
+                read_x(0, rd);
+                read_x(1, rd);
+            }
         }
     }
+    __syncthreads();                                         // the first sums of a unit that does not exist have been read
     float finite = 0.f;                                      // 0, or NaN if a result is not finite
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -273,7 +277,7 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
             for (int n = 0; n < 4; ++n)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) finite = fmaf(acc[h][j][n][r], 0.f, finite);
-    if (!(peak <= F16_MAX) || finite != 0.f) raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);
+    if (finite != 0.f) raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);
 
     // ---- out: the rows of the 16 windows are one contiguous piece; a lane's four dims go through LDS into it
     // (lane: window m, dims 16 n + 4 g .. + 3 of head 2 wave + h; the rows of a window are 16 bytes apart from a multiple of the banks)
@@ -286,7 +290,7 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
             for (int n = 0; n < 4; ++n) {
                 const f32x4_t a = acc[h][j][n];
                 *reinterpret_cast<uint2*>(smem + m * WIN + j * ROW + ((2 * wave + h) * QV_DIM + n * 16 + 4 * g) * 2) =
-                    make_uint2(pack_bf16x2(a[0] * descale, a[1] * descale), pack_bf16x2(a[2] * descale, a[3] * descale));
+                    make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
             }
     __syncthreads();
     unsigned char* dst = reinterpret_cast<unsigned char*>(o) + (int64_t)w0 * (NQ * ROW);
@@ -298,7 +302,7 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
 }
 
 template <int NQ>
-static void launch_values(const uint16_t* enc_h, const float* scores, const uint16_t* w_frag, float descale, const QWindow* wins, int n_windows, int d_enc,
+static void launch_values(const uint16_t* enc_h, const float* scores, const uint16_t* w_frag, const QWindow* wins, int n_windows, int d_enc,
                           uint16_t* o, int32_t* flags, hipStream_t st) {
     auto kern = qformer_values_kernel<NQ>;
     constexpr int lds = qv_lds_bytes<NQ>();
@@ -308,12 +312,12 @@ static void launch_values(const uint16_t* enc_h, const float* scores, const uint
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3((n_windows + QV_WINDOWS - 1) / QV_WINDOWS), dim3(64 * QV_WAVES), lds, st, enc_h, scores, w_frag, wins, n_windows, d_enc, descale, o, flags);
+    hipLaunchKernelGGL(kern, dim3((n_windows + QV_WINDOWS - 1) / QV_WINDOWS), dim3(64 * QV_WAVES), lds, st, enc_h, scores, w_frag, wins, n_windows, d_enc, o, flags);
 }
-void launch_qformer_values(const uint16_t* enc_h, const float* scores, const uint16_t* w_frag, float descale, const QWindow* wins, int n_windows, int n_q,
+void launch_qformer_values(const uint16_t* enc_h, const float* scores, const uint16_t* w_frag, const QWindow* wins, int n_windows, int n_q,
                            int d_enc, uint16_t* o, int32_t* flags, hipStream_t st) {
     if (n_windows <= 0) return;
-#define SSD_QV(NQ) launch_values<NQ>(enc_h, scores, w_frag, descale, wins, n_windows, d_enc, o, flags, st)
+#define SSD_QV(NQ) launch_values<NQ>(enc_h, scores, w_frag, wins, n_windows, d_enc, o, flags, st)
     if (n_q == 1) SSD_QV(1); else if (n_q == 2) SSD_QV(2); else SSD_QV(3);
 #undef SSD_QV
 }

@@ -66,10 +66,10 @@ void launch_qformer_pool(const float* scores, const uint16_t* vals, const QWindo
                          int d_h, uint16_t* o, hipStream_t st);
 
 // ---- qformer_values.hip: the same with the values projected after the pooling; for 16 heads of 64 dims, at most 3 queries and
-// windows of at most 16 frames.  w_frag: fragment-ordered copy of w_v [d_h, d_enc] as IEEE half times `scale`, a power of two.
+// windows of at most 16 frames.  w_frag: fragment-ordered copy of w_v [d_h, d_enc].
 bool qformer_values_supported(int n_q, int n_heads, int d_h, int d_enc, int window);
-void launch_qformer_value_fragments(const uint16_t* w_v, int d_enc, float scale, uint16_t* w_frag, hipStream_t st);
-void launch_qformer_values(const uint16_t* enc_h, const float* scores, const uint16_t* w_frag, float descale, const QWindow* wins, int n_windows, int n_q,
+void launch_qformer_value_fragments(const uint16_t* w_v, int d_enc, uint16_t* w_frag, hipStream_t st);
+void launch_qformer_values(const uint16_t* enc_h, const float* scores, const uint16_t* w_frag, const QWindow* wins, int n_windows, int n_q,
                            int d_enc, uint16_t* o, int32_t* flags, hipStream_t st);
 
 // ---- row metadata built on the host for one verify_forward call

@@ -119,3 +119,62 @@ def test_qformer_pool_values_after_pooling(n_q, d_enc, window, windows):
     ref, cu_ref = O.qformer_window_pool(h, cu, q, w_k, w_v, w_o, 16, window)
     assert cu_s[-1] == n_q * windows and np.array_equal(cu_s, cu_ref)
     _check(got, ref)
+
+
+def _unusual(kind, d_enc, windows, seed):
+    """Weights and states of `windows` whole windows with `kind` in window 7; the oracle's rows, and which windows have none."""
+    g = torch.Generator().manual_seed(seed)
+    r = lambda *s: torch.randn(*s, generator=g)
+    q, w_k, w_v = r(3, 1024), r(1024, d_enc) * d_enc ** -0.5, r(1024, d_enc) * d_enc ** -0.5
+    h = r(15 * windows, d_enc)
+    if kind == "large_states":                                 # far beyond the range of half; values and scores of unit spread
+        h, w_k, w_v = h * 2.0 ** 20, w_k * 2.0 ** -20, w_v * 2.0 ** -20
+    elif kind == "small_states":                               # far below it
+        h, w_k, w_v = h * 2.0 ** -30, w_k * 2.0 ** 30, w_v * 2.0 ** 30
+    elif kind == "uneven_weights":                             # 45 binades between the heads' rows of w_v
+        w_v[3 * 64:4 * 64] *= 2.0 ** -45
+    elif kind == "uneven_columns":                             # a tiny state column that its weights bring back
+        h[:, 5] *= 2.0 ** -30
+        w_v[:, 5] *= 2.0 ** 30
+        w_k[:, 5] *= 2.0 ** 30
+    elif kind == "large_values":
+        w_v = w_v * 2.0 ** 17
+    q, w_k, w_v, h = (t.bfloat16() for t in (q, w_k, w_v, h))
+    w_o = torch.eye(1024).bfloat16()
+    ref, _ = O.qformer_window_pool(h, [0, len(h)], q, w_k, w_v, w_o, 16, 15)
+    if kind in ("nan", "inf"):
+        h[7 * 15 + 4, 11] = float(kind)
+    return q, w_k, w_v, w_o, h, ref
+
+
+# The values pass through half in one order and are not rounded in the other: 40 windows take the one, 2048 the other
+@pytest.mark.parametrize("windows", [40, 2048])
+@pytest.mark.parametrize("kind", ["nan", "inf", "large_states", "small_states", "uneven_weights", "uneven_columns", "large_values"])
+def test_qformer_pool_range(kind, windows):
+    """States and weights of any scale give the oracle's rows (each head against its own largest magnitude), and states that are not
+    finite give NaN in their window and the flag.  Values beyond 65504 are clamped and flagged where they pass through half."""
+    from paper_2603_11243_amd.binding import Context
+    from workloads import make_model_weights
+    q, w_k, w_v, w_o, h, ref = _unusual(kind, 128, windows, windows)
+    model = WORKLOADS["cfg1_tiny_f32"].model                   # a context without a model has no flags
+    ctx = Context(model, make_model_weights(model, 1))
+    try:
+        ctx.set_qformer(q.cuda(), w_k.cuda(), w_v.cuda(), w_o.cuda(), n_heads=16, window=15)
+        ctx.reserve(max_frames=len(h), max_utts=1)
+        ctx.device_flags()
+        got, _ = ctx.qformer_pool(h.cuda(), [0, len(h)])
+        got, flags = got.float().cpu().numpy(), ctx.device_flags()
+    finally:
+        ctx.close()
+    keep = np.ones(len(ref), bool)
+    if kind in ("nan", "inf"):
+        keep[21:24] = False
+        assert np.isnan(got[21:24]).all()
+    clamped = kind == "large_values" and windows == 40
+    assert flags == (2 if clamped or kind in ("nan", "inf") else 0)
+    if clamped:
+        assert np.isfinite(got).all() and np.abs(got).max() <= 65536      # 65504 as bfloat16
+        return
+    for head in range(16):
+        if not (kind == "uneven_weights" and head == 3 and windows == 40):      # (values of 2^-45 are zeros in half)
+            _check(got[keep, 64 * head:64 * head + 64], ref[keep, 64 * head:64 * head + 64])
