@@ -233,8 +233,8 @@ int ctc_head_gate(ssd_ctx *ctx, const void *enc_h, const int32_t *cu_frames /*ho
  * filled with the prefix sums S_b = n_q * ceil(T_b / window) that verify_forward takes.  In small calls, and for other shapes than 16
  * heads of 64 dims with n_q <= 3 and window <= 16, the projected values w_v h_t pass through IEEE half: one beyond 65504
  * is clamped and raises SSD_FLAG_ACT_OVERFLOW.  Large calls pool the states first and project the sums, o = w_v sum_t p_t h_t, in at least 16
- * significant bits and the range of fp32: nothing is clamped.  A state that is not finite makes the rows of its window NaN and
- * raises the flag in both.  The rest of a q-former
+ * significant bits and the range of fp32: nothing is clamped.  A state that is not finite raises the
+ * flag and makes the rows of its window NaN in both, unless its frame has probability 0 for every query.  The rest of a q-former
  * layer (self-attention among the queries, feed-forward block, normalisation, second layer) is not described in
  * the paper and not part of this call.
  * enc_h: dev [cu_frames[B], d_enc] bf16 packed rows; speech_emb: dev [n_q * (frames / window + B), d_out] is enough.

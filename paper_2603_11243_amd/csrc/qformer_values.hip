@@ -90,12 +90,10 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
     // (the transposing reads take 32 bytes of rows r .. r + 3 and r + 8 .. r + 11 at a time: the halves of rows 8 .. 15 are exchanged.
     // Through registers because the compiler lets every other LDS access wait for all direct loads to LDS in flight: 2 us a step.)
     const __amdgpu_buffer_rsrc_t h_rsrc = make_rsrc(enc_h), w_rsrc = make_rsrc(w_frag);
-    unsigned h_off[2];
+    auto row_offset = [&](int i, int frame) { return (unsigned)(win[i].frame0 + frame) * (unsigned)d_enc * 2u + (unsigned)(((lane % 4) ^ (2 * (lane / 32))) * 16); };
+    unsigned h_off[2];                                       // lane / 4: the frame
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int r = lane / 4;
-        h_off[i] = (unsigned)(win[i].frame0 + min(r, win[i].n_frames - 1)) * (unsigned)d_enc * 2u + (unsigned)(((lane % 4) ^ (2 * (r / 8))) * 16);
-    }
+    for (int i = 0; i < 2; ++i) h_off[i] = row_offset(i, min(lane / 4, win[i].n_frames - 1));
     const int n32 = d_enc / 32;
     uint4 h_reg[2][2];                                       // two steps ahead of the fragments
     auto load_h = [&](int c, uint4 (&dst)[2]) {
@@ -108,6 +106,7 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
     // ---- probabilities: lane (head m, frames 8 (g % 2) .. + 7), hi for g < 2 and lo for the others.  The lanes with g < 2 make the
     // first window's pairs and the others the second window's; half of each is exchanged.
     f16x8_t p_frag[2][NQ];
+    bool lost;                                               // a frame has no finite score
     {
         const int f0 = g < 2 ? win[0].frame0 : win[1].frame0, nf = g < 2 ? win[0].n_frames : win[1].n_frames;
         float s[NQ][8];
@@ -115,6 +114,27 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
         for (int j = 0; j < NQ; ++j)
 #pragma unroll
             for (int e = 0; e < 8; ++e) s[j][e] = scores[(int64_t)(f0 + min(8 * (g % 2) + e, nf - 1)) * QF_SCORE_COLS + j * QV_HEADS + m];
+        unsigned finite[2] = {0, 0};                         // frames of the two windows that have a finite score
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < NQ; ++j) any |= fabsf(s[j][e]) < INFINITY;
+            const unsigned long long lanes = __ballot(any);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((lanes >> (16 * q)) & 0xffff) finite[q / 2] |= 1u << (8 * (q % 2) + e);
+        }
+        // Such a frame has an infinite or NaN state, and each of its probabilities is 0 or in a column of NaN.  Another frame's states
+        // take its place in the sums: 0 times infinity would reach the queries that give it no weight.
+        lost = (finite[0] & finite[1]) != 0xffffu;
+        if (lost) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (finite[i] && !(finite[i] >> (lane / 4) & 1)) h_off[i] = row_offset(i, __ffs(finite[i]) - 1);
+            load_h(0, h_reg[0]);
+            load_h(1, h_reg[1]);
+        }
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
             float mx = -INFINITY, sum = 0.f;
@@ -277,7 +297,7 @@ __global__ void __launch_bounds__(64 * QV_WAVES) qformer_values_kernel(const bf1
             for (int n = 0; n < 4; ++n)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) finite = fmaf(acc[h][j][n][r], 0.f, finite);
-    if (finite != 0.f) raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);
+    if (lost || finite != 0.f) raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);
 
     // ---- out: the rows of the 16 windows are one contiguous piece; a lane's four dims go through LDS into it
     // (lane: window m, dims 16 n + 4 g .. + 3 of head 2 wave + h; the rows of a window are 16 bytes apart from a multiple of the banks)

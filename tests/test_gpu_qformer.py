@@ -139,20 +139,26 @@ def _unusual(kind, d_enc, windows, seed):
         w_k[:, 5] *= 2.0 ** 30
     elif kind == "large_values":
         w_v = w_v * 2.0 ** 17
+    elif kind == "no_weight":                                  # every score falls with column 0
+        q, w_k[:, 0] = q.abs(), 1.0
     q, w_k, w_v, h = (t.bfloat16() for t in (q, w_k, w_v, h))
     w_o = torch.eye(1024).bfloat16()
     ref, _ = O.qformer_window_pool(h, [0, len(h)], q, w_k, w_v, w_o, 16, 15)
     if kind in ("nan", "inf"):
         h[7 * 15 + 4, 11] = float(kind)
+    if kind == "no_weight":                                    # a frame that no query gives any: as if it were not there
+        rest = torch.cat([h[105:109], h[110:120]])
+        ref[21:24] = O.qformer_window_pool(rest, [0, 14], q, w_k, w_v, w_o, 16, 15)[0]
+        h[109, 0] = -float("inf")
     return q, w_k, w_v, w_o, h, ref
 
 
 # The values pass through half in one order and are not rounded in the other: 40 windows take the one, 2048 the other
 @pytest.mark.parametrize("windows", [40, 2048])
-@pytest.mark.parametrize("kind", ["nan", "inf", "large_states", "small_states", "uneven_weights", "uneven_columns", "large_values"])
+@pytest.mark.parametrize("kind", ["nan", "inf", "large_states", "small_states", "uneven_weights", "uneven_columns", "large_values", "no_weight"])
 def test_qformer_pool_range(kind, windows):
     """States and weights of any scale give the oracle's rows (each head against its own largest magnitude), and states that are not
-    finite give NaN in their window and the flag.  Values beyond 65504 are clamped and flagged where they pass through half."""
+    finite give the flag and NaN in their window, unless no query gives their frame any weight.  Values beyond 65504 are clamped and flagged where they pass through half."""
     from paper_2603_11243_amd.binding import Context
     from workloads import make_model_weights
     q, w_k, w_v, w_o, h, ref = _unusual(kind, 128, windows, windows)
@@ -171,7 +177,7 @@ def test_qformer_pool_range(kind, windows):
         keep[21:24] = False
         assert np.isnan(got[21:24]).all()
     clamped = kind == "large_values" and windows == 40
-    assert flags == (2 if clamped or kind in ("nan", "inf") else 0)
+    assert flags == (2 if clamped or kind in ("nan", "inf", "no_weight") else 0)
     if clamped:
         assert np.isfinite(got).all() and np.abs(got).max() <= 65536      # 65504 as bfloat16
         return
