@@ -204,10 +204,14 @@ QformerPlan plan_qformer(int64_t frames, int64_t utts, int window, int n_q, int 
 
 int attn_tile_rows(int dtype) { return dtype == SSD_BF16 ? 64 : F32_ATTN_ROWS; }
 int head_groups(const ssd_model_cfg& c) { return c.dtype == SSD_BF16 ? lmhead_col_groups(c.vocab) : lmhead_f32_groups(c.vocab); }
-// Windows from which the projector's values are projected after the pooling (qformer_values.hip): a workgroup takes 16 of them and some
-// 45 us, however few there are.  us a call, projected before / after, d_out 2048 and 3072: 768 windows 65 / 77 and 66 / 79, 1024 windows
-// 82 / 79 and 87 / 84, 1536 windows 103 / 86 and 111 / 94, 4096 windows 271 / 151 and 297 / 181, 8192 windows 503 / 303 and 566 / 363.
-constexpr int QF_VALUES_MIN_WINDOWS = 1024;
+// Whether the projector's values are projected after the pooling (qformer_values.hip).  Its work goes by windows and queries, 16 windows
+// to a workgroup and some 30 us a query however few there are; the other order's goes by frames.  us a call of 1024-wide states, projected
+// before / after the pooling, d_out 2048.  3 queries, 15 frames a window: 1024 windows 83 / 100, 1536 104 / 107, 2048 132 / 114, 4096 267 /
+// 169, 16384 1001 / 670; 10 frames: 2048 windows 99 / 111, 3072 161 / 146; 6 frames: 8192 windows 282 / 288; 4 frames: 16384 windows 467 / 553.
+// 2 queries: 15 frames 1024 windows 78 / 76, 6 frames 2048 windows 68 / 83, 4096 131 / 121, 4 frames 8192 windows 198 / 203.  1 query:
+// 15 frames 512 windows 48 / 57, 1024 73 / 60, 4 frames 2048 windows 52 / 62, 3072 82 / 82, 3 frames 8192 windows 133 / 133.  2048-wide states
+// cross at the same frames, narrower ones earlier (256-wide, 3 queries: 1024 windows of 15 60 / 58, 4096 of 6 118 / 108).
+bool values_after_pooling(int64_t frames, int64_t windows, int n_q) { return frames >= 4096 * (2 * n_q + 1) && frames >= 3 * n_q * windows; }
 // SSD_FLAG_ACT_OVERFLOW is about the 16-bit operand types: fp32 models raise it nowhere
 int32_t* head_flags(const ssd_ctx* c) { return c->cfg.dtype == SSD_BF16 ? c->dev_flags : nullptr; }
 
@@ -839,7 +843,7 @@ int qformer_pool(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int 
     {
         ProfScope ps(ctx, SSD_PROF_QFORMER);
         const QWindow* d_wins = reinterpret_cast<const QWindow*>(ws + p.wins);
-        if (ctx->qf_wfrag && n_windows >= QF_VALUES_MIN_WINDOWS) {
+        if (ctx->qf_wfrag && values_after_pooling(n_rows, n_windows, n_q)) {
             launch_gemm_scores(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, (int)n_rows, d_enc, ctx->stream);
             launch_qformer_values(static_cast<const uint16_t*>(enc_h), scores, ctx->qf_wfrag, d_wins, n_windows, n_q, d_enc, o, ctx->dev_flags, ctx->stream);
         } else {

@@ -11,7 +11,7 @@
 //   2. per window: softmax over its frames of each score column, weighted sum of the value columns   (here)
 //   3. g [3 windows, d_out] = o w_o^T                      one MFMA GEMM, stored in the storage type of speech_emb
 // Large batches of the usual shape skip the value columns of the product and project the values after the pooling instead
-// (qformer_values.hip; the rule is QF_VALUES_MIN_WINDOWS in api.hip).
+// (qformer_values.hip; the rule is values_after_pooling in api.hip).
 // Windows never cross an utterance; the last window of an utterance may hold fewer frames.
 #include "device_utils.h"
 #include "ssd_internal.h"

@@ -96,9 +96,12 @@ def test_qformer_pool_argument_errors():
         ctx.close()
 
 
-# From 1024 windows on the values are projected after the pooling, 16 windows to a workgroup: a last workgroup of 1 and of 15, windows
-# of one and of 16 frames, every query count, encoder widths of one and several steps.  Fewer windows take the other order.
-@pytest.mark.parametrize("n_q,d_enc,window,windows", [(3, 1024, 15, 1025), (3, 64, 15, 1039), (2, 192, 16, 1024), (1, 128, 1, 1040), (3, 128, 4, 1023)])
+# From 28 K frames (20 K, 12 K for two queries, one) in windows of nine or more (six, three) the values are projected after the pooling,
+# 16 windows to a workgroup: a last workgroup of 1 and of 15, windows of 4 and of 16 frames, every query count, encoder widths of one
+# and several steps.  Fewer frames and shorter windows take the other order: the second line, and the last one just so.
+@pytest.mark.parametrize("n_q,d_enc,window,windows", [(3, 1024, 15, 1937), (3, 64, 15, 2047), (2, 192, 16, 1552), (1, 128, 4, 4112), (1, 64, 16, 784), (3, 128, 10, 2881),
+                                                      (3, 1024, 15, 1025), (3, 64, 15, 1039), (2, 192, 16, 1024), (1, 128, 1, 1040), (3, 128, 4, 1023),
+                                                      (3, 64, 15, 1911), (3, 64, 8, 4096)])
 def test_qformer_pool_values_after_pooling(n_q, d_enc, window, windows):
     from paper_2603_11243_amd.binding import Context
     g = torch.Generator().manual_seed(windows)
