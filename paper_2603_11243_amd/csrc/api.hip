@@ -295,12 +295,14 @@ int check_model(ssd_ctx* c, const ssd_model_cfg& m) {
 }
 
 // Without the counters the gate takes two launches: a failure is none of the caller's, and a stream under capture is left alone.
-void alloc_gate_counters(ssd_ctx* c) {
+bool capturing(hipStream_t st) {
     hipStreamCaptureStatus capture;
-    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return;
-    }
+    if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();                                       // the default stream, while another one is captured
+    return true;
+}
+void alloc_gate_counters(ssd_ctx* c) {
+    if (capturing(c->stream)) return;
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;       // captures of other streams go on
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     void* p = nullptr;
@@ -728,10 +730,13 @@ int ctc_gate(ssd_ctx* ctx, const void* logits, int dtype, const int32_t* cu_fram
         const int rc = upload(ctx, cu_frames, cu_dev, (size_t)(B + 1) * 4);
         if (rc != SSD_OK) return rc;
     }
+    // The counts are the context's, whose calls run one after the other on its stream.  A captured call may be replayed on another
+    // stream next to them, or next to another captured one: it takes the two launches, which share nothing but the workspace.
+    unsigned* arrived = ctx->gate_arrived && !capturing(ctx->stream) ? ctx->gate_arrived : nullptr;
     {
         ProfScope ps(ctx, SSD_PROF_GATE);
         if (!launch_gate_fused(logits, dtype, cu_frames, n_rows, B, V_ctc, blank_id, tau_ctc, H, arg, max_entropy, gate_pass, draft_ctc, draft_len,
-                               ctx->gate_arrived, ctx->stream)) {
+                               arrived, ctx->stream)) {
             launch_gate_frames(logits, dtype, n_rows, V_ctc, H, arg, ctx->stream);
             if (as_args) launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
             else launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);

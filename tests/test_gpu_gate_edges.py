@@ -57,7 +57,7 @@ def test_one_launch_around_its_bytes(ctx, n):  # noqa: F811
 
 
 def test_one_launch_in_a_graph(ctx):  # noqa: F811
-    """Replays next to eager calls of other sizes that use the same counts."""
+    """A captured call, which takes two launches, replayed next to eager calls of other sizes, which take one."""
     T = [40, 300, 16, 700]
     cu = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
     g = torch.Generator().manual_seed(5)
@@ -90,4 +90,57 @@ def test_one_launch_in_a_graph(ctx):  # noqa: F811
             c.ctc_gate(other, np.arange(0, 641, 64 >> (i % 2)).astype(np.int32), 0, 2.0)
             torch.cuda.synchronize()
     finally:
+        c.close()
+
+
+def _kernel_nodes(graph):
+    import ctypes
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    return n.value
+
+
+def test_captured_calls_are_independent(ctx):  # noqa: F811
+    """Two captured calls of one context with their own outputs, replayed on two streams at once: nothing may be shared.  A call with
+    frame outputs and prefix sums as arguments is the two kernels and nothing else; one launch would count in the context's memory."""
+    from paper_2603_11243_amd.binding import Context
+    side = torch.cuda.Stream()
+    c = Context(stream=side)
+    calls = []
+    try:
+        c.reserve(max_frames=4096, max_utts=64)
+        for seed, T in ((1, [200, 16, 300, 90]), (2, [500, 40, 77])):
+            cu = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
+            z = (torch.randn(int(cu[-1]), 512, generator=torch.Generator().manual_seed(seed)) * 3).to(torch.bfloat16).cuda()
+            ctx.reserve(max_frames=4096, max_utts=64)
+            want = {k: v.clone() for k, v in ctx.ctc_gate(z, cu, 0, 2.0, want_frames=True).items()}
+            out = {k: torch.zeros_like(v) for k, v in want.items()}
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph(keep_graph=True)
+            with torch.cuda.graph(graph, stream=side):
+                c.ctc_gate(z, cu, 0, 2.0, out=out)
+            assert _kernel_nodes(graph) == 2
+            graph.instantiate()
+            calls.append((graph, torch.cuda.Stream(), cu, z, want, out))
+        for i in range(10):
+            for call in calls:
+                for v in call[5].values():
+                    v.zero_()
+            torch.cuda.synchronize()
+            for _ in range(20):
+                for graph, stream, *_ in calls:
+                    with torch.cuda.stream(stream):
+                        graph.replay()
+            torch.cuda.synchronize()
+            for _, _, cu, _, want, out in calls:
+                for u in range(len(cu) - 1):
+                    n = int(want["draft_len"][u])
+                    assert torch.equal(out["draft_ctc"][cu[u]:cu[u] + n], want["draft_ctc"][cu[u]:cu[u] + n]), (i, u)
+                for k in want:
+                    if k != "draft_ctc":
+                        assert torch.equal(out[k], want[k]), (i, k)
+    finally:
+        torch.cuda.synchronize()
         c.close()
