@@ -19,8 +19,8 @@
  *   - Return value: SSD_OK or a negative ssd_status.  Argument errors are detected on the host
  *     before anything is launched, so on a non-zero return no output buffer has been written.
  *     ssd_last_error gives a message for the last failing call on that context.
- *   - Device memory is allocated only by ssd_create and ssd_set_ctc_head (re-laid-out weights, small
- *     tables) and freed by ssd_destroy.  All activations live in the caller-provided workspace
+ *   - Device memory is allocated only by ssd_create, ssd_set_ctc_head and ssd_set_qformer (re-laid-out weights, small
+ *     tables, 16 KB of counts for ctc_gate) and freed by ssd_destroy.  All activations live in the caller-provided workspace
  *     (ssd_set_workspace).
  *   - One context must not be used from two host threads at once.
  */
@@ -132,7 +132,7 @@ int ssd_device_flags(ssd_ctx *ctx, int32_t *flags /*host*/);
  * discards earlier samples.  ssd_profile_read waits for the stream, writes per class the summed
  * device time in milliseconds and the number of bracketed launches since the last select/read
  * (arrays of SSD_PROF_N_CLASSES entries, host memory), and clears the samples.  A span covers one
- * kernel launch, except SSD_PROF_GATE (the two gate kernels) and SSD_PROF_LMHEAD (LM head,
+ * kernel launch, except SSD_PROF_GATE (the one or two gate kernels of a call) and SSD_PROF_LMHEAD (LM head,
  * merge of partials and prefix scan). */
 enum ssd_prof_class {
     SSD_PROF_OFF = -2, SSD_PROF_ALL = -1,
@@ -169,7 +169,9 @@ int ssd_profile_read(ssd_ctx *ctx, float *total_ms /*host [SSD_PROF_N_CLASSES]*/
  *   max_entropy[b] = max_t H_t;  gate_pass[b] = 1 iff max_entropy[b] < tau_ctc (strict, Eq. 3).
  * logits: dev [cu_frames[B], V_ctc] packed rows, row-major, dtype SSD_F32 or SSD_BF16; -inf is a
  * legal score (probability 0), NaN/+inf give unspecified results.
- * frame_entropy / frame_argmax: optional dev outputs [cu_frames[B]] (NULL to skip). */
+ * frame_entropy / frame_argmax: optional dev outputs [cu_frames[B]] (NULL to skip).
+ * Small calls are one kernel that counts finished rows in the context's memory; calls under stream capture never are, so that
+ * captured calls with their own outputs, both frame outputs among them, and at most 256 utterances may be replayed side by side. */
 int ctc_gate(ssd_ctx *ctx, const void *logits, int dtype, const int32_t *cu_frames /*host*/, int B,
              int V_ctc, int blank_id, float tau_ctc,
              float *frame_entropy, int32_t *frame_argmax,
@@ -178,7 +180,7 @@ int ctc_gate(ssd_ctx *ctx, const void *logits, int dtype, const int32_t *cu_fram
 
 /* ctc_gate for callers that cannot allocate: code under HIP graph capture, tight serving loops and
  * harnesses that forbid allocation.  Needs no context and no workspace; calls no hipMalloc, hipFree,
- * host allocation, copy or wait: it only launches the two kernels of ctc_gate on `hip_stream`
+ * host allocation, copy or wait: it only launches the two kernels that larger ctc_gate calls take, too, on `hip_stream`
  * (a hipStream_t, NULL = default stream) of the current device.  The per-frame entropies and greedy
  * labels, which ctc_gate keeps in the workspace, live in a device array built into the library:
  * 8 bytes per frame, SSD_NOALLOC_MAX_FRAMES frames (2 MiB), one copy per GPU for the life of the process.

@@ -328,7 +328,11 @@ int ssd_create(ssd_ctx** out, const ssd_model_cfg* cfg, const ssd_weights* w, vo
     if ((cfg == nullptr) != (w == nullptr)) return SSD_EINVAL;
     ssd_ctx* c = new ssd_ctx();
     c->stream = static_cast<hipStream_t>(hip_stream);
-    if (!cfg) { *out = c; return SSD_OK; }
+    if (!cfg) {
+        alloc_gate_counters(c);
+        *out = c;
+        return SSD_OK;
+    }
     int rc = check_model(c, *cfg);
     if (rc == SSD_OK) {
         const void* const* per_layer[] = {w->wq, w->wk, w->wv, w->wo, w->w_gate, w->w_up, w->w_down, w->norm_attn, w->norm_mlp};
@@ -445,6 +449,7 @@ int ssd_create(ssd_ctx** out, const ssd_model_cfg* cfg, const ssd_weights* w, vo
     if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return bail(e, "weight packing");
     if ((e = hipGetLastError()) != hipSuccess) return bail(e, "weight packing launch");
     c->inexact_weights = (int64_t)n_inexact;
+    alloc_gate_counters(c);
     *out = c;
     return SSD_OK;
 }
@@ -454,7 +459,10 @@ int64_t ssd_inexact_weights(const ssd_ctx* ctx) { return ctx ? ctx->inexact_weig
 void ssd_destroy(ssd_ctx* c) {
     if (!c) return;
     (void)hipStreamSynchronize(c->stream);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;       // captures of other streams go on
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
     for (void* p : c->owned) if (p) (void)hipFree(p);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
     c->stager.release();
     c->prof.release();
     delete c;
@@ -490,7 +498,6 @@ int ssd_set_workspace(ssd_ctx* ctx, void* dev_ptr, size_t bytes) {
     if (reinterpret_cast<uintptr_t>(dev_ptr) & 255) return fail(ctx, SSD_EINVAL, "workspace must be 256-byte aligned");
     ctx->ws = dev_ptr;
     ctx->ws_bytes = bytes;
-    if (dev_ptr && !ctx->gate_arrived) alloc_gate_counters(ctx);
     return SSD_OK;
 }
 

@@ -144,3 +144,23 @@ def test_captured_calls_are_independent(ctx):  # noqa: F811
     finally:
         torch.cuda.synchronize()
         c.close()
+
+
+def test_device_memory_is_allocated_when_the_context_is_made():
+    from torch.profiler import ProfilerActivity, profile
+    from paper_2603_11243_amd.binding import Context
+
+    def runtime_calls(f):
+        with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+            result = f()
+            torch.cuda.synchronize()
+        return result, [e.key for e in prof.key_averages()]
+
+    buf = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    c, made = runtime_calls(Context)
+    try:
+        _, then = runtime_calls(lambda: c.set_workspace(buf))
+        assert "hipMalloc" in made                              # (what the profiler calls it)
+        assert not any("Malloc" in key or "Memset" in key for key in then), then
+    finally:
+        c.close()
