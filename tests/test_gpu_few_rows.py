@@ -159,3 +159,33 @@ def test_verify_tile_heights(shape, M):
     vi = _inputs(m, [(130 + (M - 150 * n if b == 0 else 0), 8, 12) for b in range(n)], M)
     tau = 1.0 / m.vocab
     _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
+
+
+# the QKV epilogue at the same heights with everything it stores: rotated keys and values of every row in the K/V cache, slots in
+# another order than rows, either operand type.  Two roundings to it lie before a cached row (norm, store); ROW_TOL allows for eight.
+@pytest.mark.parametrize("M", [2200, 3300])
+@pytest.mark.parametrize("operand", ["f16", "bf16"])
+def test_cached_rows_at_tile_heights(M, operand):
+    m = ModelCfg(1, 2048, 16, 8, 128, 256, 512, dtype="bf16")
+    w = make_model_weights(m, 95)
+    n = M // 150
+    vi = _inputs(m, [(130 + (M - 150 * n if b == 0 else 0), 8, 12) for b in range(n)], M)
+    rows = np.diff(vi.cu_speech) + np.diff(vi.cu_prompt) + np.diff(vi.cu_draft)
+    kv_start = (int(rows.sum()) + 3 - np.cumsum(rows)).astype(np.int32)      # the last utterance first
+    ctx = Context(m, w, operand=operand)
+    ctx.set_kv_cache(int(rows.sum()) + 3)
+    ctx._kv.zero_()
+    ctx.reserve(max_tokens=M, max_verify_rows=int(vi.cu_draft[-1]), max_utts=n)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    ctx.verify_forward(vi.speech_emb.cuda(), vi.cu_speech, dev(vi.prompt_ids), vi.cu_prompt, dev(vi.draft_ids), vi.cu_draft, kv_start=kv_start)
+    cache = ctx._kv.view(ctx.act_dtype).float().cpu().numpy().reshape(2, -1, m.d_kv)
+    assert ctx.device_flags() == 0
+    ctx.close()
+    L = {k: O._f64(v) for k, v in w["layers"][0].items()}
+    for b in range(n):
+        ids = np.concatenate([vi.prompt_ids[vi.cu_prompt[b]:vi.cu_prompt[b + 1]], vi.draft_ids[vi.cu_draft[b]:vi.cu_draft[b + 1]]]).astype(np.int64)
+        x = np.concatenate([O._f64(vi.speech_emb[vi.cu_speech[b]:vi.cu_speech[b + 1]]), O._f64(w["embed"][ids])])
+        for part, want in enumerate(_layer_kv(x, L, m)):
+            got = cache[part, kv_start[b]:kv_start[b] + rows[b]]
+            assert (np.linalg.norm(got - want, axis=1) <= ROW_TOL[operand] * np.linalg.norm(want, axis=1)).all(), (b, "kv"[part])
+    assert not cache[:, :3].any()                            # nothing beside them

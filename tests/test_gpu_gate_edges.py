@@ -164,3 +164,18 @@ def test_device_memory_is_allocated_when_the_context_is_made():
         assert not any("Malloc" in key or "Memset" in key for key in then), then
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("T,one", [([250], True), ([16] * 256, True), ([15, 250], False), ([16] * 257, False)])
+def test_which_calls_take_one_launch(ctx, T, one):  # noqa: F811
+    from torch.profiler import ProfilerActivity, profile
+    cu = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
+    z = torch.randn(int(cu[-1]), 512, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16).cuda()
+    ctx.reserve(max_frames=8192, max_utts=512)
+    out = ctx.ctc_gate(z, cu, 0, 2.0)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        ctx.ctc_gate(z, cu, 0, 2.0, out=out)
+        torch.cuda.synchronize()
+    names = [e.key for e in prof.key_averages() if "gate_" in e.key]
+    assert len(names) == (1 if one else 2) and ("gate_fused" in names[0]) == one, names
