@@ -11,6 +11,7 @@
 // stable compaction of the frames kept by B (not blank, and different from the previous frame).
 //
 // Batches that do not fill the device take both steps in one launch (gate_fused).
+#include <algorithm>
 #include "device_utils.h"
 #include "ssd_internal.h"
 
@@ -392,13 +393,16 @@ __global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__
 // next call.  Nobody waits for anybody.  (No agent-scope fences: they write back and invalidate a whole L2.)
 // us a call, two launches / one: one utterance of 250 frames of 512 bf16 scores 9.9 / 7.0, 64 of 100 10.3 / 7.1, 32 of 500 9.9 / 7.2,
 // 64 of 250 frames of 348 fp32 scores 10.0 / 8.3.
-// Where the one launch stays the faster: up to 24 MiB of scores, because a row block pays for its stores and the count with waits
-// that only pay off while the device waits for the host (two / one launch in us: 512 bf16 scores 64 x 250 frames 9.9 / 7.3, 64 x 400
-// [25 MiB] 9.9 / 8.4, 128 x 250 [31 MiB] 10.5 / 10.2; 348 fp32 scores 32 x 500 [21 MiB] 10.0 / 8.1, 32 x 750 [31 MiB] 11.0 / 10.5,
-// 256 x 100 [33 MiB] 10.4 / 12.3); up to 192 workgroups an utterance, because additions to one count go one after the other (512 fp32
-// scores, four frames a workgroup: 2 x 750 frames 9.8 / 7.3, 8 x 750 9.8 / 9.1, 8 x 1000 9.9 / 11.0, 1 x 3000 11.5 / 14.9); and as many
-// workgroups as have a place in the arguments.
-constexpr int64_t GATE_FUSED_MAX_BYTES = (int64_t)24 << 20;
+// Where the one launch stays the faster: until the device takes longer for it than the host for two (9.8 us).  A row block pays for its stores
+// and the count with waits, which add up with the scores (two / one launch in us, MiB of scores; 512 bf16, 64 utterances: 24 9.7 / 8.1,
+// 28 9.9 / 9.1, 32 10.9 / 10.0, 40 even; 348 fp32: 24 10.1 / 9.1, 28 10.1 / 9.6, 32 10.2 / 10.6, at 256 utterances 24 10.0 / 9.9, 28 9.9 /
+// 10.3, 32 10.2 / 11.8; 256 and 512 fp32: 28 9.8 / 8.0 and 10.1 / 7.6); and additions to one count go one after the other, so that
+// the last block of a long utterance waits for all before it.  That shows where the device is late already: 4 utterances of 188 blocks,
+// 16 MiB, 10.0 / 11.3; of 192, 12 MiB, 9.7 / 10.6; of 141, 12 MiB, 10.1 / 10.0; of 128, 8 MiB, 9.8 / 8.0; 16 of 96, 24 MiB, 9.8 / 10.1; 16 of
+// 80, 20 MiB, 9.7 / 8.3; 2 of 188, 3 MiB, 9.8 / 7.3.  Of 209 calls measured these limits take 168, of which one is more than 2 % slower (4 %);
+// they leave 12 to the two launches that the one would take 5 to 20 % less for.  And no more workgroups than have a place in the arguments.
+constexpr int64_t GATE_FUSED_MAX_BYTES = (int64_t)28 << 20;
+constexpr int64_t GATE_FUSED_MAX_UTT_BYTES = (int64_t)2000 << 20;     // blocks of the longest utterance times bytes of the call
 constexpr int GATE_FUSED_MAX_BLOCKS = 2048, GATE_FUSED_MAX_UTT_BLOCKS = 192;
 constexpr int ARRIVED_STRIDE = GATE_ARRIVED_BYTES / GATE_MAX_ARG_UTTS / 4;
 struct GateTail {
@@ -546,13 +550,15 @@ bool launch_gate_fused(const void* logits, int dtype, const int32_t* cu_frames, 
     const int lanes = dtype == SSD_BF16 ? vec_lanes(static_cast<const bf16_t*>(logits), n_rows, V) : vec_lanes(static_cast<const float*>(logits), n_rows, V);
     if (!arrived || B > GATE_MAX_ARG_UTTS || !lanes) return false;
     const int rows = 256 / lanes;
-    if (n_rows > (int64_t)rows * GATE_FUSED_MAX_BLOCKS || n_rows * V * (dtype == SSD_BF16 ? 2 : 4) > GATE_FUSED_MAX_BYTES) return false;
+    const int64_t bytes = n_rows * V * (dtype == SSD_BF16 ? 2 : 4);
+    if (n_rows > (int64_t)rows * GATE_FUSED_MAX_BLOCKS || bytes > GATE_FUSED_MAX_BYTES) return false;
+    const int longest = rows * (int)std::min<int64_t>(GATE_FUSED_MAX_UTT_BLOCKS, GATE_FUSED_MAX_UTT_BYTES / bytes);
     GateTail tail;
     int block = 0;
     tail.cu[0] = 0;
     for (int b = 0; b < B; ++b) {
         const int length = cu_frames[b + 1] - cu_frames[b];
-        if (length < rows || length > rows * GATE_FUSED_MAX_UTT_BLOCKS) return false;
+        if (length < rows || length > longest) return false;
         tail.cu[b + 1] = cu_frames[b + 1];
         for (; block * rows < cu_frames[b + 1]; ++block) tail.first[block] = (uint8_t)b;
     }

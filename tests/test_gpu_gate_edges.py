@@ -31,7 +31,7 @@ def test_fp32_rows_around_chunk_counts(ctx, V, n):  # noqa: F811
 
 
 # one launch for both steps: utterances around a workgroup's 16 or 4 rows (one row fewer takes two launches), around the 192
-# workgroups an utterance may have and the 2048 of a call, around 24 MiB, and through the 1024 frames a trip of the collapse.  Long
+# workgroups an utterance may have and the 2048 of a call, around 24 and 28 MiB, and through the 1024 frames a trip of the collapse.  Long
 # and short ones in turn, so that every call finds the counts as the one before left them.
 @pytest.mark.parametrize("dtype,V,rows", [("bfloat16", 512, 16), ("bfloat16", 40, 16), ("bfloat16", 1024, 4), ("float32", 256, 16), ("float32", 348, 4)])
 def test_one_launch_around_its_limits(ctx, dtype, V, rows):  # noqa: F811
@@ -50,7 +50,7 @@ def test_one_launch_around_its_limits(ctx, dtype, V, rows):  # noqa: F811
         _run_and_compare(ctx, z, cu, 7, 0.7)
 
 
-@pytest.mark.parametrize("n", [24576 - 16, 24576, 24576 + 16])
+@pytest.mark.parametrize("n", [24576 - 16, 24576, 24576 + 16, 28672 - 16, 28672, 28672 + 16])
 def test_one_launch_around_its_bytes(ctx, n):  # noqa: F811
     z = torch.randn(n, 512, generator=torch.Generator().manual_seed(n)) * 3
     _run_and_compare(ctx, z.to(torch.bfloat16), np.linspace(0, n, 65).astype(np.int32), 0, 2.0)
@@ -166,12 +166,14 @@ def test_device_memory_is_allocated_when_the_context_is_made():
         c.close()
 
 
-@pytest.mark.parametrize("T,one", [([250], True), ([16] * 256, True), ([15, 250], False), ([16] * 257, False)])
+# (28 MiB; 2000 blocks of the longest utterance times MiB: 178 x 11.1 and 180 x 11.3)
+@pytest.mark.parametrize("T,one", [([250], True), ([16] * 256, True), ([15, 250], False), ([16] * 257, False), ([448] * 64, True),
+                                   ([448] * 63 + [464], False), ([2848] * 4, True), ([2880] * 4, False)])
 def test_which_calls_take_one_launch(ctx, T, one):  # noqa: F811
     from torch.profiler import ProfilerActivity, profile
     cu = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
     z = torch.randn(int(cu[-1]), 512, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16).cuda()
-    ctx.reserve(max_frames=8192, max_utts=512)
+    ctx.reserve(max_frames=len(z), max_utts=512)
     out = ctx.ctc_gate(z, cu, 0, 2.0)
     torch.cuda.synchronize()
     with profile(activities=[ProfilerActivity.CUDA]) as prof:
