@@ -743,11 +743,14 @@ void launch_stream_layout(const uint16_t* w, void* out, int N, int K, hipStream_
 // The last term is TILE_OVERHEAD row-slices, about eleven slices of the highest tile: 40 K x 3072 outputs of K = 1024 take 290 us
 // in ten rounds of 192 rows and 268 us in eight of 256.  Five heights because a coarser step leaves up to a quarter of a round
 // empty (256, 192 and 128 only, against these, us: QKV of 3400 rows 68.9 -> 62.4 and 136.6 -> 125.2 at 2048 and 3072 wide, gate/up of
-// 2600 rows 162.5 -> 149.4, down of 4200 rows 166 -> 157, of 6400 rows 196 -> 184 and 327 -> 310; over 24 row counts from 2300 to
-// 15390 and four projections at two widths 1.5 % less, none more than 0.5 % slower).  Rounds of 160 rows that are filled are
-// no faster than three quarters of a round of 192, where all CUs store at once (QKV of 4788 rows, 1.88 rounds of 160: 99.1 us, 1.56
-// of 192: 92.8; with 1.69 rounds, 4200 rows, 91.0 and 94.3); the residual's adds stand more of it (down of 4788 rows 164 and 169, of
-// 5056 rows, a round of exactly 256, 163 and 161).
+// 2600 rows 162.5 -> 149.4, down of 4200 rows 166 -> 157, of 6400 rows 196 -> 184 and 327 -> 310).  Over 84 row counts from 2060 to 15340
+// and four projections at two widths the rule is 0.12 % from the best of the five heights on average and 6 % at most; 256, 192 and 128
+// with the same cost, 1.35 % and 19 %.
+// One exception: in whole sums of K <= 2048 the stores are a large part of a round, and two or more nearly full rounds of 160 rows, where
+// all CUs store at once, are no faster than those of 192 with room in the last (QKV, K = 2048, two rounds, 160 / 192 rows in us: 4460 rows,
+// 0.88 of a round full, 89 / 93; 4620, 0.91, 90 / 97; 4780, 0.94, 101 / 97; 4940, 0.97, 101 / 97; 5100, 1.0, 102 / 97).  Not in one round
+// (2380 rows, 0.94, 52 / 54; 2540, 1.0, 52 / 52), not with K = 3072 (3820 rows, 0.94, 124 / 130; 3980, 0.98, 127 / 132), not
+// for the residuals (K = 2048: 4940 rows, 0.97, 57 / 60; 9580, 0.94, 101 / 104; 10060, 0.98, 104 / 104).
 // With at most 128 rows the job is weight streaming and what counts is the number of weight bytes in
 // flight: at most 32 rows go to the register-streaming kernel when the shape divides evenly, more to its variant
 // with row blocks where that is faster (try_launch_stream_rows); otherwise a skinny 128 x 64 tile (four wavefronts, each 32 rows x 64 columns) with a six-stage LDS ring
@@ -777,14 +780,13 @@ template <class Epi>
 static void launch_big(const f16_t* A, const f16_t* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
     const int heights[5] = {256, 224, 192, 160, 128};
     const double eff[5] = {1.0, 0.98, 0.96, 0.92, 0.86};
-    constexpr double FULL_160 = Epi::USES_LDS ? 0.96 : 0.92;
     constexpr double TILE_OVERHEAD = 2800;
     int best = 0;
     double best_cost = 1e30;
     for (int c = 0; c < 5; ++c) {
         const long tiles = (long)((M + heights[c] - 1) / heights[c]) * (N / 256);
         const long rounds = (tiles + 255) / 256;
-        if (heights[c] == 160 && tiles > FULL_160 * 256 * rounds) continue;
+        if (heights[c] == 160 && !Epi::USES_LDS && K <= 2048 && rounds > 1 && tiles > 0.92 * 256 * rounds) continue;
         const double cost = (double)rounds * (heights[c] / eff[c] * (K / GEMM_BK) + TILE_OVERHEAD);
         if (cost < best_cost - 1e-9) { best_cost = cost; best = c; }
     }
