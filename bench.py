@@ -370,11 +370,12 @@ def qformer_leg(ctx, wl, device, d_enc=1024, d_h=1024, n_heads=16, window=15, n_
     ctx.profile_select(-2)
     ms /= n
     S = int(cu_s[-1])
-    flops = 2.0 * n_rows * d_enc * (n_q * n_heads + d_h) + 2.0 * S * d_h * wl.model.d_model
+    # scores and pooled states of every (frame, query, head); values and outputs of the pooled rows (large calls project after pooling)
+    flops = 4.0 * n_rows * d_enc * n_q * n_heads + 2.0 * S * d_h * (d_enc + wl.model.d_model)
     tf = flops / (ms * 1e-3) / 1e12
     return {"frames": n_rows, "speech_rows": S, "d_enc": d_enc, "d_h": d_h, "d_out": wl.model.d_model, "ms_per_call": ms,
             "frames_per_s": n_rows / (ms * 1e-3),
-            "roofline": {"bound": "mfma", "kernel": "two gemm_mfma16 launches (scores | values, output projection) + qformer_pool_kernel",
+            "roofline": {"bound": "mfma", "kernel": "gemm_mfma (scores) + qformer_values_kernel + gemm_mfma16 (output projection)",
                          "achieved": tf, "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": tf / PEAK_MFMA_TFLOPS, "flops_per_call": flops}}
 
 
