@@ -17,8 +17,9 @@
 // unit spread, four times and a twentieth of it): 2.717e-3, 3.574e-3 and 2.343e-3; the other order 2.725e-3, 3.581e-3 and 2.352e-3
 // (bf16 results and score rows: 2.7e-3, 3.6e-3 and 2.3e-3 of each).
 // What bounds it: nothing alone.  32 columns are 60 products a wavefront (1920 cycles of the matrix cores), 64 KB of weights (1024
-// cycles of the address path), 225 KB through LDS (1760 cycles) and 336 conversions; the parts overlap in half.  Sums as half values
-// (36 products, 130 KB) are 75 us faster at 198 K frames, but lose what is outside their range.
+// cycles of the address path), 225 KB through LDS (1760 cycles) and 336 conversions; the parts overlap in half.  At 198 K frames (842
+// workgroups, 3.3 rounds over the CUs) 346 us under a trace and 94 us for the scores, against 578 us for scores and values in one product
+// and 114 us for the pooling.  Sums as half values (36 products, 130 KB) are 254 us there, but lose what is outside their range.
 #include "gemm_core.h"
 #include "ssd_internal.h"
 
