@@ -3,34 +3,25 @@
 // rows (16-bit models, head_dim 128; the fp32 model's is in f32_path.hip).
 // Everything else of a decode step reuses the verification kernels on a batch of Br rows
 // (RMSNorm, skinny weight-streaming GEMMs with split-K, LM head with argmax).
-#include "device_utils.h"
+#include "gemm_core.h"
 #include "ssd_internal.h"
 
 namespace ssd {
 
-// eight 16-bit operand patterns (IEEE half or bfloat16) as fp32
-template <bool BF>
-__device__ __forceinline__ void unpack8(const uint4& w, float (&v)[8]) {
-    if constexpr (BF) {
-        v[0] = bf16_lo(w.x); v[1] = bf16_hi(w.x); v[2] = bf16_lo(w.y); v[3] = bf16_hi(w.y);
-        v[4] = bf16_lo(w.z); v[5] = bf16_hi(w.z); v[6] = bf16_lo(w.w); v[7] = bf16_hi(w.w);
-    } else {
-        typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-        const h8 a = __builtin_bit_cast(h8, w);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
-    }
-}
-
 // head_dim 128: a workgroup is DEC_WAVES wavefronts and serves one (utterance, G query heads of one K/V head): every
-// cached row is read once for its G heads (one workgroup per query head read each row G times, from whichever XCD it
-// ran on).  Per launch, before and after: 13.2 -> 9.8 us at 27 utterances of 16 heads over 8; at 70 utterances of 24 over 8
-// 21.6 -> 20.7 us, the QKV splits now added here included (206 registers: two workgroups per CU, 560 of them).  Lane = (key group kg
-// of 4, chunk dc of 8 dims).  A block of DEC_KEYS keys is 8 loads of K and 8 of V per lane (the rows are 256 bytes, a
-// 16-lane group reads one row); a score is a 16-lane reduction, the softmax statistics are reduced over the four key
-// groups, and P.V accumulates in the lane, reduced over the key groups at the end.  The wavefronts take the blocks of
-// a context in turn and merge their (max, sum, output) triples through LDS: the blocks are loaded at once instead of
-// one after the other, and the next block's keys are requested as soon as this block's scores are known.
+// cached row is read once for its G heads.  The wavefronts take the blocks of DEC_KEYS keys of a context in turn and merge
+// their (max, sum, output) triples through LDS.
+// Both products are v_mfma_f32_16x16x32: S^T = K Q^T with the key rows straight from memory in operand registers, then
+// O^T += V^T P^T with the values in LDS (global -> LDS loads, read back through the transposing ds_read_b64_tr_b16), whose
+// key order is chosen so that a lane's scores are its operand of the second product.  Of the 16 columns of an operand G are
+// needed; the columns hold the heads four times over (column c: head c % 4, part c / 4), and the parts carry the probabilities
+// as a sum of 16-bit pieces (two of IEEE half = 22 bits, three of bfloat16 = 24), so that nothing is lost against fp32
+// probabilities: the copies' outputs are added at the end.
+// What bounds it is the chain of a launch: index, rows, score, output, with little else on the CU.  Scores and outputs on the vector
+// ALU took 700 instructions a block and 206 registers (560 workgroups in two rounds); here 152 (three per CU).  The partial sums of
+// the new row are requested before anything that waits for the context length and added lane by lane (loads return in order: behind
+// the keys they cost a second round trip, and 32 cross-lane adds).  Per launch, traced: 27 utterances of 16 heads over 8 10.7 -> 7.3 us,
+// 70 of 24 over 8 21.1 -> 14.1 us; with eight wavefronts instead of four 8.2 and 16.9, with 128 registers (four per CU) 7.7 and 14.5.
 constexpr int DEC_WAVES = 4;
 constexpr int DEC_KEYS = 32;
 constexpr int DEC_MAX_HEADS = 3;                             // one wavefront of the fused variant per head and one for the new k / v row
@@ -40,14 +31,18 @@ constexpr int DEC_MAX_HEADS = 3;                             // one wavefront of
 // rotary pairs (i, i+64) sit 32 columns apart in 64-column groups, V columns are in natural order).
 // The kernel adds the splits, rotates q and the new k, appends the new k / v row to the cache (first query
 // head of each K/V group) and treats that row as the last key without reading it back.
-// a value as the cache / the next kernel will see it: rounded to the operand type, saturated for IEEE half
-template <bool BF> __device__ __forceinline__ float round_like_stored(float v, bool& bad) {
-    if constexpr (BF) return bf16_to_f32(f32_to_bf16(v));
-    else return f16_to_f32(f32_to_f16_sat(v, bad));
+template <bool BF> __device__ __forceinline__ uint16_t round_sat(float v, bool& bad) {
+    if constexpr (BF) return f32_to_bf16(v);
+    else return f32_to_f16_sat(v, bad);
 }
-template <bool BF> __device__ __forceinline__ uint32_t pack2_sat(float lo, float hi, bool& bad) {
-    if constexpr (BF) return pack_bf16x2(lo, hi);
-    else return pack_f16x2_sat(lo, hi, bad);
+// what is left of p after its first `part` pieces of the operand type; nothing after the last piece
+template <bool BF> __device__ __forceinline__ float piece_of(float p, int part) {
+    const float r1 = p - Op16<BF>::to_f32(Op16<BF>::cvt(p));
+    if constexpr (BF) {
+        const float r2 = r1 - Op16<BF>::to_f32(Op16<BF>::cvt(r1));
+        return part == 0 ? p : part == 1 ? r1 : part == 2 ? r2 : 0.f;
+    }
+    return part == 0 ? p : part == 1 ? r1 : 0.f;
 }
 
 struct DecodeFused {
@@ -58,59 +53,38 @@ struct DecodeFused {
     // The new row's position is the number of rows its utterance has in the cache (cache row i of an
     // utterance is position i), and its slot is kv_start + that number: no further index arrays.
 };
-// Sum over the splits of eight consecutive packed columns starting at `col` of row b.  Key group kg adds splits kg and
-// kg + 4 (SKINNY_MAX_SPLITS is 8), the groups are added over the wavefront: one round trip whatever the split count.
-struct SplitSum { float v[8]; };
-static_assert(SKINNY_MAX_SPLITS <= 8, "two splits per key group");
-__device__ __forceinline__ void load_splits8(const DecodeFused& f, int64_t row_off, int col, int kg, float4 (&t)[2][2]) {
+// Sums over the splits of two packed columns of a row, in split order.  All loads of a lane are requested at once (a split beyond
+// the last is a second copy of it and left out), before anything that depends on the context length.
+static_assert(SKINNY_MAX_SPLITS <= 8, "loads of a lane");
+struct SplitPair { float a[SKINNY_MAX_SPLITS], b[SKINNY_MAX_SPLITS]; };
+__device__ __forceinline__ void load_splits(const DecodeFused& f, int64_t off_a, int64_t off_b, SplitPair& t) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int s = kg + 4 * k;
-        t[k][0] = t[k][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (s < f.n_splits) {
-            const float4* src = reinterpret_cast<const float4*>(f.part + s * f.split_stride + row_off + col);
-            t[k][0] = src[0];
-            t[k][1] = src[1];
-        }
+    for (int s = 0; s < SKINNY_MAX_SPLITS; ++s) {
+        const float* src = f.part + min(s, f.n_splits - 1) * f.split_stride;
+        t.a[s] = src[off_a];
+        t.b[s] = src[off_b];
     }
 }
-__device__ __forceinline__ SplitSum add_splits8(const float4 (&t)[2][2]) {
-    SplitSum r;
-    r.v[0] = t[0][0].x + t[1][0].x; r.v[1] = t[0][0].y + t[1][0].y; r.v[2] = t[0][0].z + t[1][0].z; r.v[3] = t[0][0].w + t[1][0].w;
-    r.v[4] = t[0][1].x + t[1][1].x; r.v[5] = t[0][1].y + t[1][1].y; r.v[6] = t[0][1].z + t[1][1].z; r.v[7] = t[0][1].w + t[1][1].w;
+__device__ __forceinline__ float2 add_splits(const DecodeFused& f, const SplitPair& t) {
+    float2 r = make_float2(t.a[0], t.b[0]);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        r.v[e] += __shfl_xor(r.v[e], 16);
-        r.v[e] += __shfl_xor(r.v[e], 32);
+    for (int s = 1; s < SKINNY_MAX_SPLITS; ++s) {
+        r.x += s < f.n_splits ? t.a[s] : 0.f;
+        r.y += s < f.n_splits ? t.b[s] : 0.f;
     }
-    return r;
-}
-// dims 8 dc .. 8 dc + 7 of rotated head `head_col0` (packed column of the head's first dim) at position p
-__device__ __forceinline__ SplitSum rotated_chunk(const DecodeFused& f, int64_t row_off, int head_col0, int dc, int kg, int p) {
-    const int i0 = (dc % 8) * 8;                              // dim inside the first half of the head
-    const int col_lo = head_col0 + (i0 / 32) * 64 + (i0 % 32);
-    float4 tlo[2][2], thi[2][2];
-    load_splits8(f, row_off, col_lo, kg, tlo);
-    load_splits8(f, row_off, col_lo + 32, kg, thi);
-    float2 cs[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) cs[e] = f.rope_tab[(int64_t)p * 64 + i0 + e];
-    const SplitSum lo = add_splits8(tlo), hi = add_splits8(thi);
-    SplitSum r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r.v[e] = dc < 8 ? lo.v[e] * cs[e].x - hi.v[e] * cs[e].y : hi.v[e] * cs[e].x + lo.v[e] * cs[e].y;
     return r;
 }
 
 template <bool FUSED, bool BF, int G>
-__global__ void __launch_bounds__(64 * DEC_WAVES) decode_attn_hd128_kernel(const f16_t* __restrict__ qkv, const f16_t* __restrict__ kc,
+__global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(const f16_t* __restrict__ qkv, const f16_t* __restrict__ kc,
                                                                const f16_t* __restrict__ vc, const int32_t* __restrict__ kv_start,
                                                                const int32_t* __restrict__ n_ctx, int n_q_heads, int n_kv_heads,
                                                                f16_t* __restrict__ out, DecodeFused fu) {
-    constexpr int HD = 128, ITS = DEC_KEYS / 4;
+    constexpr int HD = 128, ROW = HD * 2, STEP = DEC_KEYS * DEC_WAVES;
     static_assert(G <= DEC_MAX_HEADS && DEC_MAX_HEADS < DEC_WAVES, "wavefronts of the fused variant");
-    __shared__ __align__(16) float new_rows[G + 2][HD];      // fused: the G scaled queries, the new k row, the new v row
-    __shared__ float merge_o[DEC_WAVES][G][HD];
+    static_assert(G * HD * 4 <= DEC_KEYS * ROW, "a wavefront's output fits its block of values");
+    __shared__ __align__(1024) unsigned char v_s[DEC_WAVES][DEC_KEYS * ROW];   // a wavefront's block of values, later its output [G][HD] fp32
+    __shared__ uint4 new_rows[G + 2][HD / 8];                // fused: the G queries, the new k row, the new v row (operand type)
     __shared__ float merge_ml[DEC_WAVES][G][2];
     const int lane = threadIdx.x % 64, kg = lane / 16, dc = lane % 16;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
@@ -118,157 +92,185 @@ __global__ void __launch_bounds__(64 * DEC_WAVES) decode_attn_hd128_kernel(const
     const int kvh = h0 / (n_q_heads / n_kv_heads);
     const int d_q = n_q_heads * HD, d_kv = n_kv_heads * HD;
     const float sc = 0.08838834764831845f * 1.4426950408889634f;      // log2(e) / sqrt(128)
-    float qf[G][8], m[G], l[G], o[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        m[g] = -INFINITY;
-        l[g] = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[g][e] = 0.f;
+    const float P_SHIFT = 14.f;                              // probabilities are kept times 2^14: their low halves stay normal numbers
+    const int head = min(dc % 4, G - 1), part = dc / 4;      // of this lane's column
+    const int n_rows = n_ctx[b], slot0 = kv_start[b];
+    // fused: wavefront g < G finishes query head g, wavefront DEC_MAX_HEADS the new k / v row; lane i has rotary pair (i, i + 64).
+    // (Wavefronts in between repeat the last head: with a branch around these loads the rotary entries are fetched behind it.)
+    const int job = wave == DEC_MAX_HEADS ? G : min(wave, G - 1);
+    SplitPair tq, tv;
+    if constexpr (FUSED) {
+        const int64_t row_off = (int64_t)b * (d_q + 2 * d_kv);
+        const int64_t col = row_off + (job < G ? (h0 + job) * HD : d_q + kvh * HD) + (lane / 32) * 64 + lane % 32;
+        load_splits(fu, col, col + 32, tq);
+        if (wave == DEC_MAX_HEADS) load_splits(fu, row_off + d_q + d_kv + kvh * HD + lane, row_off + d_q + d_kv + kvh * HD + lane + 64, tv);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    const int n = n_ctx[b] - (FUSED ? 1 : 0);                // rows to read from the cache
-    const f16_t* kbase = kc + (int64_t)kv_start[b] * d_kv + kvh * HD + dc * 8;
-    const f16_t* vbase = vc + (int64_t)kv_start[b] * d_kv + kvh * HD + dc * 8;
-    uint4 kr[ITS], vr[ITS];
-    auto load_rows = [&](const f16_t* base, int k0, uint4 (&r)[ITS]) {
+    const int n = n_rows - (FUSED ? 1 : 0);                  // rows to read from the cache; the position of the new token
+    const int64_t first = (int64_t)slot0 * d_kv + kvh * HD;
+    float2 cs = make_float2(1.f, 0.f);
+    if constexpr (FUSED) cs = fu.rope_tab[(int64_t)n * 64 + lane];
+    const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(kc + first), v_rsrc = make_rsrc(vc + first);
+    const int d_kv2 = d_kv * 2, last = max(n - 1, 0);
+    u32x4_t kr[2][4];
+    // Keys k0 .. k0 + 31: lane (row dc of a half of 16, dims 8 kg + 32 s) in registers.  Values: four rows of 256 bytes per
+    // instruction, the sixteen 16-byte chunks of row r at chunk ^ 4 (r & 3) ^ 2 (r >> 2 & 1), which spreads the eight 32-byte
+    // pieces that half a wavefront reads over all LDS banks.  Rows beyond the context are copies of the last one.
+    auto load_keys = [&](int k0) {
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            const int key = min(k0 + it * 4 + kg, n - 1);
-            r[it] = *reinterpret_cast<const uint4*>(base + (int64_t)key * d_kv);
+        for (int c = 0; c < 2; ++c) {
+            const int off = min(k0 + 16 * c + dc, last) * d_kv2 + kg * 16;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) kr[c][s] = __builtin_amdgcn_raw_buffer_load_b128(k_rsrc, off + 64 * s, 0, 0);
         }
     };
-    // the first block of keys and values is requested before q is put together
-    if (wave * DEC_KEYS < n) {
-        load_rows(kbase, wave * DEC_KEYS, kr);
-        load_rows(vbase, wave * DEC_KEYS, vr);
-    }
+    auto load_values = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < DEC_KEYS / 4; ++i) {
+            const int off = min(k0 + 4 * i + kg, last) * d_kv2 + (dc ^ (4 * kg + 2 * (i & 1))) * 16;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lds_void_t*)(v_s[wave] + i * 1024), 16, off, 0, 0, 0);
+        }
+    };
+    // The first block is requested before q is put together, by every wavefront: a branch here would make the wait for the partial
+    // sums one for everything.
+    load_keys(wave * DEC_KEYS);
+    load_values(wave * DEC_KEYS);
+    f16x8_t qf[4];
+    float m = -INFINITY, l = 0.f;
+    f32x4_t o[HD / 16];
+#pragma unroll
+    for (int i = 0; i < HD / 16; ++i) o[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     if constexpr (FUSED) {
-        // wavefront g < G finishes query head g, wavefront DEC_MAX_HEADS the new k / v row
-        const int64_t row_off = (int64_t)b * (d_q + 2 * d_kv);
-        const int p = n;                                     // position of the new token
         bool bad = false;
-        if (wave < G) {
-            const SplitSum q = rotated_chunk(fu, row_off, (h0 + wave) * HD, dc, kg, p);
-            if (kg == 0) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) new_rows[wave][dc * 8 + e] = round_like_stored<BF>(q.v[e], bad) * sc;   // rounded (and saturated) like a stored row
-            }
-        } else if (wave == DEC_MAX_HEADS) {
-            float4 tv[2][2];
-            load_splits8(fu, row_off, d_q + d_kv + kvh * HD + dc * 8, kg, tv);
-            const SplitSum kn = rotated_chunk(fu, row_off, d_q + kvh * HD, dc, kg, p);
-            const SplitSum vn = add_splits8(tv);
-            if (kg == 0) {
-                // the cache holds 16 bits: the new row takes part in this step with the values later steps read
-                uint4 kw, vw;
-                kw.x = pack2_sat<BF>(kn.v[0], kn.v[1], bad); kw.y = pack2_sat<BF>(kn.v[2], kn.v[3], bad); kw.z = pack2_sat<BF>(kn.v[4], kn.v[5], bad); kw.w = pack2_sat<BF>(kn.v[6], kn.v[7], bad);
-                vw.x = pack2_sat<BF>(vn.v[0], vn.v[1], bad); vw.y = pack2_sat<BF>(vn.v[2], vn.v[3], bad); vw.z = pack2_sat<BF>(vn.v[4], vn.v[5], bad); vw.w = pack2_sat<BF>(vn.v[6], vn.v[7], bad);
-                if (h0 % (n_q_heads / n_kv_heads) == 0) {
-                    const int64_t so = ((int64_t)kv_start[b] + n) * d_kv + kvh * HD + dc * 8;
-                    *reinterpret_cast<uint4*>(fu.kc_w + so) = kw;
-                    *reinterpret_cast<uint4*>(fu.vc_w + so) = vw;
-                }
-                float t[8];
-                unpack8<BF>(kw, t);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) new_rows[G][dc * 8 + e] = t[e];
-                unpack8<BF>(vw, t);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) new_rows[G + 1][dc * 8 + e] = t[e];
+        // as later steps and the next kernel read them: rounded to the operand type, saturated for IEEE half
+        const float2 t = add_splits(fu, tq);
+        const uint16_t lo = round_sat<BF>(t.x * cs.x - t.y * cs.y, bad), hi = round_sat<BF>(t.y * cs.x + t.x * cs.y, bad);
+        uint16_t* row = reinterpret_cast<uint16_t*>(new_rows[job]);
+        row[lane] = lo;
+        row[lane + 64] = hi;
+        if (wave == DEC_MAX_HEADS) {
+            const float2 v = add_splits(fu, tv);
+            const uint16_t v0 = round_sat<BF>(v.x, bad), v1 = round_sat<BF>(v.y, bad);
+            uint16_t* vrow = reinterpret_cast<uint16_t*>(new_rows[G + 1]);
+            vrow[lane] = v0;
+            vrow[lane + 64] = v1;
+            if (h0 % (n_q_heads / n_kv_heads) == 0) {
+                f16_t* kd = fu.kc_w + first + (int64_t)n * d_kv + lane;
+                f16_t* vd = fu.vc_w + first + (int64_t)n * d_kv + lane;
+                kd[0] = lo; kd[64] = hi;
+                vd[0] = v0; vd[64] = v1;
             }
         }
         if (bad) raise_flag(fu.flags, SSD_FLAG_ACT_OVERFLOW);
-        __syncthreads();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);                  // the LDS stores above; a barrier with a fence would wait for the values as well
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+        for (int s = 0; s < 4; ++s) qf[s] = as_f16x8(new_rows[head][4 * s + kg]);
+        if (wave == 0) {                                     // the new row is wavefront 0's first key: every row of the operand
+            f32x4_t s_new = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) qf[g][e] = new_rows[g][dc * 8 + e];
-        if (wave == 0) {                                     // the new row is wavefront 0's first key
+            for (int s = 0; s < 4; ++s) s_new = mfma_16x16x32<BF>(as_f16x8(new_rows[G][4 * s + kg]), qf[s], s_new);
+            m = s_new[0] * sc;
+            l = __builtin_amdgcn_exp2f(P_SHIFT);
+            const uint2* vn = reinterpret_cast<const uint2*>(new_rows[G + 1]);
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                float acc = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc = fmaf(qf[g][e], new_rows[G][dc * 8 + e], acc);
-                m[g] = group_allreduce<16>(acc, OpSum());
-                l[g] = 1.f;
-                if (kg == 0) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) o[g][e] = new_rows[G + 1][dc * 8 + e];
-                }
+            for (int i = 0; i < HD / 16; ++i) {
+                const uint2 w = vn[4 * i + kg];              // dims 16 i + 4 kg .. + 3
+                const float f = part == 0 ? l : 0.f;
+                o[i] = (f32x4_t){Op16<BF>::to_f32((uint16_t)w.x) * f, Op16<BF>::to_f32((uint16_t)(w.x >> 16)) * f,
+                                 Op16<BF>::to_f32((uint16_t)w.y) * f, Op16<BF>::to_f32((uint16_t)(w.y >> 16)) * f};
             }
         }
     } else {
+        const f16_t* q = qkv + (int64_t)b * (d_q + 2 * d_kv) + (h0 + head) * HD + kg * 8;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            unpack8<BF>(*reinterpret_cast<const uint4*>(qkv + (int64_t)b * (d_q + 2 * d_kv) + (h0 + g) * HD + dc * 8), qf[g]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) qf[g][e] *= sc;
-        }
+        for (int s = 0; s < 4; ++s) qf[s] = as_f16x8(*reinterpret_cast<const uint4*>(q + 32 * s));
     }
-    for (int k0 = wave * DEC_KEYS; k0 < n; k0 += DEC_KEYS * DEC_WAVES) {
-        const bool more = k0 + DEC_KEYS * DEC_WAVES < n;
-        float s[G][ITS], alpha[G];
+    // transposing read: lane i of 16 passes row i / 4 and dims 4 (i % 4) .. + 3 of a 16-dim block, lane j receives dim j of four rows
+    const int v_row = 4 * kg + dc / 4, v_low = (dc % 4) / 2, v_sub = (dc % 2) * 8;
+    const int v_swz = 4 * (v_row & 3) + 2 * ((v_row >> 2) & 1);           // the same for row v_row + 16
+    auto block = [&](auto more_c, int k0) {                  // more: another block follows, its keys are requested as soon as these are used
+        constexpr bool MORE = decltype(more_c)::value;
+        f32x4_t s[2];
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            float kk[8];
-            unpack8<BF>(kr[it], kk);
+        for (int c = 0; c < 2; ++c) {
+            s[c] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                float acc = 0.f;
+            for (int t = 0; t < 4; ++t) s[c] = mfma_16x16x32<BF>(__builtin_bit_cast(f16x8_t, kr[c][t]), qf[t], s[c]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MORE) load_keys(k0 + STEP);
+        __builtin_amdgcn_sched_barrier(0);
+        float mx = -INFINITY;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc = fmaf(qf[g][e], kk[e], acc);
-                acc = group_allreduce<16>(acc, OpSum());
-                s[g][it] = (k0 + it * 4 + kg < n) ? acc : -INFINITY;
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[c][r] = k0 + 16 * c + 4 * kg + r < n ? s[c][r] * sc : -INFINITY;
+                mx = fmaxf(mx, s[c][r]);
             }
-        }
-        if (more) load_rows(kbase, k0 + DEC_KEYS * DEC_WAVES, kr);
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);                    // finite: key k0 exists
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new), ref = m_new - P_SHIFT;
+        float ps = 0.f;
+        uint32_t pw[4];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float cm = s[g][0];
+        for (int c = 0; c < 2; ++c) {
+            float v[4];
 #pragma unroll
-            for (int it = 1; it < ITS; ++it) cm = fmaxf(cm, s[g][it]);
-            cm = fmaxf(cm, __shfl_xor(cm, 16));
-            cm = fmaxf(cm, __shfl_xor(cm, 32));
-            const float m_new = fmaxf(m[g], cm);             // finite: key k0 exists
-            alpha[g] = __builtin_amdgcn_exp2f(m[g] - m_new);
-            float ps = 0.f;
-#pragma unroll
-            for (int it = 0; it < ITS; ++it) {
-                s[g][it] = __builtin_amdgcn_exp2f(s[g][it] - m_new);
-                ps += s[g][it];
+            for (int r = 0; r < 4; ++r) {
+                const float pr = __builtin_amdgcn_exp2f(s[c][r] - ref);
+                ps += pr;
+                v[r] = piece_of<BF>(pr, part);
             }
-            ps += __shfl_xor(ps, 16);
-            ps += __shfl_xor(ps, 32);
-            l[g] = l[g] * alpha[g] + ps;
-            m[g] = m_new;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[g][e] *= alpha[g];
+            pw[2 * c] = op_pack2<BF>(v[0], v[1]);
+            pw[2 * c + 1] = op_pack2<BF>(v[2], v[3]);
         }
+        ps += __shfl_xor(ps, 16);
+        ps += __shfl_xor(ps, 32);
+        l = l * alpha + ps;
+        m = m_new;
+        const f16x8_t pf = as_f16x8(make_uint4(pw[0], pw[1], pw[2], pw[3]));
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (MORE ? 8 : 0));  // the values of this block have landed (a wavefront reads its own only)
+        __builtin_amdgcn_sched_barrier(0);
+        tr_v4i16 vf[HD / 16][2];                             // all reads first: one LDS latency, not eight
 #pragma unroll
-        for (int it = 0; it < ITS; ++it) {
-            float vv[8];
-            unpack8<BF>(vr[it], vv);
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[g][e] = fmaf(s[g][it], vv[e], o[g][e]);
+        for (int i = 0; i < HD / 16; ++i) {
+            const unsigned char* a = v_s[wave] + v_row * ROW + (((2 * i) | v_low) ^ v_swz) * 16 + v_sub;
+            vf[i][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)a);
+            vf[i][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_v4i16*)(a + 16 * ROW));
         }
-        if (more) load_rows(vbase, k0 + DEC_KEYS * DEC_WAVES, vr);
-    }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < HD / 16; ++i) {
+            o[i] *= alpha;
+            o[i] = mfma_16x16x32<BF>(__builtin_bit_cast(f16x8_t, __builtin_shufflevector(vf[i][0], vf[i][1], 0, 1, 2, 3, 4, 5, 6, 7)), pf, o[i]);
+        }
+        if constexpr (MORE) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);              // the reads of this block are done
+            __builtin_amdgcn_sched_barrier(0);
+            load_values(k0 + STEP);
+        }
+    };
+    int k0 = wave * DEC_KEYS;
+    for (; k0 + STEP < n; k0 += STEP) block(std::true_type(), k0);
+    if (k0 < n) block(std::false_type(), k0);
     // merge the wavefronts: wave w's partial is (m, l, o) with o scaled by 2^-m; a wavefront without a block has l = 0
+    float* mine = reinterpret_cast<float*>(v_s[wave]);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
+    for (int i = 0; i < HD / 16; ++i) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            o[g][e] += __shfl_xor(o[g][e], 16);
-            o[g][e] += __shfl_xor(o[g][e], 32);
+        for (int r = 0; r < 4; ++r) {                        // the parts of a column lie 4 lanes apart
+            o[i][r] += dpp_f<DPP_ROW_ROR8>(o[i][r]);
+            o[i][r] += dpp_f<DPP_ROW_ROR4>(o[i][r]);
         }
-        if (kg == 0) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) merge_o[wave][g][dc * 8 + e] = o[g][e];
-            if (dc == 0) { merge_ml[wave][g][0] = m[g]; merge_ml[wave][g][1] = l[g]; }
-        }
+        if (dc < G) *reinterpret_cast<f32x4_t*>(mine + dc * HD + 16 * i + 4 * kg) = o[i];
     }
+    if (lane < G) { merge_ml[wave][lane][0] = m; merge_ml[wave][lane][1] = l; }
     __syncthreads();
     if (wave < G && kg == 0) {                               // wavefront g finishes head g
         const int g = wave;
@@ -283,8 +285,9 @@ __global__ void __launch_bounds__(64 * DEC_WAVES) decode_attn_hd128_kernel(const
             const float lw = merge_ml[w][g][1];
             const float f = lw > 0.f ? __builtin_amdgcn_exp2f(merge_ml[w][g][0] - mt) : 0.f;
             lt = fmaf(lw, f, lt);
+            const float* src = reinterpret_cast<const float*>(v_s[w]) + g * HD + dc * 8;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) ot[e] = fmaf(merge_o[w][g][dc * 8 + e], f, ot[e]);
+            for (int e = 0; e < 8; ++e) ot[e] = fmaf(src[e], f, ot[e]);
         }
         const float inv = 1.0f / lt;
         uint4 w;

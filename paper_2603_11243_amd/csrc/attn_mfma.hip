@@ -33,8 +33,6 @@ constexpr int ATT_KB = 64;                    // keys per block
 constexpr int ATT_ROW_BYTES = ATT_HD * 2;     // a K or V row in LDS (unpadded)
 constexpr int ATT_BLOCK_BYTES = ATT_KB * ATT_ROW_BYTES;
 constexpr int ATT_O_STRIDE = ATT_HD + 8;      // output staging rows, elements
-typedef short tr_v4i16 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) tr_v4i16 lds_tr_v4i16;
 
 template <bool BF>
 __global__ void __launch_bounds__(128, 2) attn_mfma_kernel(const f16_t* __restrict__ qkv, f16_t* __restrict__ out,

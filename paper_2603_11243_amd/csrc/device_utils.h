@@ -98,6 +98,7 @@ constexpr int DPP_XOR1 = 0xB1;          // quad_perm [1,0,3,2]
 constexpr int DPP_XOR2 = 0x4E;          // quad_perm [2,3,0,1]
 constexpr int DPP_HALF_MIRROR = 0x141;  // lane i <-> 7-i inside each 8
 constexpr int DPP_MIRROR = 0x140;       // lane i <-> 15-i inside each 16
+constexpr int DPP_ROW_ROR4 = 0x124, DPP_ROW_ROR8 = 0x128;     // rotations by 4 and 8 lanes inside each 16
 
 struct OpMax { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 struct OpSum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };

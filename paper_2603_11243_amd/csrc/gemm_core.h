@@ -31,6 +31,10 @@ typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void_t;
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// operand and address of the transposing LDS read ds_read_b64_tr_b16
+typedef short tr_v4i16 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) tr_v4i16 lds_tr_v4i16;
 
 constexpr int GEMM_BK = 64;
 constexpr int GEMM_ROW_BYTES = GEMM_BK * 2;

@@ -27,8 +27,6 @@
 
 namespace ssd {
 
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
 constexpr int STREAM_STEP_UNITS = 8 * 64;          // 16-byte units of one (column tile, K step) block of W
 
 template <int NW, int DEPTH>
