@@ -168,76 +168,64 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(float* __restrict__ x, con
     }
 }
 
-// Same operation with one workgroup per row, for launches with few rows (there a wavefront per row
-// leaves most of the chip idle and serialises the split sums): every thread owns d/1024 float4s
-// and all its split loads are issued together.
-template <typename T, int MAXV, bool BF>
-__global__ void __launch_bounds__(256) rmsnorm_row_kernel(float* __restrict__ x, const T* __restrict__ gain,
-                                                          const int32_t* __restrict__ row_idx, int d, float eps,
-                                                          T* __restrict__ out, const float* __restrict__ partials,
-                                                          int n_splits, int64_t split_stride, int32_t* __restrict__ flags) {
-    __shared__ float red[4];
+// Same operation with one workgroup per row and one float4 per thread (d / 4 <= 1024 threads), for launches with few rows: there a
+// wavefront per row leaves most of the chip idle, and what a launch takes is its chain of memory round trips.  Row, split sums and
+// gain are one of them: all loads are issued before the first is used (SPLITS: at least n_splits; a split beyond the last is a second
+// copy of it and left out).  With 256 threads and up to four float4 each, a round trip per float4: 27 rows of 2048 4.6 -> 3.9 us (an
+// empty launch is 2.4), 16 greedy steps of 27 rows 21.1 -> 20.6 ms, 8 of 70 rows of 3072 22.85 -> 22.46.
+template <typename T, int SPLITS, bool BF>
+__global__ void __launch_bounds__(1024) rmsnorm_row_kernel(float* __restrict__ x, const T* __restrict__ gain,
+                                                           const int32_t* __restrict__ row_idx, int d, float eps,
+                                                           T* __restrict__ out, const float* __restrict__ partials,
+                                                           int n_splits, int64_t split_stride, int32_t* __restrict__ flags) {
+    __shared__ float red[16];
     const int r = blockIdx.x;
     const int64_t row = row_idx ? row_idx[r] : r;
-    float4* src = reinterpret_cast<float4*>(x + row * d);
-    const int n4 = d / 4;
-    float4 v[MAXV];
-    float ss = 0.f;
-    // the gain is fetched up front: its cache round trip overlaps with the row loads and the reduction
-    uint2 g16[sizeof(T) == 2 ? MAXV : 1];
+    const bool live = (int)threadIdx.x < d / 4;
+    const int i = live ? threadIdx.x : 0;
+    float4* src = reinterpret_cast<float4*>(x + row * d) + i;
+    float4 v = *src, p[SPLITS];
+    if constexpr (SPLITS > 1) {
+#pragma unroll
+        for (int s = 0; s < SPLITS; ++s) p[s] = reinterpret_cast<const float4*>(partials + min(s, n_splits - 1) * split_stride + row * d)[i];
+    }
+    float4 g;
     if constexpr (sizeof(T) == 2) {
-#pragma unroll
-        for (int k = 0; k < MAXV; ++k) {
-            const int i = threadIdx.x + k * 256;
-            g16[k] = i < n4 ? reinterpret_cast<const uint2*>(gain)[i] : make_uint2(0u, 0u);
-        }
+        const uint2 t = reinterpret_cast<const uint2*>(gain)[i];
+        g = make_float4(bf16_lo(t.x), bf16_hi(t.x), bf16_lo(t.y), bf16_hi(t.y));
+    } else {
+        g = reinterpret_cast<const float4*>(gain)[i];
     }
+    if constexpr (SPLITS > 1) {
 #pragma unroll
-    for (int k = 0; k < MAXV; ++k) {
-        const int i = threadIdx.x + k * 256;
-        v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i < n4) {
-            v[k] = src[i];
-            float4 p[SKINNY_MAX_SPLITS];
-#pragma unroll
-            for (int s = 0; s < SKINNY_MAX_SPLITS; ++s)
-                if (n_splits > 1 && s < n_splits) p[s] = reinterpret_cast<const float4*>(partials + s * split_stride + row * d)[i];
-#pragma unroll
-            for (int s = 0; s < SKINNY_MAX_SPLITS; ++s)
-                if (n_splits > 1 && s < n_splits) { v[k].x += p[s].x; v[k].y += p[s].y; v[k].z += p[s].z; v[k].w += p[s].w; }
-            if (n_splits > 1 && !row_idx) src[i] = v[k];
-            ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
+        for (int s = 0; s < SPLITS; ++s) {                  // (selects: with a branch per split the last loads would move into them)
+            const bool have = s < n_splits;
+            v.x += have ? p[s].x : 0.f; v.y += have ? p[s].y : 0.f; v.z += have ? p[s].z : 0.f; v.w += have ? p[s].w : 0.f;
         }
+        if (live && !row_idx) *src = v;
     }
+    float ss = live ? v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w : 0.f;
     ss = group_allreduce<64>(ss, OpSum());
     if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = ss;
     __syncthreads();
-    ss = (red[0] + red[1]) + (red[2] + red[3]);
+    ss = (int)(threadIdx.x % 16) < (int)blockDim.x / 64 ? red[threadIdx.x % 16] : 0.f;
+    ss = group_allreduce<16>(ss, OpSum());
+    if (!live) return;
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
     T* dst = out + (int64_t)r * d;
-    float peak = 0.f;
-    auto store_row = [&](auto clamp_c) {
-        constexpr bool CLAMP = decltype(clamp_c)::value;
-#pragma unroll
-        for (int k = 0; k < MAXV; ++k) {
-            const int i = threadIdx.x + k * 256;
-            if (i >= n4) continue;
-            if constexpr (sizeof(T) == 2) {
-                const uint2 g = g16[k];
-                uint2 o;
-                o.x = op_store2<BF, CLAMP>(v[k].x * inv * bf16_lo(g.x), v[k].y * inv * bf16_hi(g.x), peak);
-                o.y = op_store2<BF, CLAMP>(v[k].z * inv * bf16_lo(g.y), v[k].w * inv * bf16_hi(g.y), peak);
-                reinterpret_cast<uint2*>(dst)[i] = o;
-            } else {
-                const float4 g = reinterpret_cast<const float4*>(gain)[i];
-                reinterpret_cast<float4*>(dst)[i] = make_float4(v[k].x * inv * g.x, v[k].y * inv * g.y, v[k].z * inv * g.z, v[k].w * inv * g.w);
-            }
+    if constexpr (sizeof(T) == 2) {
+        float peak = 0.f;
+        uint2 o;
+        o.x = op_store2<BF, false>(v.x * inv * g.x, v.y * inv * g.y, peak);
+        o.y = op_store2<BF, false>(v.z * inv * g.z, v.w * inv * g.w, peak);
+        if (!(peak <= F16_MAX)) {                           // a gain large enough to leave the half range: store saturated
+            o.x = op_store2<BF, true>(v.x * inv * g.x, v.y * inv * g.y, peak);
+            o.y = op_store2<BF, true>(v.z * inv * g.z, v.w * inv * g.w, peak);
+            raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);
         }
-    };
-    store_row(std::false_type());
-    if (!(peak <= F16_MAX)) {
-        store_row(std::true_type());
-        raise_flag(flags, SSD_FLAG_ACT_OVERFLOW);
+        reinterpret_cast<uint2*>(dst)[i] = o;
+    } else {
+        reinterpret_cast<float4*>(dst)[i] = make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
     }
 }
 
@@ -246,10 +234,14 @@ void launch_rmsnorm(int dtype, float* x, const void* gain, const int32_t* row_id
                     hipStream_t st) {
     if (n_rows <= 0) return;
     if ((n_rows <= 512 || n_splits > 1) && d <= 4096 && n_splits <= SKINNY_MAX_SPLITS) {
-#define SSD_RMSNORM_ROW(T, BF) \
-        hipLaunchKernelGGL((rmsnorm_row_kernel<T, 4, BF>), dim3(n_rows), dim3(256), 0, st, x, (const T*)gain, row_idx, d, eps, (T*)out, partials, n_splits, split_stride, flags)
-        if (dtype == SSD_BF16) { if (bf16_ops) SSD_RMSNORM_ROW(bf16_t, true); else SSD_RMSNORM_ROW(bf16_t, false); }
-        else SSD_RMSNORM_ROW(float, false);
+        const dim3 block((d / 4 + 63) / 64 * 64);
+#define SSD_RMSNORM_ROW(T, S, BF) \
+        hipLaunchKernelGGL((rmsnorm_row_kernel<T, S, BF>), dim3(n_rows), block, 0, st, x, (const T*)gain, row_idx, d, eps, (T*)out, partials, n_splits, split_stride, flags)
+#define SSD_RMSNORM_ROW_SPLITS(T, BF) do { \
+        if (n_splits <= 1) SSD_RMSNORM_ROW(T, 1, BF); else if (n_splits == 2) SSD_RMSNORM_ROW(T, 2, BF); else if (n_splits <= 4) SSD_RMSNORM_ROW(T, 4, BF); else SSD_RMSNORM_ROW(T, SKINNY_MAX_SPLITS, BF); } while (0)
+        if (dtype == SSD_BF16) { if (bf16_ops) SSD_RMSNORM_ROW_SPLITS(bf16_t, true); else SSD_RMSNORM_ROW_SPLITS(bf16_t, false); }
+        else SSD_RMSNORM_ROW_SPLITS(float, false);
+#undef SSD_RMSNORM_ROW_SPLITS
 #undef SSD_RMSNORM_ROW
         return;
     }
