@@ -65,18 +65,21 @@ struct Layout32Quarter {
 // (Layout16T instead of Layout16); the loop, the fragments and their reads are the same.
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool BF16 = false, bool SWAP = false>
 struct GemmTile16 {
-    static constexpr int NSTAGE = 2;
     static constexpr int WAVES = WAVES_M * WAVES_N;
     static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
     static constexpr int TM = WTM / 16, TN = WTN / 16;
     static constexpr int TH0 = (TM + 1) / 2, TH1 = TM / 2;   // row blocks of the lower and the upper half
     static constexpr int A_LOADS = (BM + 8 * WAVES - 1) / (8 * WAVES);    // 1 KB (8 rows) per wavefront load instruction
     static constexpr int B_LOADS = BN / (8 * WAVES);
-    static constexpr int A_ROWS = A_LOADS * 8 * WAVES;       // rows of LDS: every wavefront issues the same number of loads, whatever BM
-    static constexpr int A_BYTES = A_ROWS * GEMM_ROW_BYTES, B_BYTES = BN * GEMM_ROW_BYTES;
+    static constexpr int A_BYTES = BM * GEMM_ROW_BYTES, B_BYTES = BN * GEMM_ROW_BYTES;
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
+    // As many stages as a CU's LDS holds, up to four; three for the tiles of four wavefronts, of which two run on a CU.  A tile of a
+    // round or less waits for its slices: with two stages only one is in flight while another is multiplied.  One round, two / three
+    // stages: 128 x 256 tiles, gate/up of 392 rows 40 / 34 us (2048 wide) and 61 / 48 us (3072).
+    static constexpr int NSTAGE = WAVES == 4 ? 3 : 160 * 1024 / STAGE_BYTES < 4 ? 160 * 1024 / STAGE_BYTES : 4;
     static constexpr size_t LDS_BYTES = (size_t)NSTAGE * STAGE_BYTES;
     static_assert(BN % (8 * WAVES) == 0, "tile/thread mismatch");
+    static_assert(BM % 8 == 0 && NSTAGE >= 2, "pieces of eight rows, two stages");
     static_assert(WTM % 16 == 0 && WTN % 16 == 0 && TH1 >= 1, "wave tile: at least two 16-row blocks, 16-column blocks");
 
     // acc is accumulated onto.  smem: LDS_BYTES bytes, 16-byte aligned.  K slices kt0 <= kt < kt1.
@@ -88,15 +91,15 @@ struct GemmTile16 {
         const int wm = wave / WAVES_N, wn = wave % WAVES_N;
         const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(A), w_rsrc = make_rsrc(W);
 
-        // ---- global -> LDS (identical to gemm_core.h): instruction i of this wavefront fills rows (i*WAVES + wave)*8 .. +7
+        // ---- global -> LDS (as in gemm_core.h): instruction i of this wavefront fills rows (i*WAVES + wave)*8 .. +7
         const int lrow = lane / 8, lslot = lane % 8;
+        // (every wavefront issues the same number of loads whatever BM: pieces beyond the tile are second copies of its first ones)
+        auto a_piece = [&](int i) { const int p = i * WAVES + wave; return BM % (8 * WAVES) == 0 || p < BM / 8 ? p : p - BM / 8; };
         unsigned a_off[A_LOADS], b_off[B_LOADS];
 #pragma unroll
         for (int i = 0; i < A_LOADS; ++i) {
-            const int r = (i * WAVES + wave) * 8 + lrow;
-            // rows of LDS beyond the tile are read by nobody: one cache line fills them
-            a_off[i] = A_ROWS == BM || r < BM ? (unsigned)min(m0 + r, M - 1) * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16)
-                                              : (unsigned)min(m0, M - 1) * (unsigned)K * 2u + (unsigned)(lslot * 16);
+            const int r = a_piece(i) * 8 + lrow;
+            a_off[i] = (unsigned)min(m0 + r, M - 1) * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
         }
 #pragma unroll
         for (int i = 0; i < B_LOADS; ++i) {
@@ -109,7 +112,7 @@ struct GemmTile16 {
             const int koff = kt * GEMM_ROW_BYTES;
 #pragma unroll
             for (int i = 0; i < A_LOADS; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void_t*)(sa + (i * WAVES + wave) * 1024), 16, a_off[i], koff, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void_t*)(sa + a_piece(i) * 1024), 16, a_off[i], koff, 0, 0);
 #pragma unroll
             for (int i = 0; i < B_LOADS; ++i)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void_t*)(sb + (i * WAVES + wave) * 1024), 16, b_off[i], koff, 0, 0);
@@ -164,7 +167,10 @@ struct GemmTile16 {
 #pragma unroll
         for (int s = 0; s < NSTAGE; ++s)
             if (s < n) issue_loads(kt0 + s, s);
-        if (n >= NSTAGE) __builtin_amdgcn_s_waitcnt(0x0F70 | (NL & 15) | ((NL >> 4) << 14)); else __builtin_amdgcn_s_waitcnt(0x0F70);
+        // s_waitcnt immediates: vmcnt(V), V low 4 bits in [3:0], high 2 bits in [15:14], with lgkmcnt(0) or any lgkmcnt
+        constexpr int V0 = (NSTAGE - 1) * NL, V1 = (NSTAGE - 2) * NL;
+        static_assert(V0 < 64, "vmcnt range");
+        if (n >= NSTAGE) __builtin_amdgcn_s_waitcnt(0x0F70 | (V0 & 15) | ((V0 >> 4) << 14)); else __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
         read_a(0, 0, lower, alo);
         read_b(0, 0, b0);
@@ -186,9 +192,9 @@ struct GemmTile16 {
             mfma_half(lower, alo, b1);
             interleave_reads(lower, std::integral_constant<int, TH1>());
             __builtin_amdgcn_sched_barrier(0);
-            // all reads of `stage` are issued; wait for them and for slice i+1 (its loads are the oldest)
-            const int next = 1 - stage;
-            __builtin_amdgcn_s_waitcnt(0x0070);
+            // all reads of `stage` are issued; wait for them and for slice i+1 (its loads are the oldest in flight)
+            const int next = stage + 1 == NSTAGE ? 0 : stage + 1;
+            if (STEADY || i + NSTAGE - 1 < n) __builtin_amdgcn_s_waitcnt(0x0070 | (V1 & 15) | ((V1 >> 4) << 14)); else __builtin_amdgcn_s_waitcnt(0x0070);
             __syncthreads();
             if constexpr (STEADY) {                          // phase (1, upper) with the refill and the next slice's first reads
                 issue_loads(kt0 + i + NSTAGE, stage);

@@ -743,14 +743,9 @@ void launch_stream_layout(const uint16_t* w, void* out, int N, int K, hipStream_
 // The last term is TILE_OVERHEAD row-slices, about eleven slices of the highest tile: 40 K x 3072 outputs of K = 1024 take 290 us
 // in ten rounds of 192 rows and 268 us in eight of 256.  Five heights because a coarser step leaves up to a quarter of a round
 // empty (256, 192 and 128 only, against these, us: QKV of 3400 rows 68.9 -> 62.4 and 136.6 -> 125.2 at 2048 and 3072 wide, gate/up of
-// 2600 rows 162.5 -> 149.4, down of 4200 rows 166 -> 157, of 6400 rows 196 -> 184 and 327 -> 310).  Over 84 row counts from 2060 to 15340
-// and four projections at two widths the rule is 0.12 % from the best of the five heights on average and 6 % at most; 256, 192 and 128
-// with the same cost, 1.35 % and 19 %.
-// One exception: in whole sums of K <= 2048 the stores are a large part of a round, and two or more nearly full rounds of 160 rows, where
-// all CUs store at once, are no faster than those of 192 with room in the last (QKV, K = 2048, two rounds, 160 / 192 rows in us: 4460 rows,
-// 0.88 of a round full, 89 / 93; 4620, 0.91, 90 / 97; 4780, 0.94, 101 / 97; 4940, 0.97, 101 / 97; 5100, 1.0, 102 / 97).  Not in one round
-// (2380 rows, 0.94, 52 / 54; 2540, 1.0, 52 / 52), not with K = 3072 (3820 rows, 0.94, 124 / 130; 3980, 0.98, 127 / 132), not
-// for the residuals (K = 2048: 4940 rows, 0.97, 57 / 60; 9580, 0.94, 101 / 104; 10060, 0.98, 104 / 104).
+// 2600 rows 162.5 -> 149.4, down of 4200 rows 166 -> 157, of 6400 rows 196 -> 184 and 327 -> 310).  Over 30 row counts from 2100 to 15214
+// and four projections at two widths the rule is 0.04 % from the best of the five heights on average and 2 % at most.  (Tiles of 160 rows,
+// which three ring stages fit since their pieces have no padding: QKV of 4620 rows of 2048, two rounds, 97 -> 86.7 us, 192 rows 94.)
 // With at most 128 rows the job is weight streaming and what counts is the number of weight bytes in
 // flight: at most 32 rows go to the register-streaming kernel when the shape divides evenly, more to its variant
 // with row blocks where that is faster (try_launch_stream_rows); otherwise a skinny 128 x 64 tile (four wavefronts, each 32 rows x 64 columns) with a six-stage LDS ring
@@ -779,14 +774,13 @@ static void launch_skinny(const f16_t* A, const f16_t* W, const void* Ws, int M,
 template <class Epi>
 static void launch_big(const f16_t* A, const f16_t* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
     const int heights[5] = {256, 224, 192, 160, 128};
-    const double eff[5] = {1.0, 0.98, 0.96, 0.92, 0.86};
+    const double eff[5] = {1.0, 0.98, 0.96, 0.94, 0.86};
     constexpr double TILE_OVERHEAD = 2800;
     int best = 0;
     double best_cost = 1e30;
     for (int c = 0; c < 5; ++c) {
         const long tiles = (long)((M + heights[c] - 1) / heights[c]) * (N / 256);
         const long rounds = (tiles + 255) / 256;
-        if (heights[c] == 160 && !Epi::USES_LDS && K <= 2048 && rounds > 1 && tiles > 0.92 * 256 * rounds) continue;
         const double cost = (double)rounds * (heights[c] / eff[c] * (K / GEMM_BK) + TILE_OVERHEAD);
         if (cost < best_cost - 1e-9) { best_cost = cost; best = c; }
     }
@@ -797,18 +791,18 @@ static void launch_big(const f16_t* A, const f16_t* W, int M, int N, int K, cons
     else launch_gemm16<128, 256, 2, 4>(A, W, M, N, K, 1, epi, st);
 }
 // Whole sums (QKV, gate/up, the projector).  Beyond 128 rows the 256-wide tiles leave most of the chip idle until there
-// are about 256 of them, and a workgroup then has its whole K range in front of it whatever the row count (QKV of 136 to
-// 784 rows: 35 us at 2048 x 4096, 60 us at 3072 x 5120).  The narrow LDS-ring tiles are faster while they are at most one
-// workgroup per CU (136 rows: 12.8 and 17.8 us as 64 x 64, 392 rows: 16.4 us as 128 x 64; two rounds of them are not,
-// 392 rows at 3072: 39.3), then 64 x 128 tiles while at most two per CU (784 rows: 27.5 and 56.6 us; gate/up of 136 rows
-// 38.9 -> 30.7 and 61.6 -> 44.7; with 800 of them, 1568 rows, 50.6 against 39.4).
+// are about 256 of them, and a workgroup then has its whole K range in front of it whatever the row count.  Narrower tiles are
+// faster while they run in one round, the narrowest that do: 64 x 64 (LDS ring), 64 x 128, 128 x 128 of eight wavefronts.
+// Cold weights, us, 2048 / 3072 wide: QKV of 136 rows 16.0 / 21.8 as 64 x 64 (18.2 / 25.2 as 64 x 128), 256 rows of 3072 26.6 as 64 x 128
+// (34.6 as 128 x 128), 512 rows of 2048 19.5 as 64 x 128 (23.6), 640 rows 23.9 / 34.7 as 128 x 128 (27.9 / 41.5 as two rounds of
+// 64 x 128), 980 rows of 2048 27.6 as 128 x 128 (34.4 as 128 x 256); gate/up of 256 rows 26.3 / 38.8 as 128 x 128 (32.1 / 47.0 as 64 x 128).
 template <class Epi>
 static void launch_by_shape(const f16_t* A, const f16_t* W, const void* Ws, int M, int N, int K, const Epi& epi, hipStream_t st) {
     auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * (N / bn); };
     if (M <= SKINNY_MAX_ROWS) launch_skinny(A, W, Ws, M, N, K, 1, epi, st);
     else if (tiles(64, 64) <= 256) launch_gemm<64, 64, 2, 1, 6>(A, W, M, N, K, 1, epi, st);
-    else if (tiles(128, 64) <= 256) launch_gemm<128, 64, 4, 1, 6>(A, W, M, N, K, 1, epi, st);
-    else if (tiles(64, 128) <= 512) launch_gemm16<64, 128, 2, 2>(A, W, M, N, K, 1, epi, st);
+    else if (tiles(64, 128) <= 256) launch_gemm16<64, 128, 2, 2>(A, W, M, N, K, 1, epi, st);
+    else if (tiles(128, 128) <= 256) launch_gemm16<128, 128, 4, 2>(A, W, M, N, K, 1, epi, st);
     else launch_big(A, W, M, N, K, epi, st);
 }
 
@@ -844,18 +838,30 @@ int launch_gemm_qkv_partial(const uint16_t* A, const uint16_t* W, const void* W_
     return splits;
 }
 
-// Residual projections of more than 128 rows: as many K splits of 128 x 256 tiles as one round over the CUs takes, or of
-// 128 x 64 LDS-ring tiles if those use more CUs.  Unsplit, a workgroup walks the whole K range (down, K = 8192, of 136 to
-// 1568 rows: 132-136 us); with splits, at 2048 and 3072 columns: 136 rows 16.4 and 23.5 us, 392 rows 25.0 and 35.5, 784 rows
-// 41.3 and 57.0, 1176 rows 54.8 and 78.0; O projection of 784 rows 36.4 -> 14.4 and 54.4 -> 24.3.  From 129 tiles on
-// (2049 rows at 2048 columns, 1281 at 3072) there is no second split and the projection adds to x in place.
-struct ResidualSplit { int splits; bool narrow; };
+// Residual projections of more than 128 rows.  Unsplit in 256-wide tiles, a workgroup walks the whole K range (down, K = 8192, of
+// 136 to 1568 rows: 132-136 us), so K is split, or the tile is narrower, until one round fills the CUs.  Three tiles, up to eight
+// splits: the cheapest by
+//   us = fixed + K steps of a workgroup * (step + busy * workgroups / 256) + MB of split sums * (write + read by the RMSNorm)
+// fitted to 700 launches (O and down of 136 to 1960 rows at 2048 and 3072 columns, cold weights; 7-9 % off on average), which picks
+// within 2 % of the best of ten tiles on average and 11 % at worst.  At 392 rows of 2048 columns: O 9.6 us (two splits of 128 x 64), down
+// 21.6 (four of 128 x 128); 128 x 256 tiles with eight splits 10.2 and 23.8, and a norm that reads twice the sums.  Without a split the
+// projection adds to x in place: from the row count at which 128 x 128 tiles alone fill the round.
+struct ResidualSplit { int splits, tile; };                  // tile: 0 128 x 64, 1 128 x 128, 2 128 x 256 or, unsplit, launch_big's choice
 static ResidualSplit mid_residual_split(int M, int N, int K) {
-    const int64_t wide = (int64_t)((M + 127) / 128) * (N / 256), narrow = 4 * wide;
-    const int most = max(1, min(SKINNY_MAX_SPLITS, K / GEMM_BK / 4));
-    const int sw = (int)std::min<int64_t>(most, 256 / wide), sn = (int)std::min<int64_t>(most, 256 / narrow);
-    if (sn >= 2 && narrow * sn > wide * sw) return {sn, true};
-    return {max(1, sw), false};
+    static const struct { int bn, least; double fixed, step, busy, write; } T[3] = {
+        {64, 2, 2.6, 0.293, 0.066, 0.335}, {128, 1, 2.1, 0.408, 0.119, 0.302}, {256, 1, 3.7, 0.661, 0.149, 0.206}};
+    ResidualSplit best{1, 2};
+    double best_us = 1e30;
+    for (int t = 0; t < 3; ++t) {
+        const int64_t tiles = (int64_t)((M + 127) / 128) * (N / T[t].bn);
+        for (int s = T[t].least; s <= SKINNY_MAX_SPLITS; ++s) {
+            if (tiles * s > 256 || K / GEMM_BK < 4 * s) break;
+            const double mb = (double)M * N * 4e-6 * s;
+            const double us = T[t].fixed + K / GEMM_BK / (double)s * (T[t].step + T[t].busy * tiles * s / 256) + mb * (T[t].write + 0.2);
+            if (us < best_us) { best_us = us; best = {s, t}; }
+        }
+    }
+    return best;
 }
 
 int gemm_residual_splits(int M, int N, int K, bool have_stream) {
@@ -878,14 +884,17 @@ template <bool BF>
 static int gemm_residual_impl(const uint16_t* A, const uint16_t* W, const void* W_stream, float* x, float* partials, int M, int N, int K,
                               float descale, hipStream_t st) {
     const int splits = gemm_residual_splits(M, N, K, W_stream != nullptr);
+    const int tile = M > SKINNY_MAX_ROWS ? mid_residual_split(M, N, K).tile : -1;
     if (splits > 1) {
         EpiPartial<BF> epi{partials, N, (int64_t)M * N, descale};
         if (M <= SKINNY_MAX_ROWS) launch_skinny(A, W, W_stream, M, N, K, splits, epi, st);
-        else if (mid_residual_split(M, N, K).narrow) launch_gemm<128, 64, 4, 1, 6>(A, W, M, N, K, splits, epi, st);
+        else if (tile == 0) launch_gemm<128, 64, 4, 1, 6>(A, W, M, N, K, splits, epi, st);
+        else if (tile == 1) launch_gemm16<128, 128, 4, 2>(A, W, M, N, K, splits, epi, st);
         else launch_gemm16<128, 256, 2, 4>(A, W, M, N, K, splits, epi, st);
         return splits;
     }
-    if (M > SKINNY_MAX_ROWS) launch_big(A, W, M, N, K, EpiResidualLds<BF>{x, N, descale}, st);
+    if (tile == 1) launch_gemm16<128, 128, 4, 2>(A, W, M, N, K, 1, EpiResidualLds<BF>{x, N, descale}, st);
+    else if (M > SKINNY_MAX_ROWS) launch_big(A, W, M, N, K, EpiResidualLds<BF>{x, N, descale}, st);
     else launch_skinny(A, W, W_stream, M, N, K, 1, EpiResidual<BF>{x, N, descale}, st);
     return 1;
 }

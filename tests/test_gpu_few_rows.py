@@ -135,14 +135,27 @@ def test_fallback_row_blocks(Br):
     _continue_and_check(m, _weights(m, 70 + Br), vi, 2, "f16", ROW_TOL["f16"], LOGIT_TOL["f16"], sample=range(0, Br, 8))
 
 
-# 768 columns are 3 (12) tiles per 128 rows: K splits of 128 x 64 tiles while they use more CUs, then of 128 x 256 tiles,
-# over 12 and 50 K steps; QKV and gate/up pass from 64 x 64 over 128 x 64 and 64 x 128 to the 256-wide tiles
+# 768 columns are 12, 6 or 3 tiles per 128 rows: K splits of 128 x 64, 128 x 128 or 128 x 256 tiles over 12 and 50 K steps; QKV and
+# gate/up pass from 64 x 64 over 64 x 128 and 128 x 128 to the 256-wide tiles
 @pytest.mark.parametrize("M", [129, 256, 257, 500, 641, 1100, 1700])
 def test_verify_mid_rows(M):
     m = ModelCfg(2, 768, 6, 2, 128, 3200, 512, dtype="bf16")
     wl = replace(WORKLOADS["cfg3_1b_ragged64"], model=m)
     w = make_model_weights(m, 80 + M)
     vi = _inputs(m, [(M // 2 - 40, 3, 37), (M - M // 2 - 9, 4, 5)], M)
+    tau = 1.0 / m.vocab
+    _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
+
+
+# 128 x 128 tiles of 2048 columns that add to x in place, up to a full round (2048 rows) and one row beyond it: O over 32 K steps; down
+# over four, as many as the ring has stages; QKV and gate/up in two rounds of them would be more, so they are 256 wide there
+@pytest.mark.parametrize("M", [1281, 1409, 2048, 2049])
+def test_verify_square_tiles_in_place(M):
+    m = ModelCfg(2, 2048, 16, 8, 128, 256, 512, dtype="bf16")
+    wl = replace(WORKLOADS["cfg3_1b_ragged64"], model=m)
+    w = make_model_weights(m, 85 + M)
+    n = M // 150
+    vi = _inputs(m, [(130 + (M - 150 * n if b == 0 else 0), 8, 12) for b in range(n)], M)
     tau = 1.0 / m.vocab
     _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
 
