@@ -25,17 +25,15 @@ __device__ __forceinline__ f32x4v_t mfma_f32_k16(const float4& w, const float4& 
 }
 
 // ---------------------------------------------------------------------------------------------
-// C = A W^T for 32 rows x 16 column PAIRS per workgroup; the epilogue gets both members of a pair in one thread:
+// C = A W^T for 16 RB rows x 16 PB column PAIRS per workgroup; the end of the tile gets both members of a pair in one thread:
 //   F32_QKV      (i, i + head_dim/2) of a rotary head, or (c, c + d_kv/2) of v: rotation, store, K/V-cache row
 //   F32_SWIGLU   gate and up of one hidden unit: h = silu(gate) * up
-//   F32_RESIDUAL two columns 16 apart: x += acc
+//   F32_RESIDUAL (no pairs: single columns) x += acc
 // QKV and SWIGLU take RMSNorm(x) as A: the gain is applied to the fragments, the sum of squares of the row falls out
 // of the same loads, and 1/rms multiplies the finished sums (out = inv * sum_k (x_k g_k) w_k).
-// The wavefronts split K; their partial tiles are added through LDS in wavefront order by the first 256 threads.
+// The NW wavefronts split K; their partial tiles are added through LDS in wavefront order.
 // K % 16 == 0; M, the pair count and head_dim are arbitrary (rows and columns beyond the end are clamped on load).
-// What the epilogue reads (rotary entries, old residual values) is requested before the products.
-// 285 rows of the two-layer decoder (K 256 / 1024): QKV 7.5 us, O 5.2, gate/up 10.1, down 11.4 against 18 / 18 / 18 / 65 us
-// for a 64 x 64 LDS tile with K in one piece (down: 20 workgroups on 256 CUs), and four launches less per layer.
+// What the ends read (rotary entries, old residual values) is requested before the products.
 enum F32Pairs { F32_QKV, F32_SWIGLU, F32_RESIDUAL };
 struct F32GemmArgs {
     const float* A; const float* W; const float* gain; float* out;
@@ -60,76 +58,93 @@ __device__ __forceinline__ void pair_columns(const F32GemmArgs& g, int p, int& c
         c0 = p;
         c1 = g.n_pairs + p;
     } else {
-        c0 = (p / 16) * 32 + p % 16;
-        c1 = c0 + 16;
+        c0 = c1 = p;
     }
 }
 
-template <int EPI, int NW>
+template <int EPI, int NW, int RB, int PB>
 __global__ void __launch_bounds__(64 * NW) gemm_f32_kernel(F32GemmArgs g) {
     constexpr bool NORM = EPI != F32_RESIDUAL;
-    __shared__ float4 red[NW][4][64];                        // [wavefront][block i * 2 + j][lane]
-    __shared__ float ssl[NW][32];
+    constexpr int MEM = EPI == F32_RESIDUAL ? 1 : 2;         // members of a pair
+    constexpr int UNITS = 128 * RB * PB;                     // ends of the tile: two pairs of one row each
+    constexpr int PER = (UNITS + 64 * NW - 1) / (64 * NW);   // per thread
+    __shared__ float4 red[NW][RB][PB * MEM][64];             // [wavefront][row block][column block][lane]
+    __shared__ float ssl[NW][16 * RB];
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, x = lane % 16, kq = lane / 16;
-    const int m0 = blockIdx.y * 32, p0 = blockIdx.x * 16;
-    // what the epilogue reads (two pairs of one row per thread of the first 256) is requested before the products
-    const int slot = (threadIdx.x % 256) / 2, bi = slot / 64, ln = slot % 64, part = threadIdx.x % 2;
-    const int r = 16 * bi + ln % 16, row = m0 + r, e_row = min(row, g.M - 1);
-    int e_c0[2], e_c1[2], e_rot[2];
-    float2 e_old[2];                                         // QKV: (cos, sin); RESIDUAL: the old values of the pair
-    int e_pos = 0, e_slot = -1;
-    if constexpr (EPI == F32_QKV) {
-        e_pos = g.pos[e_row];
-        if (g.row_slot) e_slot = g.row_slot[e_row];
-    }
+    const int m0 = blockIdx.y * 16 * RB, p0 = blockIdx.x * 16 * PB;
+    // what the ends read is requested before the products
+    struct End { int bi, bj, ln, part, r, row; };
+    auto end_of = [&](int k) {
+        const int u = (k * 64 * NW + threadIdx.x) % UNITS, slot = u / 2, blk = slot / 64;
+        End e{blk / PB, blk % PB, slot % 64, u % 2, 0, 0};
+        e.r = 16 * e.bi + e.ln % 16;
+        e.row = m0 + e.r;
+        return e;
+    };
+    float2 e_old[PER][2];                                    // QKV: (cos, sin); RESIDUAL: the old value
+    int e_slot[PER];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        pair_columns<EPI>(g, min(p0 + 4 * (ln / 16) + 2 * part + e, g.n_pairs - 1), e_c0[e], e_c1[e], e_rot[e]);
-        if constexpr (EPI == F32_QKV) e_old[e] = e_rot[e] >= 0 ? g.rope_tab[(int64_t)e_pos * g.half + e_rot[e]] : make_float2(1.f, 0.f);
-        if constexpr (EPI == F32_RESIDUAL)
-            e_old[e] = make_float2(g.out[(int64_t)e_row * g.ldo + min(e_c0[e], g.N - 1)], g.out[(int64_t)e_row * g.ldo + min(e_c1[e], g.N - 1)]);
-    }
-    const float* a_row[2];
+    for (int k = 0; k < PER; ++k) {
+        const End e = end_of(k);
+        const int e_row = min(e.row, g.M - 1);
+        int e_pos = 0;
+        if constexpr (EPI == F32_QKV) {
+            e_pos = g.pos[e_row];
+            e_slot[k] = g.row_slot ? g.row_slot[e_row] : -1;
+        }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) a_row[i] = g.A + (int64_t)min(m0 + 16 * i + x, g.M - 1) * g.K + 4 * kq;
-    int c0, c1, unused;
-    pair_columns<EPI>(g, min(p0 + x, g.n_pairs - 1), c0, c1, unused);
-    const float* w_row[2] = {g.W + (int64_t)min(c0, g.N - 1) * g.K + 4 * kq, g.W + (int64_t)min(c1, g.N - 1) * g.K + 4 * kq};
-    f32x4v_t acc[2][2] = {};
-    float ss[2] = {0.f, 0.f};
+        for (int c = 0; c < 2; ++c) {
+            int c0, c1, rot;
+            pair_columns<EPI>(g, min(p0 + 16 * e.bj + 4 * (e.ln / 16) + 2 * e.part + c, g.n_pairs - 1), c0, c1, rot);
+            if constexpr (EPI == F32_QKV) e_old[k][c] = rot >= 0 ? g.rope_tab[(int64_t)e_pos * g.half + rot] : make_float2(1.f, 0.f);
+            if constexpr (EPI == F32_RESIDUAL) e_old[k][c].x = g.out[(int64_t)e_row * g.ldo + c0];
+        }
+    }
+    const float* a_row[RB];
+    const float* w_row[PB * MEM];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) a_row[i] = g.A + (int64_t)min(m0 + 16 * i + x, g.M - 1) * g.K + 4 * kq;
+#pragma unroll
+    for (int j = 0; j < PB; ++j) {
+        int c[2], unused;
+        pair_columns<EPI>(g, min(p0 + 16 * j + x, g.n_pairs - 1), c[0], c[1], unused);
+#pragma unroll
+        for (int q = 0; q < MEM; ++q) w_row[MEM * j + q] = g.W + (int64_t)c[q] * g.K + 4 * kq;
+    }
+    f32x4v_t acc[RB][PB * MEM] = {};
+    float ss[RB] = {};
     const int KT = g.K / 16, t0 = KT * wave / NW, t1 = KT * (wave + 1) / NW;
-    constexpr int U = 4;                                     // K steps in flight
+    constexpr int U = RB + PB * MEM > 4 ? 2 : 4;             // K steps in flight
     for (int t = t0; t < t1; t += U) {
-        float4 a[U][2], w[U][2], gn[U];
+        float4 a[U][RB], w[U][PB * MEM], gn[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t k = 16 * min(t + u, t1 - 1);       // a step beyond the end is loaded and left out
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[u][i] = *reinterpret_cast<const float4*>(a_row[i] + k);
-                w[u][i] = *reinterpret_cast<const float4*>(w_row[i] + k);
-            }
+            for (int i = 0; i < RB; ++i) a[u][i] = *reinterpret_cast<const float4*>(a_row[i] + k);
+#pragma unroll
+            for (int j = 0; j < PB * MEM; ++j) w[u][j] = *reinterpret_cast<const float4*>(w_row[j] + k);
             if constexpr (NORM) gn[u] = *reinterpret_cast<const float4*>(g.gain + k + 4 * kq);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (t + u >= t1) break;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < RB; ++i) {
                 float4 v = a[u][i];
                 if constexpr (NORM) {
                     ss[i] += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
                     v = make_float4(v.x * gn[u].x, v.y * gn[u].y, v.z * gn[u].z, v.w * gn[u].w);
                 }
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f32_k16(w[u][j], v, acc[i][j]);
+                for (int j = 0; j < PB * MEM; ++j) acc[i][j] = mfma_f32_k16(w[u][j], v, acc[i][j]);
             }
         }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < RB; ++i) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) red[wave][2 * i + j][lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        for (int j = 0; j < PB * MEM; ++j) red[wave][i][j][lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
         if constexpr (NORM) {
             float s = ss[i];
             s += __shfl_xor(s, 16);
@@ -138,58 +153,83 @@ __global__ void __launch_bounds__(64 * NW) gemm_f32_kernel(F32GemmArgs g) {
         }
     }
     __syncthreads();
-    if (row >= g.M || threadIdx.x >= 256) return;
-    float v[2][2] = {};
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
+    for (int k = 0; k < PER; ++k) {
+        const End e = end_of(k);
+        if (e.row >= g.M || k * 64 * NW + (int)threadIdx.x >= UNITS) continue;
+        float v[2][2] = {};
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const float2 t = reinterpret_cast<const float2*>(&red[w][2 * bi + j][ln])[part];
-            v[j][0] += t.x;
-            v[j][1] += t.y;
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int q = 0; q < MEM; ++q) {
+                const float2 t = reinterpret_cast<const float2*>(&red[w][e.bi][MEM * e.bj + q][e.ln])[e.part];
+                v[q][0] += t.x;
+                v[q][1] += t.y;
+            }
+        if constexpr (NORM) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) s += ssl[w][e.r];
+            const float inv = 1.0f / sqrtf(s / (float)g.K + g.eps);
+#pragma unroll
+            for (int q = 0; q < MEM; ++q) { v[q][0] *= inv; v[q][1] *= inv; }
         }
-    if constexpr (NORM) {
-        float s = 0.f;
+        float* o = g.out + (int64_t)e.row * g.ldo;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) s += ssl[w][r];
-        const float inv = 1.0f / sqrtf(s / (float)g.K + g.eps);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) { v[j][0] *= inv; v[j][1] *= inv; }
-    }
-    float* o = g.out + (int64_t)row * g.ldo;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int p = p0 + 4 * (ln / 16) + 2 * part + e;
-        if (p >= g.n_pairs) continue;
-        const float a = v[0][e], b = v[1][e];
-        c0 = e_c0[e]; c1 = e_c1[e];
-        if constexpr (EPI == F32_SWIGLU) {
-            o[p] = a / (1.0f + expf(-a)) * b;
-        } else if constexpr (EPI == F32_RESIDUAL) {
-            if (c0 < g.N) o[c0] = e_old[e].x + a;
-            if (c1 < g.N) o[c1] = e_old[e].y + b;
-        } else {
-            const bool rot = e_rot[e] >= 0;                  // (columns of v come with the identity rotation)
-            const float o0 = rot ? a * e_old[e].x - b * e_old[e].y : a, o1 = rot ? b * e_old[e].x + a * e_old[e].y : b;
-            o[c0] = o0;
-            o[c1] = o1;
-            if (e_slot >= 0 && c0 >= g.d_q) {                // a pair lies inside q, k or v
-                float* dst = (rot ? g.kc : g.vc) + (int64_t)e_slot * g.d_kv;
-                const int first = rot ? g.d_q : g.d_rot;
-                dst[c0 - first] = o0;
-                dst[c1 - first] = o1;
+        for (int c = 0; c < 2; ++c) {
+            const int p = p0 + 16 * e.bj + 4 * (e.ln / 16) + 2 * e.part + c;
+            if (p >= g.n_pairs) continue;
+            const float a = v[0][c], b = v[1][c];
+            int c0, c1, i_rot;
+            pair_columns<EPI>(g, p, c0, c1, i_rot);
+            if constexpr (EPI == F32_SWIGLU) {
+                o[p] = a / (1.0f + expf(-a)) * b;
+            } else if constexpr (EPI == F32_RESIDUAL) {
+                o[p] = e_old[k][c].x + a;
+            } else {
+                const bool rot = i_rot >= 0;                 // (columns of v come with the identity rotation)
+                const float2 cs = e_old[k][c];
+                const float o0 = rot ? a * cs.x - b * cs.y : a, o1 = rot ? b * cs.x + a * cs.y : b;
+                o[c0] = o0;
+                o[c1] = o1;
+                if (e_slot[k] >= 0 && c0 >= g.d_q) {         // a pair lies inside q, k or v
+                    float* dst = (rot ? g.kc : g.vc) + (int64_t)e_slot[k] * g.d_kv;
+                    const int first = rot ? g.d_q : g.d_rot;
+                    dst[c0 - first] = o0;
+                    dst[c1 - first] = o1;
+                }
             }
         }
     }
 }
 
+// Tile (row blocks of 16 x blocks of 16 pairs, single columns for RESIDUAL).  A workgroup pulls its operand rows through one CU's load
+// path, and that is what a small launch waits for: the smallest tile that still runs in one round.  Two-layer decoder (K 256 / 1024), us of
+// a launch, tiles of 32 rows x 16 pairs / as chosen: 64 rows QKV 6.1 / 4.6, O 4.8 / 3.6, gate/up 5.6 / 4.1, down 10.4 / 6.0 (also at 256
+// rows); K = 1024 / 4096 at 64 rows O 10.4 / 6.2, down 32 / 16.5.  Beyond one round larger tiles load less per product: for pairs
+// 2 x 2 or 2 x 1 by rounds times a tile's loads and products (14 to 8): gate/up of 2000 rows 35 / 30, QKV of 1024 rows (384 of the
+// 2 x 2 tiles, one and a half rounds) 11.1 as 2 x 1, 13.1 as 2 x 2.  Above K = 512 those that are left as 2 x 1, and the largest of
+// RESIDUAL, have K over eight wavefronts (down of 500 rows, K = 2048: 18.4 / 20.4 with four).
+template <int EPI, int NW, int RB, int PB>
+static void launch_pairs_tile(const F32GemmArgs& g, hipStream_t st) {
+    const dim3 grid((g.n_pairs + 16 * PB - 1) / (16 * PB), (g.M + 16 * RB - 1) / (16 * RB));
+    hipLaunchKernelGGL((gemm_f32_kernel<EPI, NW, RB, PB>), grid, dim3(64 * NW), 0, st, g);
+}
 template <int EPI>
 static void launch_pairs(const F32GemmArgs& g, hipStream_t st) {
     if (g.M <= 0) return;
-    const dim3 grid((g.n_pairs + 15) / 16, (g.M + 31) / 32);
-    // above two trips of four K steps per wavefront K goes over eight wavefronts (K = 1024: 12.8 -> 11.4 us)
-    if (g.K > 512) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 8>), grid, dim3(512), 0, st, g);
-    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 4>), grid, dim3(256), 0, st, g);
+    auto tiles = [&](int rb, int pb) { return (int64_t)((g.M + 16 * rb - 1) / (16 * rb)) * ((g.n_pairs + 16 * pb - 1) / (16 * pb)); };
+    auto rounds = [&](int rb, int pb) { return (tiles(rb, pb) + 255) / 256; };
+    if (tiles(1, 1) <= 256) { launch_pairs_tile<EPI, 4, 1, 1>(g, st); return; }
+    if (tiles(1, 2) <= 256) { launch_pairs_tile<EPI, 4, 1, 2>(g, st); return; }
+    if constexpr (EPI == F32_RESIDUAL) {
+        if (g.K > 512) launch_pairs_tile<EPI, 8, 2, 2>(g, st);
+        else launch_pairs_tile<EPI, 4, 2, 2>(g, st);
+    } else {
+        if (14 * rounds(2, 2) <= 8 * rounds(2, 1) && (g.K <= 512 || rounds(2, 2) >= 2)) launch_pairs_tile<EPI, 4, 2, 2>(g, st);
+        else if (g.K > 512) launch_pairs_tile<EPI, 8, 2, 1>(g, st);
+        else launch_pairs_tile<EPI, 4, 2, 1>(g, st);
+    }
 }
 void launch_gemm_f32_qkv(const float* x, const float* gain, float eps, const float* Wqkv, float* qkv, const int32_t* pos,
                          const float* rope_tab, int M, int d_model, int d_q, int d_kv, int head_dim, const int32_t* row_slot,
@@ -204,7 +244,7 @@ void launch_gemm_f32_swiglu(const float* x, const float* gain, float eps, const 
     launch_pairs<F32_SWIGLU>(g, st);
 }
 void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, int N, int K, hipStream_t st) {
-    F32GemmArgs g{A, W, nullptr, x, M, N, K, N, (N + 31) / 32 * 16, 0.f, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
+    F32GemmArgs g{A, W, nullptr, x, M, N, K, N, N, 0.f, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
     launch_pairs<F32_RESIDUAL>(g, st);
 }
 
