@@ -1031,9 +1031,13 @@ int verify_impl(ssd_ctx* ctx, const void* speech_emb, const int32_t* cu_speech, 
             launch_gemm_f32_qkv(x, (const float*)ctx->norm_attn[l], m.rms_eps, (const float*)ctx->wqkv[l], (float*)qkv, d_pos, ctx->rope_tab, Mi, d, dq, dkv, m.head_dim,
                                 kv_start ? d_row_slot : nullptr, kv_start ? (float*)kv_k(ctx, l) : nullptr, kv_start ? (float*)kv_v(ctx, l) : nullptr, st);
             launch_attn_f32((const float*)qkv, (float*)att, d_tiles, n_tiles, m.n_q_heads, m.n_kv_heads, m.head_dim, st);
-            launch_gemm_f32_residual((const float*)att, (const float*)ctx->wo[l], x, Mi, d, dq, st);
-            launch_gemm_f32_swiglu(x, (const float*)ctx->norm_mlp[l], m.rms_eps, (const float*)ctx->wgu[l], (float*)h, Mi, m.d_ff, d, st);
-            launch_gemm_f32_residual((const float*)h, (const float*)ctx->w_down[l], x, Mi, d, m.d_ff, st);
+            // last layer: the verification rows alone, in place.  Both layers: 64 rows 78.6 -> 78.6 us, 128 rows 81.6 -> 80.4, 256 rows
+            // 91.5 -> 88.4, 1862 rows 241 -> 214.
+            const int32_t* only = l == m.n_layers - 1 ? d_vrow : nullptr;
+            const int rows = only ? Mvi : Mi;
+            launch_gemm_f32_residual((const float*)att, (const float*)ctx->wo[l], x, rows, d, dq, only, only, st);
+            launch_gemm_f32_swiglu(x, (const float*)ctx->norm_mlp[l], m.rms_eps, (const float*)ctx->wgu[l], (float*)h, rows, m.d_ff, d, only, st);
+            launch_gemm_f32_residual((const float*)h, (const float*)ctx->w_down[l], x, rows, d, m.d_ff, nullptr, only, st);
         }
     }
     // final RMSNorm of the positions that score a draft token
@@ -1199,9 +1203,9 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
                 launch_gemm_f32_qkv(x, (const float*)ctx->norm_attn[l], m.rms_eps, (const float*)ctx->wqkv[l], (float*)qkv, d_pos, ctx->rope_tab, Br, d, dq, dkv, m.head_dim,
                                     d_slot, (float*)kv_k(ctx, l), (float*)kv_v(ctx, l), st);
                 launch_decode_attn_f32((const float*)qkv, (const float*)kv_k(ctx, l), (const float*)kv_v(ctx, l), d_kvs, d_nctx, Br, m.n_q_heads, m.n_kv_heads, m.head_dim, (float*)att, st);
-                launch_gemm_f32_residual((const float*)att, (const float*)ctx->wo[l], x, Br, d, dq, st);
-                launch_gemm_f32_swiglu(x, (const float*)ctx->norm_mlp[l], m.rms_eps, (const float*)ctx->wgu[l], (float*)h, Br, m.d_ff, d, st);
-                launch_gemm_f32_residual((const float*)h, (const float*)ctx->w_down[l], x, Br, d, m.d_ff, st);
+                launch_gemm_f32_residual((const float*)att, (const float*)ctx->wo[l], x, Br, d, dq, nullptr, nullptr, st);
+                launch_gemm_f32_swiglu(x, (const float*)ctx->norm_mlp[l], m.rms_eps, (const float*)ctx->wgu[l], (float*)h, Br, m.d_ff, d, nullptr, st);
+                launch_gemm_f32_residual((const float*)h, (const float*)ctx->w_down[l], x, Br, d, m.d_ff, nullptr, nullptr, st);
             }
         }
         launch_rmsnorm(m.dtype, x, ctx->norm_final, nullptr, Br, d, m.rms_eps, hfin, partials, pending, split_stride, ctx->dev_flags, ctx->bf16_ops, st);

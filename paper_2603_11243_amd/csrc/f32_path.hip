@@ -38,6 +38,7 @@ enum F32Pairs { F32_QKV, F32_SWIGLU, F32_RESIDUAL };
 struct F32GemmArgs {
     const float* A; const float* W; const float* gain; float* out;
     int M, N, K, ldo, n_pairs; float eps;
+    const int32_t* a_rows; const int32_t* o_rows;                               // rows of A / of out that are taken (NULL: all in order)
     int half, d_rot, d_q, d_kv; const int32_t* pos; const float2* rope_tab;     // QKV only
     const int32_t* row_slot; float* kc; float* vc;
 };
@@ -82,11 +83,14 @@ __global__ void __launch_bounds__(64 * NW) gemm_f32_kernel(F32GemmArgs g) {
         return e;
     };
     float2 e_old[PER][2];                                    // QKV: (cos, sin); RESIDUAL: the old value
-    int e_slot[PER];
+    int e_slot[PER], e_out[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const End e = end_of(k);
         const int e_row = min(e.row, g.M - 1);
+        e_out[k] = e_row;
+        if constexpr (EPI == F32_RESIDUAL)
+            if (g.o_rows) e_out[k] = g.o_rows[e_row];
         int e_pos = 0;
         if constexpr (EPI == F32_QKV) {
             e_pos = g.pos[e_row];
@@ -97,13 +101,16 @@ __global__ void __launch_bounds__(64 * NW) gemm_f32_kernel(F32GemmArgs g) {
             int c0, c1, rot;
             pair_columns<EPI>(g, min(p0 + 16 * e.bj + 4 * (e.ln / 16) + 2 * e.part + c, g.n_pairs - 1), c0, c1, rot);
             if constexpr (EPI == F32_QKV) e_old[k][c] = rot >= 0 ? g.rope_tab[(int64_t)e_pos * g.half + rot] : make_float2(1.f, 0.f);
-            if constexpr (EPI == F32_RESIDUAL) e_old[k][c].x = g.out[(int64_t)e_row * g.ldo + c0];
+            if constexpr (EPI == F32_RESIDUAL) e_old[k][c].x = g.out[(int64_t)e_out[k] * g.ldo + c0];
         }
     }
     const float* a_row[RB];
     const float* w_row[PB * MEM];
 #pragma unroll
-    for (int i = 0; i < RB; ++i) a_row[i] = g.A + (int64_t)min(m0 + 16 * i + x, g.M - 1) * g.K + 4 * kq;
+    for (int i = 0; i < RB; ++i) {
+        const int row = min(m0 + 16 * i + x, g.M - 1);
+        a_row[i] = g.A + (int64_t)(g.a_rows ? g.a_rows[row] : row) * g.K + 4 * kq;
+    }
 #pragma unroll
     for (int j = 0; j < PB; ++j) {
         int c[2], unused;
@@ -174,7 +181,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_f32_kernel(F32GemmArgs g) {
 #pragma unroll
             for (int q = 0; q < MEM; ++q) { v[q][0] *= inv; v[q][1] *= inv; }
         }
-        float* o = g.out + (int64_t)e.row * g.ldo;
+        float* o = g.out + (int64_t)e_out[k] * g.ldo;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const int p = p0 + 16 * e.bj + 4 * (e.ln / 16) + 2 * e.part + c;
@@ -234,17 +241,18 @@ static void launch_pairs(const F32GemmArgs& g, hipStream_t st) {
 void launch_gemm_f32_qkv(const float* x, const float* gain, float eps, const float* Wqkv, float* qkv, const int32_t* pos,
                          const float* rope_tab, int M, int d_model, int d_q, int d_kv, int head_dim, const int32_t* row_slot,
                          float* kc, float* vc, hipStream_t st) {
-    F32GemmArgs g{x, Wqkv, gain, qkv, M, d_q + 2 * d_kv, d_model, d_q + 2 * d_kv, (d_q + 2 * d_kv) / 2, eps, head_dim / 2, d_q + d_kv,
+    F32GemmArgs g{x, Wqkv, gain, qkv, M, d_q + 2 * d_kv, d_model, d_q + 2 * d_kv, (d_q + 2 * d_kv) / 2, eps, nullptr, nullptr, head_dim / 2, d_q + d_kv,
                   d_q, d_kv, pos, reinterpret_cast<const float2*>(rope_tab), row_slot, kc, vc};
     launch_pairs<F32_QKV>(g, st);
 }
 void launch_gemm_f32_swiglu(const float* x, const float* gain, float eps, const float* Wgu, float* h, int M, int d_ff, int d_model,
-                            hipStream_t st) {
-    F32GemmArgs g{x, Wgu, gain, h, M, 2 * d_ff, d_model, d_ff, d_ff, eps, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
+                            const int32_t* x_rows, hipStream_t st) {
+    F32GemmArgs g{x, Wgu, gain, h, M, 2 * d_ff, d_model, d_ff, d_ff, eps, x_rows, nullptr, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
     launch_pairs<F32_SWIGLU>(g, st);
 }
-void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, int N, int K, hipStream_t st) {
-    F32GemmArgs g{A, W, nullptr, x, M, N, K, N, N, 0.f, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
+void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, int N, int K, const int32_t* a_rows, const int32_t* x_rows,
+                              hipStream_t st) {
+    F32GemmArgs g{A, W, nullptr, x, M, N, K, N, N, 0.f, a_rows, x_rows, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
     launch_pairs<F32_RESIDUAL>(g, st);
 }
 

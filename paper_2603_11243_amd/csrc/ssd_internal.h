@@ -108,11 +108,12 @@ void launch_rmsnorm(int dtype, float* x, const void* gain, const int32_t* row_id
 void launch_gemm_f32_qkv(const float* x, const float* gain, float eps, const float* Wqkv, float* qkv, const int32_t* pos,
                          const float* rope_tab, int M, int d_model, int d_q, int d_kv, int head_dim, const int32_t* row_slot,
                          float* kc, float* vc, hipStream_t st);
-// h = silu(gate) * up with [gate | up] = rmsnorm(x) Wgu^T
+// h = silu(gate) * up with [gate | up] = rmsnorm(x) Wgu^T.  Row lists (distinct rows) may be NULL: all rows in order
 void launch_gemm_f32_swiglu(const float* x, const float* gain, float eps, const float* Wgu, float* h, int M, int d_ff, int d_model,
-                            hipStream_t st);
-// x += A W^T
-void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, int N, int K, hipStream_t st);
+                            const int32_t* x_rows, hipStream_t st);
+// x[x_rows] += A[a_rows] W^T
+void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, int N, int K, const int32_t* a_rows, const int32_t* x_rows,
+                              hipStream_t st);
 constexpr int F32_ATTN_ROWS = 16;        // query rows of one attention work item
 void launch_attn_f32(const float* qkv, float* out, const AttnTile* tiles, int n_tiles, int n_q_heads,
                      int n_kv_heads, int head_dim, hipStream_t st);
