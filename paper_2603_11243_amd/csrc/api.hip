@@ -154,6 +154,16 @@ int upload(ssd_ctx* c, const void* host, void* dev, size_t bytes) {
     return SSD_OK;
 }
 
+// second half of the gate: prefix sums as kernel arguments where they fit, else uploaded to cu_dev
+int gate_utterances_of(ssd_ctx* c, const float* H, const int32_t* arg, const int32_t* cu_frames, int32_t* cu_dev, int64_t n_rows, int B, int blank,
+                       float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len) {
+    if (launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank, tau, max_entropy, gate_pass, draft, draft_len, c->stream)) return SSD_OK;
+    const int rc = upload(c, cu_frames, cu_dev, (size_t)(B + 1) * 4);
+    if (rc != SSD_OK) return rc;
+    launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank, tau, max_entropy, gate_pass, draft, draft_len, c->stream);
+    return SSD_OK;
+}
+
 // Brackets the launches issued during its lifetime with two events when the class is being timed.
 struct ProfScope {
     ssd_ctx* c; int cls; int e0 = -1;
@@ -732,11 +742,6 @@ int ctc_gate(ssd_ctx* ctx, const void* logits, int dtype, const int32_t* cu_fram
     float* H = frame_entropy ? frame_entropy : reinterpret_cast<float*>(ws + p.H);
     int32_t* arg = frame_argmax ? frame_argmax : reinterpret_cast<int32_t*>(ws + p.arg);
     int32_t* cu_dev = reinterpret_cast<int32_t*>(ws + p.cu);
-    const bool as_args = B <= GATE_MAX_ARG_UTTS;
-    if (!as_args) {
-        const int rc = upload(ctx, cu_frames, cu_dev, (size_t)(B + 1) * 4);
-        if (rc != SSD_OK) return rc;
-    }
     // The counts are the context's, whose calls run one after the other on its stream.  A captured call may be replayed on another
     // stream next to them, or next to another captured one: it takes the two launches, which share nothing but the workspace.
     unsigned* arrived = ctx->gate_arrived && !capturing(ctx->stream) ? ctx->gate_arrived : nullptr;
@@ -745,8 +750,8 @@ int ctc_gate(ssd_ctx* ctx, const void* logits, int dtype, const int32_t* cu_fram
         if (!launch_gate_fused(logits, dtype, cu_frames, n_rows, B, V_ctc, blank_id, tau_ctc, H, arg, max_entropy, gate_pass, draft_ctc, draft_len,
                                arrived, ctx->stream)) {
             launch_gate_frames(logits, dtype, n_rows, V_ctc, H, arg, ctx->stream);
-            if (as_args) launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
-            else launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len, ctx->stream);
+            const int rc = gate_utterances_of(ctx, H, arg, cu_frames, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len);
+            if (rc != SSD_OK) return rc;
         }
     }
     HIP_TRY(ctx, hipGetLastError());
@@ -836,32 +841,42 @@ int qformer_pool(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int 
     const QformerPlan p = plan_qformer(n_rows, B, window, n_q, d_h);
     if (!ctx->ws || ctx->ws_bytes < p.total)
         return fail(ctx, SSD_EWORKSPACE, "qformer_pool: workspace of %zu bytes needed, %zu set", p.total, ctx->ws_bytes);
-    std::vector<QWindow> wins;
-    wins.reserve((size_t)p.max_windows);
     cu_speech[0] = 0;
-    for (int b = 0; b < B; ++b) {
-        for (int f = cu_frames[b]; f < cu_frames[b + 1]; f += window)
-            wins.push_back(QWindow{f, std::min(window, cu_frames[b + 1] - f)});
-        cu_speech[b + 1] = (int32_t)(wins.size() * n_q);
-    }
-    const int n_windows = (int)wins.size();
+    for (int b = 0; b < B; ++b) cu_speech[b + 1] = cu_speech[b] + n_q * ((cu_frames[b + 1] - cu_frames[b] + window - 1) / window);
+    const int n_windows = cu_speech[B] / n_q;
+    const bool after = ctx->qf_wfrag && values_after_pooling(n_rows, n_windows, n_q), as_args = !after && n_windows <= QF_ARG_WINDOWS;
     char* ws = static_cast<char*>(ctx->ws);
-    int rc = upload(ctx, wins.data(), ws + p.wins, wins.size() * sizeof(QWindow));
-    if (rc != SSD_OK) return rc;
+    QWindow* d_wins = reinterpret_cast<QWindow*>(ws + p.wins);
+    QWindowArgs args;
+    CuPairs cu;
+    if (as_args) {
+        QWindow* w = args.w;
+        for (int b = 0; b < B; ++b)
+            for (int f = cu_frames[b]; f < cu_frames[b + 1]; f += window) *w++ = QWindow{f, std::min(window, cu_frames[b + 1] - f)};
+    } else if (make_cu_pairs(cu_frames, B, cu)) {
+        launch_qformer_windows(cu, B, window, d_wins, ctx->stream);
+    } else {
+        std::vector<QWindow> wins;
+        wins.reserve((size_t)n_windows);
+        for (int b = 0; b < B; ++b)
+            for (int f = cu_frames[b]; f < cu_frames[b + 1]; f += window) wins.push_back(QWindow{f, std::min(window, cu_frames[b + 1] - f)});
+        const int rc = upload(ctx, wins.data(), d_wins, wins.size() * sizeof(QWindow));
+        if (rc != SSD_OK) return rc;
+    }
     float* scores = reinterpret_cast<float*>(ws + p.scores);
     uint16_t* vals = reinterpret_cast<uint16_t*>(ws + p.vals);
     uint16_t* o = reinterpret_cast<uint16_t*>(ws + p.o);
     const int n_cat = qformer_cat_rows(d_h);
     {
         ProfScope ps(ctx, SSD_PROF_QFORMER);
-        const QWindow* d_wins = reinterpret_cast<const QWindow*>(ws + p.wins);
-        if (ctx->qf_wfrag && values_after_pooling(n_rows, n_windows, n_q)) {
+        if (after) {
             launch_gemm_scores(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, (int)n_rows, d_enc, ctx->stream);
             launch_qformer_values(static_cast<const uint16_t*>(enc_h), scores, ctx->qf_wfrag, d_wins, n_windows, n_q, d_enc, o, ctx->dev_flags, ctx->stream);
         } else {
             launch_gemm_scores_values(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, vals, (int)n_rows, n_cat, d_enc, d_h,
                                       ctx->dev_flags, true, ctx->stream);
-            launch_qformer_pool(scores, vals, d_wins, n_windows, n_q, ctx->qf_heads, d_h, o, ctx->stream);
+            if (as_args) launch_qformer_pool_host(scores, vals, args, n_windows, n_q, ctx->qf_heads, d_h, o, ctx->stream);
+            else launch_qformer_pool(scores, vals, d_wins, n_windows, n_q, ctx->qf_heads, d_h, o, ctx->stream);
         }
         launch_gemm_store_16(o, ctx->qf_wo, static_cast<uint16_t*>(speech_emb), n_windows * n_q, ctx->qf_dout, d_h, true, ctx->stream);
     }
@@ -889,8 +904,6 @@ int ctc_head_gate(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int
     float* H = frame_entropy ? frame_entropy : reinterpret_cast<float*>(ws + p.H);
     int32_t* arg = frame_argmax ? frame_argmax : reinterpret_cast<int32_t*>(ws + p.arg);
     int32_t* cu_dev = reinterpret_cast<int32_t*>(ws + p.cu);
-    int rc = upload(ctx, cu_frames, cu_dev, (size_t)(B + 1) * 4);
-    if (rc != SSD_OK) return rc;
     {
         ProfScope ps(ctx, SSD_PROF_CTC_HEAD);
         // the kernels address the states with 32-bit byte offsets: at most 4 GiB of them per launch
@@ -900,8 +913,8 @@ int ctc_head_gate(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int
             launch_ctc_head(static_cast<const uint16_t*>(enc_h) + r0 * d, ctx->head_w, ctx->head_bias, rows, d, V,
                             ctx->head_V_pad, reinterpret_cast<float4*>(ws + p.part), H + r0, arg + r0, ctx->stream);
         }
-        launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len,
-                               ctx->stream);
+        const int rc = gate_utterances_of(ctx, H, arg, cu_frames, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len);
+        if (rc != SSD_OK) return rc;
     }
     HIP_TRY(ctx, hipGetLastError());
     return SSD_OK;
@@ -910,6 +923,21 @@ int ctc_head_gate(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int
 }  // extern "C"
 
 namespace {
+
+// The parts of a metadata block (byte offset in the workspace, bytes) as arguments of the embedding launch; false: too many words.
+struct MetaPart { size_t at, bytes; };
+bool pack_meta(const std::vector<char>& meta, const MetaPart (&parts)[EmbedMeta::PARTS], EmbedMeta& out) {
+    size_t words = 0;
+    for (const MetaPart& q : parts) words += q.bytes / 4;
+    if (words > EmbedMeta::WORDS) return false;
+    int n = 0;
+    for (int s = 0; s < EmbedMeta::PARTS; ++s) {
+        memcpy(out.word + n, meta.data() + parts[s].at, parts[s].bytes);
+        out.at[s] = (int32_t)(parts[s].at / 4);
+        out.end[s] = n += (int)(parts[s].bytes / 4);
+    }
+    return true;
+}
 
 size_t kv_layer_bytes(const ssd_model_cfg& m, int64_t slots) {
     return (size_t)slots * m.n_kv_heads * m.head_dim * elem_size(m.dtype);
@@ -976,8 +1004,13 @@ int verify_impl(ssd_ctx* ctx, const void* speech_emb, const int32_t* cu_speech, 
         for (int q = 0; q < n; q += tile_rows) tiles[n_tiles++] = AttnTile{start, n, q, 0};
     }
     char* ws = static_cast<char*>(ctx->ws);
-    int rc = upload(ctx, meta.data(), ws, p.meta_bytes);
-    if (rc != SSD_OK) return rc;
+    EmbedMeta args;
+    const bool as_args = pack_meta(meta, {{p.row_src, (size_t)M * 4}, {p.pos, (size_t)M * 4}, {p.vrow, (size_t)Mv * 4},
+                                          {p.row_slot, kv_start ? (size_t)M * 4 : 0}, {p.tiles, n_tiles * sizeof(AttnTile)}}, args);
+    if (!as_args) {
+        const int rc = upload(ctx, meta.data(), ws, p.meta_bytes);
+        if (rc != SSD_OK) return rc;
+    }
     const int32_t* d_row_src = reinterpret_cast<const int32_t*>(ws + p.row_src);
     const int32_t* d_pos = reinterpret_cast<const int32_t*>(ws + p.pos);
     const int32_t* d_vrow = reinterpret_cast<const int32_t*>(ws + p.vrow);
@@ -991,7 +1024,11 @@ int verify_impl(ssd_ctx* ctx, const void* speech_emb, const int32_t* cu_speech, 
     hipStream_t st = ctx->stream;
     const int Mi = (int)M, d = m.d_model, dq = m.n_q_heads * m.head_dim, dkv = m.n_kv_heads * m.head_dim;
 
-    { ProfScope ps(ctx, SSD_PROF_OTHER); launch_embed_rows(m.dtype, speech_emb, ctx->embed, prompt_ids, draft_ids, d_row_src, Mi, d, m.vocab, x, ctx->dev_flags, st); }
+    {
+        ProfScope ps(ctx, SSD_PROF_OTHER);
+        if (as_args) launch_embed_rows_meta(m.dtype, speech_emb, ctx->embed, prompt_ids, draft_ids, args, Mi, d, m.vocab, x, ws, ctx->dev_flags, st);
+        else launch_embed_rows(m.dtype, speech_emb, ctx->embed, prompt_ids, draft_ids, d_row_src, Mi, d, m.vocab, x, ctx->dev_flags, st);
+    }
     float* rope_rows = nullptr;
     if (m.dtype == SSD_BF16 && M > SKINNY_MAX_ROWS) {
         ProfScope ps(ctx, SSD_PROF_OTHER);
@@ -1160,8 +1197,14 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
         }
     }
     char* ws = static_cast<char*>(ctx->ws);
-    int rc = upload(ctx, meta.data(), ws, p.meta_bytes);
-    if (rc != SSD_OK) return rc;
+    EmbedMeta args;
+    const size_t per_step = (size_t)n_steps * Br * 4;
+    const bool as_args = pack_meta(meta, {{p.row_src, (size_t)Br * 4}, {p.kv_start, (size_t)Br * 4}, {p.pos, per_step}, {p.n_ctx, per_step},
+                                          {p.slot, per_step}}, args);
+    if (!as_args) {
+        const int rc = upload(ctx, meta.data(), ws, p.meta_bytes);
+        if (rc != SSD_OK) return rc;
+    }
     const int32_t* d_row_src = reinterpret_cast<const int32_t*>(ws + p.row_src);
     const int32_t* d_kvs = reinterpret_cast<const int32_t*>(ws + p.kv_start);
     float* x = reinterpret_cast<float*>(ws + p.x);
@@ -1178,7 +1221,8 @@ int ar_fallback(ssd_ctx* ctx, int Br, const int32_t* kv_start, const int32_t* ct
         const int32_t* d_pos = reinterpret_cast<const int32_t*>(ws + p.pos) + (size_t)t * Br;
         const int32_t* d_nctx = reinterpret_cast<const int32_t*>(ws + p.n_ctx) + (size_t)t * Br;
         const int32_t* d_slot = reinterpret_cast<const int32_t*>(ws + p.slot) + (size_t)t * Br;
-        launch_embed_rows(m.dtype, nullptr, ctx->embed, nullptr, tok_in, d_row_src, Br, d, m.vocab, x, ctx->dev_flags, st);
+        if (t == 0 && as_args) launch_embed_rows_meta(m.dtype, nullptr, ctx->embed, nullptr, tok_in, args, Br, d, m.vocab, x, ws, ctx->dev_flags, st);
+        else launch_embed_rows(m.dtype, nullptr, ctx->embed, nullptr, tok_in, d_row_src, Br, d, m.vocab, x, ctx->dev_flags, st);
         int pending = 1;
         for (int l = 0; l < m.n_layers; ++l) {
             if (m.dtype == SSD_BF16) {

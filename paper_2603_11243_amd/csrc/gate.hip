@@ -461,13 +461,33 @@ void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* c
                        max_entropy, gate_pass, draft, draft_len);
 }
 
-void launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
+bool make_cu_pairs(const int32_t* cu, int B, CuPairs& out) {
+    if (B > GATE_MAX_PAIR_UTTS) return false;
+    for (int b = 0; b <= B; b += 2) out.even[b / 2] = cu[b];
+    for (int p = 0; 2 * p + 1 <= B; ++p) {                   // the lengths before the odd sums
+        const int len = cu[2 * p + 1] - cu[2 * p];
+        if (len > 0xffff) return false;
+        uint32_t& w = out.odd[p / 2];
+        w = p % 2 ? w | (uint32_t)len << 16 : (uint32_t)len;
+    }
+    return true;
+}
+
+bool launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
                                  float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                                  hipStream_t st) {
-    CuArgs cu;
-    for (int b = 0; b <= B; ++b) cu.cu[b] = cu_frames[b];
-    hipLaunchKernelGGL(gate_utterances<CuArgs>, dim3(B), dim3(256), 0, st, H, arg, cu, (int)n_rows, blank, tau,
+    if (B <= GATE_MAX_ARG_UTTS) {
+        CuArgs cu;
+        for (int b = 0; b <= B; ++b) cu.cu[b] = cu_frames[b];
+        hipLaunchKernelGGL(gate_utterances<CuArgs>, dim3(B), dim3(256), 0, st, H, arg, cu, (int)n_rows, blank, tau,
+                           max_entropy, gate_pass, draft, draft_len);
+        return true;
+    }
+    CuPairs cu;
+    if (!make_cu_pairs(cu_frames, B, cu)) return false;
+    hipLaunchKernelGGL(gate_utterances<CuPairs>, dim3(B), dim3(256), 0, st, H, arg, cu, (int)n_rows, blank, tau,
                        max_entropy, gate_pass, draft, draft_len);
+    return true;
 }
 
 template <typename T, int LPR>

@@ -52,12 +52,14 @@ void launch_qformer_fold(const uint16_t* q_proj, const uint16_t* w_k, const uint
 // One workgroup per window.  Scores of the window's frames go through LDS, one thread normalises one
 // (query, head) column over the frames, then every thread owns four consecutive value columns (one 8-byte load
 // per frame, whole rows coalesced) and accumulates their n_q weighted sums over the frames.
-template <int NQ>
+struct QWindowList {
+    const QWindow* w;
+};
+template <int NQ, class Wins>
 __global__ void __launch_bounds__(256) qformer_pool_kernel(const float* __restrict__ scores, const f16_t* __restrict__ vals,
-                                                           const QWindow* __restrict__ wins, int n_heads, int d_h,
-                                                           bf16_t* __restrict__ o) {
+                                                           Wins wins, int n_heads, int d_h, bf16_t* __restrict__ o) {
     __shared__ float p_s[QF_SCORE_COLS][QF_MAX_WINDOW + 1];
-    const QWindow w = wins[blockIdx.x];
+    const QWindow w = wins.w[blockIdx.x];
     const int n_pairs = NQ * n_heads;
     const float* sbase = scores + (int64_t)w.frame0 * QF_SCORE_COLS;
     for (int i = threadIdx.x; i < w.n_frames * QF_SCORE_COLS; i += 256)        // the window's scores are one contiguous piece
@@ -100,12 +102,38 @@ __global__ void __launch_bounds__(256) qformer_pool_kernel(const float* __restri
     }
 }
 
-void launch_qformer_pool(const float* scores, const uint16_t* vals, const QWindow* wins, int n_windows, int n_q, int n_heads,
-                         int d_h, uint16_t* o, hipStream_t st) {
+template <class Wins>
+static void launch_pool(const float* scores, const uint16_t* vals, const Wins& wins, int n_windows, int n_q, int n_heads, int d_h, uint16_t* o,
+                        hipStream_t st) {
     if (n_windows <= 0) return;
-#define SSD_QF(NQ) hipLaunchKernelGGL(qformer_pool_kernel<NQ>, dim3(n_windows), dim3(256), 0, st, scores, vals, wins, n_heads, d_h, o)
+#define SSD_QF(NQ) hipLaunchKernelGGL((qformer_pool_kernel<NQ, Wins>), dim3(n_windows), dim3(256), 0, st, scores, vals, wins, n_heads, d_h, o)
     if (n_q == 1) SSD_QF(1); else if (n_q == 2) SSD_QF(2); else if (n_q == 3) SSD_QF(3); else SSD_QF(4);
 #undef SSD_QF
+}
+void launch_qformer_pool(const float* scores, const uint16_t* vals, const QWindow* wins, int n_windows, int n_q, int n_heads,
+                         int d_h, uint16_t* o, hipStream_t st) {
+    launch_pool(scores, vals, QWindowList{wins}, n_windows, n_q, n_heads, d_h, o, st);
+}
+void launch_qformer_pool_host(const float* scores, const uint16_t* vals, const QWindowArgs& wins, int n_windows, int n_q, int n_heads,
+                              int d_h, uint16_t* o, hipStream_t st) {
+    launch_pool(scores, vals, wins, n_windows, n_q, n_heads, d_h, o, st);
+}
+
+// The windows of utterance blockIdx.x, behind those of the utterances before it.
+__global__ void __launch_bounds__(256) qformer_windows_kernel(CuPairs cu, int window, QWindow* __restrict__ wins) {
+    __shared__ int part[4];
+    const int b = blockIdx.x;
+    int before = 0;
+    for (int i = threadIdx.x; i < b; i += 256) before += (cu(i + 1) - cu(i) + window - 1) / window;
+    before = group_allreduce_i<64>(before, [] __device__(int a, int c) { return a + c; });
+    if (threadIdx.x % 64 == 0) part[threadIdx.x / 64] = before;
+    __syncthreads();
+    before = part[0] + part[1] + part[2] + part[3];
+    const int first = cu(b), n = cu(b + 1) - first;
+    for (int i = threadIdx.x; i * window < n; i += 256) wins[before + i] = QWindow{first + i * window, min(window, n - i * window)};
+}
+void launch_qformer_windows(const CuPairs& cu, int B, int window, QWindow* wins, hipStream_t st) {
+    hipLaunchKernelGGL(qformer_windows_kernel, dim3(B), dim3(256), 0, st, cu, window, wins);
 }
 
 }  // namespace ssd

@@ -20,8 +20,9 @@ void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* c
                             float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                             hipStream_t st);
 
-// The same with the prefix sums in host memory, B <= GATE_MAX_ARG_UTTS: they travel as kernel arguments (1 KB), which spares
-// a small batch its upload (one ten-second utterance: 15.2 -> 10.7 us a call).
+// The same with the prefix sums in host memory: they travel as kernel arguments, which spares the call its upload (one ten-second
+// utterance 15.2 -> 10.7 us, 400 utterances of 3 to 9 s 23.2 -> 17.4 us, 1024 of 1 to 30 s 76.5 -> 70.5 us).  Up to GATE_MAX_ARG_UTTS
+// utterances 1 KB of them as they are;
 constexpr int GATE_MAX_ARG_UTTS = 256;
 struct CuArray {                             // prefix sums in device memory
     const int32_t* cu;
@@ -31,7 +32,20 @@ struct CuArgs {                              // among the kernel's arguments
     int32_t cu[GATE_MAX_ARG_UTTS + 1];
     __device__ __forceinline__ int operator()(int b) const { return cu[b]; }
 };
-void launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
+// up to GATE_MAX_PAIR_UTTS of at most 65535 frames: every second prefix sum, and the lengths between in 16 bits (a thousand 32-bit
+// sums are more than the 4 KB of arguments a launch has).
+constexpr int GATE_MAX_PAIR_UTTS = 1280;
+struct CuPairs {
+    int32_t even[GATE_MAX_PAIR_UTTS / 2 + 1];
+    uint32_t odd[GATE_MAX_PAIR_UTTS / 4];        // two lengths a word
+    __device__ __forceinline__ int operator()(int b) const {
+        const int p = b / 2;
+        return even[p] + (b % 2 ? (int)(odd[p / 2] >> (16 * (p % 2)) & 0xffffu) : 0);
+    }
+};
+bool make_cu_pairs(const int32_t* cu, int B, CuPairs& out);      // false: more utterances or longer ones
+// false: not served, nothing was launched
+bool launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
                                  float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                                  hipStream_t st);
 
@@ -64,6 +78,14 @@ void launch_qformer_fold(const uint16_t* q_proj, const uint16_t* w_k, const uint
 // columns over its frames, then the weighted sum of its value columns: o [n_windows * n_q, d_h] bf16
 void launch_qformer_pool(const float* scores, const uint16_t* vals, const QWindow* wins, int n_windows, int n_q, int n_heads,
                          int d_h, uint16_t* o, hipStream_t st);
+// At most QF_ARG_WINDOWS windows in host memory, as kernel arguments; more of them listed on the device from the prefix sums of the
+// frames.  Either spares the upload: the front end of 2 utterances (19 windows) 54.5 -> 42.8 us, of 30 (280) 68.6 -> 59.5, of 300 (3000; the host
+// does not build the list either) 204 -> 173.
+constexpr int QF_ARG_WINDOWS = 448;
+struct QWindowArgs { QWindow w[QF_ARG_WINDOWS]; };
+void launch_qformer_pool_host(const float* scores, const uint16_t* vals, const QWindowArgs& wins, int n_windows, int n_q, int n_heads,
+                              int d_h, uint16_t* o, hipStream_t st);
+void launch_qformer_windows(const CuPairs& cu, int B, int window, QWindow* wins, hipStream_t st);
 
 // ---- qformer_values.hip: the same with the values projected after the pooling; for 16 heads of 64 dims, at most 3 queries and
 // windows of at most 16 frames.  w_frag: fragment-ordered copy of w_v [d_h, d_enc].
@@ -92,6 +114,15 @@ struct AttnTile {
 void launch_embed_rows(int dtype, const void* speech_emb, const void* embed, const int32_t* prompt_ids,
                        const int32_t* draft_ids, const int32_t* row_src, int M, int d, int vocab, float* x,
                        int32_t* flags, hipStream_t st);
+// Metadata of one call small enough for kernel arguments (4 KB with the rest): PARTS arrays of 32-bit words one behind the other, the
+// first of them the row sources; part s goes to word at[s] of the workspace and ends before word end[s].
+struct EmbedMeta {
+    static constexpr int PARTS = 5, WORDS = 960;
+    int32_t at[PARTS], end[PARTS];
+    uint32_t word[WORDS];
+};
+void launch_embed_rows_meta(int dtype, const void* speech_emb, const void* embed, const int32_t* prompt_ids, const int32_t* draft_ids,
+                            const EmbedMeta& meta, int M, int d, int vocab, float* x, void* ws, int32_t* flags, hipStream_t st);
 void launch_gather_rows(const void* src, const int32_t* row_idx, int n_rows, int64_t row_bytes, void* dst, hipStream_t st);
 // out[i] = src[idx[i]], passed through table (clamped into [0, n_table)) when table is not NULL
 void launch_gather_ids(const int32_t* src, const int32_t* idx, int n, const int32_t* table, int n_table, int32_t* out, hipStream_t st);
