@@ -3,10 +3,9 @@
 // The encoder's output layer (Sec. 3.1: 1024-wide states, 348 CTC symbols) produces the scores that
 // Eq. 2 (greedy symbol per frame) and Eq. 3 (frame entropy) consume.  Here the scores
 //     z[t, v] = enc_h[t] . W[v] + b[v]
-// only ever exist in MFMA accumulators.  The product is formed transposed, Z^T = W . enc_h^T, so that
-// an accumulator lane owns one frame (its column) and 16 symbols per 32x32 block (its registers):
-// the per-frame reductions over symbols run inside the lane, with a single exchange between the two
-// lane halves at the end.  Every wavefront reduces its [64 symbols x frames] slab to
+// only ever exist in MFMA accumulators.  The accumulator blocks are transposed, so that a lane owns one frame and
+// four consecutive symbols of a 16x16 block: the per-frame reductions over symbols run inside the lane, with two
+// exchanges between the 16-lane groups at the end.  Every wavefront reduces its [frames x 64 symbols] slab to
 //     m = max_v z,  arg = lowest v with z = m,  S = sum_v e^(z-m),  W = sum_v e^(z-m) (z-m)
 // per frame (16 bytes), and a second small kernel merges the symbol groups of a frame into
 //     H_t = log S - W / S   ( = -sum_v p log p for p = softmax(z) ),   argmax_t.
@@ -14,80 +13,81 @@
 // bf16 scores and the gate's load of them).  Operands are the stored bf16 values (bf16 MFMA, exact
 // products, fp32 accumulation); the accumulators start at the bias, and symbols added as padding
 // have zero weights and bias -inf, i.e. probability zero.
-#include "gemm_core.h"
+#include "gemm_core16.h"
 #include "ssd_internal.h"
 
 namespace ssd {
 
-constexpr int CH_BM = 128;          // symbols per tile
-constexpr int CH_GROUP = 64;        // symbols per partial: the wave tile height of every variant below
+constexpr int CH_BN = 128;          // symbols per tile
+constexpr int CH_GROUP = 64;        // symbols per partial: the width of a wavefront's tile
 constexpr int CH_PAD = 128;         // symbol count is padded to a multiple of this
 
-template <int BN, int WM, int WN, int NS>
-__global__ void __launch_bounds__(64 * WM * WN)
+// BM frames x CH_BN symbols on v_mfma_f32_16x16x32_bf16 with transposed blocks: a lane has one frame (lane % 16 of a block) and four
+// consecutive symbols, the four 16-lane groups of a wavefront share a frame.
+template <int BM, int WM>
+__global__ void __launch_bounds__(128 * WM)
 ctc_head_partials_kernel(const uint16_t* __restrict__ enc_h, const uint16_t* __restrict__ w_pad,
                          const float* __restrict__ bias_pad, int n_rows, int d_enc, int V, int V_pad,
                          float4* __restrict__ part) {
-    using Tile = GemmTile<CH_BM, BN, WM, WN, NS, true>;
-    static_assert(Tile::WTM == CH_GROUP, "one partial per wave tile of 64 symbols");
+    using Tile = GemmTile16<BM, CH_BN, WM, 2, true, true>;
+    using L = Layout16T;
+    static_assert(Tile::WTN == CH_GROUP, "one partial per wave tile of 64 symbols");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     // symbol tiles vary fastest, and the tiles of one slab of frames run on one XCD (one fetch of the slab)
-    const int tiles_v = V_pad / CH_BM;
+    const int tiles_v = V_pad / CH_BN;
     const int v = xcd_contiguous_index(blockIdx.x, gridDim.x);
     const int tv = v % tiles_v, tf = v / tiles_v;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int wm = wave / WN, wn = wave % WN;
-    const int sym0 = tv * CH_BM + wm * Tile::WTM;            // first symbol of this wavefront
-    const int frame0 = tf * BN + wn * Tile::WTN;
-    const int half = lane / 32;
+    const int wm = wave / 2, wn = wave % 2;
+    const int sym0 = tv * CH_BN + wn * Tile::WTN;            // first symbol of this wavefront
+    const int frame0 = tf * BM + wm * Tile::WTM;
 
-    f32x16_t acc[Tile::TM][Tile::TN];
+    f32x4_t acc[Tile::TM][Tile::TN];
 #pragma unroll
-    for (int i = 0; i < Tile::TM; ++i)
+    for (int j = 0; j < Tile::TN; ++j) {
+        const f32x4_t b4 = *reinterpret_cast<const f32x4_t*>(bias_pad + sym0 + L::col4(j, lane));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 b4 = *reinterpret_cast<const float4*>(bias_pad + sym0 + i * 32 + 8 * q + 4 * half);
-#pragma unroll
-            for (int j = 0; j < Tile::TN; ++j) {
-                acc[i][j][4 * q + 0] = b4.x; acc[i][j][4 * q + 1] = b4.y;
-                acc[i][j][4 * q + 2] = b4.z; acc[i][j][4 * q + 3] = b4.w;
-            }
-        }
-    Tile::run(reinterpret_cast<const f16_t*>(w_pad), reinterpret_cast<const f16_t*>(enc_h), V_pad, d_enc, tv * CH_BM,
-              tf * BN, 0, d_enc / GEMM_BK, smem_raw, acc, n_rows);
+        for (int i = 0; i < Tile::TM; ++i) acc[i][j] = b4;
+    }
+    Tile::run(reinterpret_cast<const f16_t*>(enc_h), reinterpret_cast<const f16_t*>(w_pad), n_rows, d_enc, tf * BM, tv * CH_BN, 0,
+              d_enc / GEMM_BK, smem_raw, acc);
 
     if (sym0 >= V) return;                                   // slab made of padding symbols only
     const int group = sym0 / CH_GROUP;
     constexpr float LOG2E = 1.4426950408889634f;
 #pragma unroll
-    for (int j = 0; j < Tile::TN; ++j) {
-        const int frame = frame0 + j * 32 + lane % 32;
+    for (int i = 0; i < Tile::TM; ++i) {
+        const int frame = frame0 + L::row(i, lane);
         float m = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < Tile::TM; ++i)
+        for (int j = 0; j < Tile::TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) m = fmaxf(m, fmaxf(acc[i][j][r], acc[i][j][r + 1]));
+            for (int r = 0; r < 4; r += 2) m = fmaxf(m, fmaxf(acc[i][j][r], acc[i][j][r + 1]));
+        m = fmaxf(m, __shfl_xor(m, 16));
         m = fmaxf(m, __shfl_xor(m, 32));                     // finite: symbol sym0 is real
         const float mL = m * LOG2E;
         float s = 0.f, w = 0.f;
-        int rel = 0x7fffffff;                                // symbol index relative to sym0 + 4*half
+        int rel = 0x7fffffff;                                // symbol index relative to sym0 + 4 * (lane / 16)
         // descending symbol order: the last match is the lowest index
 #pragma unroll
-        for (int i = Tile::TM - 1; i >= 0; --i)
+        for (int j = Tile::TN - 1; j >= 0; --j)
 #pragma unroll
-            for (int r = 15; r >= 0; --r) {
+            for (int r = 3; r >= 0; --r) {
                 const float z = acc[i][j][r];
                 const float t2 = fmaf(z, LOG2E, -mL);        // (z - m) log2 e  <= 0; -inf for padding
                 const float e = __builtin_amdgcn_exp2f(t2);
                 s += e;
                 w = fmaf(e, fmaxf(t2, -200.f), w);           // e is 0 there; keeps 0 * inf out
-                if (z == m) rel = i * 32 + 8 * (r / 4) + (r % 4);
+                if (z == m) rel = 16 * j + r;
             }
-        int arg = rel == 0x7fffffff ? rel : sym0 + 4 * half + rel;
-        s += __shfl_xor(s, 32);
-        w += __shfl_xor(w, 32);
-        arg = min(arg, __shfl_xor(arg, 32));
-        if (frame < n_rows && half == 0)
+        int arg = rel == 0x7fffffff ? rel : sym0 + 4 * (lane / 16) + rel;
+#pragma unroll
+        for (int o = 16; o < 64; o *= 2) {
+            s += __shfl_xor(s, o);
+            w += __shfl_xor(w, o);
+            arg = min(arg, __shfl_xor(arg, o));
+        }
+        if (frame < n_rows && lane < 16)
             part[(int64_t)group * n_rows + frame] = make_float4(m, s, w * (1.0f / LOG2E), __int_as_float(arg));
     }
 }
@@ -114,18 +114,17 @@ __global__ void __launch_bounds__(256) ctc_head_finalize_kernel(const float4* __
     arg[row] = best;
 }
 
-template <int BN, int WM, int WN, int NS>
+template <int BM, int WM>
 static void launch_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc,
                             int V, int V_pad, float4* part, hipStream_t st) {
-    constexpr size_t lds = gemm_lds_bytes<CH_BM, BN, NS>();
-    auto kern = ctc_head_partials_kernel<BN, WM, WN, NS>;
+    constexpr size_t lds = GemmTile16<BM, CH_BN, WM, 2, true, true>::LDS_BYTES;
+    auto kern = ctc_head_partials_kernel<BM, WM>;
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         attr_set = true;
     }
-    const int tiles_f = (n_rows + BN - 1) / BN;
-    hipLaunchKernelGGL(kern, dim3(tiles_f * (V_pad / CH_BM)), dim3(64 * WM * WN), lds, st, enc_h, w_pad, bias_pad,
+    hipLaunchKernelGGL(kern, dim3((n_rows + BM - 1) / BM * (V_pad / CH_BN)), dim3(128 * WM), lds, st, enc_h, w_pad, bias_pad,
                        n_rows, d_enc, V, V_pad, part);
 }
 
@@ -137,7 +136,12 @@ int ctc_head_padded(int V) { return (V + CH_PAD - 1) / CH_PAD * CH_PAD; }
 void launch_ctc_head(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc, int V,
                      int V_pad, float4* part, float* H, int32_t* arg, hipStream_t st) {
     if (n_rows <= 0) return;
-    launch_partials<256, 2, 4, 3>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
+    // The smallest tile of frames that runs in one round: in 256-frame tiles a few thousand frames leave most CUs idle.  Front end of 275 /
+    // 4100 frames 42.7 -> 37.5 / 60.2 -> 50.3 us (mostly this kernel); 198 K frames, 256-frame tiles: 188 -> 173 us with the 16x16x32
+    // instruction instead of 32x32x16.
+    if ((int64_t)((n_rows + 63) / 64) * (V_pad / CH_BN) <= 256) launch_partials<64, 2>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
+    else if ((int64_t)((n_rows + 127) / 128) * (V_pad / CH_BN) <= 256) launch_partials<128, 4>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
+    else launch_partials<256, 4>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
     hipLaunchKernelGGL(ctc_head_finalize_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, part, ctc_head_groups(V),
                        n_rows, H, arg);
 }

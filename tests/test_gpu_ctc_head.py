@@ -108,6 +108,15 @@ def test_head_gate_many_frames_takes_the_tall_tile(ctx):
     _run_and_compare(ctx, torch.from_numpy(h).bfloat16(), w, bias, cu, 0, 1.0)
 
 
+# three tiles of symbols: 64-frame tiles up to 85 of them, then 128, from 10881 frames on 256; one frame more than a tile each
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 5440, 5441, 10880, 10881, 11009])
+def test_head_gate_frames_around_tile_heights(ctx, n):
+    g = torch.Generator().manual_seed(n)
+    enc = torch.randn(n, 128, generator=g).to(torch.bfloat16)
+    w = (torch.randn(348, 128, generator=g) / 8).to(torch.bfloat16)
+    _run_and_compare(ctx, enc, w, torch.randn(348, generator=g) * 0.1, np.unique([0, n // 3, n // 2, n]), 0, 2.0)
+
+
 def test_head_gate_uniform_and_one_hot_rows(ctx):
     # zero weight: every frame has softmax(bias); closed forms ln V (flat bias) and the one-peak entropy
     V, d_enc = 348, 64
