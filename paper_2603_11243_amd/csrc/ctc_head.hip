@@ -7,12 +7,15 @@
 // four consecutive symbols of a 16x16 block: the per-frame reductions over symbols run inside the lane, with two
 // exchanges between the 16-lane groups at the end.  Every wavefront reduces its [frames x 64 symbols] slab to
 //     m = max_v z,  arg = lowest v with z = m,  S = sum_v e^(z-m),  W = sum_v e^(z-m) (z-m)
-// per frame (16 bytes), and a second small kernel merges the symbol groups of a frame into
+// per frame (16 bytes), and a second small kernel merges the symbol groups of a frame (and mostly goes on to the gate's decisions) into
 //     H_t = log S - W / S   ( = -sum_v p log p for p = softmax(z) ),   argmax_t.
 // Written per frame: 16 bytes per group of 64 symbols instead of 2 x 2 bytes per symbol (a store of
 // bf16 scores and the gate's load of them).  Operands are the stored bf16 values (bf16 MFMA, exact
 // products, fp32 accumulation); the accumulators start at the bias, and symbols added as padding
 // have zero weights and bias -inf, i.e. probability zero.
+#include <algorithm>
+
+#include "gate_utterance.h"
 #include "gemm_core16.h"
 #include "ssd_internal.h"
 
@@ -114,6 +117,61 @@ __global__ void __launch_bounds__(256) ctc_head_finalize_kernel(const float4* __
     arg[row] = best;
 }
 
+// The merge and the second half of the gate in one launch, a workgroup per utterance; H and arg may be null.  Both are small: a launch of
+// its own costs the merge more than its work does.  All partials of a frame are requested at once (a group beyond the last is
+// a second copy of it and left out).
+struct MergeOut { float* H; int32_t* arg; float* max_entropy; uint8_t* gate_pass; int32_t* draft; int32_t* draft_len; };
+template <int NG, int WAVES, int AHEAD, class CU>
+__global__ void __launch_bounds__(64 * WAVES) ctc_head_utterances_kernel(const float4* __restrict__ part, int n_groups, int n_rows, const CU cu, int blank,
+                                                                  float tau, MergeOut out) {
+    const int b = blockIdx.x, lo = cu(b), hi = cu(b + 1);
+    auto merge = [&](int t, float& h, int& best) {
+        float4 p[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) p[g] = part[(int64_t)min(g, n_groups - 1) * n_rows + t];
+        float M = p[0].x;
+#pragma unroll
+        for (int g = 1; g < NG; ++g) M = fmaxf(M, p[g].x);
+        float S = 0.f, W = 0.f;
+        best = 0x7fffffff;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (g >= n_groups) continue;
+            const float shift = p[g].x - M, f = __expf(shift);
+            S += f * p[g].y;
+            W += f * (p[g].z + shift * p[g].y);
+            if (p[g].x == M) best = min(best, __float_as_int(p[g].w));
+        }
+        h = logf(S) - W / S;
+    };
+    gate_utterance<WAVES, AHEAD>(b, lo, hi, blank, tau, out.max_entropy, out.gate_pass, out.draft, out.draft_len,
+                      [&](int t, float& h, int& a) {
+                          merge(t, h, a);
+                          if (out.H) out.H[t] = h;
+                          if (out.arg) out.arg[t] = a;
+                      },
+                      [&](int t, int a) {                    // the lane before has it; the first lane merges that frame as well
+                          float h;
+                          int edge;
+                          merge(max(__builtin_amdgcn_readfirstlane(t) - 1, lo), h, edge);
+                          const int before = __shfl_up(a, 1);
+                          return threadIdx.x % 64 == 0 ? edge : before;
+                      });
+}
+// Every trip of a workgroup over its utterance is a chain of memory and barriers, so one trip is made of all frames: four wavefronts with two
+// frames a lane up to 512, sixteen with one beyond.  us of the merge and the decisions, their own launches / four / sixteen wavefronts: one
+// utterance of 250 frames 5.0 / 3.6 / 3.5, of 1000 6.2 / 6.6 / 4.4, of 2000 6.3 / 11.2 / 6.8 (and a gap between launches less), of 4000 9.5 / 20.6 / 12.0;
+// 300 of 212 9.8 / 5.4 / 7.6, 64 of 1000 9.6 / 7.2 / 5.0, 256 of 2000 20.3 / 16.8 / 13.9.
+constexpr int MERGE_FEW_FRAMES = 512, MERGE_MAX_FRAMES = 2048, MERGE_MAX_GROUPS = 8;
+template <class CU>
+static void launch_merge(const float4* part, int n_groups, int n_rows, const CU& cu, int B, int longest, int blank, float tau, const MergeOut& out, hipStream_t st) {
+#define SSD_MERGE(NG) do { \
+        if (longest <= MERGE_FEW_FRAMES) hipLaunchKernelGGL((ctc_head_utterances_kernel<NG, 4, 2, CU>), dim3(B), dim3(256), 0, st, part, n_groups, n_rows, cu, blank, tau, out); \
+        else hipLaunchKernelGGL((ctc_head_utterances_kernel<NG, 16, 1, CU>), dim3(B), dim3(1024), 0, st, part, n_groups, n_rows, cu, blank, tau, out); } while (0)
+    if (n_groups <= 2) SSD_MERGE(2); else if (n_groups <= 6) SSD_MERGE(6); else SSD_MERGE(MERGE_MAX_GROUPS);
+#undef SSD_MERGE
+}
+
 template <int BM, int WM>
 static void launch_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc,
                             int V, int V_pad, float4* part, hipStream_t st) {
@@ -133,8 +191,8 @@ int ctc_head_padded(int V) { return (V + CH_PAD - 1) / CH_PAD * CH_PAD; }
 
 // enc_h [n_rows, d_enc] bf16; w_pad [V_pad, d_enc] bf16 with zero rows beyond V; bias_pad [V_pad] fp32, -inf
 // beyond V; part: ctc_head_groups(V) * n_rows float4.  n_rows * d_enc * 2 must stay below 4 GiB.
-void launch_ctc_head(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc, int V,
-                     int V_pad, float4* part, float* H, int32_t* arg, hipStream_t st) {
+void launch_ctc_head_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc, int V,
+                              int V_pad, float4* part, hipStream_t st) {
     if (n_rows <= 0) return;
     // The smallest tile of frames that runs in one round: in 256-frame tiles a few thousand frames leave most CUs idle.  Front end of 275 /
     // 4100 frames 42.7 -> 37.5 / 60.2 -> 50.3 us (mostly this kernel); 198 K frames, 256-frame tiles: 188 -> 173 us with the 16x16x32
@@ -142,8 +200,28 @@ void launch_ctc_head(const uint16_t* enc_h, const uint16_t* w_pad, const float* 
     if ((int64_t)((n_rows + 63) / 64) * (V_pad / CH_BN) <= 256) launch_partials<64, 2>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
     else if ((int64_t)((n_rows + 127) / 128) * (V_pad / CH_BN) <= 256) launch_partials<128, 4>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
     else launch_partials<256, 4>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
-    hipLaunchKernelGGL(ctc_head_finalize_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, part, ctc_head_groups(V),
-                       n_rows, H, arg);
+}
+void launch_ctc_head_merge(const float4* part, int V, int n_rows, float* H, int32_t* arg, hipStream_t st) {
+    if (n_rows <= 0) return;
+    hipLaunchKernelGGL(ctc_head_finalize_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, part, ctc_head_groups(V), n_rows, H, arg);
+}
+bool launch_ctc_head_merge_gate(const float4* part, int V, int n_rows, const int32_t* cu_frames, int B, int blank, float tau, float* H, int32_t* arg,
+                                float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len, hipStream_t st) {
+    const int n_groups = ctc_head_groups(V);
+    int longest = 0;
+    for (int b = 0; b < B; ++b) longest = std::max(longest, cu_frames[b + 1] - cu_frames[b]);
+    if (n_groups > MERGE_MAX_GROUPS || longest > MERGE_MAX_FRAMES) return false;
+    const MergeOut out{H, arg, max_entropy, gate_pass, draft, draft_len};
+    if (B <= GATE_MAX_ARG_UTTS) {
+        CuArgs cu;
+        for (int b = 0; b <= B; ++b) cu.cu[b] = cu_frames[b];
+        launch_merge(part, n_groups, n_rows, cu, B, longest, blank, tau, out, st);
+        return true;
+    }
+    CuPairs cu;
+    if (!make_cu_pairs(cu_frames, B, cu)) return false;
+    launch_merge(part, n_groups, n_rows, cu, B, longest, blank, tau, out, st);
+    return true;
 }
 
 // padded copy of the output layer: rows [V, V_pad) are zero and their bias is -inf

@@ -13,6 +13,7 @@
 // Batches that do not fill the device take both steps in one launch (gate_fused).
 #include <algorithm>
 #include "device_utils.h"
+#include "gate_utterance.h"
 #include "ssd_internal.h"
 
 namespace ssd {
@@ -315,64 +316,6 @@ __global__ void __launch_bounds__(256) gate_frames_generic(const T* __restrict__
 
 // One workgroup (256 threads) per utterance.  The frame range of an utterance is clamped into
 // [0, n_rows], so that prefix sums that were never seen by the host cannot lead outside H / arg / draft.
-// The decision about one utterance and its collapsed path, by 256 threads.  frame(t, H, arg) and symbol(t) read frame t's statistics.
-// 1024 frames a trip: every trip waits for memory once and for the other wavefronts twice (with 256 a trip, 1500 frames were six waits).
-template <class Frame, class Symbol>
-__device__ __forceinline__ void gate_utterance(int b, int lo, int hi, int blank, float tau, float* __restrict__ max_entropy, uint8_t* __restrict__ gate_pass,
-                                               int32_t* __restrict__ draft, int32_t* __restrict__ draft_len, Frame frame, Symbol symbol) {
-    constexpr int AHEAD = 4;
-    __shared__ int wave_cnt[AHEAD][4];
-    __shared__ float wave_max[4];
-    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    float mx = -INFINITY;
-    int written = 0;                                   // same value in every thread
-    for (int t0 = lo; t0 < hi; t0 += 256 * AHEAD) {
-        int a[AHEAD], prev[AHEAD];
-        float H[AHEAD];
-        unsigned long long mask[AHEAD];
-#pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            const int t = min(t0 + u * 256 + (int)threadIdx.x, hi - 1);
-            frame(t, H[u], a[u]);
-            prev[u] = symbol(max(t - 1, lo));
-        }
-#pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            const int t = t0 + u * 256 + threadIdx.x;
-            bool keep = false;
-            if (t < hi) {
-                mx = fmaxf(mx, H[u]);
-                keep = (a[u] != blank) && (t == lo || a[u] != prev[u]);
-            }
-            mask[u] = __ballot(keep);
-            if (lane == 0) wave_cnt[u][wave] = __popcll(mask[u]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            int wave_off = 0, total = 0;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const int c = wave_cnt[u][w];
-                if (w < wave) wave_off += c;
-                total += c;
-            }
-            const unsigned long long below = (1ull << lane) - 1ull;
-            if (mask[u] >> lane & 1) draft[lo + written + wave_off + __popcll(mask[u] & below)] = a[u];
-            written += total;
-        }
-        __syncthreads();
-    }
-    mx = group_allreduce<64>(mx, OpMax());
-    if (lane == 0) wave_max[wave] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const float m = fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]));
-        max_entropy[b] = m;
-        gate_pass[b] = (m < tau) ? 1 : 0;
-        draft_len[b] = written;
-    }
-}
 template <class CU>
 __global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__ H,
                                                        const int32_t* __restrict__ arg,
@@ -382,8 +325,8 @@ __global__ void __launch_bounds__(256) gate_utterances(const float* __restrict__
                                                        int32_t* __restrict__ draft, int32_t* __restrict__ draft_len) {
     const int b = blockIdx.x;
     const int lo = min(max(cu_frames(b), 0), n_rows), hi = min(max(cu_frames(b + 1), lo), n_rows);
-    gate_utterance(b, lo, hi, blank, tau, max_entropy, gate_pass, draft, draft_len,
-                        [&](int t, float& h, int& a) { a = arg[t]; h = H[t]; }, [&](int t) { return arg[t]; });
+    gate_utterance<4, 4>(b, lo, hi, blank, tau, max_entropy, gate_pass, draft, draft_len,
+                        [&](int t, float& h, int& a) { a = arg[t]; h = H[t]; }, [&](int t, int) { return arg[max(t - 1, lo)]; });
 }
 
 // ---- Both steps in one launch: the workgroup whose rows complete an utterance finishes it.
@@ -450,8 +393,8 @@ __global__ void __launch_bounds__(256) gate_fused(const T* __restrict__ logits, 
 #pragma unroll 1
     for (int u = 0; u < 2; ++u)
         if (__builtin_amdgcn_readfirstlane(complete_s[u]))
-            gate_utterance(b0 + u, g.cu[b0 + u], g.cu[b0 + u + 1], g.blank, g.tau, g.max_entropy, g.gate_pass, g.draft, g.draft_len,
-                           [&](int t, float& h, int& a) { a = load_shared(arg + t); h = load_shared(H + t); }, [&](int t) { return load_shared(arg + t); });
+            gate_utterance<4, 4>(b0 + u, g.cu[b0 + u], g.cu[b0 + u + 1], g.blank, g.tau, g.max_entropy, g.gate_pass, g.draft, g.draft_len,
+                           [&](int t, float& h, int& a) { a = load_shared(arg + t); h = load_shared(H + t); }, [&](int t, int) { return load_shared(arg + max(t - 1, g.cu[b0 + u])); });
 }
 
 void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* cu_frames_dev, int64_t n_rows, int B, int blank,

@@ -117,6 +117,19 @@ def test_head_gate_frames_around_tile_heights(ctx, n):
     _run_and_compare(ctx, enc, w, torch.randn(348, generator=g) * 0.1, np.unique([0, n // 3, n // 2, n]), 0, 2.0)
 
 
+# Merge and decisions in one launch: up to 8 groups of 64 symbols and 2048 frames an utterance, up to 512 in four wavefronts of two frames a
+# lane, prefix sums of up to 256 and up to 1280 utterances as arguments; beyond, launches of their own.
+@pytest.mark.parametrize("V,lengths", [(64, [512, 1, 256]), (100, [1, 255, 257]), (348, [513, 64]), (384, [3, 1024]), (385, [1025, 128, 129]), (512, [2048]),
+                                       (348, [2, 2049]), (513, [300, 65]), (348, [3] * 256), (348, [3] * 257), (40, [1] * 1281)])
+def test_head_gate_utterances_around_the_merge(ctx, V, lengths):
+    n = sum(lengths)
+    g = torch.Generator().manual_seed(V * n)
+    enc = torch.randn(n, 64, generator=g).to(torch.bfloat16)
+    enc[1::2] = enc[:n - n % 2:2]                            # pairs of equal frames: repeats to collapse, across wavefronts and utterances
+    w = (torch.randn(V, 64, generator=g) / 4).to(torch.bfloat16)
+    _run_and_compare(ctx, enc, w, torch.randn(V, generator=g) * 0.1, np.concatenate([[0], np.cumsum(lengths)]), 0, 2.0)
+
+
 def test_head_gate_uniform_and_one_hot_rows(ctx):
     # zero weight: every frame has softmax(bias); closed forms ln V (flat bias) and the one-peak entropy
     V, d_enc = 348, 64
