@@ -904,6 +904,7 @@ int ctc_head_gate(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int
     float* H = frame_entropy ? frame_entropy : reinterpret_cast<float*>(ws + p.H);
     int32_t* arg = frame_argmax ? frame_argmax : reinterpret_cast<int32_t*>(ws + p.arg);
     int32_t* cu_dev = reinterpret_cast<int32_t*>(ws + p.cu);
+    float4* part = reinterpret_cast<float4*>(ws + p.part);
     {
         ProfScope ps(ctx, SSD_PROF_CTC_HEAD);
         // the kernels address the states with 32-bit byte offsets: at most 4 GiB of them per launch
