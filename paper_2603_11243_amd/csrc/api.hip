@@ -866,14 +866,13 @@ int qformer_pool(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int 
     float* scores = reinterpret_cast<float*>(ws + p.scores);
     uint16_t* vals = reinterpret_cast<uint16_t*>(ws + p.vals);
     uint16_t* o = reinterpret_cast<uint16_t*>(ws + p.o);
-    const int n_cat = qformer_cat_rows(d_h);
     {
         ProfScope ps(ctx, SSD_PROF_QFORMER);
         if (after) {
             launch_gemm_scores(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, (int)n_rows, d_enc, ctx->stream);
             launch_qformer_values(static_cast<const uint16_t*>(enc_h), scores, ctx->qf_wfrag, d_wins, n_windows, n_q, d_enc, o, ctx->dev_flags, ctx->stream);
         } else {
-            launch_gemm_scores_values(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, vals, (int)n_rows, n_cat, d_enc, d_h,
+            launch_gemm_scores_values(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, vals, (int)n_rows, QF_SCORE_COLS + d_h, d_enc, d_h,
                                       ctx->dev_flags, true, ctx->stream);
             if (as_args) launch_qformer_pool_host(scores, vals, args, n_windows, n_q, ctx->qf_heads, d_h, o, ctx->stream);
             else launch_qformer_pool(scores, vals, d_wins, n_windows, n_q, ctx->qf_heads, d_h, o, ctx->stream);

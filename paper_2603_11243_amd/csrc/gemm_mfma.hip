@@ -786,6 +786,8 @@ void launch_stream_layout(const uint16_t* w, void* out, int N, int K, hipStream_
 // with row blocks where that is faster (try_launch_stream_rows); otherwise a skinny 128 x 64 tile (four wavefronts, each 32 rows x 64 columns) with a six-stage LDS ring
 // (144 KB, five slices in flight), and for at most 32 rows a 32 x 64 tile of one wavefront, six stages
 // of 12 KB, two workgroups per CU.
+// four K groups, at least four slices each
+static bool kgroups_shape_ok(int K) { return (K / GEMM_BK) % 4 == 0 && K / GEMM_BK >= 16; }
 template <class Epi>
 static void launch_skinny(const f16_t* A, const f16_t* W, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
     if (try_launch_stream(A, Ws, M, N, K, splits, epi, st)) return;
@@ -796,7 +798,7 @@ static void launch_skinny(const f16_t* A, const f16_t* W, const void* Ws, int M,
     const int col_tiles = (N / 64) * splits;
     if constexpr (!Epi::WANTS_SPLIT) {
         // whole sums wanted (no K split across workgroups) and few column tiles: split K inside the workgroup
-        if (col_tiles <= 96 && M > 32 && (K / GEMM_BK) % 4 == 0 && K / GEMM_BK >= 16) {
+        if (col_tiles <= 96 && M > 32 && kgroups_shape_ok(K)) {
             launch_gemm_kgroups<32, 64, 3, 4>(A, W, M, N, K, epi, st);
             return;
         }
@@ -828,18 +830,22 @@ static void launch_big(const f16_t* A, const f16_t* W, int M, int N, int K, cons
 }
 // Whole sums (QKV, gate/up, the projector).  Beyond 128 rows the 256-wide tiles leave most of the chip idle until there
 // are about 256 of them, and a workgroup then has its whole K range in front of it whatever the row count.  Narrower tiles are
-// faster while they run in one round, the narrowest that do: 64 x 64 (LDS ring), 64 x 128, 128 x 128 of eight wavefronts.
+// faster while they run in one round, the narrowest that do: 32 x 64 with K split over four wavefronts, 64 x 64 (LDS ring), 64 x 128,
+// 128 x 128 of eight wavefronts.  (The projector's fused product, 1088 columns of K = 1024, 250 frames: 6.0 us as 32 x 64, 10.8 as 64 x 64; 1250
+// frames: 12.0 us in the one round of 64 x 128 that it is without columns of padding.  N is rounded up to the tile's width.)
 // Cold weights, us, 2048 / 3072 wide: QKV of 136 rows 16.0 / 21.8 as 64 x 64 (18.2 / 25.2 as 64 x 128), 256 rows of 3072 26.6 as 64 x 128
 // (34.6 as 128 x 128), 512 rows of 2048 19.5 as 64 x 128 (23.6), 640 rows 23.9 / 34.7 as 128 x 128 (27.9 / 41.5 as two rounds of
 // 64 x 128), 980 rows of 2048 27.6 as 128 x 128 (34.4 as 128 x 256); gate/up of 256 rows 26.3 / 38.8 as 128 x 128 (32.1 / 47.0 as 64 x 128).
 template <class Epi>
 static void launch_by_shape(const f16_t* A, const f16_t* W, const void* Ws, int M, int N, int K, const Epi& epi, hipStream_t st) {
-    auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * (N / bn); };
-    if (M <= SKINNY_MAX_ROWS) launch_skinny(A, W, Ws, M, N, K, 1, epi, st);
-    else if (tiles(64, 64) <= 256) launch_gemm<64, 64, 2, 1, 6>(A, W, M, N, K, 1, epi, st);
-    else if (tiles(64, 128) <= 256) launch_gemm16<64, 128, 2, 2>(A, W, M, N, K, 1, big_tile_epilogue(epi), st);
-    else if (tiles(128, 128) <= 256) launch_gemm16<128, 128, 4, 2>(A, W, M, N, K, 1, big_tile_epilogue(epi), st);
-    else launch_big(A, W, M, N, K, epi, st);
+    auto cols = [&](int bn) { return (N + bn - 1) / bn * bn; };
+    auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * (cols(bn) / bn); };
+    if (M <= SKINNY_MAX_ROWS) launch_skinny(A, W, Ws, M, cols(64), K, 1, epi, st);
+    else if (tiles(32, 64) <= 256 && kgroups_shape_ok(K)) launch_gemm_kgroups<32, 64, 3, 4>(A, W, M, cols(64), K, epi, st);
+    else if (tiles(64, 64) <= 256) launch_gemm<64, 64, 2, 1, 6>(A, W, M, cols(64), K, 1, epi, st);
+    else if (tiles(64, 128) <= 256) launch_gemm16<64, 128, 2, 2>(A, W, M, cols(128), K, 1, big_tile_epilogue(epi), st);
+    else if (tiles(128, 128) <= 256) launch_gemm16<128, 128, 4, 2>(A, W, M, cols(128), K, 1, big_tile_epilogue(epi), st);
+    else launch_big(A, W, M, cols(256), K, epi, st);
 }
 
 void launch_gemm_qkv_rope(const uint16_t* A, const uint16_t* Wqkv_packed, const void* W_stream, uint16_t* qkv, const int32_t* pos,

@@ -187,7 +187,8 @@ void launch_gemm_swiglu(const uint16_t* A, const uint16_t* Wgu_packed, const voi
                         float descale, int32_t* flags, bool bf16_ops, hipStream_t st);
 // plain products C[M,N] = A[M,K] W[N,K]^T with fp32 accumulation, stored as fp32 or rounded to the operand type
 // (N % 256 == 0, K % 64 == 0, row-major 16-bit operands of the type bf16_ops selects)
-// C = A W^T with W = [64 score rows | d_h value rows | zero rows up to N]: scores [M, 64] fp32, vals [M, d_h] IEEE half (saturating)
+// C = A W^T with W = [64 score rows | d_h value rows | zero rows up to a multiple of 256], N = 64 + d_h: scores [M, 64] fp32, vals [M, d_h]
+// IEEE half (saturating)
 void launch_gemm_scores_values(const uint16_t* A, const uint16_t* W, float* scores, uint16_t* vals, int M, int N, int K, int d_h,
                                int32_t* flags, bool bf16_ops, hipStream_t st);
 // the score rows of the same W alone: scores [M, 64] fp32 (bfloat16 operands)

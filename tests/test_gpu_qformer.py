@@ -75,6 +75,13 @@ def test_qformer_pool_frame_counts(frames):
     _check(got, ref)
 
 
+# The 1088 columns of scores and values are 17 tiles of 64 and 9 of 128: K-split 32 x 64 tiles up to 480 frames, 64 x 64 to 960,
+# 64 x 128 to 1792, 128 x 128 to 3584.
+@pytest.mark.parametrize("frames", [160, 161, 480, 481, 960, 961, 1792, 1793, 3584, 3585])
+def test_qformer_pool_frames_around_tile_widths(frames):
+    test_qformer_pool_frame_counts(frames)
+
+
 def test_qformer_pool_argument_errors():
     from paper_2603_11243_amd.binding import Context, SsdError
     ctx = Context()
