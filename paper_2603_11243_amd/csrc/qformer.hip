@@ -49,56 +49,101 @@ void launch_qformer_fold(const uint16_t* q_proj, const uint16_t* w_k, const uint
                        d_enc, w_cat);
 }
 
-// One workgroup per window.  Scores of the window's frames go through LDS, one thread normalises one
+// One workgroup per window.  Scores of the window's frames go through LDS, four threads normalise one
 // (query, head) column over the frames, then every thread owns four consecutive value columns (one 8-byte load
 // per frame, whole rows coalesced) and accumulates their n_q weighted sums over the frames.
+// A chain of loads, two barriers and sums with little on the CU beside it: the first 16 frames' values are requested with the scores, and the
+// softmax of a column is four threads' work.  17 windows 7.5 -> 5.4 us, 350 windows 7.9 -> 6.5 (values loaded in the loop, a thread a column).
 struct QWindowList {
     const QWindow* w;
 };
 template <int NQ, class Wins>
 __global__ void __launch_bounds__(256) qformer_pool_kernel(const float* __restrict__ scores, const f16_t* __restrict__ vals,
                                                            Wins wins, int n_heads, int d_h, bf16_t* __restrict__ o) {
-    __shared__ float p_s[QF_SCORE_COLS][QF_MAX_WINDOW + 1];
+    constexpr int AHEAD = 16, PER = QF_MAX_WINDOW / 4;       // PER: frames of a thread in the two steps before the sums
+    static_assert(QF_SCORE_COLS == 64, "a wavefront reads the scores of a frame, four threads take a column");
+    __shared__ __align__(16) float p_s[QF_SCORE_COLS][QF_MAX_WINDOW + 4];
     const QWindow w = wins.w[blockIdx.x];
-    const int n_pairs = NQ * n_heads;
+    const int n = w.n_frames, n_pairs = NQ * n_heads;
     const float* sbase = scores + (int64_t)w.frame0 * QF_SCORE_COLS;
-    for (int i = threadIdx.x; i < w.n_frames * QF_SCORE_COLS; i += 256)        // the window's scores are one contiguous piece
-        p_s[i % QF_SCORE_COLS][i / QF_SCORE_COLS] = sbase[i];
+    const f16_t* vbase = vals + (int64_t)w.frame0 * d_h;
+    float s_reg[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int t = threadIdx.x / 64 + 4 * k;
+        s_reg[k] = t < n ? sbase[t * QF_SCORE_COLS + threadIdx.x % 64] : 0.f;
+    }
+    uint2 v[AHEAD];
+    auto load = [&](int c, int t0) {
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t) v[t] = *reinterpret_cast<const uint2*>(vbase + (int64_t)min(t0 + t, n - 1) * d_h + c);
+    };
+    int c = 4 * threadIdx.x;
+    if (c < d_h) load(c, 0);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) p_s[threadIdx.x % 64][threadIdx.x / 64 + 4 * k] = s_reg[k];
     __syncthreads();
-    if ((int)threadIdx.x < n_pairs) {
-        float* p = p_s[threadIdx.x];
-        float m = -INFINITY;
-        for (int t = 0; t < w.n_frames; ++t) m = fmaxf(m, p[t]);
-        float sum = 0.f;
-        for (int t = 0; t < w.n_frames; ++t) { const float e = __expf(p[t] - m); p[t] = e; sum += e; }
+    if ((int)threadIdx.x / 4 < n_pairs) {
+        float* p = p_s[threadIdx.x / 4] + threadIdx.x % 4;
+        float e[PER], m = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            e[k] = (int)threadIdx.x % 4 + 4 * k < n ? p[4 * k] : -INFINITY;
+            m = fmaxf(m, e[k]);
+        }
+        m = fmaxf(m, __shfl_xor(m, 1));
+        m = fmaxf(m, __shfl_xor(m, 2));
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            e[k] = __expf(e[k] - m);
+            sum += (int)threadIdx.x % 4 + 4 * k < n ? e[k] : 0.f;
+        }
+        sum += __shfl_xor(sum, 1);
+        sum += __shfl_xor(sum, 2);
         const float inv = 1.0f / sum;
-        for (int t = 0; t < w.n_frames; ++t) p[t] *= inv;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) p[4 * k] = e[k] * inv;
     }
     __syncthreads();
     const int dh = d_h / n_heads;                                              // a multiple of 4: four columns share a head
-    const f16_t* vbase = vals + (int64_t)w.frame0 * d_h;
-    for (int c = 4 * threadIdx.x; c < d_h; c += 1024) {
+    while (c < d_h) {
         const int h = c / dh;
         float acc[NQ][4];
 #pragma unroll
         for (int j = 0; j < NQ; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[j][e] = 0.f;
-        for (int t = 0; t < w.n_frames; ++t) {
-            const uint2 raw = *reinterpret_cast<const uint2*>(vbase + (int64_t)t * d_h + c);
-            const float v[4] = {f16_to_f32((f16_t)(raw.x & 0xffffu)), f16_to_f32((f16_t)(raw.x >> 16)),
-                                f16_to_f32((f16_t)(raw.y & 0xffffu)), f16_to_f32((f16_t)(raw.y >> 16))};
+        for (int t0 = 0;;) {
 #pragma unroll
-            for (int j = 0; j < NQ; ++j) {
-                const float p = p_s[j * n_heads + h][t];
+            for (int t4 = 0; t4 < AHEAD; t4 += 4) {
+                if (t0 + t4 >= n) break;
+                float4 p4[NQ];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(p, v[e], acc[j][e]);
+                for (int j = 0; j < NQ; ++j) p4[j] = *reinterpret_cast<const float4*>(&p_s[j * n_heads + h][t0 + t4]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (t0 + t4 + u >= n) break;
+                    const uint2 raw = v[t4 + u];
+                    const float x[4] = {f16_to_f32((f16_t)(raw.x & 0xffffu)), f16_to_f32((f16_t)(raw.x >> 16)),
+                                        f16_to_f32((f16_t)(raw.y & 0xffffu)), f16_to_f32((f16_t)(raw.y >> 16))};
+#pragma unroll
+                    for (int j = 0; j < NQ; ++j) {
+                        const float p = u == 0 ? p4[j].x : u == 1 ? p4[j].y : u == 2 ? p4[j].z : p4[j].w;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(p, x[e], acc[j][e]);
+                    }
+                }
             }
+            t0 += AHEAD;
+            if (t0 >= n) break;
+            load(c, t0);
         }
 #pragma unroll
         for (int j = 0; j < NQ; ++j)
             *reinterpret_cast<uint2*>(o + ((int64_t)blockIdx.x * NQ + j) * d_h + c) =
                 make_uint2(pack_bf16x2(acc[j][0], acc[j][1]), pack_bf16x2(acc[j][2], acc[j][3]));
+        c += 1024;
+        if (c < d_h) load(c, 0);
     }
 }
 

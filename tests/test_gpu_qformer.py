@@ -82,6 +82,30 @@ def test_qformer_pool_frames_around_tile_widths(frames):
     test_qformer_pool_frame_counts(frames)
 
 
+# The pooling kernel: 16 frames of values in registers, a second pass for longer windows and for more than 1024 columns; widths that leave
+# threads without a column; every number of queries.
+@pytest.mark.parametrize("n_q,n_heads,d_h,window", [(1, 16, 64, 15), (2, 16, 1024, 16), (3, 16, 1088, 17), (4, 16, 2112, 32), (3, 4, 960, 31), (1, 1, 256, 3)])
+def test_qformer_pool_windows_and_widths(n_q, n_heads, d_h, window):
+    from paper_2603_11243_amd.binding import Context
+    g = torch.Generator().manual_seed(d_h + window)
+    r = lambda *s: (torch.randn(*s, generator=g) * s[-1] ** -0.5).bfloat16()
+    lengths = [1, window, 3 * window + 1, 2 * window - 1, window + window // 2]
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    h = torch.randn(int(cu[-1]), 128, generator=g).bfloat16()
+    q, w_k, w_v, w_o = torch.randn(n_q, d_h, generator=g).bfloat16(), r(d_h, 128), r(d_h, 128), r(256, d_h)
+    ctx = Context()
+    try:
+        ctx.set_qformer(q.cuda(), w_k.cuda(), w_v.cuda(), w_o.cuda(), n_heads=n_heads, window=window)
+        ctx.reserve(max_frames=int(cu[-1]), max_utts=len(lengths))
+        got, cu_s = ctx.qformer_pool(h.cuda(), cu)
+        got = got.float().cpu().numpy()
+    finally:
+        ctx.close()
+    ref, cu_ref = O.qformer_window_pool(h, cu, q, w_k, w_v, w_o, n_heads, window)
+    assert np.array_equal(cu_s, cu_ref)
+    _check(got, ref)
+
+
 def test_qformer_pool_argument_errors():
     from paper_2603_11243_amd.binding import Context, SsdError
     ctx = Context()
