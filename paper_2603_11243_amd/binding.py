@@ -125,11 +125,13 @@ def lib() -> C.CDLL:
     return _lib
 
 
+# What a small call costs is mostly the host: the arguments below are plain ints and bytes, which the argtypes take as pointers (of a gate
+# call's 8 us of Python 1.1 went to one array's .ctypes and 0.7 to c_void_p objects; bytes of 1025 prefix sums are copied in 0.2).
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous()
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _host_i32(a: Sequence[int]) -> np.ndarray:
@@ -259,7 +261,7 @@ class Context:
             if want_frames:
                 out["frame_entropy"] = torch.empty(n_rows, dtype=torch.float32, device=dev)
                 out["frame_argmax"] = torch.empty(n_rows, dtype=torch.int32, device=dev)
-        self._check(self._lib.ctc_gate(self._h, _ptr(logits), _DTYPE_CODE[logits.dtype], cu.ctypes.data, B, V,
+        self._check(self._lib.ctc_gate(self._h, _ptr(logits), _DTYPE_CODE[logits.dtype], cu.tobytes(), B, V,
                                        blank_id, tau_ctc, _ptr(out.get("frame_entropy")),
                                        _ptr(out.get("frame_argmax")), _ptr(out["max_entropy"]),
                                        _ptr(out["gate_pass"]), _ptr(out["draft_ctc"]), _ptr(out["draft_len"])))
@@ -291,7 +293,7 @@ class Context:
         if want_frames:
             out["frame_entropy"] = torch.empty(n_rows, dtype=torch.float32, device=dev)
             out["frame_argmax"] = torch.empty(n_rows, dtype=torch.int32, device=dev)
-        self._check(self._lib.ctc_head_gate(self._h, _ptr(enc_h), cu.ctypes.data, B, blank_id, tau_ctc,
+        self._check(self._lib.ctc_head_gate(self._h, _ptr(enc_h), cu.tobytes(), B, blank_id, tau_ctc,
                                             _ptr(out.get("frame_entropy")), _ptr(out.get("frame_argmax")),
                                             _ptr(out["max_entropy"]), _ptr(out["gate_pass"]),
                                             _ptr(out["draft_ctc"]), _ptr(out["draft_len"])))
@@ -318,8 +320,8 @@ class Context:
         cso, cpo, cdo = (np.empty(n + 1, dtype=np.int32) for _ in range(3))
         V = 0 if ctc_to_llm is None else int(ctc_to_llm.numel())
         self._check(self._lib.ssd_select_unconfident(
-            self._h, B, n, sel.ctypes.data, cuf.ctypes.data, dl.ctypes.data, _ptr(draft_ctc), _ptr(ctc_to_llm), V,
-            _ptr(speech_all), cs.ctypes.data, _ptr(prompt_all), cp.ctypes.data, d, _DTYPE_CODE[sdt],
+            self._h, B, n, sel.tobytes(), cuf.tobytes(), dl.tobytes(), _ptr(draft_ctc), _ptr(ctc_to_llm), V,
+            _ptr(speech_all), cs.tobytes(), _ptr(prompt_all), cp.tobytes(), d, _DTYPE_CODE[sdt],
             _ptr(out["speech"]) if nS else None, _ptr(out["prompt"]) if nP else None, _ptr(out["draft_ids"]) if nU else None,
             cso.ctypes.data, cpo.ctypes.data, cdo.ctypes.data))
         return {"speech": out["speech"][:nS], "prompt": out["prompt"][:nP], "draft_ids": out["draft_ids"][:nU],
@@ -330,7 +332,7 @@ class Context:
         ix = _host_i32(idx)
         if out is None:
             out = torch.empty(len(ix), dtype=torch.int32, device=self.device)
-        self._check(self._lib.ssd_gather_i32(self._h, _ptr(src), ix.ctypes.data, len(ix), _ptr(out)))
+        self._check(self._lib.ssd_gather_i32(self._h, _ptr(src), ix.tobytes(), len(ix), _ptr(out)))
         return out
 
     def set_qformer(self, q_proj: torch.Tensor, w_k: torch.Tensor, w_v: torch.Tensor, w_o: torch.Tensor, n_heads: int,
@@ -352,11 +354,11 @@ class Context:
             raise ValueError("enc_h must be a contiguous bfloat16 tensor with d_enc columns")
         cu = _host_i32(cu_frames)
         B = len(cu) - 1
-        n_rows = int(n_q * sum(-(-int(t) // window) for t in np.diff(cu)))
+        n_rows = n_q * int((-(-np.diff(cu) // window)).sum())
         if out is None:
             out = torch.empty((n_rows, d_out), dtype=torch.bfloat16, device=self.device)
         cu_s = np.empty(B + 1, dtype=np.int32)
-        self._check(self._lib.qformer_pool(self._h, _ptr(enc_h), cu.ctypes.data, B, _ptr(out), cu_s.ctypes.data))
+        self._check(self._lib.qformer_pool(self._h, _ptr(enc_h), cu.tobytes(), B, _ptr(out), cu_s.ctypes.data))
         return out[:n_rows], cu_s
 
     def verify_forward(self, speech_emb: torch.Tensor, cu_speech, prompt_ids: torch.Tensor, cu_prompt,
@@ -368,13 +370,13 @@ class Context:
         if out is None:
             out = torch.empty((int(cd[-1]), self.cfg.d_model), dtype=self.act_dtype, device=self.device)
         if kv_start is None:
-            self._check(self._lib.verify_forward(self._h, _ptr(speech_emb), cs.ctypes.data, _ptr(prompt_ids),
-                                                 cp.ctypes.data, _ptr(draft_ids), cd.ctypes.data, Bv, _ptr(out)))
+            self._check(self._lib.verify_forward(self._h, _ptr(speech_emb), cs.tobytes(), _ptr(prompt_ids),
+                                                 cp.tobytes(), _ptr(draft_ids), cd.tobytes(), Bv, _ptr(out)))
         else:
             ks = _host_i32(kv_start)
-            self._check(self._lib.verify_forward_kv(self._h, _ptr(speech_emb), cs.ctypes.data, _ptr(prompt_ids),
-                                                    cp.ctypes.data, _ptr(draft_ids), cd.ctypes.data, Bv,
-                                                    ks.ctypes.data, _ptr(out)))
+            self._check(self._lib.verify_forward_kv(self._h, _ptr(speech_emb), cs.tobytes(), _ptr(prompt_ids),
+                                                    cp.tobytes(), _ptr(draft_ids), cd.tobytes(), Bv,
+                                                    ks.tobytes(), _ptr(out)))
         return out
 
     def gate_grid(self, max_entropy: torch.Tensor, taus_ctc) -> torch.Tensor:
@@ -390,7 +392,7 @@ class Context:
         Bv = len(cd) - 1
         out = {"accept_len": torch.empty((len(t), Bv), dtype=torch.int32, device=self.device),
                "all_accepted": torch.empty((len(t), Bv), dtype=torch.uint8, device=self.device)}
-        self._check(self._lib.ssd_accept_grid(self._h, _ptr(draft_logp), cd.ctypes.data, Bv, t.ctypes.data, len(t),
+        self._check(self._lib.ssd_accept_grid(self._h, _ptr(draft_logp), cd.tobytes(), Bv, t.ctypes.data, len(t),
                                               _ptr(out["accept_len"]), _ptr(out["all_accepted"])))
         return out
 
@@ -406,7 +408,7 @@ class Context:
         Br = len(ks)
         if out is None:
             out = torch.empty((n_steps, Br), dtype=torch.int32, device=self.device)
-        self._check(self._lib.ar_fallback(self._h, Br, ks.ctypes.data, cl.ctypes.data, _ptr(first_tok), n_steps, _ptr(out)))
+        self._check(self._lib.ar_fallback(self._h, Br, ks.tobytes(), cl.tobytes(), _ptr(first_tok), n_steps, _ptr(out)))
         return out
 
     def accept_prefix(self, h_verify: torch.Tensor, draft_ids: torch.Tensor, cu_draft, tau_slm: float,
@@ -420,7 +422,7 @@ class Context:
                    "all_accepted": torch.empty(max(Bv, 0), dtype=torch.uint8, device=dev)}
             if want_greedy:
                 out["greedy_tok"] = torch.empty(Mv, dtype=torch.int32, device=dev)
-        self._check(self._lib.accept_prefix(self._h, _ptr(h_verify), _ptr(draft_ids), cd.ctypes.data, Bv, tau_slm,
+        self._check(self._lib.accept_prefix(self._h, _ptr(h_verify), _ptr(draft_ids), cd.tobytes(), Bv, tau_slm,
                                             _ptr(out["draft_logp"]), _ptr(out["accept_len"]),
                                             _ptr(out["all_accepted"]), _ptr(out.get("greedy_tok"))))
         return out
@@ -437,7 +439,7 @@ def ctc_gate_noalloc(logits: torch.Tensor, cu_frames_dev: torch.Tensor, blank_id
     B, n_frames, V = int(cu_frames_dev.numel()) - 1, int(logits.shape[0]), int(logits.shape[1])
     assert cu_frames_dev.dtype == torch.int32
     err = C.create_string_buffer(256)
-    rc = lib().ctc_gate_noalloc(C.c_void_p(st.cuda_stream), _ptr(logits), _DTYPE_CODE[logits.dtype], _ptr(cu_frames_dev), B,
+    rc = lib().ctc_gate_noalloc(st.cuda_stream, _ptr(logits), _DTYPE_CODE[logits.dtype], _ptr(cu_frames_dev), B,
                                 n_frames, V, blank_id, tau_ctc, _ptr(out["max_entropy"]), _ptr(out["gate_pass"]),
                                 _ptr(out["draft_ctc"]), _ptr(out["draft_len"]), err, len(err))
     if rc != 0:
