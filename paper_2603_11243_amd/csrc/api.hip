@@ -910,13 +910,13 @@ int ctc_head_gate(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int
         const int64_t chunk = ((int64_t)0xffffffffu / ((int64_t)d * 2)) / 256 * 256;
         for (int64_t r0 = 0; r0 < n_rows; r0 += chunk) {
             const int rows = (int)std::min<int64_t>(chunk, n_rows - r0);
-            launch_ctc_head_partials(static_cast<const uint16_t*>(enc_h) + r0 * d, ctx->head_w, ctx->head_bias, rows, d, V, ctx->head_V_pad, part, ctx->stream);
-            if (rows == n_rows && launch_ctc_head_merge_gate(part, V, rows, cu_frames, B, blank_id, tau_ctc, frame_entropy, frame_argmax, max_entropy,
+            const int groups = launch_ctc_head_partials(static_cast<const uint16_t*>(enc_h) + r0 * d, ctx->head_w, ctx->head_bias, rows, d, V, ctx->head_V_pad, part, ctx->stream);
+            if (rows == n_rows && launch_ctc_head_merge_gate(part, groups, rows, cu_frames, B, blank_id, tau_ctc, frame_entropy, frame_argmax, max_entropy,
                                                              gate_pass, draft_ctc, draft_len, ctx->stream)) {
                 HIP_TRY(ctx, hipGetLastError());
                 return SSD_OK;
             }
-            launch_ctc_head_merge(part, V, rows, H + r0, arg + r0, ctx->stream);
+            launch_ctc_head_merge(part, groups, rows, H + r0, arg + r0, ctx->stream);
         }
         const int rc = gate_utterances_of(ctx, H, arg, cu_frames, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len);
         if (rc != SSD_OK) return rc;

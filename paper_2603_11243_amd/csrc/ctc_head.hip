@@ -7,9 +7,9 @@
 // four consecutive symbols of a 16x16 block: the per-frame reductions over symbols run inside the lane, with two
 // exchanges between the 16-lane groups at the end.  Every wavefront reduces its [frames x 64 symbols] slab to
 //     m = max_v z,  arg = lowest v with z = m,  S = sum_v e^(z-m),  W = sum_v e^(z-m) (z-m)
-// per frame (16 bytes), and a second small kernel merges the symbol groups of a frame (and mostly goes on to the gate's decisions) into
+// per frame (16 bytes; slabs of 96 symbols in the widest tiles), and a second small kernel merges the symbol groups of a frame (and mostly goes on to the gate's decisions) into
 //     H_t = log S - W / S   ( = -sum_v p log p for p = softmax(z) ),   argmax_t.
-// Written per frame: 16 bytes per group of 64 symbols instead of 2 x 2 bytes per symbol (a store of
+// Written per frame: 16 bytes per group of 64 or 96 symbols instead of 2 x 2 bytes per symbol (a store of
 // bf16 scores and the gate's load of them).  Operands are the stored bf16 values (bf16 MFMA, exact
 // products, fp32 accumulation); the accumulators start at the bias, and symbols added as padding
 // have zero weights and bias -inf, i.e. probability zero.
@@ -21,28 +21,28 @@
 
 namespace ssd {
 
-constexpr int CH_BN = 128;          // symbols per tile
-constexpr int CH_GROUP = 64;        // symbols per partial: the width of a wavefront's tile
+constexpr int CH_BN = 128, CH_WIDE = 384;    // symbols per tile
+constexpr int CH_GROUP = 64;        // fewest symbols per partial: the width of a wavefront's tile, 96 in the wide tiles
 constexpr int CH_PAD = 128;         // symbol count is padded to a multiple of this
 
-// BM frames x CH_BN symbols on v_mfma_f32_16x16x32_bf16 with transposed blocks: a lane has one frame (lane % 16 of a block) and four
+// BM frames x BN symbols on v_mfma_f32_16x16x32_bf16 with transposed blocks: a lane has one frame (lane % 16 of a block) and four
 // consecutive symbols, the four 16-lane groups of a wavefront share a frame.
-template <int BM, int WM>
-__global__ void __launch_bounds__(128 * WM)
+template <int BM, int BN, int WM, int WN>
+__global__ void __launch_bounds__(64 * WM * WN)
 ctc_head_partials_kernel(const uint16_t* __restrict__ enc_h, const uint16_t* __restrict__ w_pad,
                          const float* __restrict__ bias_pad, int n_rows, int d_enc, int V, int V_pad,
                          float4* __restrict__ part) {
-    using Tile = GemmTile16<BM, CH_BN, WM, 2, true, true>;
+    using Tile = GemmTile16<BM, BN, WM, WN, true, true>;
     using L = Layout16T;
-    static_assert(Tile::WTN == CH_GROUP, "one partial per wave tile of 64 symbols");
+    static_assert(Tile::WTN >= CH_GROUP, "one partial per wave tile");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     // symbol tiles vary fastest, and the tiles of one slab of frames run on one XCD (one fetch of the slab)
-    const int tiles_v = V_pad / CH_BN;
+    const int tiles_v = V_pad / BN;
     const int v = xcd_contiguous_index(blockIdx.x, gridDim.x);
     const int tv = v % tiles_v, tf = v / tiles_v;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int wm = wave / 2, wn = wave % 2;
-    const int sym0 = tv * CH_BN + wn * Tile::WTN;            // first symbol of this wavefront
+    const int wm = wave / WN, wn = wave % WN;
+    const int sym0 = tv * BN + wn * Tile::WTN;            // first symbol of this wavefront
     const int frame0 = tf * BM + wm * Tile::WTM;
 
     f32x4_t acc[Tile::TM][Tile::TN];
@@ -52,11 +52,11 @@ ctc_head_partials_kernel(const uint16_t* __restrict__ enc_h, const uint16_t* __r
 #pragma unroll
         for (int i = 0; i < Tile::TM; ++i) acc[i][j] = b4;
     }
-    Tile::run(reinterpret_cast<const f16_t*>(enc_h), reinterpret_cast<const f16_t*>(w_pad), n_rows, d_enc, tf * BM, tv * CH_BN, 0,
+    Tile::run(reinterpret_cast<const f16_t*>(enc_h), reinterpret_cast<const f16_t*>(w_pad), n_rows, d_enc, tf * BM, tv * BN, 0,
               d_enc / GEMM_BK, smem_raw, acc);
 
     if (sym0 >= V) return;                                   // slab made of padding symbols only
-    const int group = sym0 / CH_GROUP;
+    const int group = sym0 / Tile::WTN;
     constexpr float LOG2E = 1.4426950408889634f;
 #pragma unroll
     for (int i = 0; i < Tile::TM; ++i) {
@@ -168,22 +168,23 @@ static void launch_merge(const float4* part, int n_groups, int n_rows, const CU&
 #define SSD_MERGE(NG) do { \
         if (longest <= MERGE_FEW_FRAMES) hipLaunchKernelGGL((ctc_head_utterances_kernel<NG, 4, 2, CU>), dim3(B), dim3(256), 0, st, part, n_groups, n_rows, cu, blank, tau, out); \
         else hipLaunchKernelGGL((ctc_head_utterances_kernel<NG, 16, 1, CU>), dim3(B), dim3(1024), 0, st, part, n_groups, n_rows, cu, blank, tau, out); } while (0)
-    if (n_groups <= 2) SSD_MERGE(2); else if (n_groups <= 6) SSD_MERGE(6); else SSD_MERGE(MERGE_MAX_GROUPS);
+    if (n_groups <= 2) SSD_MERGE(2); else if (n_groups <= 4) SSD_MERGE(4); else if (n_groups <= 6) SSD_MERGE(6); else SSD_MERGE(MERGE_MAX_GROUPS);
 #undef SSD_MERGE
 }
 
-template <int BM, int WM>
-static void launch_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc,
-                            int V, int V_pad, float4* part, hipStream_t st) {
-    constexpr size_t lds = GemmTile16<BM, CH_BN, WM, 2, true, true>::LDS_BYTES;
-    auto kern = ctc_head_partials_kernel<BM, WM>;
+template <int BM, int BN, int WM, int WN>
+static int launch_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc,
+                           int V, int V_pad, float4* part, hipStream_t st) {
+    using Tile = GemmTile16<BM, BN, WM, WN, true, true>;
+    auto kern = ctc_head_partials_kernel<BM, BN, WM, WN>;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)Tile::LDS_BYTES);
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3((n_rows + BM - 1) / BM * (V_pad / CH_BN)), dim3(128 * WM), lds, st, enc_h, w_pad, bias_pad,
+    hipLaunchKernelGGL(kern, dim3((n_rows + BM - 1) / BM * (V_pad / BN)), dim3(64 * WM * WN), Tile::LDS_BYTES, st, enc_h, w_pad, bias_pad,
                        n_rows, d_enc, V, V_pad, part);
+    return (V + Tile::WTN - 1) / Tile::WTN;
 }
 
 int ctc_head_groups(int V) { return (V + CH_GROUP - 1) / CH_GROUP; }
@@ -191,23 +192,40 @@ int ctc_head_padded(int V) { return (V + CH_PAD - 1) / CH_PAD * CH_PAD; }
 
 // enc_h [n_rows, d_enc] bf16; w_pad [V_pad, d_enc] bf16 with zero rows beyond V; bias_pad [V_pad] fp32, -inf
 // beyond V; part: ctc_head_groups(V) * n_rows float4.  n_rows * d_enc * 2 must stay below 4 GiB.
-void launch_ctc_head_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc, int V,
-                              int V_pad, float4* part, hipStream_t st) {
-    if (n_rows <= 0) return;
+int launch_ctc_head_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc, int V,
+                             int V_pad, float4* part, hipStream_t st) {
+    if (n_rows <= 0) return 0;
+    auto tiles = [&](int bm, int bn) { return (int64_t)((n_rows + bm - 1) / bm) * (V_pad / bn); };
+#define SSD_HEAD(BM, BN, WM, WN) return launch_partials<BM, BN, WM, WN>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st)
     // The smallest tile of frames that runs in one round: in 256-frame tiles a few thousand frames leave most CUs idle.  Front end of 275 /
-    // 4100 frames 42.7 -> 37.5 / 60.2 -> 50.3 us (mostly this kernel); 198 K frames, 256-frame tiles: 188 -> 173 us with the 16x16x32
-    // instruction instead of 32x32x16.
-    if ((int64_t)((n_rows + 63) / 64) * (V_pad / CH_BN) <= 256) launch_partials<64, 2>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
-    else if ((int64_t)((n_rows + 127) / 128) * (V_pad / CH_BN) <= 256) launch_partials<128, 4>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
-    else launch_partials<256, 4>(enc_h, w_pad, bias_pad, n_rows, d_enc, V, V_pad, part, st);
+    // 4100 frames 42.7 -> 37.5 / 60.2 -> 50.3 us (mostly this kernel).
+    if (tiles(64, CH_BN) <= 256) SSD_HEAD(64, CH_BN, 2, 2);
+    if (tiles(128, CH_BN) <= 256) SSD_HEAD(128, CH_BN, 4, 2);
+    // More: 256 x 128 tiles fetch the states three times for the paper's 348 symbols and read two LDS bytes for every three that tiles of
+    // all 384 columns do.  Those are up to 192 frames high (242 registers) and come in three heights, whose rounds over the CUs
+    // take these us at K = 1024.  us of the launch, 256 x 128 / the height that wins: 22 K frames 32.6 / 24.0 (128), 40 K 35.1 / 31.8 (160),
+    // 45 K 49.1 / 34.5 (192), 64 K 55.8 / 48.0 (128), 90 K 85.2 / 66.8 (192), 120 K 110 / 87.0 (160), 140 K 138 / 106 (192), 160 K 156 / 137
+    // (160), 198 K 179 / 168 (160); up to 21760 frames, one round, 19.2 / 23.9.
+    constexpr double NARROW = 18.5, H128 = 26.5, H160 = 32, H192 = 35;
+    auto cost = [&](int bm, int bn, double round) { return (double)((tiles(bm, bn) + 255) / 256) * round; };
+    if (V_pad % CH_WIDE == 0) {
+        const double c128 = cost(128, CH_WIDE, H128), c160 = cost(160, CH_WIDE, H160), c192 = cost(192, CH_WIDE, H192);
+        const double least = std::min({c128, c160, c192});
+        if (least < cost(256, CH_BN, NARROW)) {
+            if (least == c192) SSD_HEAD(192, CH_WIDE, 2, 4);
+            if (least == c160) SSD_HEAD(160, CH_WIDE, 2, 4);
+            SSD_HEAD(128, CH_WIDE, 2, 4);
+        }
+    }
+    SSD_HEAD(256, CH_BN, 4, 2);
+#undef SSD_HEAD
 }
-void launch_ctc_head_merge(const float4* part, int V, int n_rows, float* H, int32_t* arg, hipStream_t st) {
+void launch_ctc_head_merge(const float4* part, int n_groups, int n_rows, float* H, int32_t* arg, hipStream_t st) {
     if (n_rows <= 0) return;
-    hipLaunchKernelGGL(ctc_head_finalize_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, part, ctc_head_groups(V), n_rows, H, arg);
+    hipLaunchKernelGGL(ctc_head_finalize_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, st, part, n_groups, n_rows, H, arg);
 }
-bool launch_ctc_head_merge_gate(const float4* part, int V, int n_rows, const int32_t* cu_frames, int B, int blank, float tau, float* H, int32_t* arg,
+bool launch_ctc_head_merge_gate(const float4* part, int n_groups, int n_rows, const int32_t* cu_frames, int B, int blank, float tau, float* H, int32_t* arg,
                                 float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len, hipStream_t st) {
-    const int n_groups = ctc_head_groups(V);
     int longest = 0;
     for (int b = 0; b < B; ++b) longest = std::max(longest, cu_frames[b + 1] - cu_frames[b]);
     if (n_groups > MERGE_MAX_GROUPS || longest > MERGE_MAX_FRAMES) return false;

@@ -61,11 +61,12 @@ int ctc_head_padded(int V);      // symbol count after padding
 void launch_ctc_head_pack(const uint16_t* w, const float* bias, int V, int V_pad, int d_enc, uint16_t* w_pad,
                           float* bias_pad, hipStream_t st);
 // part: ctc_head_groups(V) * n_rows float4 of scratch; n_rows * d_enc * 2 bytes must stay below 4 GiB
-void launch_ctc_head_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc, int V,
-                              int V_pad, float4* part, hipStream_t st);
-void launch_ctc_head_merge(const float4* part, int V, int n_rows, float* H, int32_t* arg, hipStream_t st);
+// returns the number of symbol groups it left partials of, at most ctc_head_groups(V)
+int launch_ctc_head_partials(const uint16_t* enc_h, const uint16_t* w_pad, const float* bias_pad, int n_rows, int d_enc, int V,
+                             int V_pad, float4* part, hipStream_t st);
+void launch_ctc_head_merge(const float4* part, int n_groups, int n_rows, float* H, int32_t* arg, hipStream_t st);
 // the merge with the second half of the gate, H and arg if they are wanted; false: the symbols, the longest utterance or the batch are too many
-bool launch_ctc_head_merge_gate(const float4* part, int V, int n_rows, const int32_t* cu_frames, int B, int blank, float tau, float* H, int32_t* arg,
+bool launch_ctc_head_merge_gate(const float4* part, int n_groups, int n_rows, const int32_t* cu_frames, int B, int blank, float tau, float* H, int32_t* arg,
                                 float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len, hipStream_t st);
 
 // ---- qformer.hip: windowed cross-attention of the projector (Sec. 3.1)

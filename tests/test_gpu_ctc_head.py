@@ -117,6 +117,16 @@ def test_head_gate_frames_around_tile_heights(ctx, n):
     _run_and_compare(ctx, enc, w, torch.randn(348, generator=g) * 0.1, np.unique([0, n // 3, n // 2, n]), 0, 2.0)
 
 
+# Tiles of 384 symbols in four groups of 96, from 21761 frames on: 128, 160, 192 frames high and 128 again in two rounds, a frame beyond a
+# round each; symbol counts that leave the last group empty, partly or completely filled, and two tiles of symbols.
+@pytest.mark.parametrize("V,n", [(348, 21761), (348, 32769), (348, 40961), (348, 49153), (257, 22000), (289, 22000), (384, 22000), (700, 11000), (768, 23000)])
+def test_head_gate_wide_tiles(ctx, V, n):
+    g = torch.Generator().manual_seed(n + V)
+    enc = torch.randn(n, 128, generator=g).to(torch.bfloat16)
+    w = (torch.randn(V, 128, generator=g) / 8).to(torch.bfloat16)
+    _run_and_compare(ctx, enc, w, torch.randn(V, generator=g) * 0.1, np.append(np.arange(0, n, 700), n), 0, 2.0)
+
+
 # Merge and decisions in one launch: up to 8 groups of 64 symbols and 2048 frames an utterance, up to 512 in four wavefronts of two frames a
 # lane, prefix sums of up to 256 and up to 1280 utterances as arguments; beyond, launches of their own.
 @pytest.mark.parametrize("V,lengths", [(64, [512, 1, 256]), (100, [1, 255, 257]), (348, [513, 64]), (384, [3, 1024]), (385, [1025, 128, 129]), (512, [2048]),
