@@ -739,11 +739,14 @@ static bool try_launch_stream(const f16_t* A, const void* Ws, int M, int N, int 
 //   K splits, at most 64 rows: down 9.8 / 12.6 and 12.9 / 16.7, O 5.4 / 5.9 and 7.3 / 8.9, QKV 6.7 / 8.5 and 9.6 / 12.4
 //   K splits, 65..96 rows: down 11.6 / 13.2 and 15.4 / 18.1 (16 and 25 K steps per workgroup), QKV 3072 11.7 / 13.0 (16),
 //     but O 7.2 / 6.3 and 9.2 / 9.4 (4 and 9), QKV 2048 8.9 / 8.7 (8): short K ranges don't pay for adding three row blocks
+//     (these with two wavefronts of three stages; four of two, from 8 K steps on, and two stages instead of three for whole sums:
+//     eight greedy steps, 3072 wide, 70 rows 22.35 -> 22.15 ms, 90 rows 23.52 -> 23.06, 2048 wide 13.20 -> 13.09 and 14.23 -> 13.88)
 //   K splits, 97..128 rows: never faster (O 8.1 / 6.8, down 13.5 / 14.0 and 17.7 / 17.7)
 //   whole QKV sums: the in-workgroup K split is faster (10.4 and 14.8 at 70 rows) while its row tiles of 32 give at most one
 //     workgroup per CU; with 320 of them (116 rows, 5120 columns) 27.5 against 17.5 here with two row tiles of 64
-// (The limits of 12 K steps and 96 column tiles lie between these two widths' figures; no other width was measured.)
-// Two wavefronts per workgroup rather than four: half of the partial products to be added at the end (O at 48 rows 6.8 -> 5.4).
+// (The limits of 8 K steps and 96 column tiles lie between these two widths' figures; no other width was measured.)
+// Two wavefronts per workgroup rather than four: half of the partial products to be added at the end (O at 48 rows 6.8 -> 5.4); at 65..96
+// rows what a step has in flight counts more.
 template <class Epi>
 static bool try_launch_stream_rows(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
     if (M <= STREAM_MAX_ROWS || M > SKINNY_MAX_ROWS || !stream_layout_supported(N, K) || (int64_t)N * K * 2 >= (int64_t)1 << 31) return false;
@@ -751,7 +754,7 @@ static bool try_launch_stream_rows(const f16_t* A, const void* Ws, int M, int N,
     if constexpr (Epi::WANTS_SPLIT) {
         if (KT < 2 * splits) return false;                   // every wavefront needs a step
         if (M <= 64) launch_stream_rows<2, 2, 2>(A, Ws, M, N, K, splits, epi, st);
-        else if (M <= 96 && KT >= 12 * splits) launch_stream_rows<3, 2, 3>(A, Ws, M, N, K, splits, epi, st);
+        else if (M <= 96 && KT >= 8 * splits) launch_stream_rows<3, 4, 2>(A, Ws, M, N, K, splits, epi, st);
         else return false;
     } else {
         if (splits != 1 || KT < 4) return false;
@@ -760,7 +763,7 @@ static bool try_launch_stream_rows(const f16_t* A, const void* Ws, int M, int N,
             launch_stream_rows<2, 4, 4>(A, Ws, M, N, K, 1, epi, st);
         }
         else if (M <= 64) launch_stream_rows<2, 2, 4>(A, Ws, M, N, K, 1, epi, st);
-        else if (M <= 96) launch_stream_rows<3, 2, 3>(A, Ws, M, N, K, 1, epi, st);
+        else if (M <= 96) launch_stream_rows<3, 2, 2>(A, Ws, M, N, K, 1, epi, st);
         else launch_stream_rows<4, 2, 2>(A, Ws, M, N, K, 1, epi, st);
     }
     return true;
