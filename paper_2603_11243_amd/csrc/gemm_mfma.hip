@@ -689,9 +689,9 @@ static void launch_gemm16(const f16_t* A, const f16_t* W, int M, int N, int K, i
 // Register-streaming kernel for at most 32 rows (gemm_stream.h); it reads the stream-layout copy of the
 // weights.  A workgroup takes K/64/splits steps of 64; they must divide evenly over 8 or 4 wavefronts.
 constexpr int STREAM_MAX_ROWS = 32;
-template <int NW, int DEPTH, class Epi>
-static void launch_stream_cfg(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
-    auto kern = gemm_stream_kernel<NW, DEPTH, Epi::BF, Epi>;
+template <int NW, int DEPTH, int AQ, class Epi>
+static void launch_stream_pieces(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
+    auto kern = gemm_stream_kernel<NW, DEPTH, AQ, Epi::BF, Epi>;
     constexpr size_t lds = gemm_stream_lds_bytes<NW, DEPTH>();
     static bool attr_set = false;
     if (!attr_set) {
@@ -699,6 +699,16 @@ static void launch_stream_cfg(const f16_t* A, const void* Ws, int M, int N, int 
         attr_set = true;
     }
     hipLaunchKernelGGL(kern, dim3((N / 64) * splits), dim3(64 * NW), lds, st, A, static_cast<const u32x4_t*>(Ws), M, N, K, splits, epi);
+}
+// Loads of rows that do not exist take the address path of ones that do, and their outputs the time of the epilogue.  Eight greedy steps, 32
+// rows' worth / as many eights as there are: 2048 wide, 1 row 8.76 / 8.33 ms, 8 rows 9.29 / 8.82, 16 rows 9.62 / 9.34, 24 rows 10.03 / 9.83; 3072 wide, 2 rows 15.66 /
+// 14.75, 8 rows 16.17 / 15.39, 16 rows 16.45 / 16.09.
+template <int NW, int DEPTH, class Epi>
+static void launch_stream_cfg(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {
+    if (M <= 8) launch_stream_pieces<NW, DEPTH, 1>(A, Ws, M, N, K, splits, epi, st);
+    else if (M <= 16) launch_stream_pieces<NW, DEPTH, 2>(A, Ws, M, N, K, splits, epi, st);
+    else if (M <= 24) launch_stream_pieces<NW, DEPTH, 3>(A, Ws, M, N, K, splits, epi, st);
+    else launch_stream_pieces<NW, DEPTH, 4>(A, Ws, M, N, K, splits, epi, st);
 }
 template <int R, int NW, int D, class Epi>
 static void launch_stream_rows(const f16_t* A, const void* Ws, int M, int N, int K, int splits, const Epi& epi, hipStream_t st) {

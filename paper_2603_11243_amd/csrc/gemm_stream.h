@@ -38,11 +38,12 @@ constexpr size_t gemm_stream_lds_bytes() {
 // [j][r / 4][lane] float4 (512 of them), then the quarters r / 4 are summed in wavefront order and finished by different
 // wavefronts.  (One wavefront doing all of it was up to 2 us of a launch: 16 greedy steps at 27 rows 23.8 -> 22.3 ms,
 // verification of 116 rows 1.86 -> 1.76 ms.)
+template <int QUARTERS = 4>
 __device__ __forceinline__ void store_partial(float4* dst, const f32x16_t (&acc)[2], int lane) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int g = 0; g < QUARTERS; ++g)
             dst[(j * 4 + g) * 64 + lane] = make_float4(acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]);
 }
 template <int NW, class Epi>
@@ -63,7 +64,9 @@ __device__ __forceinline__ void finish_quarter(const float4* red, int stride, in
         epi.template operator()<1, 2, Layout32Quarter>(out, row0 + 8 * q, col0, M, lane);
 }
 
-template <int NW, int DEPTH, bool BF, class Epi>
+// AQ: pieces of eight rows that are loaded, summed and finished (M <= 8 AQ).  What LDS holds in the place of the others only reaches
+// accumulator rows that nobody reads.
+template <int NW, int DEPTH, int AQ, bool BF, class Epi>
 __global__ void __launch_bounds__(64 * NW)
 gemm_stream_kernel(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, int M, int N, int K, int splits, Epi epi) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -77,12 +80,12 @@ gemm_stream_kernel(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, 
     const int t_first = (split * NW + wave) * steps;
     unsigned char* my_lds = smem_raw + wave * WAVE_LDS;
 
-    // A: global -> LDS, four 1 KB instructions per K step (eight rows of 128 bytes each)
+    // A: global -> LDS, 1 KB instructions, AQ per K step (eight rows of 128 bytes each)
     const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(A);
     const int lrow = lane / 8, lslot = lane % 8;
-    unsigned a_off[4];
+    unsigned a_off[4];                                       // (an array of AQ makes the host compiler drop the kernel's stub without a word)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < AQ; ++q) {
         const int r = q * 8 + lrow;
         a_off[q] = (unsigned)min(r, M - 1) * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
     }
@@ -105,7 +108,7 @@ gemm_stream_kernel(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, 
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < AQ; ++q)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void_t*)(my_lds + d * 4096 + q * 1024), 16, a_off[q],
                                                          (t_first + t0 + d) * GEMM_ROW_BYTES, 0, 0);
         // keep the issue order A, then W: the wait below counts on it
@@ -134,9 +137,9 @@ gemm_stream_kernel(const f16_t* __restrict__ A, const u32x4_t* __restrict__ Ws, 
 
     // ---- add the NW partial products in wavefront order
     __syncthreads();                                         // every wavefront is done with its A region
-    store_partial(reinterpret_cast<float4*>(smem_raw) + wave * 512, acc, lane);
+    store_partial<AQ>(reinterpret_cast<float4*>(smem_raw) + wave * 512, acc, lane);
     __syncthreads();
-    for (int q = wave; q < 4; q += NW) finish_quarter<NW>(reinterpret_cast<const float4*>(smem_raw), 512, q, 0, tile * 64, M, lane, split, epi);
+    for (int q = wave; q < AQ; q += NW) finish_quarter<NW>(reinterpret_cast<const float4*>(smem_raw), 512, q, 0, tile * 64, M, lane, split, epi);
 }
 
 // The same product for more rows (33..128 and beyond): a workgroup owns 64 columns, 32 R rows and one K split; its NW

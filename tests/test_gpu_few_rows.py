@@ -137,6 +137,12 @@ def test_fallback_row_blocks(Br):
 
 # 768 columns are 12, 6 or 3 tiles per 128 rows: K splits of 128 x 64, 128 x 128 or 128 x 256 tiles over 12 and 50 K steps; QKV and
 # gate/up pass from 64 x 64 over 64 x 128 and 128 x 128 to the 256-wide tiles
+# pieces of eight rows in the register-streaming kernel
+@pytest.mark.parametrize("Br", [1, 7, 8, 9, 16, 17, 24, 25, 32])
+def test_fallback_pieces_of_eight_rows(Br):
+    test_fallback_row_blocks(Br)
+
+
 @pytest.mark.parametrize("M", [129, 256, 257, 500, 641, 1100, 1700])
 def test_verify_mid_rows(M):
     m = ModelCfg(2, 768, 6, 2, 128, 3200, 512, dtype="bf16")
