@@ -196,14 +196,17 @@ static void launch_lmhead_cfg(const f16_t* hv, const f16_t* w_lm, const int32_t*
         hipLaunchKernelGGL(kern_plain, dim3(tiles), dim3(64 * WM * WN), lds, st, hv, w_lm, targets, Mv, d, vocab, part_ms, tgt_logit, part_arg, descale);
 }
 
-// Tile by row count: up to 32 rows the whole job is streaming W_lm once (32 x 256 tile, four-stage
-// ring); up to 128 rows a 128 x 64 tile; otherwise the compute-bound 256 x 256 tile (lmhead_mfma16_kernel).
+// Tile by row count: up to 128 rows the job is streaming W_lm, by two workgroups a CU, one of which loads while the other reduces its
+// slab: up to 32 rows a 32 x 128 tile with a four-stage ring, up to 128 rows a 128 x 64 tile with three; otherwise the compute-bound 256 x
+// 256 tile (lmhead_mfma16_kernel).  us of a launch behind a large write, one workgroup a CU (32 x 256, four stages of 128 x 64) / two: vocabulary
+// 49152 of 2048, 4 rows 94 / 86, 27 rows 95 / 88, 40 rows 100 / 91, 128 rows 105 / 90; 100352 of 2048, 27 rows 141 / 142, 40 rows 171 / 146, 128 rows
+// 183 / 151; 49152 of 3072, 27 rows 115 / 114, 40 rows 121 / 114, 128 rows 133 / 121.
 template <bool BF>
 static void lmhead_impl(const uint16_t* hv, const uint16_t* w_lm, const int32_t* targets, int Mv, int d, int vocab,
                         float2* part_ms, float* tgt_logit, int2* part_arg, bool want_greedy, float descale,
                         hipStream_t st) {
-    if (Mv <= 32) launch_lmhead_cfg<32, 256, 1, 4, 4, BF>(hv, w_lm, targets, Mv, d, vocab, part_ms, tgt_logit, part_arg, want_greedy, descale, st);
-    else if (Mv <= 128) launch_lmhead_cfg<128, 64, 4, 1, 4, BF>(hv, w_lm, targets, Mv, d, vocab, part_ms, tgt_logit, part_arg, want_greedy, descale, st);
+    if (Mv <= 32) launch_lmhead_cfg<32, 128, 1, 2, 4, BF>(hv, w_lm, targets, Mv, d, vocab, part_ms, tgt_logit, part_arg, want_greedy, descale, st);
+    else if (Mv <= 128) launch_lmhead_cfg<128, 64, 4, 1, 3, BF>(hv, w_lm, targets, Mv, d, vocab, part_ms, tgt_logit, part_arg, want_greedy, descale, st);
     else {
         constexpr size_t lds = lmhead16_lds_bytes();
         static_assert(lds <= 160 * 1024, "LDS of a compute unit");
