@@ -1,7 +1,7 @@
 // Main loop of the big-tile GEMM on v_mfma_f32_16x16x32_f16:  acc[M,N] = A[M,K] * W[N,K]^T, fp32 accumulation.
 //
 // Same tiling, LDS ring and global -> LDS loads as gemm_core.h (which keeps the 32x32x16 instruction for
-// the skinny tiles, the LM head and the CTC output layer); only the matrix instruction and with it the
+// the skinny tiles and the LM head of few rows); only the matrix instruction and with it the
 // fragment and accumulator layouts differ.  Why a second instruction shape: on this chip the big GEMMs
 // run against the power limit, and the 16x16x32 shape moves half as many accumulator registers per
 // flop (a 16x16 block of fp32 is read and written once per 32 k instead of a 32x32 block once per 16 k).
