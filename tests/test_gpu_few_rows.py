@@ -153,6 +153,17 @@ def test_verify_mid_rows(M):
     _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
 
 
+# 32 x 64 tiles with K split over the wavefronts beyond 128 rows: 24 tiles of QKV columns, one round up to 320 rows, 8 of gate/up, 1024
+@pytest.mark.parametrize("M", [129, 320, 321, 1024])
+def test_verify_k_groups(M):
+    m = ModelCfg(2, 1024, 8, 2, 128, 256, 512, dtype="bf16")
+    wl = replace(WORKLOADS["cfg3_1b_ragged64"], model=m)
+    w = make_model_weights(m, 90 + M)
+    vi = _inputs(m, [(M // 2 - 40, 3, 37), (M - M // 2 - 9, 4, 5)], M)
+    tau = 1.0 / m.vocab
+    _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
+
+
 # 128 x 128 tiles of 2048 columns that add to x in place, up to a full round (2048 rows) and one row beyond it: O over 32 K steps; down
 # over four, as many as the ring has stages; QKV and gate/up in two rounds of them would be more, so they are 256 wide there
 @pytest.mark.parametrize("M", [1281, 1409, 2048, 2049])
