@@ -92,7 +92,9 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
     const int kvh = h0 / (n_q_heads / n_kv_heads);
     const int d_q = n_q_heads * HD, d_kv = n_kv_heads * HD;
     const float sc = 0.08838834764831845f * 1.4426950408889634f;      // log2(e) / sqrt(128)
-    const float P_SHIFT = 14.f;                              // probabilities are kept times 2^14: their low halves stay normal numbers
+    // probabilities are kept times 2^14 where the pieces are IEEE half: their low halves stay normal numbers (bfloat16 has fp32's range: there it
+    // would only overflow the sums, of values from 2^114 on)
+    const float P_SHIFT = BF ? 0.f : 14.f;
     const int head = min(dc % 4, G - 1), part = dc / 4;      // of this lane's column
     const int n_rows = n_ctx[b], slot0 = kv_start[b];
     // fused: wavefront g < G finishes query head g, wavefront DEC_MAX_HEADS the new k / v row; lane i has rotary pair (i, i + 64).

@@ -1,0 +1,80 @@
+"""The decode attention of 16-bit models launched by itself on cache rows of the caller's choice, against 64 bits: what tokens and
+cache rows of a whole step cannot show, the ends of its number range and the precision of its probabilities."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_11243_amd.binding import lib
+
+pytestmark = pytest.mark.gpu
+
+HD = 128
+DTYPE = {"f16": torch.float16, "bf16": torch.bfloat16}
+LOG2_SCALE = np.log2(np.e) / np.sqrt(HD)
+
+
+def _launch(operand, fused, q, k, v, n):
+    """q [Br, query heads, 128] over the first n[b] rows of k, v [Br, slots, K/V heads, 128]; fused: the last of them is not in the
+    cache but the new row, and the products of the projection come as partial sums of three K splits (all but one of them zero)."""
+    Br, Hq, _ = q.shape
+    slots, Hkv = k.shape[1:3]
+    p = lambda t: C.c_void_p(t.data_ptr())
+    out = torch.zeros(Br, Hq, HD, dtype=DTYPE[operand], device="cuda")
+    start = torch.arange(Br, dtype=torch.int32, device="cuda") * slots
+    rows = torch.tensor(n, dtype=torch.int32, device="cuda")
+    st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if fused:
+        at = torch.arange(Br, device="cuda"), rows.long() - 1
+        new_k, new_v = k[at].float(), v[at].float()
+        k, v = k.clone(), v.clone()
+        k[at], v[at] = float("nan"), float("nan")            # written by the launch, not read
+        pairs = lambda t: t.view(Br, -1, 2, 2, 32).transpose(2, 3).reshape(Br, -1)     # dims i and i + 64 lie 32 columns apart
+        packed = torch.cat([pairs(q.float()), pairs(new_k), new_v.reshape(Br, -1)], 1)
+        part = torch.zeros(3, *packed.shape, device="cuda")
+        part[1] = packed
+        rope = torch.tensor([1.0, 0.0], device="cuda").repeat(max(n), 64, 1)          # no rotation
+        flags = torch.zeros(64, dtype=torch.int32, device="cuda")
+        f = lib()._ZN3ssd24launch_decode_attn_fusedEPKfiS1_PvS2_PKiS4_iiiS2_PibP12ihipStream_t
+        f.restype = None
+        f(p(part), 3, p(rope), p(k), p(v), p(start), p(rows), Br, Hq, Hkv, p(out), p(flags), C.c_bool(operand == "bf16"), st)
+    else:
+        qkv = torch.cat([q.reshape(Br, -1), torch.zeros(Br, 2 * Hkv * HD, dtype=q.dtype, device="cuda")], 1)
+        f = lib()._ZN3ssd18launch_decode_attnEPKvS1_S1_PKiS3_iiiPvbP12ihipStream_t
+        f.restype = None
+        f(p(qkv), p(k), p(v), p(start), p(rows), Br, Hq, Hkv, p(out), C.c_bool(operand == "bf16"), st)
+    torch.cuda.synchronize()
+    return out.double().cpu().numpy()
+
+
+def _exact(q, k, v, n):
+    """(out, sum of p |v|) in 64 bits"""
+    q, k, v = (t.double().cpu().numpy() for t in (q, k, v))
+    out, mag = np.zeros_like(q), np.zeros_like(q)
+    for b in range(len(q)):
+        for h in range(q.shape[1]):
+            kv = h * k.shape[2] // q.shape[1]
+            s = k[b, :n[b], kv] @ q[b, h] * LOG2_SCALE
+            p = np.exp2(s - s.max())
+            p /= p.sum()
+            out[b, h], mag[b, h] = p @ v[b, :n[b], kv], p @ abs(v[b, :n[b], kv])
+    return out, mag
+
+
+def _random(operand, heads, n, seed):
+    g = torch.Generator().manual_seed(seed)
+    r = lambda *s: torch.randn(*s, generator=g).to(DTYPE[operand]).cuda()
+    return r(len(n), heads[0], HD), r(len(n), max(n), heads[1], HD), r(len(n), max(n), heads[1], HD)
+
+
+# Output: one rounding to eight bits (2^-9 of it).  Sums over the keys: fp32, a few ulp of what is added; 2^-18 of that is allowed.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2), (3, 1)])
+def test_bfloat16_values_up_to_the_end_of_the_range(fused, heads):
+    n = [1, 2, 31, 33, 40, 129, 300]
+    q, k, v = _random("bf16", heads, n, 3)
+    v = (v.float().clamp(-3.5, 3.5) * 2.0 ** 118).bfloat16()     # a sum of 300 of them is within fp32's range
+    got, (want, mag) = _launch("bf16", fused, q, k, v, n), _exact(q, k, v, n)
+    assert np.isfinite(got).all()
+    assert (abs(got - want) <= 2.0 ** -8 * abs(want) + 2.0 ** -18 * mag).all()
