@@ -180,9 +180,9 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
 #pragma unroll
             for (int i = 0; i < HD / 16; ++i) {
                 const uint2 w = vn[4 * i + kg];              // dims 16 i + 4 kg .. + 3
-                const float f = part == 0 ? l : 0.f;
-                o[i] = (f32x4_t){Op16<BF>::to_f32((uint16_t)w.x) * f, Op16<BF>::to_f32((uint16_t)(w.x >> 16)) * f,
-                                 Op16<BF>::to_f32((uint16_t)w.y) * f, Op16<BF>::to_f32((uint16_t)(w.y >> 16)) * f};
+                o[i] = (f32x4_t){Op16<BF>::to_f32((uint16_t)w.x), Op16<BF>::to_f32((uint16_t)(w.x >> 16)),
+                                 Op16<BF>::to_f32((uint16_t)w.y), Op16<BF>::to_f32((uint16_t)(w.y >> 16))};
+                o[i] = part == 0 ? o[i] * l : (f32x4_t){0.f, 0.f, 0.f, 0.f};
             }
         }
     } else {
@@ -263,12 +263,16 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
     if (k0 < n) block(std::false_type(), k0);
     // merge the wavefronts: wave w's partial is (m, l, o) with o scaled by 2^-m; a wavefront without a block has l = 0
     float* mine = reinterpret_cast<float*>(v_s[wave]);
+    const float lower = part == 0 ? 0.f : 1.f;
 #pragma unroll
     for (int i = 0; i < HD / 16; ++i) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {                        // the parts of a column lie 4 lanes apart
-            o[i][r] += dpp_f<DPP_ROW_ROR8>(o[i][r]);
-            o[i][r] += dpp_f<DPP_ROW_ROR4>(o[i][r]);
+            // an infinite value times a lower piece of 0 is NaN: where the sum of part 0 is not finite it is the output
+            float rest = o[i][r] * lower;
+            rest += dpp_f<DPP_ROW_ROR8>(rest);
+            rest += dpp_f<DPP_ROW_ROR4>(rest);
+            o[i][r] = fabsf(o[i][r]) < INFINITY ? o[i][r] + rest : o[i][r];
         }
         if (dc < G) *reinterpret_cast<f32x4_t*>(mine + dc * HD + 16 * i + 4 * kg) = o[i];
     }

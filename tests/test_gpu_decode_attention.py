@@ -78,3 +78,23 @@ def test_bfloat16_values_up_to_the_end_of_the_range(fused, heads):
     got, (want, mag) = _launch("bf16", fused, q, k, v, n), _exact(q, k, v, n)
     assert np.isfinite(got).all()
     assert (abs(got - want) <= 2.0 ** -8 * abs(want) + 2.0 ** -18 * mag).all()
+
+
+# An infinite value (the caller's cache is not checked; new rows of bfloat16 models are stored as they are) is the output of its column,
+# whichever pieces its probability has, and nothing else's.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("operand", ["f16", "bf16"])
+def test_infinite_values(operand, fused):
+    n = [31, 40, 200]
+    q, k, v = _random(operand, (4, 2), n, 4)
+    want, mag = _exact(q, k, v, n)
+    for b, rows in enumerate(n):
+        at = [0, rows // 2] + ([rows - 1] if fused and operand == "bf16" else [])        # the last one: the new row
+        for i, row in enumerate(at):
+            v[b, row, 1, 5 + 20 * i] = float("inf") if (b + i) % 2 else float("-inf")
+            want[b, 2:, 5 + 20 * i] = float("inf") if (b + i) % 2 else float("-inf")
+    got = _launch(operand, fused, q, k, v, n)
+    inf = np.isinf(want)
+    assert (got[inf] == want[inf]).all()
+    tol = (2.0 ** -8 if operand == "bf16" else 2.0 ** -11) * abs(want) + 2.0 ** -18 * mag
+    assert (abs(got - want)[~inf] <= tol[~inf]).all()
