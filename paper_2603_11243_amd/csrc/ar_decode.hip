@@ -112,24 +112,28 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
     const int64_t first = (int64_t)slot0 * d_kv + kvh * HD;
     float2 cs = make_float2(1.f, 0.f);
     if constexpr (FUSED) cs = fu.rope_tab[(int64_t)n * 64 + lane];
-    const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(kc + first), v_rsrc = make_rsrc(vc + first);
     const int d_kv2 = d_kv * 2, last = max(n - 1, 0);
     u32x4_t kr[2][4];
     // Keys k0 .. k0 + 31: lane (row dc of a half of 16, dims 8 kg + 32 s) in registers.  Values: four rows of 256 bytes per
     // instruction, the sixteen 16-byte chunks of row r at chunk ^ 4 (r & 3) ^ 2 (r >> 2 & 1), which spreads the eight 32-byte
     // pieces that half a wavefront reads over all LDS banks.  Rows beyond the context are copies of the last one.
+    // (32-bit offsets from the block's first row: a context may be longer than 4 GiB.)
     auto load_keys = [&](int k0) {
+        const int r0 = min(k0, last), beyond = last - r0;
+        const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(kc + first + (int64_t)r0 * d_kv);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const int off = min(k0 + 16 * c + dc, last) * d_kv2 + kg * 16;
+            const int off = min(16 * c + dc, beyond) * d_kv2 + kg * 16;
 #pragma unroll
             for (int s = 0; s < 4; ++s) kr[c][s] = __builtin_amdgcn_raw_buffer_load_b128(k_rsrc, off + 64 * s, 0, 0);
         }
     };
     auto load_values = [&](int k0) {
+        const int r0 = min(k0, last), beyond = last - r0;
+        const __amdgpu_buffer_rsrc_t v_rsrc = make_rsrc(vc + first + (int64_t)r0 * d_kv);
 #pragma unroll
         for (int i = 0; i < DEC_KEYS / 4; ++i) {
-            const int off = min(k0 + 4 * i + kg, last) * d_kv2 + (dc ^ (4 * kg + 2 * (i & 1))) * 16;
+            const int off = min(4 * i + kg, beyond) * d_kv2 + (dc ^ (4 * kg + 2 * (i & 1))) * 16;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lds_void_t*)(v_s[wave] + i * 1024), 16, off, 0, 0, 0);
         }
     };

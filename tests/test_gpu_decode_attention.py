@@ -98,3 +98,17 @@ def test_infinite_values(operand, fused):
     assert (got[inf] == want[inf]).all()
     tol = (2.0 ** -8 if operand == "bf16" else 2.0 ** -11) * abs(want) + 2.0 ** -18 * mag
     assert (abs(got - want)[~inf] <= tol[~inf]).all()
+
+
+# 64 K/V heads: 16 KB a row, 2^18 rows are 4 GiB.  All keys are alike; the rows behind that point hold the only values.
+@pytest.mark.parametrize("fused", [False, True])
+def test_cached_rows_beyond_four_gib(fused):
+    rows, far = 2 ** 18, 64
+    n = [rows + far]
+    q = torch.ones(1, 64, HD, dtype=torch.float16, device="cuda")
+    k = torch.zeros(1, n[0] + 1, 64, HD, dtype=torch.float16, device="cuda")
+    v = torch.zeros_like(k)
+    v[:, rows:] = 1024.0
+    got = _launch("f16", fused, q, k, v, n)
+    want = 1024.0 * far / n[0]                               # sums of whole numbers below 2^24: one rounding to 11 bits, one division
+    assert (abs(got - want) <= 2.0 ** -10 * want).all()
