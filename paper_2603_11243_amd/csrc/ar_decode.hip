@@ -14,11 +14,10 @@ namespace ssd {
 // Both products are v_mfma_f32_16x16x32: S^T = K Q^T with the key rows straight from memory in operand registers, then
 // O^T += V^T P^T with the values in LDS (global -> LDS loads, read back through the transposing ds_read_b64_tr_b16), whose
 // key order is chosen so that a lane's scores are its operand of the second product.  Of the 16 columns of an operand G are
-// needed; the columns hold the heads four times over (column c: head c % 4, part c / 4), and the parts carry the probabilities
-// as a sum of 16-bit pieces (two of IEEE half = 22 bits, three of bfloat16 = 24), so that nothing is lost against fp32
-// probabilities: the copies' outputs are added at the end.
+// needed; the columns hold the heads four times over (column c: head c % 4, part c / 4), and parts 0 to 2 carry the probabilities
+// as a sum of three 16-bit pieces, which hold the 24 bits of an fp32 probability: the copies' outputs are added at the end.
 // What bounds it is the chain of a launch: index, rows, score, output, with little else on the CU.  Scores and outputs on the vector
-// ALU took 700 instructions a block and 206 registers (560 workgroups in two rounds); here 152 (three per CU).  The partial sums of
+// ALU took 700 instructions a block and 206 registers (560 workgroups in two rounds); here 160 (three per CU).  The partial sums of
 // the new row are requested before anything that waits for the context length and added lane by lane (loads return in order: behind
 // the keys they cost a second round trip, and 32 cross-lane adds).  Per launch, traced: 27 utterances of 16 heads over 8 10.7 -> 7.3 us,
 // 70 of 24 over 8 21.1 -> 14.1 us; with eight wavefronts instead of four 8.2 and 16.9, with 128 registers (four per CU) 7.7 and 14.5.
@@ -35,14 +34,17 @@ template <bool BF> __device__ __forceinline__ uint16_t round_sat(float v, bool& 
     if constexpr (BF) return f32_to_bf16(v);
     else return f32_to_f16_sat(v, bad);
 }
-// what is left of p after its first `part` pieces of the operand type; nothing after the last piece
+// The pieces of a probability p: piece 0 is p times P_SCALE, piece k + 1 what the operand type leaves of piece k, times PIECE_SCALE (a power
+// of two below the first bit that is left, so that every piece keeps the magnitude of p: IEEE half would lose bits of a small one).
+// P_SCALE is for half alone: with it all bits of a p down to 2^-37 are held, and of a smaller one those down to 2^-61; bfloat16 has fp32's
+// range, and a scale would overflow its sums.  The exponent of p is formed without it: added there, the 14 took four bits of a p near 1.
+template <bool BF> constexpr float P_SCALE = BF ? 1.f : 16384.f;
+template <bool BF> constexpr float PIECE_SCALE = BF ? 256.f : 2048.f;
 template <bool BF> __device__ __forceinline__ float piece_of(float p, int part) {
-    const float r1 = p - Op16<BF>::to_f32(Op16<BF>::cvt(p));
-    if constexpr (BF) {
-        const float r2 = r1 - Op16<BF>::to_f32(Op16<BF>::cvt(r1));
-        return part == 0 ? p : part == 1 ? r1 : part == 2 ? r2 : 0.f;
-    }
-    return part == 0 ? p : part == 1 ? r1 : 0.f;
+    const float r0 = p * P_SCALE<BF>;
+    const float r1 = (r0 - Op16<BF>::to_f32(Op16<BF>::cvt(r0))) * PIECE_SCALE<BF>;
+    const float r2 = (r1 - Op16<BF>::to_f32(Op16<BF>::cvt(r1))) * PIECE_SCALE<BF>;
+    return part == 0 ? r0 : part == 1 ? r1 : r2;
 }
 
 struct DecodeFused {
@@ -92,9 +94,6 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
     const int kvh = h0 / (n_q_heads / n_kv_heads);
     const int d_q = n_q_heads * HD, d_kv = n_kv_heads * HD;
     const float sc = 0.08838834764831845f * 1.4426950408889634f;      // log2(e) / sqrt(128)
-    // probabilities are kept times 2^14 where the pieces are IEEE half: their low halves stay normal numbers (bfloat16 has fp32's range: there it
-    // would only overflow the sums, of values from 2^114 on)
-    const float P_SHIFT = BF ? 0.f : 14.f;
     const int head = min(dc % 4, G - 1), part = dc / 4;      // of this lane's column
     const int n_rows = n_ctx[b], slot0 = kv_start[b];
     // fused: wavefront g < G finishes query head g, wavefront DEC_MAX_HEADS the new k / v row; lane i has rotary pair (i, i + 64).
@@ -179,14 +178,14 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
 #pragma unroll
             for (int s = 0; s < 4; ++s) s_new = mfma_16x16x32<BF>(as_f16x8(new_rows[G][4 * s + kg]), qf[s], s_new);
             m = s_new[0] * sc;
-            l = __builtin_amdgcn_exp2f(P_SHIFT);
+            l = 1.f;
             const uint2* vn = reinterpret_cast<const uint2*>(new_rows[G + 1]);
 #pragma unroll
             for (int i = 0; i < HD / 16; ++i) {
                 const uint2 w = vn[4 * i + kg];              // dims 16 i + 4 kg .. + 3
                 o[i] = (f32x4_t){Op16<BF>::to_f32((uint16_t)w.x), Op16<BF>::to_f32((uint16_t)(w.x >> 16)),
                                  Op16<BF>::to_f32((uint16_t)w.y), Op16<BF>::to_f32((uint16_t)(w.y >> 16))};
-                o[i] = part == 0 ? o[i] * l : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+                o[i] = part == 0 ? o[i] * P_SCALE<BF> : (f32x4_t){0.f, 0.f, 0.f, 0.f};
             }
         }
     } else {
@@ -220,7 +219,7 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m, mx);                    // finite: key k0 exists
-        const float alpha = __builtin_amdgcn_exp2f(m - m_new), ref = m_new - P_SHIFT;
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
         float ps = 0.f;
         uint32_t pw[4];
 #pragma unroll
@@ -228,7 +227,7 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
             float v[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float pr = __builtin_amdgcn_exp2f(s[c][r] - ref);
+                const float pr = __builtin_amdgcn_exp2f(s[c][r] - m_new);
                 ps += pr;
                 v[r] = piece_of<BF>(pr, part);
             }
@@ -265,14 +264,14 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
     int k0 = wave * DEC_KEYS;
     for (; k0 + STEP < n; k0 += STEP) block(std::true_type(), k0);
     if (k0 < n) block(std::false_type(), k0);
-    // merge the wavefronts: wave w's partial is (m, l, o) with o scaled by 2^-m; a wavefront without a block has l = 0
+    // merge the wavefronts: wave w's partial is (m, l, o) with o scaled by 2^-m and P_SCALE; a wavefront without a block has l = 0
     float* mine = reinterpret_cast<float*>(v_s[wave]);
-    const float lower = part == 0 ? 0.f : 1.f;
+    const float lower = part == 1 ? 1.f / PIECE_SCALE<BF> : part == 2 ? 1.f / (PIECE_SCALE<BF> * PIECE_SCALE<BF>) : 0.f;
 #pragma unroll
     for (int i = 0; i < HD / 16; ++i) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {                        // the parts of a column lie 4 lanes apart
-            // an infinite value times a lower piece of 0 is NaN: where the sum of part 0 is not finite it is the output
+            // (part 3 is a copy of part 2.)  An infinite value times a lower piece of 0 is NaN: where the sum of part 0 is not finite it is the output
             float rest = o[i][r] * lower;
             rest += dpp_f<DPP_ROW_ROR8>(rest);
             rest += dpp_f<DPP_ROW_ROR4>(rest);
@@ -299,7 +298,7 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
 #pragma unroll
             for (int e = 0; e < 8; ++e) ot[e] = fmaf(src[e], f, ot[e]);
         }
-        const float inv = 1.0f / lt;
+        const float inv = 1.0f / P_SCALE<BF> / lt;
         uint4 w;
         w.x = op_pack2<BF>(ot[0] * inv, ot[1] * inv); w.y = op_pack2<BF>(ot[2] * inv, ot[3] * inv);
         w.z = op_pack2<BF>(ot[4] * inv, ot[5] * inv); w.w = op_pack2<BF>(ot[6] * inv, ot[7] * inv);

@@ -112,3 +112,43 @@ def test_cached_rows_beyond_four_gib(fused):
     got = _launch("f16", fused, q, k, v, n)
     want = 1024.0 * far / n[0]                               # sums of whole numbers below 2^24: one rounding to 11 bits, one division
     assert (abs(got - want) <= 2.0 ** -10 * want).all()
+
+
+# One key with the value 0, and 4095 whose probabilities are 2^-40.8 of its own, with values that make up for it.
+@pytest.mark.parametrize("operand", ["f16", "bf16"])
+def test_small_probabilities_count(operand):
+    n = [4096]
+    q = torch.zeros(1, 2, HD, dtype=DTYPE[operand], device="cuda")
+    q[..., 0] = 16.0
+    k, v = torch.zeros(1, 4096, 1, HD, dtype=q.dtype, device="cuda"), torch.full((1, 4096, 1, HD), 32768.0, dtype=q.dtype, device="cuda")
+    k[:, 0, :, 0], v[:, 0] = 20.0, 0.0
+    got, (want, _) = _launch(operand, False, q, k, v, n), _exact(q, k, v, n)
+    assert want.min() > 2.0 ** -14                               # a normal number of either type
+    # the exponent 40.8 in fp32 (2^-19 ln 2 of the probability), sums, output
+    assert (abs(got - want) <= (2.0 ** -8 if operand == "bf16" else 2.0 ** -10) * want).all()
+
+
+# Two probabilities, 1 and p2 (0.8 to 1) before the division: the second one's keys, three of them alike, hold -V / p2 in three pieces, so that
+# the output is the error of p2.  It may be an ulp of the exponential function (2^-24), the rounding of the score (2^-25 at most, below 1) and of the
+# factor to base 2 (2^-24 of 0.3), times ln 2, times 1.23 V; the sums of the products lose two ulp of V at most.  Together 3.9 ulp of V.
+@pytest.mark.parametrize("operand", ["f16", "bf16"])
+def test_probabilities_have_the_precision_of_fp32(operand):
+    V, Br = 2.0 ** 14, 256
+    g = torch.Generator().manual_seed(9)
+    a = (1 + torch.rand(Br, generator=g)).to(DTYPE[operand]).cuda()
+    b = (-0.1 - torch.rand(Br, generator=g)).to(a.dtype).cuda()
+    q, k, v = (torch.zeros(Br, s, 1, HD, dtype=a.dtype, device="cuda") for s in (1, 4, 4))
+    q[:, 0, 0, 0] = a
+    k[:, 1:, 0, 0] = b[:, None]
+    v[:, 0] = V
+    p2 = torch.exp2(a.double() * b.double() * LOG2_SCALE)
+    rest = -V / p2
+    for i in range(3):
+        v[:, 1 + i, 0] = rest[:, None].to(a.dtype)
+        rest = rest - v[:, 1 + i, 0, 0].double()
+    assert 0.7 < p2.min() and p2.max() < 1
+    q, n = q[:, :, 0], [4] * Br
+    got, (want, _) = _launch(operand, False, q, k, v, n), _exact(q, k, v, n)
+    err = abs(got - want).max(axis=(1, 2)) * (1 + 3 * p2.cpu().numpy()) / (V * 2.0 ** -24)
+    print(f"errors in ulp of V: largest {err.max():.2f}, root mean square {np.sqrt((err ** 2).mean()):.2f}")
+    assert err.max() <= 3.9 * (1 + 2.0 ** -8)                # and the rounding of the output
