@@ -265,6 +265,9 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
     for (; k0 + STEP < n; k0 += STEP) block(std::true_type(), k0);
     if (k0 < n) block(std::false_type(), k0);
     // merge the wavefronts: wave w's partial is (m, l, o) with o scaled by 2^-m and P_SCALE; a wavefront without a block has l = 0
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                      // the values of a wavefront without a block: they land where its output goes
+    __builtin_amdgcn_sched_barrier(0);
     float* mine = reinterpret_cast<float*>(v_s[wave]);
     const float lower = part == 1 ? 1.f / PIECE_SCALE<BF> : part == 2 ? 1.f / (PIECE_SCALE<BF> * PIECE_SCALE<BF>) : 0.f;
 #pragma unroll
