@@ -47,6 +47,12 @@ template <bool BF> __device__ __forceinline__ float piece_of(float p, int part) 
     return part == 0 ? r0 : part == 1 ? r1 : r2;
 }
 
+// v and that of the lane the rotation names (with the bound control set, which no rotation needs, the two are one instruction)
+template <int CTRL> __device__ __forceinline__ float add_rotated(float v) {
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr float F32_LARGEST = 3.4028234663852886e38f;
+
 struct DecodeFused {
     const float* part; int n_splits; int64_t split_stride;    // split_stride = rows * (d_q + 2 d_kv)
     const float2* rope_tab;                                   // [position][64] (cos, sin)
@@ -274,11 +280,9 @@ __global__ void __launch_bounds__(64 * DEC_WAVES, 3) decode_attn_hd128_kernel(co
     for (int i = 0; i < HD / 16; ++i) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {                        // the parts of a column lie 4 lanes apart
-            // (part 3 is a copy of part 2.)  An infinite value times a lower piece of 0 is NaN: where the sum of part 0 is not finite it is the output
-            float rest = o[i][r] * lower;
-            rest += dpp_f<DPP_ROW_ROR8>(rest);
-            rest += dpp_f<DPP_ROW_ROR4>(rest);
-            o[i][r] = fabsf(o[i][r]) < INFINITY ? o[i][r] + rest : o[i][r];
+            // part 3 is a copy of part 2.  An infinite value times a lower piece of 0 is NaN, which the clamp makes finite: the infinite sum of part 0 stays
+            const float rest = add_rotated<DPP_ROW_ROR4>(add_rotated<DPP_ROW_ROR8>(o[i][r] * lower));
+            o[i][r] += __builtin_amdgcn_fmed3f(rest, -F32_LARGEST, F32_LARGEST);
         }
         if (dc < G) *reinterpret_cast<f32x4_t*>(mine + dc * HD + 16 * i + 4 * kg) = o[i];
     }
