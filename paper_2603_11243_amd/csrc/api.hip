@@ -154,14 +154,12 @@ int upload(ssd_ctx* c, const void* host, void* dev, size_t bytes) {
     return SSD_OK;
 }
 
-// second half of the gate: prefix sums as kernel arguments where they fit, else uploaded to cu_dev
-int gate_utterances_of(ssd_ctx* c, const float* H, const int32_t* arg, const int32_t* cu_frames, int32_t* cu_dev, int64_t n_rows, int B, int blank,
-                       float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len) {
-    if (launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank, tau, max_entropy, gate_pass, draft, draft_len, c->stream)) return SSD_OK;
-    const int rc = upload(c, cu_frames, cu_dev, (size_t)(B + 1) * 4);
-    if (rc != SSD_OK) return rc;
+// second half of the gate: prefix sums as kernel arguments where they fit, else from cu_dev.  Where they don't they have to be there, uploaded
+// before the first launch of the call: one that fails has written nothing.
+void gate_utterances_of(ssd_ctx* c, const float* H, const int32_t* arg, const int32_t* cu_frames, const int32_t* cu_dev, int64_t n_rows, int B,
+                        int blank, float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len) {
+    if (launch_gate_utterances_host(H, arg, cu_frames, n_rows, B, blank, tau, max_entropy, gate_pass, draft, draft_len, c->stream)) return;
     launch_gate_utterances(H, arg, cu_dev, n_rows, B, blank, tau, max_entropy, gate_pass, draft, draft_len, c->stream);
-    return SSD_OK;
 }
 
 // Brackets the launches issued during its lifetime with two events when the class is being timed.
@@ -742,6 +740,10 @@ int ctc_gate(ssd_ctx* ctx, const void* logits, int dtype, const int32_t* cu_fram
     float* H = frame_entropy ? frame_entropy : reinterpret_cast<float*>(ws + p.H);
     int32_t* arg = frame_argmax ? frame_argmax : reinterpret_cast<int32_t*>(ws + p.arg);
     int32_t* cu_dev = reinterpret_cast<int32_t*>(ws + p.cu);
+    if (!gate_prefix_fits_arguments(cu_frames, B)) {
+        const int rc = upload(ctx, cu_frames, cu_dev, (size_t)(B + 1) * 4);
+        if (rc != SSD_OK) return rc;
+    }
     // The counts are the context's, whose calls run one after the other on its stream.  A captured call may be replayed on another
     // stream next to them, or next to another captured one: it takes the two launches, which share nothing but the workspace.
     unsigned* arrived = ctx->gate_arrived && !capturing(ctx->stream) ? ctx->gate_arrived : nullptr;
@@ -750,8 +752,7 @@ int ctc_gate(ssd_ctx* ctx, const void* logits, int dtype, const int32_t* cu_fram
         if (!launch_gate_fused(logits, dtype, cu_frames, n_rows, B, V_ctc, blank_id, tau_ctc, H, arg, max_entropy, gate_pass, draft_ctc, draft_len,
                                arrived, ctx->stream)) {
             launch_gate_frames(logits, dtype, n_rows, V_ctc, H, arg, ctx->stream);
-            const int rc = gate_utterances_of(ctx, H, arg, cu_frames, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len);
-            if (rc != SSD_OK) return rc;
+            gate_utterances_of(ctx, H, arg, cu_frames, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len);
         }
     }
     HIP_TRY(ctx, hipGetLastError());
@@ -904,6 +905,10 @@ int ctc_head_gate(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int
     int32_t* arg = frame_argmax ? frame_argmax : reinterpret_cast<int32_t*>(ws + p.arg);
     int32_t* cu_dev = reinterpret_cast<int32_t*>(ws + p.cu);
     float4* part = reinterpret_cast<float4*>(ws + p.part);
+    if (!gate_prefix_fits_arguments(cu_frames, B)) {
+        const int rc = upload(ctx, cu_frames, cu_dev, (size_t)(B + 1) * 4);
+        if (rc != SSD_OK) return rc;
+    }
     {
         ProfScope ps(ctx, SSD_PROF_CTC_HEAD);
         // the kernels address the states with 32-bit byte offsets: at most 4 GiB of them per launch
@@ -918,8 +923,7 @@ int ctc_head_gate(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int
             }
             launch_ctc_head_merge(part, groups, rows, H + r0, arg + r0, ctx->stream);
         }
-        const int rc = gate_utterances_of(ctx, H, arg, cu_frames, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len);
-        if (rc != SSD_OK) return rc;
+        gate_utterances_of(ctx, H, arg, cu_frames, cu_dev, n_rows, B, blank_id, tau_ctc, max_entropy, gate_pass, draft_ctc, draft_len);
     }
     HIP_TRY(ctx, hipGetLastError());
     return SSD_OK;

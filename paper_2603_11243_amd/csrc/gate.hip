@@ -404,12 +404,18 @@ void launch_gate_utterances(const float* H, const int32_t* arg, const int32_t* c
                        max_entropy, gate_pass, draft, draft_len);
 }
 
-bool make_cu_pairs(const int32_t* cu, int B, CuPairs& out) {
+static bool pairs_fit(const int32_t* cu, int B) {
     if (B > GATE_MAX_PAIR_UTTS) return false;
+    for (int b = 0; b < B; b += 2)                           // the lengths before the odd sums
+        if (cu[b + 1] - cu[b] > 0xffff) return false;
+    return true;
+}
+bool gate_prefix_fits_arguments(const int32_t* cu, int B) { return B <= GATE_MAX_ARG_UTTS || pairs_fit(cu, B); }
+bool make_cu_pairs(const int32_t* cu, int B, CuPairs& out) {
+    if (!pairs_fit(cu, B)) return false;
     for (int b = 0; b <= B; b += 2) out.even[b / 2] = cu[b];
-    for (int p = 0; 2 * p + 1 <= B; ++p) {                   // the lengths before the odd sums
+    for (int p = 0; 2 * p + 1 <= B; ++p) {
         const int len = cu[2 * p + 1] - cu[2 * p];
-        if (len > 0xffff) return false;
         uint32_t& w = out.odd[p / 2];
         w = p % 2 ? w | (uint32_t)len << 16 : (uint32_t)len;
     }

@@ -44,7 +44,8 @@ struct CuPairs {
     }
 };
 bool make_cu_pairs(const int32_t* cu, int B, CuPairs& out);      // false: more utterances or longer ones
-// false: not served, nothing was launched
+bool gate_prefix_fits_arguments(const int32_t* cu, int B);       // as one or the other
+// false: they do not fit, nothing was launched
 bool launch_gate_utterances_host(const float* H, const int32_t* arg, const int32_t* cu_frames, int64_t n_rows, int B, int blank,
                                  float tau, float* max_entropy, uint8_t* gate_pass, int32_t* draft, int32_t* draft_len,
                                  hipStream_t st);
