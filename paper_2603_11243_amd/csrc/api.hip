@@ -850,13 +850,12 @@ int qformer_pool(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int 
     QWindow* d_wins = reinterpret_cast<QWindow*>(ws + p.wins);
     QWindowArgs args;
     CuPairs cu;
+    bool list_windows = false;                               // on the device
     if (as_args) {
         QWindow* w = args.w;
         for (int b = 0; b < B; ++b)
             for (int f = cu_frames[b]; f < cu_frames[b + 1]; f += window) *w++ = QWindow{f, std::min(window, cu_frames[b + 1] - f)};
-    } else if (make_cu_pairs(cu_frames, B, cu)) {
-        launch_qformer_windows(cu, B, window, d_wins, ctx->stream);
-    } else {
+    } else if (!(list_windows = make_cu_pairs(cu_frames, B, cu))) {
         std::vector<QWindow> wins;
         wins.reserve((size_t)n_windows);
         for (int b = 0; b < B; ++b)
@@ -869,6 +868,7 @@ int qformer_pool(ssd_ctx* ctx, const void* enc_h, const int32_t* cu_frames, int 
     uint16_t* o = reinterpret_cast<uint16_t*>(ws + p.o);
     {
         ProfScope ps(ctx, SSD_PROF_QFORMER);
+        if (list_windows) launch_qformer_windows(cu, B, window, d_wins, ctx->stream);
         if (after) {
             launch_gemm_scores(static_cast<const uint16_t*>(enc_h), ctx->qf_wcat, scores, (int)n_rows, d_enc, ctx->stream);
             launch_qformer_values(static_cast<const uint16_t*>(enc_h), scores, ctx->qf_wfrag, d_wins, n_windows, n_q, d_enc, o, ctx->dev_flags, ctx->stream);
