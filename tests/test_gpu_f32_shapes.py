@@ -39,3 +39,22 @@ def test_f32_edges_of_tiles(shape, lengths):
         res = _run_chain(wl, w, vi, tau, 3)
         if len(res[1]):
             _check_against_oracle(wl, w, vi, tau, 3, *res, tol=TOL_LOGP["f32"])
+
+
+# Rows beyond one round of the smallest tiles.  tiny (K = 256 / 1024), 908 rows, 600 of them scored: QKV 32 x 16 pairs, gate/up 32 x 32 and on
+# the scored rows 32 x 16, O and down 32 x 32 with K over four and eight wavefronts, on all rows and on the scored ones.  768 wide: gate/up of
+# K > 512 in 32 x 32.  1008 wide: QKV and gate/up in 32 x 16 with K over eight wavefronts.
+@pytest.mark.parametrize("shape", [(2, 256, 4, 4, 64, 1024, 512), (1, 768, 4, 2, 64, 3072, 512), (1, 1008, 4, 1, 128, 144, 512)])
+@pytest.mark.parametrize("lengths", [[(150, 8, 300), (149, 1, 300)], [(270, 0, 360), (300, 2, 247), (200, 5, 301)]])
+def test_f32_rows_beyond_one_round(shape, lengths):
+    m = ModelCfg(*shape, dtype="f32")
+    wl = replace(WORKLOADS["cfg1_tiny_f32"], model=m)
+    w = make_model_weights(m, 50 + shape[1])
+    w["embed"] *= 25
+    S, P, U = map(list, zip(*lengths))
+    cu = lambda a: np.concatenate([[0], np.cumsum(a)]).astype(np.int32)
+    r, g = np.random.default_rng(shape[1]), torch.Generator().manual_seed(shape[1])
+    vi = VerifyInputs(torch.randn(sum(S), m.d_model, generator=g), cu(S), r.integers(0, m.vocab, sum(P)).astype(np.int32), cu(P),
+                      r.integers(0, m.vocab, sum(U)).astype(np.int32), cu(U))
+    tau = 1.0 / m.vocab
+    _compare(wl, w, vi, _run_gpu(wl, w, vi, tau), tau)
