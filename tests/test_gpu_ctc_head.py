@@ -127,6 +127,17 @@ def test_head_gate_wide_tiles(ctx, V, n):
     _run_and_compare(ctx, enc, w, torch.randn(V, generator=g) * 0.1, np.append(np.arange(0, n, 700), n), 0, 2.0)
 
 
+# The same tiles with more K slices than their rings have stages (two where they are 384 symbols wide, three or four otherwise): five, an odd
+# count, and sixteen as in the paper's layer.  64 x 128, 128 x 128, 256 x 128; then 128, 160 and 192 frames high.
+@pytest.mark.parametrize("d_enc,n", [(320, 5440), (320, 10880), (320, 21760), (320, 21761), (320, 32769), (320, 40961), (1024, 32769), (1024, 40961)])
+def test_head_gate_tiles_in_the_steady_loop(ctx, d_enc, n):
+    assert d_enc // 64 > 4
+    g = torch.Generator().manual_seed(n + d_enc)
+    enc = torch.randn(n, d_enc, generator=g).to(torch.bfloat16)
+    w = (torch.randn(348, d_enc, generator=g) / d_enc ** 0.5 * 1.4).to(torch.bfloat16)
+    _run_and_compare(ctx, enc, w, torch.randn(348, generator=g) * 0.1, np.append(np.arange(0, n, 700), n), 0, 2.0)
+
+
 # Merge and decisions in one launch: up to 8 groups of 64 symbols and 2048 frames an utterance, up to 512 in four wavefronts of two frames a
 # lane, prefix sums of up to 256 and up to 1280 utterances as arguments; beyond, launches of their own.
 @pytest.mark.parametrize("V,lengths", [(64, [512, 1, 256]), (100, [1, 255, 257]), (348, [513, 64]), (384, [3, 1024]), (385, [1025, 128, 129]), (512, [2048]),
