@@ -135,14 +135,14 @@ def test_fallback_row_blocks(Br):
     _continue_and_check(m, _weights(m, 70 + Br), vi, 2, "f16", ROW_TOL["f16"], LOGIT_TOL["f16"], sample=range(0, Br, 8))
 
 
-# 768 columns are 12, 6 or 3 tiles per 128 rows: K splits of 128 x 64, 128 x 128 or 128 x 256 tiles over 12 and 50 K steps; QKV and
-# gate/up pass from 64 x 64 over 64 x 128 and 128 x 128 to the 256-wide tiles
 # pieces of eight rows in the register-streaming kernel
 @pytest.mark.parametrize("Br", [1, 7, 8, 9, 16, 17, 24, 25, 32])
 def test_fallback_pieces_of_eight_rows(Br):
     test_fallback_row_blocks(Br)
 
 
+# 768 columns are 12, 6 or 3 tiles per 128 rows: K splits of 128 x 64, 128 x 128 or 128 x 256 tiles over 12 and 50 K steps; QKV and
+# gate/up pass from 64 x 64 over 64 x 128 and 128 x 128 to the 256-wide tiles
 @pytest.mark.parametrize("M", [129, 256, 257, 500, 641, 1100, 1700])
 def test_verify_mid_rows(M):
     m = ModelCfg(2, 768, 6, 2, 128, 3200, 512, dtype="bf16")
@@ -219,3 +219,28 @@ def test_cached_rows_at_tile_heights(M, operand):
             got = cache[part, kv_start[b]:kv_start[b] + rows[b]]
             assert (np.linalg.norm(got - want, axis=1) <= ROW_TOL[operand] * np.linalg.norm(want, axis=1)).all(), (b, "kv"[part])
     assert not cache[:, :3].any()                            # nothing beside them
+
+
+# K splits of at least eight K steps on 65 to 96 rows, row blocks of the stream layout by four wavefronts: down of 512 columns in eight
+# splits of eight steps each (4096), or of eight and nine (4352), which the wavefronts share unevenly
+@pytest.mark.parametrize("d_ff", [4096, 4352])
+@pytest.mark.parametrize("rows", [65, 70, 96])
+@pytest.mark.parametrize("operand", ["f16", "bf16"])
+def test_row_blocks_of_k_splits(d_ff, rows, operand):
+    m = ModelCfg(2, 512, 4, 2, 128, d_ff, 512, dtype="bf16")
+    vi = _inputs(m, [(1 + 5 * (b % 9), 1, 1) for b in range(rows)], rows)
+    _continue_and_check(m, _weights(m, 75 + rows), vi, 2, operand, ROW_TOL[operand], LOGIT_TOL[operand], sample=range(0, rows, 8))
+    if operand == "f16":
+        wl = replace(WORKLOADS["cfg3_1b_ragged64"], model=m)
+        w = make_model_weights(m, 76 + rows)
+        vi = _inputs(m, [(rows - 20, 3, 5), (4, 4, 4)], rows)
+        _compare(wl, w, vi, _run_gpu(wl, w, vi, 1.0 / m.vocab), 1.0 / m.vocab)
+
+
+# the QKV projection of 2048 columns: four splits of eight K steps, finished in the decode attention
+@pytest.mark.parametrize("rows", [65, 96])
+@pytest.mark.parametrize("operand", ["f16", "bf16"])
+def test_row_blocks_of_k_split_qkv(rows, operand):
+    m = ModelCfg(2, 2048, 16, 8, 128, 256, 512, dtype="bf16")
+    vi = _inputs(m, [(1 + 5 * (b % 9), 1, 1) for b in range(rows)], rows)
+    _continue_and_check(m, _weights(m, 78 + rows), vi, 2, operand, ROW_TOL[operand], LOGIT_TOL[operand], sample=range(0, rows, 16))
