@@ -37,7 +37,7 @@ __device__ __forceinline__ f32x4v_t mfma_f32_k16(const float4& w, const float4& 
 enum F32Pairs { F32_QKV, F32_SWIGLU, F32_RESIDUAL };
 struct F32GemmArgs {
     const float* A; const float* W; const float* gain; float* out;
-    int M, N, K, ldo, n_pairs; float eps;
+    int M, K, ldo, n_pairs; float eps;
     const int32_t* a_rows; const int32_t* o_rows;                               // rows of A / of out that are taken (NULL: all in order)
     int half, d_rot, d_q, d_kv; const int32_t* pos; const float2* rope_tab;     // QKV only
     const int32_t* row_slot; float* kc; float* vc;
@@ -241,18 +241,18 @@ static void launch_pairs(const F32GemmArgs& g, hipStream_t st) {
 void launch_gemm_f32_qkv(const float* x, const float* gain, float eps, const float* Wqkv, float* qkv, const int32_t* pos,
                          const float* rope_tab, int M, int d_model, int d_q, int d_kv, int head_dim, const int32_t* row_slot,
                          float* kc, float* vc, hipStream_t st) {
-    F32GemmArgs g{x, Wqkv, gain, qkv, M, d_q + 2 * d_kv, d_model, d_q + 2 * d_kv, (d_q + 2 * d_kv) / 2, eps, nullptr, nullptr, head_dim / 2, d_q + d_kv,
+    F32GemmArgs g{x, Wqkv, gain, qkv, M, d_model, d_q + 2 * d_kv, (d_q + 2 * d_kv) / 2, eps, nullptr, nullptr, head_dim / 2, d_q + d_kv,
                   d_q, d_kv, pos, reinterpret_cast<const float2*>(rope_tab), row_slot, kc, vc};
     launch_pairs<F32_QKV>(g, st);
 }
 void launch_gemm_f32_swiglu(const float* x, const float* gain, float eps, const float* Wgu, float* h, int M, int d_ff, int d_model,
                             const int32_t* x_rows, hipStream_t st) {
-    F32GemmArgs g{x, Wgu, gain, h, M, 2 * d_ff, d_model, d_ff, d_ff, eps, x_rows, nullptr, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
+    F32GemmArgs g{x, Wgu, gain, h, M, d_model, d_ff, d_ff, eps, x_rows, nullptr, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
     launch_pairs<F32_SWIGLU>(g, st);
 }
 void launch_gemm_f32_residual(const float* A, const float* W, float* x, int M, int N, int K, const int32_t* a_rows, const int32_t* x_rows,
                               hipStream_t st) {
-    F32GemmArgs g{A, W, nullptr, x, M, N, K, N, N, 0.f, a_rows, x_rows, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
+    F32GemmArgs g{A, W, nullptr, x, M, K, N, N, 0.f, a_rows, x_rows, 1, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
     launch_pairs<F32_RESIDUAL>(g, st);
 }
 

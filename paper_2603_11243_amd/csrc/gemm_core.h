@@ -19,7 +19,7 @@
 // (consecutive rows, same logical chunk) then spreads every 16 lanes over all sixteen 16-byte
 // columns of the 256-byte LDS data path (measured: SQ_LDS_BANK_CONFLICT drops to zero; with
 // c ^ (r & 7) half of the LDS cycles were conflict cycles).
-// Rows >= M (and columns >= n_rows_w, if given) are clamped on load and must be skipped by the epilogue.
+// Rows >= M are clamped on load and must be skipped by the epilogue.
 // Requirements: N % BN == 0, K % 64 == 0, A and W 16-byte aligned and smaller than 4 GiB.
 #pragma once
 #include <type_traits>
@@ -91,14 +91,11 @@ struct GemmTile {
     static_assert(BM % (8 * WAVES) == 0 && BN % (8 * WAVES) == 0, "tile/thread mismatch");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of 32x32");
 
-    // acc is accumulated onto (zero it for a plain product).  Rows of W at and beyond n_rows_w are
-    // clamped on load like the rows of A beyond M (for callers whose ragged dimension is N).  smem: gemm_lds_bytes<BM,BN,NSTAGE>() bytes, 16-byte
+    // acc is accumulated onto (zero it for a plain product).  smem: gemm_lds_bytes<BM,BN,NSTAGE>() bytes, 16-byte
     // aligned.  Slices kt0 <= kt < kt1 of K are accumulated (K itself is the row stride of A and W).
     static __device__ __forceinline__ void run(const f16_t* __restrict__ A, const f16_t* __restrict__ W, int M, int K,
                                                int m0, int n0, int kt0, int kt1, unsigned char* smem,
-                                               f32x16_t (&acc)[TM][TN], int n_rows_w = 0x7fffffff, int lda = 0, int ldw = 0) {
-        if (lda == 0) lda = K;                               // row strides in elements (default: dense rows)
-        if (ldw == 0) ldw = K;
+                                               f32x16_t (&acc)[TM][TN]) {
         // Wavefronts beyond WAVES form further groups of WAVES that run the same tile on their own smem and K range
         // (in-workgroup K split: the caller adds the groups' accumulators); every group must run the same number
         // of slices, since the barriers below are workgroup barriers.
@@ -115,12 +112,12 @@ struct GemmTile {
         for (int i = 0; i < A_LOADS; ++i) {
             const int r = (i * WAVES + wave) * 8 + lrow;
             const int grow = min(m0 + r, M - 1);
-            a_off[i] = (unsigned)grow * (unsigned)lda * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
+            a_off[i] = (unsigned)grow * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
         }
 #pragma unroll
         for (int i = 0; i < B_LOADS; ++i) {
             const int r = (i * WAVES + wave) * 8 + lrow;
-            b_off[i] = (unsigned)min(n0 + r, n_rows_w - 1) * (unsigned)ldw * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
+            b_off[i] = (unsigned)(n0 + r) * (unsigned)K * 2u + (unsigned)((lslot ^ ((r >> 1) & 7)) * 16);
         }
         auto issue_loads = [&](int kt, int stage) {
             unsigned char* sa = smem + stage * STAGE_BYTES;
