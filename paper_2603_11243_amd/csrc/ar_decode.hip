@@ -19,8 +19,9 @@ namespace ssd {
 // What bounds it is the chain of a launch: index, rows, score, output, with little else on the CU.  Scores and outputs on the vector
 // ALU took 700 instructions a block and 206 registers (560 workgroups in two rounds); here 160 (three per CU).  The partial sums of
 // the new row are requested before anything that waits for the context length and added lane by lane (loads return in order: behind
-// the keys they cost a second round trip, and 32 cross-lane adds).  Per launch, traced: 27 utterances of 16 heads over 8 10.7 -> 7.3 us,
-// 70 of 24 over 8 21.1 -> 14.1 us; with eight wavefronts instead of four 8.2 and 16.9, with 128 registers (four per CU) 7.7 and 14.5.
+// the keys they cost a second round trip, and 32 cross-lane adds).  Per launch, traced: 27 utterances of 16 heads over 8 10.7 -> 7.7 us,
+// 70 of 24 over 8 21.1 -> 14.6 us (0.4 and 0.5 of them for exact probabilities: third piece, scales, the sum of the parts; before it eight
+// wavefronts instead of four 8.2 and 16.9 against 7.3 and 14.1, 128 registers, four per CU, 7.7 and 14.5).
 constexpr int DEC_WAVES = 4;
 constexpr int DEC_KEYS = 32;
 constexpr int DEC_MAX_HEADS = 3;                             // one wavefront of the fused variant per head and one for the new k / v row

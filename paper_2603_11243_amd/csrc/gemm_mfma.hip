@@ -751,7 +751,8 @@ static bool try_launch_stream(const f16_t* A, const void* Ws, int M, int N, int 
 //     but O 7.2 / 6.3 and 9.2 / 9.4 (4 and 9), QKV 2048 8.9 / 8.7 (8): short K ranges don't pay for adding three row blocks
 //     (these with two wavefronts of three stages; four of two, from 8 K steps on, and two stages instead of three for whole sums:
 //     eight greedy steps, 3072 wide, 70 rows 22.35 -> 22.15 ms, 90 rows 23.52 -> 23.06, 2048 wide 13.20 -> 13.09 and 14.23 -> 13.88)
-//   K splits, 97..128 rows: never faster (O 8.1 / 6.8, down 13.5 / 14.0 and 17.7 / 17.7)
+//   K splits, 97..128 rows: O 8.1 / 6.8, down 13.5 / 14.0 and 17.7 / 17.7, with two wavefronts of three stages; four of two, which are faster at
+//     65..96 rows, were not measured here
 //   whole QKV sums: the in-workgroup K split is faster (10.4 and 14.8 at 70 rows) while its row tiles of 32 give at most one
 //     workgroup per CU; with 320 of them (116 rows, 5120 columns) 27.5 against 17.5 here with two row tiles of 64
 // (The limits of 8 K steps and 96 column tiles lie between these two widths' figures; no other width was measured.)

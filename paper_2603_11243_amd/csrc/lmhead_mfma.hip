@@ -200,7 +200,9 @@ static void launch_lmhead_cfg(const f16_t* hv, const f16_t* w_lm, const int32_t*
 // slab: up to 32 rows a 32 x 128 tile with a four-stage ring, up to 128 rows a 128 x 64 tile with three; otherwise the compute-bound 256 x
 // 256 tile (lmhead_mfma16_kernel).  us of a launch behind a large write, one workgroup a CU (32 x 256, four stages of 128 x 64) / two: vocabulary
 // 49152 of 2048, 4 rows 94 / 86, 27 rows 95 / 88, 40 rows 100 / 91, 128 rows 105 / 90; 100352 of 2048, 27 rows 141 / 142, 40 rows 171 / 146, 128 rows
-// 183 / 151; 49152 of 3072, 27 rows 115 / 114, 40 rows 121 / 114, 128 rows 133 / 121.
+// 183 / 151; 49152 of 3072, 27 rows 115 / 114, 40 rows 121 / 114, 128 rows 133 / 121.  Up to 32 rows it depends on how the tiles fill the last round: behind a
+// large read, 27 rows of 2048, vocabulary 32768 49 / 47, 65536 80 / 74, 100352 100 / 112, 131072 145 / 129, 152064 177 / 143; of 3072 to 8192 0.77 to 1.13 of
+// the one workgroup's time.  Greedy steps with the 100352 vocabulary take the same time either way (0.97 to 1.01).
 template <bool BF>
 static void lmhead_impl(const uint16_t* hv, const uint16_t* w_lm, const int32_t* targets, int Mv, int d, int vocab,
                         float2* part_ms, float* tgt_logit, int2* part_arg, bool want_greedy, float descale,

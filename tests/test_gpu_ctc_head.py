@@ -92,7 +92,7 @@ def test_head_gate_symbol_counts_widths_and_ragged_tails(ctx, V, d_enc, with_bia
 
 
 def test_head_gate_many_frames_takes_the_tall_tile(ctx):
-    # more than 255 row tiles of 256 frames: the 256-row tile variant
+    # more than 255 row tiles of 256 frames (which take 160 x 384 tiles in two rounds, where 256 x 128 would be four)
     rng = np.random.default_rng(99)
     V, d_enc, B = 348, 128, 90
     T = rng.integers(600, 900, size=B)

@@ -53,8 +53,8 @@ def test_qformer_pool_matches_oracle(name, B, d_out):
     print(f"{wl.name}: {int(hb.cu_frames[-1])} frames -> {int(cu_s[-1])} rows, worst relative row error {worst:.2e}")
 
 
-# 20 column tiles of 64 for scores and values, 48 for the output: both projections pass from the few-row kernels over 64 x 64,
-# 128 x 64 and 64 x 128 tiles to the 256-wide ones, at 128, 768, 1536 and 3264 frames and at 128, 320, 640 and 1344 rows
+# 17 column tiles of 64 for scores and values, 48 for the output: both projections pass from the few-row kernels over 32 x 64 (K split in the
+# workgroup), 64 x 64, 64 x 128 and 128 x 128 tiles to the 256-wide ones, at 128, 480, 960, 1792 and 3584 frames and at 128, 160, 320, 640 and 1280 rows
 @pytest.mark.parametrize("frames", [128, 129, 768, 769, 1536, 1537, 3264, 3265, 6730])
 def test_qformer_pool_frame_counts(frames):
     from paper_2603_11243_amd.binding import Context
